@@ -176,10 +176,10 @@ int nwq_set_fusion(nwq_handle h, int k, int* k_out);
 
 /* Low tile bits of fused blocks: every block's tile holds the lowest c bits
  * of the index (contiguous runs of 2^c entries in HBM) plus up to k - c high
- * bits its gates touch.  c = 0 (default) picks 6 for state vectors and 4 for
+ * bits its gates touch.  c = 0 (default) picks 3 for state vectors and 4 for
  * density matrices (on vec(rho) a qubit above the low bits needs two high
  * bits, q and q + n, so fewer low bits leave room for more qubits per block);
- * otherwise c in [3, 8], used as max(k - 8, min(c, k - 2)) at width k.  Only
+ * otherwise c in [3, 8].  Used as max(k - 8, min(c, k - 2)) at width k.  Only
  * the grouping into blocks changes, and results agree to rounding.  Changing
  * it on a DM handle runs the queued superoperators first.  Other values:
  * NWQ_EINVAL. */

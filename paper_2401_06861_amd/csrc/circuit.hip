@@ -1,12 +1,12 @@
 // Whole-circuit application and the fusion planner.
 //
-// The planner walks the gate list and builds blocks greedily: a block owns a
-// tile set T = {0..c-1} u H with |H| <= k - c high qubits.  A gate joins the
-// current block when none of its qubits is held by an earlier gate that was
-// left out (so moving it forward never crosses a gate it does not commute
-// with by disjointness) and its qubits fit in T after adding the new high
-// qubits it needs.  Left-out gates start the next block.  Each block is one
-// read and one write of the state through LDS.
+// The planner walks the gate list and builds blocks: a block owns a tile set
+// T = {0..c-1} u H with |H| <= k - c high qubits.  A gate joins the current
+// block when its qubits lie in T and none of them is held by an earlier gate
+// that was left out (so moving it forward never crosses a gate it does not
+// commute with by disjointness).  Left-out gates start the next block.  Each
+// block is one read and one write of the state through LDS, so the planner
+// picks H for the most gates per block (grow_sets).
 #include <algorithm>
 #include <array>
 #include <cmath>
@@ -16,73 +16,207 @@
 
 namespace nwq {
 
-// A state vector's blocks keep 6 low bits (each wave's loads cover 1 KiB
-// runs).  On vec(rho) a qubit above the low bits takes two high slots (its
-// column bit q and row bit q + n), so density matrices keep 4: at n=14,
-// k=12 the noisy TFIM needs 35 blocks instead of 46.
+// Fewer low bits leave room for more of the circuit's bits per block and give
+// shorter HBM runs.  State vectors take as few as the block's 8 high slots
+// allow (at least 3: whole 128-byte lines): the depth-40 brickwork on 30
+// qubits runs in 281 ms at width 13 with 5 low bits (29 blocks), 332 with 6
+// (38) and 380 with 7 (49); a 384-gate circuit of random pairs on 24 qubits in
+// 1.69 ms at width 12 with 4, 1.72 with 5 and 1.84 with 6.  On vec(rho) a
+// qubit above the low bits takes two high slots (its column bit q and row bit
+// q + n); density matrices keep at least 4 (n=14, width 12, noisy TFIM: 65 ms
+// and 25 blocks with 4, 83 ms and 41 with 5).
 int fusion_low_bits(const nwq_state* h, int nbits, int k) {
   if (nbits <= k) return nbits;
-  const int c = h->fuse_c > 0 ? h->fuse_c : (h->kind == NWQ_KIND_DM ? 4 : 6);
+  const int c = h->fuse_c > 0 ? h->fuse_c : (h->kind == NWQ_KIND_DM ? 4 : 3);
   return std::min(std::max(c, k - 8), k - 2);
 }
+
+// ---------------------------------------------------------------------------
+// Splitting a gate list into sets of bits (a block's high qubits, a phase's
+// register bits).  Each round grows one set H (at most `room` bits beside the
+// always-present `low` bits) from a first gate's bits, by the bits of a gate
+// waiting at the front that lets the most gates in per added bit, and takes
+// every gate the set then reaches.  Growing by gain follows the light cone of
+// the bits it holds instead of the order of the list: the depth-40 brickwork
+// on 30 qubits needs 31 sets of 13 bits (5 low) where taking gates in list
+// order until the set is full needed 73, and the 20-qubit, 8-layer VQE ansatz
+// 8 of 12 bits instead of 17.  `seeds` bounds the first gates tried per round
+// (the set that takes the most gates is kept).  A round visits gates only
+// until every bit is held, so planning costs about (sets) x (bits per set) x
+// (front gates) x (gates in a cone): 0.1 ms for that brickwork with one seed.
+// Returns false when a gate needs more than `room` bits outside `low`.
+// ---------------------------------------------------------------------------
+namespace {
+
+typedef unsigned long long u64;
+inline int bits_of(u64 m) { return __builtin_popcountll(m); }
+
+struct BitSet {
+  u64 H = 0;                 // bits of the set outside low
+  std::vector<int> gates;    // positions in the mask list, in order
+};
+
+bool grow_sets(const std::vector<u64>& masks, u64 all, u64 low, int room, int seeds, std::vector<BitSet>& out) {
+  std::vector<int> rem(masks.size());
+  std::vector<u64> rm(masks);   // masks of the remaining gates
+  for (size_t i = 0; i < rem.size(); ++i) rem[i] = (int)i;
+  std::vector<u64> front, cand;
+  // a gate of several bits weighs more: one-bit gates join whichever set holds their bit
+  auto weight = [](u64 m) { return (m & (m - 1)) ? 4 : 1; };
+  while (!rem.empty()) {
+    front.clear();
+    u64 blocked = 0;
+    for (size_t r = 0; r < rm.size() && blocked != all; ++r) {
+      const u64 m = rm[r];
+      if (!(m & blocked)) {
+        const u64 s = m & ~low;
+        if (r == 0 && bits_of(s) > room) return false;
+        if (bits_of(s) <= room && std::find(front.begin(), front.end(), s) == front.end()) front.push_back(s);
+      }
+      blocked |= m;
+    }
+    // the first gate's bits, then evenly spaced ones
+    const int tries = std::min<int>(seeds, (int)front.size());
+    int best_score = -1;
+    u64 best_H = 0;
+    for (int t = 0; t < tries; ++t) {
+      u64 H = front[(size_t)t * front.size() / tries];
+      int score = 0;
+      for (;;) {
+        const int free = room - bits_of(H);
+        const u64 T = low | H;
+        cand.clear();
+        score = 0;
+        blocked = 0;
+        for (size_t r = 0; r < rm.size() && blocked != all; ++r) {
+          const u64 m = rm[r];
+          if (m & blocked) {
+            blocked |= m;
+          } else if (m & ~T) {
+            const u64 need = m & ~T;
+            if (bits_of(need) <= free && std::find(cand.begin(), cand.end(), need) == cand.end()) cand.push_back(need);
+            blocked |= m;
+          } else {
+            score += weight(m);
+          }
+        }
+        if (cand.empty()) break;
+        double gain_best = -1.0;
+        u64 add = 0;
+        for (u64 need : cand) {
+          const u64 T2 = T | need;
+          int s2 = 0;
+          blocked = 0;
+          for (size_t r = 0; r < rm.size() && blocked != all; ++r) {
+            const u64 m = rm[r];
+            if ((m & blocked) || (m & ~T2)) blocked |= m;
+            else s2 += weight(m);
+          }
+          const double gain = (double)(s2 - score) / bits_of(need);
+          if (gain > gain_best) {
+            gain_best = gain;
+            add = need;
+          }
+        }
+        H |= add;
+      }
+      if (score > best_score) {
+        best_score = score;
+        best_H = H;
+      }
+    }
+    BitSet b;
+    b.H = best_H;
+    const u64 T = low | best_H;
+    blocked = 0;
+    size_t w = 0;
+    for (size_t r = 0; r < rm.size(); ++r) {
+      const u64 m = rm[r];
+      if ((m & blocked) || (m & ~T)) {
+        blocked |= m;
+        rem[w] = rem[r];
+        rm[w++] = m;
+      } else {
+        b.gates.push_back(rem[r]);
+      }
+    }
+    rem.resize(w);
+    rm.resize(w);
+    out.push_back(std::move(b));
+  }
+  return true;
+}
+
+// The sets of a list planned from its end: a plan of the reversed list, read
+// backwards, is a plan of the list.
+bool grow_sets_from_end(const std::vector<u64>& masks, u64 all, u64 low, int room, int seeds,
+                        std::vector<BitSet>& out) {
+  const std::vector<u64> rev(masks.rbegin(), masks.rend());
+  if (!grow_sets(rev, all, low, room, seeds, out)) return false;
+  const int last = (int)masks.size() - 1;
+  std::reverse(out.begin(), out.end());
+  for (BitSet& b : out) {
+    std::reverse(b.gates.begin(), b.gates.end());
+    for (int& i : b.gates) i = last - i;
+  }
+  return true;
+}
+
+// Passes over the state that a plan costs from |0...0>: per block the share of
+// the tiles that can be nonzero (see apply_fused).
+double passes_from_zero(const std::vector<BitSet>& sets, u64 all, u64 low) {
+  double cost = 0.0;
+  u64 support = 0;
+  for (const BitSet& b : sets) {
+    const u64 T = low | b.H;
+    cost += std::ldexp(1.0, bits_of(support & ~T) - bits_of(all & ~T));
+    support |= T;
+  }
+  return cost;
+}
+
+}  // namespace
 
 // Every block has at least two high slots (c <= k - 2), so the first
 // remaining one- or two-qubit gate always fits and each round absorbs at
 // least one gate (a four-bit DM superoperator is queued only when the width
-// leaves four).
-std::vector<Block> plan_blocks(const std::vector<PGate>& g, int n, int k, int c_req) {
-  int c = c_req < 0 ? std::min(6, k - 2) : std::min(std::max(c_req, k - 8), k - 2);
-  if (n <= k) c = n;
-  const int mmax = n <= k ? 0 : k - c;
-  std::vector<int> rem(g.size());
-  for (size_t i = 0; i < g.size(); ++i) rem[i] = (int)i;
-  std::vector<Block> out;
-  std::vector<char> blocked(n);
-  while (!rem.empty()) {
-    Block b;
-    b.c = c;
-    std::vector<int> keep;
-    std::fill(blocked.begin(), blocked.end(), 0);
-    int nblocked = 0;
-    std::vector<int> H;
-    for (size_t r = 0; r < rem.size(); ++r) {
-      if (nblocked == n) {   // every qubit is held by a left-out gate: the rest waits
-        keep.insert(keep.end(), rem.begin() + r, rem.end());
-        break;
-      }
-      const int idx = rem[r];
-      const PGate& gg = g[idx];
-      bool hit = false;
-      for (int j = 0; j < gg.nq; ++j) hit |= blocked[gg.q[j]] != 0;
-      bool take = false;
-      if (!hit && nblocked < n) {
-        std::vector<int> need;
-        for (int j = 0; j < gg.nq; ++j)
-          if (gg.q[j] >= c && std::find(H.begin(), H.end(), gg.q[j]) == H.end()) need.push_back(gg.q[j]);
-        if ((int)(H.size() + need.size()) <= mmax) {
-          H.insert(H.end(), need.begin(), need.end());
-          take = true;
-        }
-      }
-      if (take) {
-        b.gates.push_back(idx);
-      } else {
-        keep.push_back(idx);
-        for (int j = 0; j < gg.nq; ++j)
-          if (!blocked[gg.q[j]]) {
-            blocked[gg.q[j]] = 1;
-            ++nblocked;
-          }
-      }
-    }
-    if (b.gates.empty()) return {};   // cannot happen with two high slots; caller reports it
-    std::sort(H.begin(), H.end());
-    b.m = (int)H.size();
-    for (int i = 0; i < b.m; ++i) b.hi[i] = H[i];
-    out.push_back(std::move(b));
-    rem.swap(keep);
+// leaves four).  Planned from both ends of the list; the plan with fewer
+// blocks is kept, or with `from_zero` (the plan only ever runs from |0...0>)
+// the one with fewer passes.  Circuits plan the same way from any state, so
+// that nwq_run_circuit gives the bits of nwq_reset + nwq_apply_circuit.
+std::vector<Block> plan_blocks(const std::vector<PGate>& g, int n, int k, int c_req, int seeds, bool from_zero) {
+  const int c = n <= k ? n : std::min(std::max(c_req, k - 8), k - 2);
+  const int room = n <= k ? 0 : k - c;
+  std::vector<u64> masks(g.size());
+  for (size_t i = 0; i < g.size(); ++i)
+    for (int j = 0; j < g[i].nq; ++j) masks[i] |= 1ull << g[i].q[j];
+  const u64 all = (1ull << n) - 1ull, low = (1ull << c) - 1ull;
+  std::vector<BitSet> sets, other;
+  if (!grow_sets(masks, all, low, room, seeds, sets)) return {};   // cannot happen with two high slots; caller reports it
+  if (sets.size() > 1 && grow_sets_from_end(masks, all, low, room, seeds, other)) {
+    const double a = passes_from_zero(sets, all, low), b = passes_from_zero(other, all, low);
+    if (from_zero ? b < a : (other.size() < sets.size() || (other.size() == sets.size() && b < a))) sets.swap(other);
+  }
+  std::vector<Block> out(sets.size());
+  for (size_t i = 0; i < sets.size(); ++i) {
+    out[i].c = c;
+    for (int q = c; q < n; ++q)
+      if ((sets[i].H >> q) & 1ull) out[i].hi[out[i].m++] = q;
+    out[i].gates = std::move(sets[i].gates);
   }
   return out;
+}
+
+// Tile index bit j is the j-th qubit (ascending) outside the tile.
+unsigned long long tile_mask_of(unsigned long long tile, unsigned long long support, int nbits) {
+  unsigned long long mask = 0;
+  int j = 0;
+  for (int q = 0; q < nbits; ++q) {
+    if ((tile >> q) & 1ull) continue;
+    if ((support >> q) & 1ull) mask |= 1ull << j;
+    ++j;
+  }
+  return mask;
 }
 
 // Widen a block's tile with unused high qubits (ascending) up to width
@@ -369,44 +503,32 @@ std::vector<FuseItem> gate_products(const std::vector<int>& seq, const std::vect
 
 }  // namespace
 
-// Split a block's gates (tile-local bits) into register phases: greedily
-// take, in order, every gate whose bits fit the phase's rbits register bits
-// and that no earlier left-out gate shares a bit with; pad the set to rbits,
-// from tile bit c up first (a set above the low c bits keeps each wave's
-// lanes on contiguous amplitudes, so the phase can move between registers and
-// HBM directly when it is the block's first or last).
+// Split a block's gates (tile-local bits) into register phases of at most
+// rbits bits (grow_sets); pad each set to rbits, from tile bit c up first (a
+// set above the low c bits keeps each wave's lanes on contiguous amplitudes,
+// so the phase can move between registers and HBM directly when it is the
+// block's first or last).  Empty when a gate has more than rbits bits.
 std::vector<Phase> plan_phases(const std::vector<int>& order, const std::vector<std::array<int, 4>>& lb,
                                const std::vector<int>& nq, int k, int c, int rbits) {
-  std::vector<Phase> out;
-  std::vector<int> rem = order;
-  while (!rem.empty()) {
-    unsigned S = 0, blocked = 0;
-    Phase ph;
-    std::vector<int> keep;
-    for (int gi : rem) {
-      unsigned B = 0;
-      for (int t = 0; t < nq[gi]; ++t) B |= 1u << lb[gi][t];
-      if (B & blocked) {
-        blocked |= B;
-        keep.push_back(gi);
-        continue;
-      }
-      if (__builtin_popcount(S | B) <= rbits) {
-        S |= B;
-        ph.gates.push_back(gi);
-      } else {
-        blocked |= B;
-        keep.push_back(gi);
-      }
-    }
+  std::vector<u64> masks(order.size());
+  for (size_t i = 0; i < order.size(); ++i)
+    for (int t = 0; t < nq[order[i]]; ++t) masks[i] |= 1ull << lb[order[i]][t];
+  const u64 all = (1ull << k) - 1ull;
+  std::vector<BitSet> sets, other;
+  if (!grow_sets(masks, all, 0, rbits, 2, sets)) return {};
+  if (sets.size() > 1 && grow_sets_from_end(masks, all, 0, rbits, 2, other) && other.size() < sets.size())
+    sets.swap(other);
+  std::vector<Phase> out(sets.size());
+  for (size_t i = 0; i < sets.size(); ++i) {
+    unsigned S = (unsigned)sets[i].H;
     for (int b = c; b < k && __builtin_popcount(S) < rbits; ++b) S |= 1u << b;
     for (int b = 0; b < k && __builtin_popcount(S) < rbits; ++b) S |= 1u << b;
+    Phase& ph = out[i];
     int r = 0;
     for (int b = 0; b < k; ++b)
       if ((S >> b) & 1u) ph.reg[r++] = b;
     for (; r < 4; ++r) ph.reg[r] = -1;
-    out.push_back(std::move(ph));
-    rem.swap(keep);
+    for (int p : sets[i].gates) ph.gates.push_back(order[p]);
   }
   return out;
 }
@@ -489,7 +611,12 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
     h->last_blocks = h->last_fused_gates = h->last_phases = 0;
     return NWQ_OK;
   }
-  const std::vector<Block> blocks = plan_blocks(gates, nbits, h->fuse_k, fusion_low_bits(h, nbits, h->fuse_k));
+  // The search for each block's bits is widened as the passes it saves get
+  // dearer: a pass over 2^22 entries takes about 25 us, and each seed adds
+  // about 0.1 ms to planning a deep circuit.
+  const int seeds = nbits < 22 ? 1 : (nbits < 26 ? 2 : 8);
+  const std::vector<Block> blocks =
+      plan_blocks(gates, nbits, h->fuse_k, fusion_low_bits(h, nbits, h->fuse_k), seeds, false);
   if (blocks.empty()) return set_error(NWQ_EINVAL, "fusion planner made no progress");
   // Program: [phase table][op table][matrix table] in one upload.
   std::vector<FusedPhase> phases;
@@ -655,13 +782,7 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
     for (int q = 0; q < L.d.c; ++q) tiles_of |= 1ull << q;
     for (int i = 0; i < L.d.m; ++i) tiles_of |= 1ull << L.d.hi[i];
     if (from_zero) {
-      tile_mask = 0;
-      int j = 0;   // tile index bit j = the j-th qubit (ascending) outside the tile
-      for (int q = 0; q < h->nbits; ++q) {
-        if ((tiles_of >> q) & 1ull) continue;
-        if ((support >> q) & 1ull) tile_mask |= 1ull << j;
-        ++j;
-      }
+      tile_mask = tile_mask_of(tiles_of, support, h->nbits);
       support |= tiles_of;
     }
     timing_begin(h, KC_FUSED);
@@ -866,7 +987,8 @@ int nwq_fusion_plan(int n, int k, int n_gates, const int* types, const int* qubi
   std::vector<PGate> gates;
   int rc = parse_circuit(n, n_gates, types, qubits, nullptr, false, gates);
   if (rc) return rc;
-  const std::vector<Block> blocks = plan_blocks(gates, n, k);
+  nwq_state defaults;   // a state vector's low tile bits (no device memory)
+  const std::vector<Block> blocks = plan_blocks(gates, n, k, fusion_low_bits(&defaults, n, k), 8, false);
   if (n_gates > 0 && blocks.empty()) return set_error(NWQ_EINVAL, "fusion planner made no progress");
   *n_blocks = (int)blocks.size();
   for (size_t b = 0; b < blocks.size(); ++b) {

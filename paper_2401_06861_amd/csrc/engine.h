@@ -95,9 +95,14 @@ struct Phase {
   int reg[4];
   std::vector<int> gates;
 };
-// c: the low bits every block's tile holds (c <= k - 2, k - c <= 8); -1 =
-// min(6, k - 2).  Ignored when the n bits fit one tile.
-std::vector<Block> plan_blocks(const std::vector<PGate>& g, int n, int k, int c = -1);
+// c: the low bits every block's tile holds (c <= k - 2, k - c <= 8); ignored
+// when the n bits fit one tile.  seeds: first gates tried per block.
+// from_zero: the plan only ever runs from |0...0>, so its first blocks are cheap.
+std::vector<Block> plan_blocks(const std::vector<PGate>& g, int n, int k, int c, int seeds, bool from_zero);
+// The tile indices (over the nbits qubits outside the tile's mask `tile`) that
+// can hold nonzero entries when the state is zero outside `support`: those with
+// bits in the returned mask only.
+unsigned long long tile_mask_of(unsigned long long tile, unsigned long long support, int nbits);
 // Low tile bits for a handle's fused blocks of width k over nbits bits.
 int fusion_low_bits(const nwq_state* h, int nbits, int k);
 // internal gate type: dense 4x4 whose matrix is entry p[0] of a side table

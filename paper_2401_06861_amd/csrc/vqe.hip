@@ -830,7 +830,7 @@ struct VqeBwdOp {
 };
 
 constexpr int kBwdBlock = 256;
-constexpr int kBwdMaxOps = 128;
+constexpr int kBwdMaxOps = 256;   // 8 KiB of partial sums; two workgroups per CU still fit the LDS
 constexpr int kBwdStage = 8;   // tile entries per thread staged together (loads issued before LDS writes)
 
 __device__ __forceinline__ unsigned long long bwd_index(unsigned long long base, unsigned l, unsigned cmask, int c,
@@ -1188,6 +1188,14 @@ __device__ __forceinline__ void bgst(double2* p, vd2 v) {
   else st(p, v);
 }
 
+// The bits of v deposited, lowest first, at the set bits of mask.
+__device__ __forceinline__ unsigned long long pdep_u64(unsigned long long v, unsigned long long mask) {
+  unsigned long long r = 0;
+  for (; mask; mask &= mask - 1, v >>= 1)
+    if (v & 1ull) r |= mask & (~mask + 1ull);
+  return r;
+}
+
 template <int R, bool NT>
 __global__ __launch_bounds__(kWave * kBwdRbMaxWaves) void k_vqe_bwd_rb(double2* __restrict__ phi0,
                                                                       double2* __restrict__ lam0, int n,
@@ -1197,7 +1205,8 @@ __global__ __launch_bounds__(kWave * kBwdRbMaxWaves) void k_vqe_bwd_rb(double2* 
                                                                       const double2* __restrict__ table0,
                                                                       int mat_stride, int nslots,
                                                                       double* __restrict__ gpart,
-                                                                      unsigned long long ntiles) {
+                                                                      unsigned long long ntiles, int sparse,
+                                                                      unsigned long long tmask) {
   constexpr int NV = 1 << R;
   extern __shared__ double2 sh[];
   __shared__ double acc[kBwdMaxOps][kBwdRbMaxWaves];
@@ -1220,8 +1229,9 @@ __global__ __launch_bounds__(kWave * kBwdRbMaxWaves) void k_vqe_bwd_rb(double2* 
   const int nops = last.op_begin + last.op_count - op0;
   for (int i = tid; i < nops * kBwdRbMaxWaves; i += nt) acc[i / kBwdRbMaxWaves][i % kBwdRbMaxWaves] = 0.0;
   const unsigned long long glane = bwd_index(0ull, tid, cmask, c, m, blk);
+  // sparse: tiles t = 0, 1, ... are the tile indices pdep(t, tmask)
   auto tile_off = [&](unsigned long long tile) {
-    unsigned long long base = tile << c;
+    unsigned long long base = (sparse ? pdep_u64(tile, tmask) : tile) << c;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       if (i < m) {
@@ -1372,10 +1382,13 @@ struct nwq_vqe {
   bool bwd_rb = false;         // backward sweep register-blocked (3 bits) when every tile has >= 2^9 entries
   size_t fused_rop_off = 0;    // offset of the register-blocked backward ops in d_fused
   std::vector<nwq::FusedBlockDev> fwd_blocks, bwd_blocks;
-  // backward dispatches of the first planned block (the last of the sweep):
-  // phi is non-zero in tile 0 only there (it equals that block applied to
-  // |0...0>), and lambda is not read after the sweep, so they run tile 0 only
-  std::vector<char> bwd_tile0;
+  // Tiles of each backward dispatch: tile indices with bits in the mask only.
+  // Before a block's gates phi is zero wherever a qubit that no earlier block
+  // touched is set, so tiles set on such a qubit (outside the block's own) add
+  // nothing to any Im<lambda|P|phi>; the dispatches that follow in the sweep
+  // (earlier blocks, smaller supports) read none of them, and neither vector
+  // is read after the sweep.  The first planned block runs tile 0 only.
+  std::vector<unsigned long long> bwd_mask;
   // lambda = H phi of the fused schedule: tiled passes (and a gather pass for
   // terms that fit no tile), in launch order
   struct HLaunch {
@@ -1522,6 +1535,7 @@ static int launch_global(nwq_vqe* h, int B, const double* theta, const double* c
 // shorter runs cost less than the passes they save (n=20, L=8, B=256: 129 ->
 // 119 ms per batch).
 constexpr int kVqeLowBits = 3;
+constexpr int kVqeSeeds = 2;   // as many as it takes: 8 seeds plan no fewer blocks for the HEA ansatz
 
 static int build_fused(nwq_vqe* h) {
   if (h->fused_built) return NWQ_OK;
@@ -1534,14 +1548,14 @@ static int build_fused(nwq_vqe* h) {
     g[i] = PGate{0, {op.q0, two ? op.q1 : -1}, two ? 2 : 1, {0, 0, 0}};
   }
   const int k = std::min(h->fused_k, n);
-  const std::vector<Block> blocks = plan_blocks(g, n, std::max(k, 6), low);
+  const std::vector<Block> blocks = plan_blocks(g, n, std::max(k, 6), low, kVqeSeeds, true);
   if (blocks.empty() && h->nops > 0) return set_error(NWQ_EINVAL, "fusion planner made no progress");
   std::vector<FusedPhase> phases;
   std::vector<FusedOp> fops;
   std::vector<VqeBwdOp> bops;
   h->fwd_blocks.clear();
   h->bwd_blocks.clear();
-  h->bwd_tile0.clear();
+  h->bwd_mask.clear();
   std::vector<Block> padded(blocks);
   for (Block& b : padded) pad_block(b, n, std::max(k, 8));
   size_t max_bwd_lds = 0;
@@ -1610,13 +1624,23 @@ static int build_fused(nwq_vqe* h) {
   if (kbw == k) {
     bpadded = padded;
   } else {
-    bpadded = plan_blocks(g, n, std::max(kbw, 6), low);
+    bpadded = plan_blocks(g, n, std::max(kbw, 6), low, kVqeSeeds, true);
     if (bpadded.empty() && h->nops > 0) return set_error(NWQ_EINVAL, "fusion planner made no progress");
     for (Block& b : bpadded) pad_block(b, n, std::max(kbw, 8));
   }
   for (const Block& b : bpadded) max_bwd_lds = std::max(max_bwd_lds, (size_t)2 * sizeof(double2) << (b.c + b.m));
   h->bwd_rb = true;
   for (const Block& b : bpadded) h->bwd_rb = h->bwd_rb && (b.c + b.m) - kBwdBits >= 6;
+  std::vector<unsigned long long> masks;   // tile masks of bpadded, in its order
+  {
+    unsigned long long support = 0;
+    for (const Block& b : bpadded) {
+      unsigned long long tile = (1ull << b.c) - 1ull;
+      for (int i = 0; i < b.m; ++i) tile |= 1ull << b.hi[i];
+      masks.push_back(tile_mask_of(tile, support, n));
+      support |= tile;
+    }
+  }
   std::vector<VqeBwdRop> rops;
   for (auto bit = bpadded.rbegin(); h->bwd_rb && bit != bpadded.rend(); ++bit) {
     const Block& b = *bit;
@@ -1674,7 +1698,7 @@ static int build_fused(nwq_vqe* h) {
       d.op_count = (int)phases.size() - d.op_begin;
       fill_entry_offsets(d, kBwdBits);
       h->bwd_blocks.push_back(d);
-      h->bwd_tile0.push_back(bit + 1 == bpadded.rend() ? 1 : 0);
+      h->bwd_mask.push_back(masks[bpadded.rend() - bit - 1]);
     }
   }
   for (auto bit = bpadded.rbegin(); !h->bwd_rb && bit != bpadded.rend(); ++bit) {
@@ -1705,7 +1729,7 @@ static int build_fused(nwq_vqe* h) {
       for (size_t i = s0; i < e; ++i) bops.push_back(rev[i]);
       d.op_count = (int)(e - s0);
       h->bwd_blocks.push_back(d);
-      h->bwd_tile0.push_back(bit + 1 == bpadded.rend() ? 1 : 0);
+      h->bwd_mask.push_back(masks[bpadded.rend() - bit - 1]);
     }
   }
   // lambda = H phi: the first pass takes tiles of the low kt bits with every
@@ -1851,14 +1875,10 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
   unsigned long long support = 0;
   for (size_t bi = 0; bi < h->fwd_blocks.size(); ++bi) {
     const FusedBlockDev& d = h->fwd_blocks[bi];
-    unsigned long long tiles_of = 0, tile_mask = 0;
+    unsigned long long tiles_of = 0;
     for (int q = 0; q < d.c; ++q) tiles_of |= 1ull << q;
     for (int i = 0; i < d.m; ++i) tiles_of |= 1ull << d.hi[i];
-    for (int q = 0, j = 0; q < h->n; ++q) {
-      if ((tiles_of >> q) & 1ull) continue;
-      if ((support >> q) & 1ull) tile_mask |= 1ull << j;
-      ++j;
-    }
+    const unsigned long long tile_mask = tile_mask_of(tiles_of, support, h->n);
     support |= tiles_of;
     launch_fused_rb(s, h->d_phi, h->n, d, dph, dfo, h->d_table, h->fused_rbits, B, stride, G, h->fused_flags, 0,
                     tile_mask);
@@ -1885,15 +1905,19 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
     for (size_t bi = 0; bi < h->bwd_blocks.size(); ++bi) {
       const FusedBlockDev& d = h->bwd_blocks[bi];
       const int kb = d.c + d.m;
-      const unsigned long long nt = h->bwd_tile0[bi] ? 1ull : 1ull << (h->n - kb);
+      const unsigned long long mask = h->bwd_mask[bi], nt = 1ull << __builtin_popcountll(mask);
+      const int sparse = __builtin_popcountll(mask) < h->n - kb ? 1 : 0;
       if (h->bwd_rb) {
         if (h->fused_flags & kFusedNonTemporal)
           hipLaunchKernelGGL((k_vqe_bwd_rb<3, true>), grid, dim3(1u << (kb - 3)), 2 * bwd_rb_tile_bytes(kb), s,
-                             h->d_phi, h->d_lam, h->n, d, dph, dro, h->d_table, stride, h->nslots, h->d_gpart, nt);
+                             h->d_phi, h->d_lam, h->n, d, dph, dro, h->d_table, stride, h->nslots, h->d_gpart, nt, sparse,
+                             mask);
         else
           hipLaunchKernelGGL((k_vqe_bwd_rb<3, false>), grid, dim3(1u << (kb - 3)), 2 * bwd_rb_tile_bytes(kb), s,
-                             h->d_phi, h->d_lam, h->n, d, dph, dro, h->d_table, stride, h->nslots, h->d_gpart, nt);
+                             h->d_phi, h->d_lam, h->n, d, dph, dro, h->d_table, stride, h->nslots, h->d_gpart, nt, sparse,
+                             mask);
       } else {
+        // tiles below 2^9 entries: the whole state is one tile
         const size_t lds = 2 * sizeof(double2) << kb;
         hipLaunchKernelGGL(k_vqe_bwd_tile, grid, dim3(kBwdBlock), lds, s, h->d_phi, h->d_lam, h->n, d, dbo,
                            h->d_table, stride, h->nslots, h->d_gpart, nt);

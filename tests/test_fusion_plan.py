@@ -59,3 +59,11 @@ def test_plan_rejects_bad_input(nwq):
         nwq.nwq_fusion_plan(4, 8, types, qs)      # qubit 4 out of range
     with pytest.raises(nwq.NwqError):
         nwq.nwq_fusion_plan(8, 5, types, qs)      # width below 6
+
+
+@pytest.mark.parametrize("n,k,at_most", [(20, 10, 30), (20, 12, 20), (30, 12, 40), (30, 13, 36)])
+def test_blocks_follow_the_light_cone(nwq, n, k, at_most):
+    """A block of w high bits can hold a cone of the brickwork about w/2
+    layers deep (w^2/4 of its pairs), so the planner must need far fewer
+    blocks than taking gates in list order (73 at n=30, k=13)."""
+    assert check_plan(nwq, W.brickwork_circuit(n, 40, seed=0), n, k) <= at_most
