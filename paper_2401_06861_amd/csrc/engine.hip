@@ -496,6 +496,33 @@ extern "C" {
 
 const char* nwq_last_error(void) { return g_last_error.c_str(); }
 
+// Launch shapes of a handle that has not been autotuned.  Up to 2^25 entries
+// (512 MB, partly held by the 256 MB Infinity Cache between gates) the
+// autotuner picks four groups per thread with plain accesses on most bits
+// (n=24: 62-64 us per dense 1q gate, 2q DM gates with one 16-entry group).
+// Above, every pass streams from HBM and it picks, with the non-temporal
+// hint, one entry per thread: the split workgroups (32, 64, 128) or the
+// XCD-contiguous diagonal kernel; the plain shapes take 1.58 instead of 1.27
+// ms per U3 at n=28 and 0.39 instead of 0.31-0.35 ms per noisy gate on 13
+// qubits.
+static void default_shapes(nwq_state* h) {
+  auto set = [&](int cls, LaunchCfg low, LaunchCfg mid, LaunchCfg high) {
+    h->cfg[cls][0] = low;
+    h->cfg[cls][1] = mid;
+    h->cfg[cls][2] = high;
+  };
+  if (h->nbits < 26) {
+    set(KC_DM2, {1, 0}, {1, 0}, {1, 0});
+    return;
+  }
+  set(KC_SV1Q, {64, 3}, {64, 3}, {128, 3});
+  set(KC_DIAG, {1, 3}, {1, 3}, {1, 3});
+  set(KC_PERM, {32, 3}, {32, 3}, {128, 3});
+  set(KC_SV2Q, {1, 0}, {32, 1}, {32, 1});
+  set(KC_DM1, {4, 1}, {32, 1}, {32, 1});
+  set(KC_DM2, {1, 1}, {64, 1}, {64, 1});
+}
+
 static int create_common(int kind, int n, void* dev_ptr, void* stream, nwq_handle* out) {
   if (out == nullptr) return set_error(NWQ_EINVAL, "out handle pointer is NULL");
   *out = nullptr;
@@ -503,10 +530,10 @@ static int create_common(int kind, int n, void* dev_ptr, void* stream, nwq_handl
   if (n < 1 || n > nmax)
     return set_error(NWQ_ERANGE, "n=" + std::to_string(n) + " outside [1, " + std::to_string(nmax) + "]");
   std::unique_ptr<nwq_state> h(new nwq_state());
-  for (int b = 0; b < kBuckets; ++b) h->cfg[KC_DM2][b].ppt = 1;   // one 16-entry group per thread
   h->kind = kind;
   h->n = n;
   h->nbits = kind == NWQ_KIND_SV ? n : 2 * n;
+  default_shapes(h.get());
   h->len = 1ull << h->nbits;
   h->stream = static_cast<hipStream_t>(stream);
   if (dev_ptr != nullptr) {
