@@ -238,89 +238,226 @@ int local_bit(const Block& b, int q) {
   return -1;
 }
 
-// Encode one gate as a FusedOp (bits are tile-local for the per-gate LDS
-// kernel, register-bit indices for the register-blocked kernel) and append
-// its matrix entries.  Returns false for the identity (nothing to do).
-static bool encode_op(const PGate& g, int b0, int b1, std::vector<double2>& mats, FusedOp& op, bool reg,
+// Encode one gate as a FusedOp of the per-gate LDS kernel (tile-local bits)
+// and append its matrix entries.  Returns false for the identity (nothing to do).
+static bool encode_op(const PGate& g, int b0, int b1, std::vector<double2>& mats, FusedOp& op,
                       const std::vector<cd>* side) {
+  cd own[16];
+  const cd* m = own;
+  if (g.type == kGateDiag4 || g.type == kGateMat2 || g.type == kGateMat4) m = side->data() + (size_t)g.p[0];
+  else gate_matrix(g.type, g.p, own);
   op = FusedOp{};
-  if (g.type == kGateDiag4) {   // diagonal 4x4 from the side table, operator order (q[0], q[1])
-    op.mat = (int)mats.size();
-    op.lo = std::min(b0, b1);
-    op.hi = std::max(b0, b1);
-    op.kind = 4;
-    op.o0 = b0;
-    op.o1 = b1;
-    const cd* M = side->data() + (size_t)g.p[0];
-    for (int u = 0; u < 4; ++u) mats.push_back(make_double2(M[5 * u].real(), M[5 * u].imag()));
-    return true;
-  }
-  if (g.type == kGateMat2) {   // 2x2 from the side table
-    const cd* M = side->data() + (size_t)g.p[0];
-    op.mat = (int)mats.size();
-    op.lo = b0;
-    if (M[1] == 0.0 && M[2] == 0.0) {
-      op.kind = 1;
-      mats.push_back(make_double2(M[0].real(), M[0].imag()));
-      mats.push_back(make_double2(M[3].real(), M[3].imag()));
-      return true;
-    }
-    op.kind = 0;
-    bool real = true;
-    for (int i = 0; i < 4; ++i) real = real && M[i].imag() == 0.0;
-    op.real00 = real ? 2 : (M[0].imag() == 0.0 ? 1 : 0);
-    for (int i = 0; i < 4; ++i) mats.push_back(make_double2(M[i].real(), M[i].imag()));
-    return true;
-  }
-  if (g.type == kGateMat4) {   // dense 4x4 from the side table, operator order (q[0], q[1])
-    op.mat = (int)mats.size();
-    op.lo = std::min(b0, b1);
-    op.hi = std::max(b0, b1);
-    op.kind = 2;
-    op.o0 = reg ? b0 : (1 << b0);
-    op.o1 = reg ? b1 : (1 << b1);
-    const cd* M = side->data() + (size_t)g.p[0];
-    for (int i = 0; i < 16; ++i) mats.push_back(make_double2(M[i].real(), M[i].imag()));
-    return true;
-  }
-  cd m[16];
-  gate_matrix(g.type, g.p, m);
   op.mat = (int)mats.size();
   op.lo = g.nq == 2 ? std::min(b0, b1) : b0;
   op.hi = g.nq == 2 ? std::max(b0, b1) : 0;
+  auto put = [&](const cd& v) { mats.push_back(make_double2(v.real(), v.imag())); };
   switch (g.type) {
     case NWQ_GATE_I:
       return false;
-    case NWQ_GATE_Z: case NWQ_GATE_S: case NWQ_GATE_SDG: case NWQ_GATE_T: case NWQ_GATE_TDG: case NWQ_GATE_RZ:
-      op.kind = 1;
-      mats.push_back(make_double2(m[0].real(), m[0].imag()));
-      mats.push_back(make_double2(m[3].real(), m[3].imag()));
-      return true;
     case NWQ_GATE_CX:
       op.kind = 3;
-      op.o0 = reg ? b0 : (1 << b0);
-      op.o1 = reg ? b1 : (1 << b0) + (1 << b1);
+      op.o0 = 1 << b0;
+      op.o1 = (1 << b0) + (1 << b1);
       return true;
     case NWQ_GATE_SWAP:
-      op.kind = reg ? 5 : 3;
-      op.o0 = reg ? b0 : (1 << b0);
-      op.o1 = reg ? b1 : (1 << b1);
+      op.kind = 3;
+      op.o0 = 1 << b0;
+      op.o1 = 1 << b1;
       return true;
-    case NWQ_GATE_CZ: case NWQ_GATE_RZZ:
+    case NWQ_GATE_CZ: case NWQ_GATE_RZZ: case kGateDiag4:   // operator order (q[0], q[1])
       op.kind = 4;
       op.o0 = b0;
       op.o1 = b1;
-      for (int u = 0; u < 4; ++u) mats.push_back(make_double2(m[5 * u].real(), m[5 * u].imag()));
+      for (int u = 0; u < 4; ++u) put(m[5 * u]);
+      return true;
+    case kGateMat4:   // operator order (q[0], q[1])
+      op.kind = 2;
+      op.o0 = 1 << b0;
+      op.o1 = 1 << b1;
+      for (int i = 0; i < 16; ++i) put(m[i]);
       return true;
     default:
-      op.kind = 0;
-      op.real00 = (m[0].imag() == 0.0 && m[1].imag() == 0.0 && m[2].imag() == 0.0 && m[3].imag() == 0.0)
-                      ? 2
-                      : (m[0].imag() == 0.0 ? 1 : 0);
-      for (int i = 0; i < 4; ++i) mats.push_back(make_double2(m[i].real(), m[i].imag()));
+      if (m[1] == 0.0 && m[2] == 0.0) {
+        op.kind = 1;
+        put(m[0]);
+        put(m[3]);
+      } else {
+        op.kind = 0;
+        for (int i = 0; i < 4; ++i) put(m[i]);
+      }
       return true;
   }
 }
+
+// ---------------------------------------------------------------------------
+// Ops of a register phase (register-blocked kernels)
+// ---------------------------------------------------------------------------
+namespace {
+
+struct RegOp {
+  enum Kind { DENSE1, DENSE2, CX, SWAP, DIAG, DENSE16 } kind;
+  int b0 = 0, b1 = 0;        // register bits, operator order (CX: control, target)
+  unsigned bits = 0;         // register bits it acts on (DIAG: bits its entries depend on)
+  std::vector<cd> m;         // DENSE1: 2x2; DENSE2: 4x4 in the order (b0, b1); DIAG: an entry per
+                             // register; DENSE16: the 16x16 in register order
+  bool perm() const { return kind == CX || kind == SWAP; }
+  int map(int j) const { return kind == CX ? reg_cx(b0, b1, j) : reg_swap(b0, b1, j); }
+};
+
+// Gate g on register bits rb[0 .. nq).  Returns false for the identity.
+bool make_reg_op(const PGate& g, const int* rb, int rbits, const std::vector<cd>* side, RegOp& op) {
+  const int nv = 1 << rbits;
+  cd own[16];
+  const cd* m = own;
+  if (g.type >= kGateMat4) m = side->data() + (size_t)g.p[0];
+  else gate_matrix(g.type, g.p, own);
+  op = RegOp{};
+  op.b0 = rb[0];
+  op.b1 = g.nq >= 2 ? rb[1] : 0;
+  for (int t = 0; t < g.nq; ++t) op.bits |= 1u << rb[t];
+  switch (g.type) {
+    case NWQ_GATE_I:
+      return false;
+    case NWQ_GATE_CX:
+      op.kind = RegOp::CX;
+      return true;
+    case NWQ_GATE_SWAP:
+      op.kind = RegOp::SWAP;
+      return true;
+    case NWQ_GATE_CZ: case NWQ_GATE_RZZ: case kGateDiag4:
+      op.kind = RegOp::DIAG;
+      for (int j = 0; j < nv; ++j) op.m.push_back(m[5 * (((j >> rb[0]) & 1) + 2 * ((j >> rb[1]) & 1))]);
+      return true;
+    case kGateMat4:
+      op.kind = RegOp::DENSE2;
+      op.m.assign(m, m + 16);
+      return true;
+    case kGateMat16: {   // operator index bit t on register bit rb[t]
+      op.kind = RegOp::DENSE16;
+      int inv[16];
+      for (int u = 0; u < 16; ++u) {
+        int j = 0;
+        for (int t = 0; t < 4; ++t) j |= ((u >> t) & 1) << rb[t];
+        inv[j] = u;
+      }
+      op.m.resize(256);
+      for (int r = 0; r < 16; ++r)
+        for (int c = 0; c < 16; ++c) op.m[r * 16 + c] = m[inv[r] * 16 + inv[c]];
+      return true;
+    }
+    default:
+      if (m[1] == 0.0 && m[2] == 0.0) {
+        op.kind = RegOp::DIAG;
+        for (int j = 0; j < nv; ++j) op.m.push_back(m[((j >> rb[0]) & 1) ? 3 : 0]);
+      } else {
+        op.kind = RegOp::DENSE1;
+        op.m.assign(m, m + 4);
+      }
+      return true;
+  }
+}
+
+// Diagonal ops of a phase move to the front, past ops on other bits and past
+// permutations (D P = P D' with D'[j] = D[P(j)]), and merge with a diagonal
+// they meet: the kernel applies any diagonal over the register bits with one
+// complex product per amplitude, so the RZZ chain of a Trotter step costs one
+// op per phase instead of one per gate.
+void merge_diagonals(std::vector<RegOp>& ops, int rbits) {
+  const int nv = 1 << rbits;
+  std::vector<RegOp> out;
+  for (RegOp& op : ops) {
+    if (op.kind != RegOp::DIAG) {
+      out.push_back(std::move(op));
+      continue;
+    }
+    std::vector<cd> d = op.m, keep = op.m;   // keep: its form behind the op it stops at
+    unsigned bits = op.bits;
+    bool merged = false;
+    for (size_t i = out.size(); i-- > 0;) {
+      RegOp& o = out[i];
+      if (o.kind == RegOp::DIAG) {
+        for (int j = 0; j < nv; ++j) o.m[j] *= d[j];
+        o.bits |= bits;
+        merged = true;
+        break;
+      }
+      if (!(o.bits & bits)) continue;
+      if (!o.perm()) break;
+      std::vector<cd> e(nv);
+      for (int j = 0; j < nv; ++j) e[j] = d[o.map(j)];
+      d.swap(e);
+      bits |= o.bits;
+    }
+    if (!merged) {
+      op.m = keep;
+      out.push_back(std::move(op));
+    }
+  }
+  ops.swap(out);
+}
+
+// The op's code, its entries appended to mats.
+RbOp emit_reg_op(const RegOp& op, int set, std::vector<double2>& mats) {
+  RbOp o{kRbCopy, (int)mats.size()};
+  auto put = [&](const cd& v) { mats.push_back(make_double2(v.real(), v.imag())); };
+  auto real = [](const cd& v) { return v.imag() == 0.0; };
+  auto imag = [](const cd& v) { return v.real() == 0.0; };
+  const std::vector<cd>& m = op.m;
+  switch (op.kind) {
+    case RegOp::CX:
+      o.code = rb_cx_code(op.b0, op.b1);
+      break;
+    case RegOp::SWAP:
+      o.code = kRbSwap + rb_pair(std::min(op.b0, op.b1), std::max(op.b0, op.b1));
+      break;
+    case RegOp::DIAG:
+      o.code = kRbDiagAll;
+      for (const cd& v : m) put(v);
+      break;
+    case RegOp::DENSE1:
+      if (real(m[0]) && real(m[1]) && real(m[2]) && real(m[3])) o.code = kRbReal1 + op.b0;
+      else if (real(m[0]) && imag(m[1]) && imag(m[2]) && real(m[3])) o.code = kRbXt1 + op.b0;
+      else if (real(m[0])) o.code = kRbR001 + op.b0;
+      else o.code = kRbGen1 + op.b0;
+      for (const cd& v : m) put(v);
+      break;
+    case RegOp::DENSE2: {
+      const bool sw = op.b0 > op.b1;   // to index order (lower bit, higher bit)
+      auto at = [&](int u) { return sw ? ((u & 1) << 1) | (u >> 1) : u; };
+      bool all_real = set == kRbSetDM, parity = set == kRbSetDM;
+      for (int r = 0; r < 4; ++r)
+        for (int c = 0; c < 4; ++c) {
+          const cd v = m[at(r) * 4 + at(c)];
+          put(v);
+          all_real = all_real && real(v);
+          parity = parity && (__builtin_popcount(r ^ c) % 2 == 0 ? real(v) : imag(v));
+        }
+      o.code = (all_real ? kRbReal2 : (parity ? kRbPar2 : kRbDense2)) + rb_pair(std::min(op.b0, op.b1), std::max(op.b0, op.b1));
+      break;
+    }
+    case RegOp::DENSE16: {
+      // a Pauli channel after a diagonal gate (RZZ, CZ, ...) leaves the
+      // entries of rho off the 4x4 diagonal scaled and mixes only the
+      // diagonal ones (registers 0, 5, 10, 15 in either qubit order)
+      bool pauli = true;
+      for (int r = 0; r < 16 && pauli; ++r)
+        for (int c = 0; c < 16 && pauli; ++c)
+          if (r != c && !(r % 5 == 0 && c % 5 == 0) && m[r * 16 + c] != 0.0) pauli = false;
+      o.code = pauli ? kRbPauli16 : kRbDense16;
+      if (pauli) {
+        for (int u = 0; u < 16; ++u) put(m[u * 17]);
+        for (int i = 0; i < 4; ++i)
+          for (int j = 0; j < 4; ++j) put(m[5 * i * 16 + 5 * j]);
+      } else {
+        for (const cd& v : m) put(v);
+      }
+      break;
+    }
+  }
+  return o;
+}
+
+}  // namespace
 
 // ---------------------------------------------------------------------------
 // Gate products.  A two-qubit gate takes the one-qubit gates next to it on
@@ -351,9 +488,10 @@ bool is_diag(const cd* m, int dim) {
 int matrix_cost(const cd* m, int nb) {
   if (nb == 2) return is_diag(m, 4) ? 4 : 16;
   if (is_diag(m, 2)) return 4;
-  bool real = true;
-  for (int i = 0; i < 4; ++i) real = real && m[i].imag() == 0.0;
-  return real ? 4 : (m[0].imag() == 0.0 ? 7 : 8);
+  auto real = [](const cd& v) { return v.imag() == 0.0; };
+  auto imag = [](const cd& v) { return v.real() == 0.0; };
+  if (real(m[0]) && real(m[3]) && ((real(m[1]) && real(m[2])) || (imag(m[1]) && imag(m[2])))) return 4;
+  return real(m[0]) ? 7 : 8;
 }
 
 int gate_cost(const PGate& g) {
@@ -620,8 +758,10 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
   if (blocks.empty()) return set_error(NWQ_EINVAL, "fusion planner made no progress");
   // Program: [phase table][op table][matrix table] in one upload.
   std::vector<FusedPhase> phases;
-  std::vector<FusedOp> ops;
+  std::vector<FusedOp> ops;    // per-gate LDS kernel
+  std::vector<RbOp> rops;      // register-blocked kernels
   std::vector<double2> mats;
+  const int set = h->kind == NWQ_KIND_DM ? kRbSetDM : kRbSetSV;
   struct Launch { FusedBlockDev d; bool rb; int rbits; };
   std::vector<Launch> launches;
   for (Block b : blocks) {
@@ -639,7 +779,7 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
         const PGate& g = gates[gi];
         if (g.nq > 2) return set_error(NWQ_EINVAL, "a four-bit operator needs the register-blocked kernel");
         FusedOp op;
-        if (encode_op(g, local_bit(b, g.q[0]), g.nq == 2 ? local_bit(b, g.q[1]) : 0, mats, op, false, side))
+        if (encode_op(g, local_bit(b, g.q[0]), g.nq == 2 ? local_bit(b, g.q[1]) : 0, mats, op, side))
           ops.push_back(op);
       }
       d.op_count = (int)ops.size() - d.op_begin;
@@ -662,76 +802,37 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
     }
     if (order.empty()) continue;
     d.op_begin = (int)phases.size();
+    const size_t rops0 = rops.size(), mats0 = mats.size();
     for (const Phase& ph : plan_phases(order, lb, nq, k, b.c, rbits)) {
       FusedPhase fp{};
       for (int i = 0; i < 4; ++i) fp.reg[i] = ph.reg[i] < 0 ? 0 : ph.reg[i];
-      fp.op_begin = (int)ops.size();
+      fp.op_begin = (int)rops.size();
       auto ridx = [&](int bit) {
         for (int i = 0; i < rbits; ++i)
           if (ph.reg[i] == bit) return i;
         return -1;
       };
-      std::vector<FusedOp> pops;
+      std::vector<RegOp> pops;
       for (int li : ph.gates) {
-        const PGate& gate = gates[gid[li]];
-        if (gate.type == kGateMat16) {   // all four register bits: the matrix in register order
-          FusedOp op{};
-          op.kind = 7;
-          op.mat = (int)mats.size();
-          int rt[4];
-          for (int t = 0; t < 4; ++t) rt[t] = ridx(lb[li][t]);
-          auto reg_index = [&](int u) {   // operator index -> register index
-            int j = 0;
-            for (int t = 0; t < 4; ++t) j |= ((u >> t) & 1) << rt[t];
-            return j;
-          };
-          int inv[16];
-          for (int u = 0; u < 16; ++u) inv[reg_index(u)] = u;
-          const cd* M = side->data() + (size_t)gate.p[0];
-          cd P[256];
-          for (int r = 0; r < 16; ++r)
-            for (int c2 = 0; c2 < 16; ++c2) P[r * 16 + c2] = M[inv[r] * 16 + inv[c2]];
-          // a Pauli channel after a diagonal gate (RZZ, CZ, ...) leaves the
-          // entries of rho off the 4x4 diagonal scaled and mixes only the
-          // diagonal ones (registers 0, 5, 10, 15 in either qubit order)
-          auto blk = [](int u) { return u % 5 == 0; };
-          bool pauli = true;
-          for (int r = 0; r < 16 && pauli; ++r)
-            for (int c2 = 0; c2 < 16 && pauli; ++c2)
-              if (r != c2 && !(blk(r) && blk(c2)) && P[r * 16 + c2] != 0.0) pauli = false;
-          if (pauli) {
-            op.kind = 8;
-            for (int u = 0; u < 16; ++u) mats.push_back(make_double2(P[u * 17].real(), P[u * 17].imag()));
-            for (int i = 0; i < 4; ++i)
-              for (int j = 0; j < 4; ++j) mats.push_back(make_double2(P[5 * i * 16 + 5 * j].real(), P[5 * i * 16 + 5 * j].imag()));
-          } else {
-            for (int i = 0; i < 256; ++i) mats.push_back(make_double2(P[i].real(), P[i].imag()));
-          }
-          op.code = rb_op_code(op);
-          pops.push_back(op);
-          continue;
-        }
-        FusedOp op;
-        if (encode_op(gate, ridx(lb[li][0]), nq[li] == 2 ? ridx(lb[li][1]) : 0, mats, op, true, side)) {
-          op.code = rb_op_code(op);
-          pops.push_back(op);
-        }
+        int rb_bits[4] = {0, 0, 0, 0};
+        for (int t = 0; t < nq[li]; ++t) rb_bits[t] = ridx(lb[li][t]);
+        RegOp op;
+        if (make_reg_op(gates[gid[li]], rb_bits, rbits, side, op)) pops.push_back(std::move(op));
       }
+      if (h->fuse_flags & kFusedGateFusion) merge_diagonals(pops, rbits);
       int ld_perm[16], st_perm[16];
       fold_permutations(
-          pops, rbits, [](const FusedOp& o) { return o.kind == 3 || o.kind == 5; },
-          [](const FusedOp& o) {
-            if (o.kind == 7 || o.kind == 8) return 15u;
-            return (o.kind == 0 || o.kind == 1 || o.kind == 6) ? (1u << o.lo) : ((1u << o.o0) | (1u << o.o1));
-          },
-          [](const FusedOp& o, int j) { return o.kind == 3 ? reg_cx(o.o0, o.o1, j) : reg_swap(o.o0, o.o1, j); },
-          ld_perm, st_perm);
-      ops.insert(ops.end(), pops.begin(), pops.end());
-      fp.op_count = (int)ops.size() - fp.op_begin;
+          pops, rbits, [](const RegOp& o) { return o.perm(); }, [](const RegOp& o) { return o.bits; },
+          [](const RegOp& o, int j) { return o.map(j); }, ld_perm, st_perm);
+      for (const RegOp& o : pops) rops.push_back(emit_reg_op(o, set, mats));
+      if (rbits == 4 && pops.size() % 2) rops.push_back(RbOp{kRbCopy, rops.back().mat});
+      fp.op_count = (int)rops.size() - fp.op_begin;
       fill_phase_offsets(fp, rbits, ld_perm, st_perm);
       phases.push_back(fp);
     }
     d.op_count = (int)phases.size() - d.op_begin;
+    d.prog_ops = (int)(rops.size() - rops0);
+    d.prog_mats = (int)(mats.size() - mats0);
     fill_entry_offsets(d, rbits);
     set_direct_io(d, phases[d.op_begin], phases.back(), rbits);
     launches.push_back({d, true, rbits});
@@ -739,11 +840,15 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
   const size_t ph_bytes = phases.size() * sizeof(FusedPhase);
   const size_t ops_off = (ph_bytes + 255) & ~size_t(255);
   const size_t ops_bytes = ops.size() * sizeof(FusedOp);
-  const size_t mats_off = (ops_off + ops_bytes + 255) & ~size_t(255);
+  for (int i = 0; i < 2; ++i) rops.push_back(RbOp{kRbCopy, 0});   // read ahead, not run
+  const size_t rops_off = (ops_off + ops_bytes + 255) & ~size_t(255);
+  const size_t rops_bytes = rops.size() * sizeof(RbOp);
+  const size_t mats_off = (rops_off + rops_bytes + 255) & ~size_t(255);
   const size_t total = mats_off + mats.size() * sizeof(double2) + 16;
   std::vector<char> prog(total, 0);
   if (!phases.empty()) std::memcpy(prog.data(), phases.data(), ph_bytes);
   if (!ops.empty()) std::memcpy(prog.data() + ops_off, ops.data(), ops_bytes);
+  std::memcpy(prog.data() + rops_off, rops.data(), rops_bytes);
   if (!mats.empty()) std::memcpy(prog.data() + mats_off, mats.data(), mats.size() * sizeof(double2));
   void* dev = nullptr;
   if (total <= (2u << 20)) {
@@ -770,6 +875,7 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
   }
   const FusedPhase* dph = static_cast<const FusedPhase*>(dev);
   const FusedOp* dops = reinterpret_cast<const FusedOp*>(static_cast<char*>(dev) + ops_off);
+  const RbOp* drops = reinterpret_cast<const RbOp*>(static_cast<char*>(dev) + rops_off);
   const double2* dmats = reinterpret_cast<const double2*>(static_cast<char*>(dev) + mats_off);
   // From |0...0>, amplitudes can be nonzero only where every bit outside the
   // qubits touched so far (`support`) is zero; a block maps each tile to
@@ -786,8 +892,8 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
       support |= tiles_of;
     }
     timing_begin(h, KC_FUSED);
-    if (L.rb) launch_fused_rb(h->stream, h->data, h->nbits, L.d, dph, dops, dmats, L.rbits, 1, 0, 0, h->fuse_flags,
-                              0, tile_mask);
+    if (L.rb) launch_fused_rb(h->stream, h->data, h->nbits, L.d, dph, drops, dmats, L.rbits, set, 1, 0, 0,
+                              h->fuse_flags, tile_mask);
     else launch_fused_block(h->stream, h->data, h->nbits, L.d, dops, dmats, h->fuse_k);
     timing_end(h);
     const int rc = check_hip(hipGetLastError(), "fused_block");

@@ -193,22 +193,28 @@ __device__ __forceinline__ unsigned padl(unsigned l) { return l + (l >> 4); }
 // reads (an in-place update ends every op with a copy of all 16 amplitudes
 // back into the loop-carried registers).  With 3 register bits the second set
 // would push the kernel past 128 VGPRs, so it updates in place.
-// R00: M[0][0] is real (U3, RX), its imaginary part is not read and the
-// first output of a pair takes two FMAs fewer.  REAL: all of M is real (RY,
-// H): four FP64 operations per output instead of eight.
-template <int NV, int B, bool R00 = false, bool REAL = false>
+//
+// The parts of a matrix known to be zero are skipped.  2x2: KIND 0 general (8
+// FP64 instructions per amplitude), 1 a real M[0][0] (U3; 7), 2 real (RY, H;
+// 4), 3 real diagonal and imaginary off-diagonal entries (RX; 4).
+template <int NV, int B, int KIND>
 __device__ __forceinline__ void rb_dense1(const vd2 (&x)[NV], vd2 (&y)[NV], const double2* __restrict__ M) {
   const vd2 m0 = ldv(M), m1 = ldv(M + 1), m2 = ldv(M + 2), m3 = ldv(M + 3);
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     if (j & (1 << B)) continue;
     const vd2 a = x[j], b = x[j | (1 << B)];
-    if constexpr (REAL) {
+    if constexpr (KIND == 2) {
       y[j] = mkv(fma(m0.x, a.x, m1.x * b.x), fma(m0.x, a.y, m1.x * b.y));
       y[j | (1 << B)] = mkv(fma(m2.x, a.x, m3.x * b.x), fma(m2.x, a.y, m3.x * b.y));
       continue;
     }
-    if constexpr (R00) {
+    if constexpr (KIND == 3) {
+      y[j] = mkv(fma(m0.x, a.x, -(m1.y * b.y)), fma(m0.x, a.y, m1.y * b.x));
+      y[j | (1 << B)] = mkv(fma(m3.x, b.x, -(m2.y * a.y)), fma(m3.x, b.y, m2.y * a.x));
+      continue;
+    }
+    if constexpr (KIND == 1) {
       const vd2 c = vmul(m1, b);
       y[j] = mkv(fma(m0.x, a.x, c.x), fma(m0.x, a.y, c.y));
     } else {
@@ -218,8 +224,11 @@ __device__ __forceinline__ void rb_dense1(const vd2 (&x)[NV], vd2 (&y)[NV], cons
   }
 }
 
-// Dense 4x4 with operator index u = bit B0 + 2 bit B1.
-template <int NV, int B0, int B1>
+// 4x4 with operator index u = bit B0 + 2 bit B1 (B0 < B1: the host orders the
+// operator).  KIND 0 dense (16 FP64 instructions per amplitude); 1 all real
+// (8); 2 entry (r, c) real where r ^ c has even parity, else imaginary (the
+// superoperator of RX with its noise; 8).
+template <int NV, int B0, int B1, int KIND>
 __device__ __forceinline__ void rb_dense2(const vd2 (&x)[NV], vd2 (&y)[NV], const double2* __restrict__ M) {
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
@@ -230,10 +239,30 @@ __device__ __forceinline__ void rb_dense2(const vd2 (&x)[NV], vd2 (&y)[NV], cons
     for (int u = 0; u < 4; ++u) in[u] = x[idx[u]];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      vd2 acc = vmul(ldv(M + 4 * r), in[0]);
+      if constexpr (KIND == 0) {
+        vd2 acc = vmul(ldv(M + 4 * r), in[0]);
 #pragma unroll
-      for (int c = 1; c < 4; ++c) acc = vfma(ldv(M + 4 * r + c), in[c], acc);
-      y[idx[r]] = acc;
+        for (int c = 1; c < 4; ++c) acc = vfma(ldv(M + 4 * r + c), in[c], acc);
+        y[idx[r]] = acc;
+      } else {
+        // the diagonal entry is real in both kinds
+        const double d = M[5 * r].x;
+        double re = d * in[r].x, im = d * in[r].y;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          if (c == r) continue;
+          if (KIND == 1 || __builtin_popcount(r ^ c) % 2 == 0) {
+            const double m = M[4 * r + c].x;
+            re = fma(m, in[c].x, re);
+            im = fma(m, in[c].y, im);
+          } else {
+            const double m = M[4 * r + c].y;
+            re = fma(-m, in[c].y, re);
+            im = fma(m, in[c].x, im);
+          }
+        }
+        y[idx[r]] = mkv(re, im);
+      }
     }
   }
 }
@@ -290,9 +319,17 @@ __device__ __forceinline__ void rb_swap2(const vd2 (&x)[NV], vd2 (&y)[NV]) {
   }
 }
 
-// 1q diagonal on register bit B: entries d0 (bit 0), d1 (bit 1).
+// Diagonal over all register bits: entry j for register j.
+template <int NV>
+__device__ __forceinline__ void rb_diag_all(const vd2 (&x)[NV], vd2 (&y)[NV], const double2* __restrict__ M) {
+#pragma unroll
+  for (int j = 0; j < NV; ++j) y[j] = vmul(ldv(M + j), x[j]);
+}
+
+// 1q diagonal of a 2x2 table entry on register bit B (M[0], M[3]).
 template <int NV, int B>
-__device__ __forceinline__ void rb_diag1(const vd2 (&x)[NV], vd2 (&y)[NV], vd2 d0, vd2 d1) {
+__device__ __forceinline__ void rb_diag1(const vd2 (&x)[NV], vd2 (&y)[NV], const double2* __restrict__ M) {
+  const vd2 d0 = ldv(M), d1 = ldv(M + 3);
 #pragma unroll
   for (int j = 0; j < NV; ++j) y[j] = vmul(((j >> B) & 1) ? d1 : d0, x[j]);
 }
@@ -307,74 +344,95 @@ __device__ __forceinline__ void rb_diag2(const vd2 (&x)[NV], vd2 (&y)[NV], const
 
 // The case bodies of rb_apply; bit positions at or above R never occur for
 // that R (the guard keeps their templates from being instantiated).
-template <int R, int B>
-__device__ __forceinline__ void rb_c1(int sel, const vd2 (&x)[1 << R], vd2 (&y)[1 << R], const double2* M) {
+template <int R, int B, int SEL>   // SEL: rb_dense1's KIND, or 4 = rb_diag1
+__device__ __forceinline__ void rb_c1(const vd2 (&x)[1 << R], vd2 (&y)[1 << R], const double2* M) {
   if constexpr (B < R) {
-    if (sel == 0) rb_dense1<(1 << R), B>(x, y, M);
-    else if (sel == 3) rb_dense1<(1 << R), B, true>(x, y, M);
-    else if (sel == 4) rb_dense1<(1 << R), B, false, true>(x, y, M);
-    else rb_diag1<(1 << R), B>(x, y, ldv(M), ldv(M + (sel == 1 ? 1 : 3)));
+    if constexpr (SEL == 4) rb_diag1<(1 << R), B>(x, y, M);
+    else rb_dense1<(1 << R), B, SEL>(x, y, M);
   }
 }
-template <int R, int B0, int B1>
-__device__ __forceinline__ void rb_c2(int sel, const vd2 (&x)[1 << R], vd2 (&y)[1 << R], const double2* M) {
+template <int R, int B0, int B1, int SEL>   // SEL: rb_dense2's KIND, 3 SWAP, 4 diagonal
+__device__ __forceinline__ void rb_c2(const vd2 (&x)[1 << R], vd2 (&y)[1 << R], const double2* M) {
   constexpr int NV = 1 << R;
-  if constexpr (B0 < R && B1 < R) {
-    if (sel == 0) rb_dense2<NV, B0, B1>(x, y, M);
-    else if (sel == 1) rb_swap2<NV, B0, B1, (1 << B0), (1 << B0) | (1 << B1)>(x, y);   // CX: control B0, target B1
-    else if (sel == 2) rb_swap2<NV, B0, B1, (1 << B0), (1 << B1)>(x, y);                 // SWAP
-    else rb_diag2<NV, B0, B1>(x, y, M);
+  if constexpr (B1 < R) {
+    if constexpr (SEL == 3) rb_swap2<NV, B0, B1, (1 << B0), (1 << B1)>(x, y);
+    else if constexpr (SEL == 4) rb_diag2<NV, B0, B1>(x, y, M);
+    else rb_dense2<NV, B0, B1, SEL>(x, y, M);
   }
+}
+template <int R, int C, int T>   // CX: control C, target T
+__device__ __forceinline__ void rb_cx(const vd2 (&x)[1 << R], vd2 (&y)[1 << R]) {
+  if constexpr (C < R && T < R) rb_swap2<(1 << R), (C < T ? C : T), (C < T ? T : C), (1 << C), (1 << C) | (1 << T)>(x, y);
 }
 
-// One gate: a single switch over the op's code (rb_op_code); every case is
-// specialised on its register bits, so diagonals select their entries at
-// compile time.
-template <int R>
+// One gate: a switch over the op's code; every case is specialised on its
+// register bits.  The compiler turns the switch into a tree of compares and
+// the cases are straight-line FP64 code, so the set of cases is kept to what
+// a kind of program can hold (SET): with every kind in one kernel the two
+// register sets took 99 KB of code, more than the 64 KB instruction cache two
+// compute units share.
+template <int R, int SET>
 __device__ __forceinline__ void rb_apply(int code, const double2* __restrict__ M, const vd2 (&x)[1 << R],
                                          vd2 (&y)[1 << R]) {
   constexpr int NV = 1 << R;
 #define NWQ_RB1(BASE, SEL) \
-  case BASE + 0: rb_c1<R, 0>(SEL, x, y, M); break; \
-  case BASE + 1: rb_c1<R, 1>(SEL, x, y, M); break; \
-  case BASE + 2: rb_c1<R, 2>(SEL, x, y, M); break; \
-  case BASE + 3: rb_c1<R, 3>(SEL, x, y, M); break;
+  case BASE + 0: rb_c1<R, 0, SEL>(x, y, M); return; \
+  case BASE + 1: rb_c1<R, 1, SEL>(x, y, M); return; \
+  case BASE + 2: rb_c1<R, 2, SEL>(x, y, M); return; \
+  case BASE + 3: rb_c1<R, 3, SEL>(x, y, M); return;
 #define NWQ_RB2(BASE, SEL) \
-  case BASE + 1: rb_c2<R, 0, 1>(SEL, x, y, M); break; \
-  case BASE + 2: rb_c2<R, 0, 2>(SEL, x, y, M); break; \
-  case BASE + 3: rb_c2<R, 0, 3>(SEL, x, y, M); break; \
-  case BASE + 4: rb_c2<R, 1, 0>(SEL, x, y, M); break; \
-  case BASE + 6: rb_c2<R, 1, 2>(SEL, x, y, M); break; \
-  case BASE + 7: rb_c2<R, 1, 3>(SEL, x, y, M); break; \
-  case BASE + 8: rb_c2<R, 2, 0>(SEL, x, y, M); break; \
-  case BASE + 9: rb_c2<R, 2, 1>(SEL, x, y, M); break; \
-  case BASE + 11: rb_c2<R, 2, 3>(SEL, x, y, M); break; \
-  case BASE + 12: rb_c2<R, 3, 0>(SEL, x, y, M); break; \
-  case BASE + 13: rb_c2<R, 3, 1>(SEL, x, y, M); break; \
-  case BASE + 14: rb_c2<R, 3, 2>(SEL, x, y, M); break;
-  switch (code) {
-    NWQ_RB1(0, 0)
-    NWQ_RB1(4, 1)
-    NWQ_RB1(8, 2)
-    NWQ_RB1(84, 3)
-    NWQ_RB1(88, 4)
-    NWQ_RB2(16, 0)
-    NWQ_RB2(32, 1)
-    NWQ_RB2(48, 2)
-    NWQ_RB2(64, 3)
-    case kRbCodeDense16:
-      rb_dense16<NV>(x, y, M);
-      break;
-    case kRbCodePauli16:
-      rb_pauli16<NV>(x, y, M);
-      break;
-    default:   // kRbCodeCopy
-#pragma unroll
-      for (int j = 0; j < NV; ++j) y[j] = x[j];
-      break;
+  case BASE + 0: rb_c2<R, 0, 1, SEL>(x, y, M); return; \
+  case BASE + 1: rb_c2<R, 0, 2, SEL>(x, y, M); return; \
+  case BASE + 2: rb_c2<R, 1, 2, SEL>(x, y, M); return; \
+  case BASE + 3: rb_c2<R, 0, 3, SEL>(x, y, M); return; \
+  case BASE + 4: rb_c2<R, 1, 3, SEL>(x, y, M); return; \
+  case BASE + 5: rb_c2<R, 2, 3, SEL>(x, y, M); return;
+#define NWQ_RBX(P, LO, HI) \
+  case kRbCx + 2 * P: rb_cx<R, LO, HI>(x, y); return; \
+  case kRbCx + 2 * P + 1: rb_cx<R, HI, LO>(x, y); return;
+  if constexpr (SET == kRbSetDM) {
+    switch (code) {
+      NWQ_RB2(kRbDense2, 0)
+      NWQ_RB2(kRbReal2, 1)
+      NWQ_RB2(kRbPar2, 2)
+      case kRbDense16: rb_dense16<NV>(x, y, M); return;
+      case kRbPauli16: rb_pauli16<NV>(x, y, M); return;
+      default: break;
+    }
+  } else {
+    switch (code) {
+      NWQ_RB1(kRbGen1, 0)
+      NWQ_RB1(kRbReal1, 2)
+      NWQ_RB1(kRbXt1, 3)
+      NWQ_RBX(0, 0, 1)
+      NWQ_RBX(1, 0, 2)
+      NWQ_RBX(2, 1, 2)
+      NWQ_RBX(3, 0, 3)
+      NWQ_RBX(4, 1, 3)
+      NWQ_RBX(5, 2, 3)
+      NWQ_RB2(kRbSwap, 3)
+      default: break;
+    }
+    if constexpr (SET == kRbSetSV) {
+      switch (code) {
+        NWQ_RB1(kRbR001, 1)
+        NWQ_RB2(kRbDense2, 0)
+        case kRbDiagAll: rb_diag_all<NV>(x, y, M); return;
+        default: break;
+      }
+    } else {
+      switch (code) {
+        NWQ_RB1(kRbDiag1, 4)
+        NWQ_RB2(kRbDiag2, 4)
+        default: break;
+      }
+    }
   }
+#pragma unroll
+  for (int j = 0; j < NV; ++j) y[j] = x[j];   // kRbCopy
 #undef NWQ_RB1
 #undef NWQ_RB2
+#undef NWQ_RBX
 }
 
 // Writes the 2^R registers of a phase back to their LDS entries.
@@ -408,6 +466,7 @@ struct RbBlockArgs {
   int op_begin, op_count;
   int direct;
   int sparse;                  // tiles t = 0, 1, ... are tile indices pdep(t, tmask)
+  int warm_ops, warm_mats;     // ops and matrix entries of the block, from its first (0: not warmed)
   unsigned long long tmask;
   unsigned long long lo[16], so[16];
 };
@@ -420,11 +479,11 @@ __device__ __forceinline__ unsigned long long pdep64(unsigned long long v, unsig
   return r;
 }
 
-template <int R, bool NT>
+template <int R, int SET, bool NT>
 __global__ __launch_bounds__(R == 4 ? 512 : 1024) void k_fused_rb(double2* __restrict__ a0, int nbits,
                                                                   RbBlockArgs blk,
                                                                   const FusedPhase* __restrict__ phases,
-                                                                  const FusedOp* __restrict__ ops,
+                                                                  const RbOp* __restrict__ ops,
                                                                   const double2* __restrict__ mats0,
                                                                   unsigned long long state_stride, int mat_stride,
                                                                   unsigned long long ntiles) {
@@ -495,6 +554,26 @@ __global__ __launch_bounds__(R == 4 ? 512 : 1024) void k_fused_rb(double2* __res
   };
   unsigned long long tile = blockIdx.x;
   load_tile(tile);
+  // Behind the first tile's loads, one load per 64-byte line brings the
+  // block's program into this XCD's L2: each phase and op is read through the
+  // scalar cache when its turn comes, one after the other, and a workgroup
+  // with few tiles would wait out a miss to memory for every one of them.
+  {
+    int x = 0;
+    const char* pp = reinterpret_cast<const char*>(phases + blk.op_begin);
+    const RbOp* po = ops + phases[blk.op_begin].op_begin;
+    for (unsigned i = tid * 64u; i < P * sizeof(FusedPhase); i += nt * 64u) x |= *reinterpret_cast<const int*>(pp + i);
+    for (unsigned i = tid * 64u; i < blk.warm_ops * sizeof(RbOp); i += nt * 64u)
+      x |= *reinterpret_cast<const int*>(reinterpret_cast<const char*>(po) + i);
+    if (blk.warm_mats > 0) {
+      const char* pm = reinterpret_cast<const char*>(mats + po[0].mat);
+      for (unsigned i = tid * 64u; i < blk.warm_mats * sizeof(double2); i += nt * 64u)
+        x |= *reinterpret_cast<const int*>(pm + i);
+    } else {   // 2x2 entries spread over a larger table
+      for (unsigned i = tid; i < (unsigned)blk.warm_ops; i += nt) x |= *reinterpret_cast<const int*>(mats + po[i].mat);
+    }
+    asm volatile("" ::"v"(x));
+  }
   take_loaded();
   if (tile + gridDim.x < ntiles) load_tile(tile + gridDim.x);
   for (;;) {
@@ -507,21 +586,27 @@ __global__ __launch_bounds__(R == 4 ? 512 : 1024) void k_fused_rb(double2* __res
 #pragma unroll
         for (int j = 0; j < NV; ++j) v[j] = ldv(tl + ph.ld_off[j]);
       }
-      const FusedOp* __restrict__ po = ops + ph.op_begin;
+      const RbOp* __restrict__ po = ops + ph.op_begin;
+      // the next ops' codes are loaded while this one runs (the table ends
+      // with two spare entries)
       if constexpr (R == 4) {
-        // two gates per trip, v -> w -> v; an odd count ends with a copy
+        // two gates per trip, v -> w -> v (the host pads an odd count with a copy)
         vd2 w[NV];
+        RbOp o0 = po[0], o1 = po[1];
         for (int oi = 0; oi < ph.op_count; oi += 2) {
-          rb_apply<R>(po[oi].code, mats + po[oi].mat, v, w);
-          int c2 = kRbCodeCopy, m2 = 0;
-          if (oi + 1 < ph.op_count) {
-            c2 = po[oi + 1].code;
-            m2 = po[oi + 1].mat;
-          }
-          rb_apply<R>(c2, mats + m2, w, v);
+          const RbOp n0 = po[oi + 2], n1 = po[oi + 3];
+          rb_apply<R, SET>(o0.code, mats + o0.mat, v, w);
+          rb_apply<R, SET>(o1.code, mats + o1.mat, w, v);
+          o0 = n0;
+          o1 = n1;
         }
       } else {
-        for (int oi = 0; oi < ph.op_count; ++oi) rb_apply<R>(po[oi].code, mats + po[oi].mat, v, v);
+        RbOp o = po[0];
+        for (int oi = 0; oi < ph.op_count; ++oi) {
+          const RbOp nx = po[oi + 1];
+          rb_apply<R, SET>(o.code, mats + o.mat, v, v);
+          o = nx;
+        }
       }
       if (pi < P - 1 || !sdd) {   // else the results stay in v
         // the tile's first LDS write when the first phase came from HBM:
@@ -551,18 +636,16 @@ size_t fused_rb_lds_bytes(int k) { return sizeof(double2) * ((1u << k) + (1u << 
 
 int fused_rb_enable_lds() {
   int rc = NWQ_OK;
-  for (const void* f : {(const void*)k_fused_rb<3, false>, (const void*)k_fused_rb<3, true>,
-                        (const void*)k_fused_rb<4, false>, (const void*)k_fused_rb<4, true>})
+  for (const void* f : {(const void*)k_fused_rb<4, kRbSetVQE, false>, (const void*)k_fused_rb<4, kRbSetVQE, true>})
     if (!rc) rc = enable_dynamic_lds(f);
   return rc;
 }
 
 void launch_fused_rb(hipStream_t s, double2* a, int nbits, const FusedBlockDev& blk, const FusedPhase* phases,
-                     const FusedOp* ops, const double2* mats, int rbits, int batch, int mat_stride, int max_grid,
-                     int flags, unsigned long long max_tiles, unsigned long long tile_mask) {
+                     const RbOp* ops, const double2* mats, int rbits, int set, int batch, int mat_stride, int max_grid,
+                     int flags, unsigned long long tile_mask) {
   const int k = blk.c + blk.m;
   unsigned long long ntiles = 1ull << (nbits - k);
-  if (max_tiles > 0 && max_tiles < ntiles) ntiles = max_tiles;
   const bool sparse = tile_mask != ~0ull && __builtin_popcountll(tile_mask) < nbits - k;
   if (sparse) ntiles = 1ull << __builtin_popcountll(tile_mask);
   // about four tiles per workgroup (so that the next tile's loads overlap
@@ -581,6 +664,8 @@ void launch_fused_rb(hipStream_t s, double2* a, int nbits, const FusedBlockDev& 
   b.direct = (flags & kFusedDirect) ? blk.direct : 0;
   b.sparse = sparse ? 1 : 0;
   b.tmask = sparse ? tile_mask : 0ull;
+  b.warm_ops = blk.prog_ops;
+  b.warm_mats = blk.prog_mats;
   for (int j = 0; j < 16; ++j) {
     b.lo[j] = (b.direct & 1) ? blk.jdir[j] : blk.joff[j];
     b.so[j] = (b.direct & 2) ? blk.sdir[j] : blk.joff[j];
@@ -591,12 +676,25 @@ void launch_fused_rb(hipStream_t s, double2* a, int nbits, const FusedBlockDev& 
                        stride, mat_stride, ntiles);
   };
   const bool nt = (flags & kFusedNonTemporal) != 0;
-  if (rbits == 3) {
-    if (nt) go(k_fused_rb<3, true>, 3);
-    else go(k_fused_rb<3, false>, 3);
+  if (set == kRbSetVQE) {   // 4 register bits only
+    if (nt) go(k_fused_rb<4, kRbSetVQE, true>, 4);
+    else go(k_fused_rb<4, kRbSetVQE, false>, 4);
+  } else if (set == kRbSetDM) {
+    if (rbits == 3) {
+      if (nt) go(k_fused_rb<3, kRbSetDM, true>, 3);
+      else go(k_fused_rb<3, kRbSetDM, false>, 3);
+    } else {
+      if (nt) go(k_fused_rb<4, kRbSetDM, true>, 4);
+      else go(k_fused_rb<4, kRbSetDM, false>, 4);
+    }
   } else {
-    if (nt) go(k_fused_rb<4, true>, 4);
-    else go(k_fused_rb<4, false>, 4);
+    if (rbits == 3) {
+      if (nt) go(k_fused_rb<3, kRbSetSV, true>, 3);
+      else go(k_fused_rb<3, kRbSetSV, false>, 3);
+    } else {
+      if (nt) go(k_fused_rb<4, kRbSetSV, true>, 4);
+      else go(k_fused_rb<4, kRbSetSV, false>, 4);
+    }
   }
 }
 

@@ -110,43 +110,45 @@ void launch_reduce_rows(hipStream_t s, const double* partials, int rows, int gri
                         const double* coeffs, double* out);
 
 // ---- fused LDS blocks (kernels_fuse.hip) ----------------------------------
-struct FusedOp {            // one gate inside a fused block, tile-local bits
-  int kind;                 // 0: 1q dense, 1: 1q diag, 2: 2q dense, 3: 2q member swap, 4: 2q diag,
-                            // 6: 1q diag read from a 2x2 entry (M[0], M[3]; register-blocked kernels only),
-                            // 7: dense 16x16 over all four register bits, in register order (4-bit kernel),
-                            // 8: the same with the pattern of a Pauli channel after a diagonal gate: diagonal
-                            //    except for a dense 4x4 among register indices 0, 5, 10, 15 (4-bit kernel)
+struct FusedOp {            // one gate inside a fused block of the per-gate LDS kernel, tile-local bits
+  int kind;                 // 0: 1q dense, 1: 1q diag, 2: 2q dense, 3: 2q member swap, 4: 2q diag
   int lo, hi;               // sorted tile-local bit positions (hi unused for 1q)
   int o0, o1;               // kind 2: local offsets of q0, q1; kind 3: offsets swapped; kind 4: local bits of q0, q1
   int mat;                  // start of its matrix in the block program's matrix table (double2 units)
-  int code;                 // register-blocked kernels: rb_op_code() of the fields above
-  int real00;               // kind 0: 1 when M[0][0] is real (U3, RX), 2 when all of M is (RY, H);
-                            // the imaginary parts known to be zero are skipped
 };
-// One switch index per register-blocked op (kind and register bits): 0 + B
-// dense 2x2, 4 + B diagonal (M[0], M[1]), 8 + B diagonal (M[0], M[3]); with
-// u = 4 o0 + o1: 16 + u dense 4x4, 32 + u CX, 48 + u SWAP, 64 + u 2q diagonal;
-// 84 + B dense 2x2 with a real M[0][0], 88 + B real dense 2x2; 96 dense 16x16
-// over the four register bits, 97 its Pauli-channel pattern (the 16 diagonal
-// entries, then the 4x4 among registers 0, 5, 10, 15; 4-register-bit kernel
-// only).
-constexpr int kRbCodeCopy = 80;   // kernel-internal copy that pads an odd gate count
-constexpr int kRbCodeDense16 = 96;
-constexpr int kRbCodePauli16 = 97;
-inline int rb_op_code(const FusedOp& op) {
-  const int u = 4 * op.o0 + op.o1;
-  switch (op.kind) {
-    case 0: return op.real00 == 2 ? 88 + op.lo : (op.real00 == 1 ? 84 + op.lo : op.lo);
-    case 1: return 4 + op.lo;
-    case 6: return 8 + op.lo;
-    case 7: return kRbCodeDense16;
-    case 8: return kRbCodePauli16;
-    case 2: return 16 + u;
-    case 3: return 32 + u;
-    case 5: return 48 + u;
-    default: return 64 + u;   // 4
-  }
+// One op of the register-blocked kernels: a code (kind and register bits) and
+// the start of its entries in the matrix table (double2 units).
+struct RbOp {
+  int code, mat;
+};
+// Pairs of register bits B0 < B1 are numbered B1 (B1 - 1) / 2 + B0.
+inline int rb_pair(int b0, int b1) { return b1 * (b1 - 1) / 2 + b0; }
+enum RbCode {
+  kRbGen1 = 0,              // + B: dense 2x2
+  kRbR001 = 4,              // + B: 2x2 with a real M[0][0]
+  kRbReal1 = 8,             // + B: real 2x2
+  kRbXt1 = 12,              // + B: real diagonal, imaginary off-diagonal entries
+  kRbDense2 = 16,           // + pair: dense 4x4, index u = bit B0 + 2 bit B1
+  kRbReal2 = 22,            // + pair: real 4x4
+  kRbPar2 = 28,             // + pair: entry (r, c) real where r ^ c has even parity, else imaginary
+  kRbCx = 34,               // + 2 pair (+ 1 when the control is B1): CX
+  kRbSwap = 46,             // + pair
+  kRbDiagAll = 52,          // diagonal over all register bits (one entry per register)
+  kRbDiag1 = 53,            // + B: 1q diagonal, entries M[0] and M[3]
+  kRbDiag2 = 57,            // + pair: 2q diagonal, entries M[u]
+  kRbDense16 = 63,          // 16x16 in register order (4 register bits)
+  kRbPauli16 = 64,          // its Pauli-channel pattern: the 16 diagonal entries, then the 4x4 among
+                            // registers 0, 5, 10, 15 (4 register bits)
+  kRbCopy = 65              // pads an odd op count (4 register bits)
+};
+inline int rb_cx_code(int control, int target) {
+  return control < target ? kRbCx + 2 * rb_pair(control, target) : kRbCx + 2 * rb_pair(target, control) + 1;
 }
+// Op sets, each with kernels of its own: state-vector circuits (1q, 4x4, one
+// diagonal form, permutations), density-matrix superoperators (4x4 and 16x16
+// kinds), VQE programs (1q kinds, 1q and 2q diagonals, permutations; matrices
+// read from per-vector tables).
+constexpr int kRbSetSV = 0, kRbSetDM = 1, kRbSetVQE = 2;
 struct FusedBlockDev {
   int c, m;                 // tile = low c bits + m high bits
   int hi[8];
@@ -161,14 +163,17 @@ struct FusedBlockDev {
   // Such a phase skips its LDS round trip and barrier.
   int direct;
   unsigned long long jdir[16], sdir[16];
+  // register-blocked kernels: ops and matrix entries of the block's program,
+  // contiguous from its first op's (0: the matrices lie elsewhere)
+  int prog_ops, prog_mats;
 };
 void launch_fused_block(hipStream_t s, double2* a, int nbits, const FusedBlockDev& blk,
                         const FusedOp* ops, const double2* mats, int lds_k);
 // Register-blocked blocks: blk.op_begin / op_count index a phase table; each
 // phase holds rbits (3 or 4) register bits (tile-local, ascending; unused
-// entries of reg ignored) and a range of ops whose lo / o0 / o1 fields are
-// register-bit indices below rbits.  Tiles of 2^k amplitudes, 8 <= k <= 13,
-// 2^(k-rbits) threads.  Op kinds as FusedOp plus 5 = SWAP (o0, o1).
+// entries of reg ignored) and a range of RbOps (an even number at 4 register
+// bits); the op table ends with two spare entries.  Tiles of 2^k amplitudes,
+// 8 <= k <= 13, 2^(k-rbits) threads.
 struct FusedPhase {
   int reg[4];
   int op_begin, op_count;
@@ -194,16 +199,15 @@ inline void fill_phase_offsets(FusedPhase& fp, int rbits, const int* ld_perm, co
   }
 }
 size_t fused_rb_lds_bytes(int k);
-// enable_dynamic_lds for every register-blocked instance (outside graph capture)
+// enable_dynamic_lds for the register-blocked VQE instances (outside graph capture)
 int fused_rb_enable_lds();
 // batch > 1: blockIdx.y = batch element b works on a + b * 2^nbits with the
 // matrix table mats + b * mat_stride; max_grid caps the tiles' grid (0 = 2^20).
 // flags: kFusedNonTemporal = non-temporal global loads and stores of the
 // tiles; kFusedDirect = load the first phase / store the last phase straight
 // between HBM and registers where the block allows it (FusedBlockDev::direct).
-// max_tiles > 0 runs only the first max_tiles tiles of each state, and
-// tile_mask != ~0 only the tiles whose index is zero outside tile_mask (the
-// block leaves the others alone: used when they are known to hold zeros,
+// tile_mask != ~0 runs only the tiles whose index is zero outside tile_mask
+// (the block leaves the others alone: used when they are known to hold zeros,
 // which a block maps to zeros).
 constexpr int kFusedNonTemporal = 1;
 constexpr int kFusedDirect = 2;
@@ -211,9 +215,8 @@ constexpr int kFusedDirect = 2;
 // they save FP64 work (circuit.hip, gate_products).
 constexpr int kFusedGateFusion = 4;
 void launch_fused_rb(hipStream_t s, double2* a, int nbits, const FusedBlockDev& blk, const FusedPhase* phases,
-                     const FusedOp* ops, const double2* mats, int rbits, int batch = 1, int mat_stride = 0,
-                     int max_grid = 0, int flags = 0, unsigned long long max_tiles = 0,
-                     unsigned long long tile_mask = ~0ull);
+                     const RbOp* ops, const double2* mats, int rbits, int set, int batch = 1, int mat_stride = 0,
+                     int max_grid = 0, int flags = 0, unsigned long long tile_mask = ~0ull);
 
 // ---- error handling (engine.hip) ------------------------------------------
 int set_error(int code, const std::string& msg);

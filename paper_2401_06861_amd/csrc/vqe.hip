@@ -1551,7 +1551,7 @@ static int build_fused(nwq_vqe* h) {
   const std::vector<Block> blocks = plan_blocks(g, n, std::max(k, 6), low, kVqeSeeds, true);
   if (blocks.empty() && h->nops > 0) return set_error(NWQ_EINVAL, "fusion planner made no progress");
   std::vector<FusedPhase> phases;
-  std::vector<FusedOp> fops;
+  std::vector<RbOp> fops;
   std::vector<VqeBwdOp> bops;
   h->fwd_blocks.clear();
   h->bwd_blocks.clear();
@@ -1582,37 +1582,44 @@ static int build_fused(nwq_vqe* h) {
           if (ph.reg[i] == bit) return i;
         return -1;
       };
+      // ops before their permutations are folded into the LDS offsets
+      struct FwdOp {
+        RbOp o;
+        int perm, b0, b1;   // perm: 1 CX, 2 SWAP
+        unsigned bits;
+      };
+      std::vector<FwdOp> pops;
       for (int gi : ph.gates) {
         const VqeOp& op = h->ops[gi];
-        FusedOp f{};
-        f.mat = 8 * gi;
         const int r0 = ridx(lb[gi][0]), r1 = nq[gi] == 2 ? ridx(lb[gi][1]) : 0;
-        f.lo = r0;
-        if (op.kind == OP_ROT && op.axis == 2) {
-          f.kind = 6;   // RZ: diagonal of its 2x2 table entry
-        } else if (op.kind == OP_ROT || op.kind == OP_FIX1) {
-          f.kind = 0;
-          // RX: M[0][0] = cos(theta / 2) is real for every theta; RY: all of M is
-          f.real00 = op.kind == OP_ROT ? (op.axis == 1 ? 2 : 1) : 0;
-        } else if (op.kind == OP_RZZ || op.kind == OP_CZ) {
-          f.kind = 4; f.o0 = r0; f.o1 = r1;
-        } else if (op.kind == OP_CX) {
-          f.kind = 3; f.o0 = r0; f.o1 = r1;
-        } else {
-          f.kind = 5; f.o0 = r0; f.o1 = r1;
-        }
-        f.code = rb_op_code(f);
-        fops.push_back(f);
+        const int pair = nq[gi] == 2 ? rb_pair(std::min(r0, r1), std::max(r0, r1)) : 0;
+        FwdOp f{{0, 8 * gi}, 0, r0, r1, nq[gi] == 2 ? (1u << r0) | (1u << r1) : 1u << r0};
+        // the parts of a rotation that are zero for every theta are skipped
+        if (op.kind == OP_ROT) f.o.code = (op.axis == 2 ? kRbDiag1 : op.axis == 1 ? kRbReal1 : kRbXt1) + r0;
+        else if (op.kind == OP_FIX1) f.o.code = kRbGen1 + r0;
+        else if (op.kind == OP_RZZ || op.kind == OP_CZ) f.o.code = kRbDiag2 + pair;   // symmetric in its qubits
+        else if (op.kind == OP_CX) f.o.code = rb_cx_code(r0, r1), f.perm = 1;
+        else f.o.code = kRbSwap + pair, f.perm = 2;
+        pops.push_back(f);
       }
+      int ld_perm[16], st_perm[16];
+      fold_permutations(
+          pops, h->fused_rbits, [](const FwdOp& o) { return o.perm != 0; }, [](const FwdOp& o) { return o.bits; },
+          [](const FwdOp& o, int j) { return o.perm == 1 ? reg_cx(o.b0, o.b1, j) : reg_swap(o.b0, o.b1, j); }, ld_perm,
+          st_perm);
+      for (const FwdOp& f : pops) fops.push_back(f.o);
+      if (pops.size() % 2) fops.push_back(RbOp{kRbCopy, fops.back().mat});
       fp.op_count = (int)fops.size() - fp.op_begin;
-      fill_phase_offsets(fp, h->fused_rbits, nullptr, nullptr);
+      fill_phase_offsets(fp, h->fused_rbits, ld_perm, st_perm);
       phases.push_back(fp);
     }
     d.op_count = (int)phases.size() - d.op_begin;
+    d.prog_ops = (int)fops.size() - phases[d.op_begin].op_begin;   // matrices: per-vector table
     fill_entry_offsets(d, h->fused_rbits);
     set_direct_io(d, phases[d.op_begin], phases.back(), h->fused_rbits);
     h->fwd_blocks.push_back(d);
   }
+  for (int i = 0; i < 2; ++i) fops.push_back(RbOp{kRbCopy, 0});   // read ahead, not run
   // Backward: register-blocked with 3 register bits when every tile gives at
   // least one full wave (2^(k-3) >= 64), else one LDS pass per gate.
   constexpr int kBwdBits = 3;
@@ -1815,14 +1822,14 @@ static int build_fused(nwq_vqe* h) {
   }
   const size_t ph_bytes = phases.size() * sizeof(FusedPhase);
   h->fused_ops_off = (ph_bytes + 255) & ~size_t(255);
-  h->fused_bwd_off = (h->fused_ops_off + fops.size() * sizeof(FusedOp) + 255) & ~size_t(255);
+  h->fused_bwd_off = (h->fused_ops_off + fops.size() * sizeof(RbOp) + 255) & ~size_t(255);
   h->fused_rop_off = (h->fused_bwd_off + bops.size() * sizeof(VqeBwdOp) + 255) & ~size_t(255);
   h->fused_hterm_off = (h->fused_rop_off + rops.size() * sizeof(VqeBwdRop) + 255) & ~size_t(255);
   h->fused_widx_off = (h->fused_hterm_off + hterms.size() * sizeof(HTerm) + 255) & ~size_t(255);
   const size_t total = h->fused_widx_off + widx.size() * sizeof(int) + 16;
   std::vector<char> prog(total, 0);
   if (!phases.empty()) std::memcpy(prog.data(), phases.data(), ph_bytes);
-  if (!fops.empty()) std::memcpy(prog.data() + h->fused_ops_off, fops.data(), fops.size() * sizeof(FusedOp));
+  if (!fops.empty()) std::memcpy(prog.data() + h->fused_ops_off, fops.data(), fops.size() * sizeof(RbOp));
   if (!bops.empty()) std::memcpy(prog.data() + h->fused_bwd_off, bops.data(), bops.size() * sizeof(VqeBwdOp));
   if (!rops.empty()) std::memcpy(prog.data() + h->fused_rop_off, rops.data(), rops.size() * sizeof(VqeBwdRop));
   if (!hterms.empty()) std::memcpy(prog.data() + h->fused_hterm_off, hterms.data(), hterms.size() * sizeof(HTerm));
@@ -1862,7 +1869,7 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
   const int G = fused_grid(h);
   const dim3 grid(G, B);
   const FusedPhase* dph = static_cast<const FusedPhase*>(h->d_fused);
-  const FusedOp* dfo = reinterpret_cast<const FusedOp*>(static_cast<char*>(h->d_fused) + h->fused_ops_off);
+  const RbOp* dfo = reinterpret_cast<const RbOp*>(static_cast<char*>(h->d_fused) + h->fused_ops_off);
   const VqeBwdOp* dbo = reinterpret_cast<const VqeBwdOp*>(static_cast<char*>(h->d_fused) + h->fused_bwd_off);
   const int stride = 8 * h->nops;
   hipLaunchKernelGGL(k_vqe_init, grid, dim3(kVqeBlock), 0, s, h->d_phi, h->n);
@@ -1880,8 +1887,8 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
     for (int i = 0; i < d.m; ++i) tiles_of |= 1ull << d.hi[i];
     const unsigned long long tile_mask = tile_mask_of(tiles_of, support, h->n);
     support |= tiles_of;
-    launch_fused_rb(s, h->d_phi, h->n, d, dph, dfo, h->d_table, h->fused_rbits, B, stride, G, h->fused_flags, 0,
-                    tile_mask);
+    launch_fused_rb(s, h->d_phi, h->n, d, dph, dfo, h->d_table, h->fused_rbits, kRbSetVQE, B, stride, G,
+                    h->fused_flags, tile_mask);
   }
   const HTerm* dht = reinterpret_cast<const HTerm*>(static_cast<char*>(h->d_fused) + h->fused_hterm_off);
   const int* dwi = reinterpret_cast<const int*>(static_cast<char*>(h->d_fused) + h->fused_widx_off);
