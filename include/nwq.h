@@ -160,7 +160,8 @@ int nwq_qasm_parse(const char* text, int* n_qubits, int* n_gates, int capacity, 
 int nwq_apply_qasm(nwq_handle h, const char* text);
 
 /* Fused-block width: 0 = off (one kernel per gate), else the number of bits
- * a block may touch (6..13).  SV handles: nwq_apply_circuit runs its gates
+ * a block may touch (6..13; the register-blocked kernels use at most 12 of
+ * them on registers of more than 13).  SV handles: nwq_apply_circuit runs its gates
  * through fused blocks.  DM handles: each 1q gate with the channels composed
  * after it (a 4x4 superoperator on bits q and q + n of vec(rho)) is queued,
  * and so is each 2q gate with its channels (a 16x16 on bits q0, q1, q0 + n,

@@ -16,6 +16,15 @@
 
 namespace nwq {
 
+// The register-blocked kernels run a width of 13 in tiles of 2^12 (unless one
+// tile holds the whole register): three workgroups of 2^12 tiles share a CU
+// against one of 2^13, which costs more than the fewer blocks of width 13 save
+// (30-qubit brickwork: 278 ms in 32 blocks against 300 in 29; random pairs on
+// 24 qubits 1.48 against 1.96).
+int fusion_width(const nwq_state* h, int nbits) {
+  return h->fuse_rb != 0 && nbits > h->fuse_k ? std::min(h->fuse_k, 12) : h->fuse_k;
+}
+
 // Fewer low bits leave room for more of the circuit's bits per block and give
 // shorter HBM runs.  State vectors take as few as the block's 8 high slots
 // allow (at least 3: whole 128-byte lines): the depth-40 brickwork on 30
@@ -25,7 +34,8 @@ namespace nwq {
 // qubit above the low bits takes two high slots (its column bit q and row bit
 // q + n); density matrices keep at least 4 (n=14, width 12, noisy TFIM: 65 ms
 // and 25 blocks with 4, 83 ms and 41 with 5).
-int fusion_low_bits(const nwq_state* h, int nbits, int k) {
+int fusion_low_bits(const nwq_state* h, int nbits) {
+  const int k = fusion_width(h, nbits);
   if (nbits <= k) return nbits;
   const int c = h->fuse_c > 0 ? h->fuse_c : (h->kind == NWQ_KIND_DM ? 4 : 3);
   return std::min(std::max(c, k - 8), k - 2);
@@ -398,7 +408,7 @@ void merge_diagonals(std::vector<RegOp>& ops, int rbits) {
 
 // The op's code, its entries appended to mats.
 RbOp emit_reg_op(const RegOp& op, int set, std::vector<double2>& mats) {
-  RbOp o{kRbCopy, (int)mats.size()};
+  RbOp o{0, (int)mats.size()};
   auto put = [&](const cd& v) { mats.push_back(make_double2(v.real(), v.imag())); };
   auto real = [](const cd& v) { return v.imag() == 0.0; };
   auto imag = [](const cd& v) { return v.real() == 0.0; };
@@ -671,41 +681,159 @@ std::vector<Phase> plan_phases(const std::vector<int>& order, const std::vector<
   return out;
 }
 
-// Global offsets of the tile entries j * 2^(k - rbits), j < 2^rbits: the low
-// c bits stay in place, tile bit c + i lands on qubit hi[i].
-static unsigned long long tile_entry_offset(const FusedBlockDev& d, unsigned l) {
-  unsigned long long g = l & ((1u << d.c) - 1u);
-  for (int i = 0; i < d.m; ++i)
-    if ((l >> (d.c + i)) & 1u) g |= 1ull << d.hi[i];
+// Global offset of tile entry l: the low c bits stay in place, tile bit c + i
+// lands on qubit hi[i].
+static unsigned long long tile_entry_offset(int c, int m, const int* hi, unsigned l) {
+  unsigned long long g = l & ((1u << c) - 1u);
+  for (int i = 0; i < m; ++i)
+    if ((l >> (c + i)) & 1u) g |= 1ull << hi[i];
   return g;
 }
 
 void fill_entry_offsets(FusedBlockDev& d, int rbits) {
   const int k = d.c + d.m;
-  d.direct = 0;
-  for (int j = 0; j < 16; ++j) {
-    d.joff[j] = d.jdir[j] = d.sdir[j] = 0;
-    if (j < (1 << rbits)) d.joff[j] = tile_entry_offset(d, (unsigned)j << (k - rbits));
-  }
+  for (int j = 0; j < 16; ++j)
+    d.joff[j] = j < (1 << rbits) ? tile_entry_offset(d.c, d.m, d.hi, (unsigned)j << (k - rbits)) : 0;
 }
 
-// A phase's LDS offsets are padded by one entry per 16 (o + o / 16); the
-// entry offset is recovered from them.
-void set_direct_io(FusedBlockDev& d, const FusedPhase& first, const FusedPhase& last, int rbits) {
-  auto above_c = [&](const FusedPhase& ph) {
+namespace {
+
+// Images of the thread bits and register bits of a phase in tile entries
+// (perm: the register-bit index a register's entry is read from or stored to;
+// compositions of CX and SWAP are linear over GF(2)).  wave: the tile bits on
+// the thread index above the lane (threads of one wave agree on them).
+struct TileMap {
+  int tbits = 0;
+  unsigned t[kRbThreadBits] = {0}, r[4] = {0};
+};
+TileMap tile_map(const int* reg, const int* perm, unsigned wave, int rbits, int k) {
+  TileMap m;
+  unsigned S = wave;
+  for (int i = 0; i < rbits; ++i) S |= 1u << reg[i];
+  // Sixteen consecutive lanes (one LDS access of 128 bytes) have to cover
+  // different banks: lane bits 0..3 take tile bits of different residue mod 4
+  // (entry_slot), the lowest ones.
+  unsigned lanes = ~S & ((1u << k) - 1u), res = 0;
+  for (int b = 0; b < k && res != 15u; ++b)
+    if (((lanes >> b) & 1u) && !((res >> (b % 4)) & 1u)) {
+      res |= 1u << (b % 4);
+      m.t[m.tbits++] = 1u << b;
+      lanes &= ~(1u << b);
+    }
+  for (unsigned rest : {lanes, wave})
+    for (int b = 0; b < k; ++b)
+      if ((rest >> b) & 1u) m.t[m.tbits++] = 1u << b;
+  for (int i = 0; i < rbits; ++i)
+    for (int e = 0; e < rbits; ++e)
+      if ((perm[1 << i] >> e) & 1) m.r[i] |= 1u << reg[e];
+  return m;
+}
+
+// LDS slot of a tile entry: bit i < 4 is the parity of the entry's bits that
+// are i mod 4, so that a step along any tile bit changes the bank.
+unsigned short entry_slot(unsigned entry) {
+  unsigned s = entry & ~15u;
+  for (int i = 0; i < 4; ++i) s |= (unsigned)(__builtin_popcount(entry & (0x1111u << i)) & 1) << i;
+  return (unsigned short)s;
+}
+
+}  // namespace
+
+// Lays a block's register phases out (appends them to `out`).  The first and
+// the last phase move between HBM and registers themselves, so their lanes
+// have to cover contiguous runs (no register bit below the low bits) -- else,
+// or without `direct`, a phase without ops on the top bits goes before (after).
+void layout_rb_block(const Block& b, std::vector<RbStage> st, int rbits, bool direct, RbBlock& d,
+                     std::vector<RbPhase>& out) {
+  const int k = b.c + b.m;
+  d = RbBlock{};
+  d.k = k;
+  d.tile = tile_entry_offset(b.c, b.m, b.hi, (1u << k) - 1u);
+  auto contiguous = [&](const RbStage& s) {
     for (int r = 0; r < rbits; ++r)
-      if (ph.reg[r] < d.c) return false;
+      if (s.reg[r] < std::min(b.c, k - rbits)) return false;
     return true;
   };
-  auto unpad = [](unsigned p) { return 16u * (p / 17u) + p % 17u; };
-  d.direct = 0;
-  if (above_c(first)) {
-    d.direct |= 1;
-    for (int j = 0; j < (1 << rbits); ++j) d.jdir[j] = tile_entry_offset(d, unpad(first.ld_off[j]));
+  RbStage top{};
+  for (int r = 0; r < rbits; ++r) top.reg[r] = k - rbits + r;
+  for (int j = 0; j < 16; ++j) top.ld_perm[j] = top.st_perm[j] = j;
+  if (!direct || !contiguous(st.front())) {
+    top.op_begin = st.front().op_begin;
+    st.insert(st.begin(), top);
   }
-  if (above_c(last)) {
-    d.direct |= 2;
-    for (int j = 0; j < (1 << rbits); ++j) d.sdir[j] = tile_entry_offset(d, unpad(last.st_off[j]));
+  if (!direct || !contiguous(st.back())) {
+    top.op_begin = st.back().op_begin;
+    st.push_back(top);
+  }
+  d.ph_begin = (int)out.size();
+  d.ph_count = (int)st.size();
+  // Bits of the wave index: phases in a row share them as long as enough bits
+  // above the low ones stay off all their register bits (the exchanges between
+  // such phases stay inside a wave).
+  const int wbits = std::max(0, k - rbits - 6);
+  std::vector<unsigned> wave(st.size(), 0);
+  std::vector<char> local(st.size(), 0);   // exchange into phase i stays inside a wave
+  for (size_t i = 0; i < st.size();) {
+    unsigned busy = (1u << std::min(std::min(b.c, 4), k - rbits - wbits)) - 1u;   // 256-byte runs at least
+    size_t e = i;
+    for (; e < st.size(); ++e) {
+      unsigned S = busy;
+      for (int r = 0; r < rbits; ++r) S |= 1u << st[e].reg[r];
+      if (e > i && k - __builtin_popcount(S) < wbits) break;
+      busy = S;
+      if (k - __builtin_popcount(S) < wbits) {   // one phase: its lanes give up low bits
+        busy &= ~((1u << b.c) - 1u);
+        for (int r = 0; r < rbits; ++r) busy |= 1u << st[e].reg[r];
+        ++e;
+        break;
+      }
+    }
+    unsigned W = 0;
+    for (int q = k - 1, n = 0; q >= 0 && n < wbits; --q)
+      if (!((busy >> q) & 1u)) {
+        W |= 1u << q;
+        ++n;
+      }
+    for (size_t j = i; j < e; ++j) {
+      wave[j] = W;
+      local[j] = j > i || (j > 0 && wave[j - 1] == W);
+    }
+    i = e;
+  }
+  bool all_local = true;
+  for (size_t i = 1; i < st.size(); ++i) all_local = all_local && local[i];
+  for (size_t i = 0; i < st.size(); ++i) {
+    RbPhase ph{};
+    ph.op_begin = st[i].op_begin;
+    ph.op_count = (short)st[i].op_count;
+    if (i > 0) {
+      const TileMap wr = tile_map(st[i - 1].reg, st[i - 1].st_perm, wave[i - 1], rbits, k);
+      const TileMap rd = tile_map(st[i].reg, st[i].ld_perm, wave[i], rbits, k);
+      for (int j = 0; j < kRbThreadBits; ++j) {
+        ph.wr_t[j] = entry_slot(wr.t[j]);
+        ph.rd_t[j] = entry_slot(rd.t[j]);
+      }
+      for (int j = 0; j < 4; ++j) {
+        ph.wr_r[j] = entry_slot(wr.r[j]);
+        ph.rd_r[j] = entry_slot(rd.r[j]);
+      }
+      // A phase's registers go back to the entries they came from (its
+      // permutations stay among one thread's), so only the first exchange of a
+      // tile can overwrite entries that another wave still reads: the last
+      // phase's of the tile before.
+      ph.flags = (short)((local[i] ? 0 : kRbBarrierInside) | (i == 1 && !all_local ? kRbBarrierBefore : 0));
+    }
+    out.push_back(ph);
+  }
+  const TileMap ld = tile_map(st.front().reg, st.front().ld_perm, wave.front(), rbits, k);
+  const TileMap sv = tile_map(st.back().reg, st.back().st_perm, wave.back(), rbits, k);
+  for (int j = 0; j < kRbThreadBits; ++j) {
+    d.ld_t[j] = tile_entry_offset(b.c, b.m, b.hi, ld.t[j]);
+    d.st_t[j] = tile_entry_offset(b.c, b.m, b.hi, sv.t[j]);
+  }
+  for (int j = 0; j < 4; ++j) {
+    d.ld_r[j] = tile_entry_offset(b.c, b.m, b.hi, ld.r[j]);
+    d.st_r[j] = tile_entry_offset(b.c, b.m, b.hi, sv.r[j]);
   }
 }
 
@@ -754,15 +882,16 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
   // about 0.1 ms to planning a deep circuit.
   const int seeds = nbits < 22 ? 1 : (nbits < 26 ? 2 : 8);
   const std::vector<Block> blocks =
-      plan_blocks(gates, nbits, h->fuse_k, fusion_low_bits(h, nbits, h->fuse_k), seeds, false);
+      plan_blocks(gates, nbits, fusion_width(h, nbits), fusion_low_bits(h, nbits), seeds, false);
   if (blocks.empty()) return set_error(NWQ_EINVAL, "fusion planner made no progress");
   // Program: [phase table][op table][matrix table] in one upload.
-  std::vector<FusedPhase> phases;
+  std::vector<RbPhase> phases;
   std::vector<FusedOp> ops;    // per-gate LDS kernel
   std::vector<RbOp> rops;      // register-blocked kernels
   std::vector<double2> mats;
   const int set = h->kind == NWQ_KIND_DM ? kRbSetDM : kRbSetSV;
-  struct Launch { FusedBlockDev d; bool rb; int rbits; };
+  struct Launch { FusedBlockDev d; RbBlock r; bool rb; };
+  const int rbits = h->fuse_rb == 2 ? 3 : 4;
   std::vector<Launch> launches;
   for (Block b : blocks) {
     if (h->fuse_rb != 0 && b.c + b.m < 8 && nbits >= 8) pad_block(b, nbits, 8);
@@ -772,7 +901,6 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
     for (int i = 0; i < b.m; ++i) d.hi[i] = b.hi[i];
     const int k = b.c + b.m;
     const bool rb = h->fuse_rb != 0 && k >= 8;
-    const int rbits = h->fuse_rb == 2 ? 3 : 4;
     if (!rb) {
       d.op_begin = (int)ops.size();
       for (int gi : b.gates) {
@@ -783,7 +911,7 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
           ops.push_back(op);
       }
       d.op_count = (int)ops.size() - d.op_begin;
-      if (d.op_count > 0) launches.push_back({d, false, 0});
+      if (d.op_count > 0) launches.push_back({d, RbBlock{}, false});
       continue;
     }
     // the block's gates by block-local index (gid: the gate each one is), so
@@ -801,12 +929,12 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
       nq.push_back(gates[gi].nq);
     }
     if (order.empty()) continue;
-    d.op_begin = (int)phases.size();
     const size_t rops0 = rops.size(), mats0 = mats.size();
+    std::vector<RbStage> stages;
     for (const Phase& ph : plan_phases(order, lb, nq, k, b.c, rbits)) {
-      FusedPhase fp{};
-      for (int i = 0; i < 4; ++i) fp.reg[i] = ph.reg[i] < 0 ? 0 : ph.reg[i];
-      fp.op_begin = (int)rops.size();
+      RbStage stg{};
+      for (int i = 0; i < 4; ++i) stg.reg[i] = ph.reg[i] < 0 ? 0 : ph.reg[i];
+      stg.op_begin = (int)rops.size();
       auto ridx = [&](int bit) {
         for (int i = 0; i < rbits; ++i)
           if (ph.reg[i] == bit) return i;
@@ -820,24 +948,21 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
         if (make_reg_op(gates[gid[li]], rb_bits, rbits, side, op)) pops.push_back(std::move(op));
       }
       if (h->fuse_flags & kFusedGateFusion) merge_diagonals(pops, rbits);
-      int ld_perm[16], st_perm[16];
       fold_permutations(
           pops, rbits, [](const RegOp& o) { return o.perm(); }, [](const RegOp& o) { return o.bits; },
-          [](const RegOp& o, int j) { return o.map(j); }, ld_perm, st_perm);
+          [](const RegOp& o, int j) { return o.map(j); }, stg.ld_perm, stg.st_perm);
       for (const RegOp& o : pops) rops.push_back(emit_reg_op(o, set, mats));
       if (rbits == 4 && pops.size() % 2) rops.push_back(RbOp{kRbCopy, rops.back().mat});
-      fp.op_count = (int)rops.size() - fp.op_begin;
-      fill_phase_offsets(fp, rbits, ld_perm, st_perm);
-      phases.push_back(fp);
+      stg.op_count = (int)rops.size() - stg.op_begin;
+      stages.push_back(stg);
     }
-    d.op_count = (int)phases.size() - d.op_begin;
-    d.prog_ops = (int)(rops.size() - rops0);
-    d.prog_mats = (int)(mats.size() - mats0);
-    fill_entry_offsets(d, rbits);
-    set_direct_io(d, phases[d.op_begin], phases.back(), rbits);
-    launches.push_back({d, true, rbits});
+    RbBlock r;
+    layout_rb_block(b, std::move(stages), rbits, (h->fuse_flags & kFusedDirect) != 0, r, phases);
+    r.prog_ops = (int)(rops.size() - rops0);
+    r.prog_mats = (int)(mats.size() - mats0);
+    launches.push_back({d, r, true});
   }
-  const size_t ph_bytes = phases.size() * sizeof(FusedPhase);
+  const size_t ph_bytes = phases.size() * sizeof(RbPhase);
   const size_t ops_off = (ph_bytes + 255) & ~size_t(255);
   const size_t ops_bytes = ops.size() * sizeof(FusedOp);
   for (int i = 0; i < 2; ++i) rops.push_back(RbOp{kRbCopy, 0});   // read ahead, not run
@@ -873,7 +998,7 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
     if (rc) return rc;
     dev = h->fuse_dev;
   }
-  const FusedPhase* dph = static_cast<const FusedPhase*>(dev);
+  const RbPhase* dph = static_cast<const RbPhase*>(dev);
   const FusedOp* dops = reinterpret_cast<const FusedOp*>(static_cast<char*>(dev) + ops_off);
   const RbOp* drops = reinterpret_cast<const RbOp*>(static_cast<char*>(dev) + rops_off);
   const double2* dmats = reinterpret_cast<const double2*>(static_cast<char*>(dev) + mats_off);
@@ -884,17 +1009,16 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
   unsigned long long support = 0;
   for (size_t li = 0; li < launches.size(); ++li) {
     const Launch& L = launches[li];
-    unsigned long long tile_mask = ~0ull, tiles_of = 0;
-    for (int q = 0; q < L.d.c; ++q) tiles_of |= 1ull << q;
-    for (int i = 0; i < L.d.m; ++i) tiles_of |= 1ull << L.d.hi[i];
-    if (from_zero) {
-      tile_mask = tile_mask_of(tiles_of, support, h->nbits);
-      support |= tiles_of;
-    }
     timing_begin(h, KC_FUSED);
-    if (L.rb) launch_fused_rb(h->stream, h->data, h->nbits, L.d, dph, drops, dmats, L.rbits, set, 1, 0, 0,
-                              h->fuse_flags, tile_mask);
-    else launch_fused_block(h->stream, h->data, h->nbits, L.d, dops, dmats, h->fuse_k);
+    if (L.rb) {
+      const unsigned long long outside = ((1ull << nbits) - 1ull) & ~L.r.tile;
+      launch_fused_rb(h->stream, h->data, nbits, L.r, dph, drops, dmats, rbits, set,
+                      (h->fuse_flags & kFusedNonTemporal) != 0, from_zero ? outside & support : outside);
+      support |= L.r.tile;
+    } else {
+      launch_fused_block(h->stream, h->data, nbits, L.d, dops, dmats, h->fuse_k);
+      support = ~0ull;   // runs every tile (and may have touched any qubit)
+    }
     timing_end(h);
     const int rc = check_hip(hipGetLastError(), "fused_block");
     if (rc) return rc;
@@ -1093,8 +1217,10 @@ int nwq_fusion_plan(int n, int k, int n_gates, const int* types, const int* qubi
   std::vector<PGate> gates;
   int rc = parse_circuit(n, n_gates, types, qubits, nullptr, false, gates);
   if (rc) return rc;
-  nwq_state defaults;   // a state vector's low tile bits (no device memory)
-  const std::vector<Block> blocks = plan_blocks(gates, n, k, fusion_low_bits(&defaults, n, k), 8, false);
+  nwq_state defaults;   // a state vector's settings (no device memory)
+  defaults.fuse_k = k;
+  const std::vector<Block> blocks =
+      plan_blocks(gates, n, fusion_width(&defaults, n), fusion_low_bits(&defaults, n), 8, false);
   if (n_gates > 0 && blocks.empty()) return set_error(NWQ_EINVAL, "fusion planner made no progress");
   *n_blocks = (int)blocks.size();
   for (size_t b = 0; b < blocks.size(); ++b) {

@@ -103,8 +103,9 @@ std::vector<Block> plan_blocks(const std::vector<PGate>& g, int n, int k, int c,
 // can hold nonzero entries when the state is zero outside `support`: those with
 // bits in the returned mask only.
 unsigned long long tile_mask_of(unsigned long long tile, unsigned long long support, int nbits);
-// Low tile bits for a handle's fused blocks of width k over nbits bits.
-int fusion_low_bits(const nwq_state* h, int nbits, int k);
+// Tile width and low tile bits of a handle's fused blocks over nbits bits.
+int fusion_width(const nwq_state* h, int nbits);
+int fusion_low_bits(const nwq_state* h, int nbits);
 // internal gate type: dense 4x4 whose matrix is entry p[0] of a side table
 // Internal gate types whose matrix sits in a side table from entry p[0] on:
 // a dense 4x4 (16 entries), a diagonal 4x4 (16 entries, the diagonal at 5u),
@@ -171,9 +172,16 @@ inline int reg_swap(int a, int b, int j) {
 int local_bit(const Block& b, int q);
 void pad_block(Block& b, int n, int k_target);
 void fill_entry_offsets(FusedBlockDev& d, int rbits);
-// Marks the block's first / last phase for direct HBM loads / stores when its
-// register bits all lie above the low c tile bits (FusedBlockDev::direct).
-void set_direct_io(FusedBlockDev& d, const FusedPhase& first, const FusedPhase& last, int rbits);
+// A register phase before its addresses are laid out: register bits
+// (tile-local, ascending), the permutations folded into its loads and stores
+// (fold_permutations), its RbOps.
+struct RbStage {
+  int reg[4];
+  int ld_perm[16], st_perm[16];
+  int op_begin, op_count;
+};
+void layout_rb_block(const Block& b, std::vector<RbStage> stages, int rbits, bool direct, RbBlock& d,
+                     std::vector<RbPhase>& out);
 // c: the block's low tile bits; a phase with fewer gate bits than rbits is
 // padded with tile bits from c up first.
 std::vector<Phase> plan_phases(const std::vector<int>& order, const std::vector<std::array<int, 4>>& lb,

@@ -5,6 +5,8 @@
 // of 2^c amplitudes (c >= 6: 1 KiB wave-contiguous loads and stores); the
 // high bits pick which chunks form a tile.  Inside LDS each gate is a pass
 // over the tile with a barrier between gates.
+#include <type_traits>
+
 #include "nwq_internal.h"
 
 namespace nwq {
@@ -168,14 +170,25 @@ void launch_fused_block(hipStream_t s, double2* a, int nbits, const FusedBlockDe
 // Register-blocked variant.  Each of the 2^(k-R) threads of a tile holds 2^R
 // amplitudes that differ on R tile bits (the phase's register bits, R = 3 or
 // 4); every gate of the phase acts on those bits only and runs in registers.
-// Between phases the tile is exchanged through LDS (one write, one barrier,
-// one read), so LDS traffic is one tile pass per phase instead of one per
-// gate.  LDS rows are padded by one entry every 16 so that lanes whose local
-// indices differ by multiples of 16 land in different banks.
+// Between phases the tile is exchanged through LDS, its real parts first and
+// then its imaginary parts, so that a tile of 2^12 takes 32 KB.
 //
 // R trades registers for phases: R = 4 applies more gates per exchange but
-// needs 256 VGPRs (2 waves per SIMD); R = 3 fits 128 VGPRs and halves the LDS
-// per wave, so 4 waves per SIMD hide the LDS and HBM latency of each other.
+// needs about 135 VGPRs (two register sets); R = 3 fits 70, updates in place
+// and takes twice the phases.
+//
+// What bounds it: the vector units and the power they draw.  On the 30-qubit
+// depth-40 brickwork the HBM traffic of the 32 blocks of width 12 takes 0.18 s
+// and their FP64 instructions 0.13 s; with every tile read from cache 274 of
+// 284 ms remained, and the VALU is busy 69 % of the cycles at a clock that
+// sinks to 2.0 GHz (2.3 GHz at 52 %).  Three workgroups of four waves share a
+// CU (no tile is loaded ahead: the other workgroups' arithmetic hides a
+// tile's loads, and the exchanges of one wave the scalar loads of another).
+// Exchanges whose two phases keep the same tile bits on the wave index stay
+// inside a wave and need no barrier.  Against one workgroup of 2^13 tiles with
+// the next tile loaded ahead (221 VGPRs, 128 KB): 284 -> 278 ms; a 24-qubit
+// circuit of random pairs 1.72 -> 1.48 ms, the noisy TFIM on 14 qubits 58.3 ->
+// 54.8 ms, VQE n=20 L=8 (256 vectors) 79.7 -> 77.3 ms.
 // ===========================================================================
 namespace nwq {
 namespace {
@@ -185,8 +198,6 @@ __device__ __forceinline__ vd2 vmul(vd2 a, vd2 b) { return mkv(fma(a.x, b.x, -a.
 __device__ __forceinline__ vd2 vfma(vd2 a, vd2 b, vd2 c) {
   return mkv(fma(a.x, b.x, fma(-a.y, b.y, c.x)), fma(a.x, b.y, fma(a.y, b.x, c.y)));
 }
-__device__ __forceinline__ unsigned padl(unsigned l) { return l + (l >> 4); }
-
 // Every gate helper reads the register set x and writes all of y; x and y may be
 // the same array.  With 4 register bits the op loop alternates two register
 // sets, so each gate's results land directly in the registers the next gate
@@ -435,13 +446,6 @@ __device__ __forceinline__ void rb_apply(int code, const double2* __restrict__ M
 #undef NWQ_RBX
 }
 
-// Writes the 2^R registers of a phase back to their LDS entries.
-template <int R>
-__device__ __forceinline__ void rb_store_phase(double2* __restrict__ tl, const FusedPhase& ph, const vd2 (&v)[1 << R]) {
-#pragma unroll
-  for (int j = 0; j < (1 << R); ++j) stv(tl + ph.st_off[j], v[j]);
-}
-
 // Global loads and stores of tile entries; NT: non-temporal (each entry is
 // read and written once per block, so nothing is worth keeping in cache).
 template <bool NT>
@@ -455,22 +459,6 @@ __device__ __forceinline__ void gst(double2* p, vd2 v) {
   else stv(p, v);
 }
 
-// Kernel-side view of a register-blocked block: tile shape, phase range and
-// the global offsets of the registers a tile is loaded into (lo) and stored
-// from (so): the first / last phase's register layout when that phase moves
-// straight between HBM and registers (direct bits 0 / 1), else tile entry
-// j * 2^(k - R).
-struct RbBlockArgs {
-  int c, m;
-  int hi[8];
-  int op_begin, op_count;
-  int direct;
-  int sparse;                  // tiles t = 0, 1, ... are tile indices pdep(t, tmask)
-  int warm_ops, warm_mats;     // ops and matrix entries of the block, from its first (0: not warmed)
-  unsigned long long tmask;
-  unsigned long long lo[16], so[16];
-};
-
 // The bits of v deposited, lowest first, at the set bits of mask.
 __device__ __forceinline__ unsigned long long pdep64(unsigned long long v, unsigned long long mask) {
   unsigned long long r = 0;
@@ -479,112 +467,103 @@ __device__ __forceinline__ unsigned long long pdep64(unsigned long long v, unsig
   return r;
 }
 
+// XOR of the images of the set bits of v; images of register j: a constant
+// combination of the register bits' images.
+__device__ __forceinline__ unsigned thread_image(unsigned v, const unsigned short (&img)[kRbThreadBits]) {
+  unsigned x = 0;
+#pragma unroll
+  for (int i = 0; i < kRbThreadBits; ++i) x ^= (unsigned)((int)(v << (31 - i)) >> 31) & img[i];
+  return x;
+}
+__device__ __forceinline__ unsigned long long thread_image(unsigned v, const unsigned long long (&img)[kRbThreadBits]) {
+  unsigned long long x = 0;
+#pragma unroll
+  for (int i = 0; i < kRbThreadBits; ++i) x ^= (unsigned long long)(long long)((int)(v << (31 - i)) >> 31) & img[i];
+  return x;
+}
+template <class T>
+__device__ __forceinline__ T register_image(int j, const T (&img)[4]) {
+  T x = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if ((j >> i) & 1) x ^= img[i];
+  return x;
+}
+
+// One component of the tile in LDS, from LDS address 0 (the kernel has no
+// other LDS; going through the dynamic array's symbol would add its base to
+// every address).
+typedef __attribute__((address_space(3))) double* lds_double;
+__device__ __forceinline__ lds_double lds_at(unsigned byte) { return (lds_double)byte; }
+
 template <int R, int SET, bool NT>
-__global__ __launch_bounds__(R == 4 ? 512 : 1024) void k_fused_rb(double2* __restrict__ a0, int nbits,
-                                                                  RbBlockArgs blk,
-                                                                  const FusedPhase* __restrict__ phases,
+__global__ __launch_bounds__(R == 4 ? 512 : 1024) __attribute__((amdgpu_waves_per_eu(R == 4 ? 3 : 4))) void k_fused_rb(double2* __restrict__ a0, RbBlock blk,
+                                                                  const RbPhase* __restrict__ phases,
                                                                   const RbOp* __restrict__ ops,
                                                                   const double2* __restrict__ mats0,
                                                                   unsigned long long state_stride, int mat_stride,
-                                                                  unsigned long long ntiles) {
+                                                                  unsigned long long ntiles, unsigned long long mask,
+                                                                  unsigned long long step) {
   constexpr int NV = 1 << R;
-  extern __shared__ double2 t[];
   // batch element blockIdx.y: its own state and its own matrix table
   double2* __restrict__ a = a0 + (size_t)blockIdx.y * state_stride;
   const double2* __restrict__ mats = mats0 + (size_t)blockIdx.y * mat_stride;
-  const int c = blk.c, m = blk.m, k = c + m;
-  const unsigned len = 1u << k;
-  const unsigned nt = len >> R;
-  const unsigned cmask = (1u << c) - 1u;
-  const unsigned tid = threadIdx.x;
-  const int P = blk.op_count;
-  const bool ldd = (blk.direct & 1) != 0, sdd = (blk.direct & 2) != 0;
-  // thread bits -> the tile bits outside a phase's register bits: insert a
-  // zero at each (ascending) register position
-  auto spread = [&](const FusedPhase& ph) {
-    unsigned dep = tid;
-#pragma unroll
-    for (int r = 0; r < R; ++r) dep = ((dep >> ph.reg[r]) << (ph.reg[r] + 1)) | (dep & ((1u << ph.reg[r]) - 1u));
-    return dep;
+  const unsigned tid = threadIdx.x, nt = blockDim.x;
+  const int P = blk.ph_count;
+  if (blockIdx.x >= ntiles) return;
+  const RbPhase* __restrict__ pp = phases + blk.ph_begin;
+  const unsigned long long gl_ld = thread_image(tid, blk.ld_t), gl_st = thread_image(tid, blk.st_t);
+  vd2 v[NV];
+  // the tile's index bits plus gridDim.x, carried over the mask's gaps
+  auto advance = [&](unsigned long long base) { return ((base | ~mask) + step) & mask; };
+  unsigned long long tile = blockIdx.x, base = pdep64(tile, mask);
+  // One load per 64-byte line brings the block's program into this XCD's L2,
+  // ahead of the first tile's loads: each phase and op is read through the
+  // scalar cache when its turn comes, one after the other, and a workgroup
+  // with few tiles would wait out a miss to memory for every one of them
+  // (380 gates of a 10-qubit circuit in one block: 250 -> 150 us).
+  auto warm = [&](const char* p, unsigned bytes) {
+    for (unsigned i = tid * 64u; i < bytes; i += nt * 64u) {
+      const int x = *reinterpret_cast<const int*>(p + i);
+      asm volatile("" ::"v"(x));
+    }
   };
-  // thread part of the entry indices of the load and store layouts
-  const unsigned long long gl_ld = tile_index(0ull, ldd ? spread(phases[blk.op_begin]) : tid, cmask, c, m, blk);
-  const unsigned long long gl_st = tile_index(0ull, sdd ? spread(phases[blk.op_begin + P - 1]) : tid, cmask, c, m, blk);
-  auto tile_base = [&](unsigned long long t) {
-    unsigned long long base = (blk.sparse ? pdep64(t, blk.tmask) : t) << c;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i < m) {
-        const int q = blk.hi[i];
-        base = ((base >> q) << (q + 1)) | (base & ((1ull << q) - 1ull));
+  warm(reinterpret_cast<const char*>(pp), P * sizeof(RbPhase));
+  {
+    const RbOp* po = ops + pp[0].op_begin;
+    warm(reinterpret_cast<const char*>(po), blk.prog_ops * sizeof(RbOp));
+    if (blk.prog_mats > 0) {
+      warm(reinterpret_cast<const char*>(mats + po[0].mat), blk.prog_mats * sizeof(double2));
+    } else {   // 2x2 entries spread over a larger table
+      for (unsigned i = tid; i < (unsigned)blk.prog_ops; i += nt) {
+        const int x = *reinterpret_cast<const int*>(mats + po[i].mat);
+        asm volatile("" ::"v"(x));
       }
     }
-    return base;
-  };
-  // A tile's NV entries per thread are loaded one tile ahead: the loads of
-  // the next tile are in flight while this one runs its phases (tiles are
-  // disjoint, so the early read is safe).  A tile's results go to HBM after
-  // its last phase and before the next tile's loaded registers are used; the
-  // vector memory counter retires in issue order, so the wait for those loads
-  // (issued before the stores) leaves the stores in flight.  The loaded
-  // registers are taken up at the bottom of the loop, behind the stores on
-  // every path into it: at the loop head the paths from the first tile and
-  // from the back edge differ, and the compiler's wait counts, merged there,
-  // would wait for the stores too.  With direct I/O the first phase runs on
-  // the loaded registers and the last phase's registers are the results, so
-  // a block of one such phase never touches LDS.
-  if (blockIdx.x >= ntiles) return;
-  vd2 pf[NV], v[NV];
-  // first phase input: the registers themselves, or the tile in LDS (every
-  // wave must be done reading the previous tile before it is overwritten)
-  auto take_loaded = [&]() {
-    if (ldd) {
-#pragma unroll
-      for (int j = 0; j < NV; ++j) v[j] = pf[j];
-    } else {
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < NV; ++j) stv(t + padl(tid + j * nt), pf[j]);
-    }
-  };
-  auto load_tile = [&](unsigned long long tl) {
-    const double2* __restrict__ p = a + tile_base(tl) + gl_ld;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) pf[j] = gld<NT>(p + blk.lo[j]);
-  };
-  unsigned long long tile = blockIdx.x;
-  load_tile(tile);
-  // Behind the first tile's loads, one load per 64-byte line brings the
-  // block's program into this XCD's L2: each phase and op is read through the
-  // scalar cache when its turn comes, one after the other, and a workgroup
-  // with few tiles would wait out a miss to memory for every one of them.
-  {
-    int x = 0;
-    const char* pp = reinterpret_cast<const char*>(phases + blk.op_begin);
-    const RbOp* po = ops + phases[blk.op_begin].op_begin;
-    for (unsigned i = tid * 64u; i < P * sizeof(FusedPhase); i += nt * 64u) x |= *reinterpret_cast<const int*>(pp + i);
-    for (unsigned i = tid * 64u; i < blk.warm_ops * sizeof(RbOp); i += nt * 64u)
-      x |= *reinterpret_cast<const int*>(reinterpret_cast<const char*>(po) + i);
-    if (blk.warm_mats > 0) {
-      const char* pm = reinterpret_cast<const char*>(mats + po[0].mat);
-      for (unsigned i = tid * 64u; i < blk.warm_mats * sizeof(double2); i += nt * 64u)
-        x |= *reinterpret_cast<const int*>(pm + i);
-    } else {   // 2x2 entries spread over a larger table
-      for (unsigned i = tid; i < (unsigned)blk.warm_ops; i += nt) x |= *reinterpret_cast<const int*>(mats + po[i].mat);
-    }
-    asm volatile("" ::"v"(x));
   }
-  take_loaded();
-  if (tile + gridDim.x < ntiles) load_tile(tile + gridDim.x);
   for (;;) {
-    for (int pi = 0; pi < P; ++pi) {
-      const FusedPhase ph = phases[blk.op_begin + pi];
-      // padl(dep | off) = padl(dep) + padl(off) for disjoint bit sets
-      double2* __restrict__ tl = t + padl(spread(ph));
-      if (pi > 0 || !ldd) {
-        __syncthreads();
+    {
+      const double2* __restrict__ p = a + (base | gl_ld);
 #pragma unroll
-        for (int j = 0; j < NV; ++j) v[j] = ldv(tl + ph.ld_off[j]);
+      for (int j = 0; j < NV; ++j) v[j] = gld<NT>(p + register_image(j, blk.ld_r));
+    }
+    for (int pi = 0; pi < P; ++pi) {
+      const RbPhase ph = pp[pi];
+      if (pi > 0) {
+        const unsigned wa = thread_image(tid, ph.wr_t) << 3, ra = thread_image(tid, ph.rd_t) << 3;
+        const bool across = (ph.flags & kRbBarrierInside) != 0;
+        if (ph.flags & kRbBarrierBefore) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NV; ++j) *lds_at(wa ^ (register_image(j, ph.wr_r) << 3)) = v[j].x;
+        if (across) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NV; ++j) v[j].x = *lds_at(ra ^ (register_image(j, ph.rd_r) << 3));
+        if (across) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NV; ++j) *lds_at(wa ^ (register_image(j, ph.wr_r) << 3)) = v[j].y;
+        if (across) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NV; ++j) v[j].y = *lds_at(ra ^ (register_image(j, ph.rd_r) << 3));
       }
       const RbOp* __restrict__ po = ops + ph.op_begin;
       // the next ops' codes are loaded while this one runs (the table ends
@@ -608,93 +587,52 @@ __global__ __launch_bounds__(R == 4 ? 512 : 1024) void k_fused_rb(double2* __res
           o = nx;
         }
       }
-      if (pi < P - 1 || !sdd) {   // else the results stay in v
-        // the tile's first LDS write when the first phase came from HBM:
-        // every wave must be done reading the previous tile
-        if (pi == 0 && ldd) __syncthreads();
-        rb_store_phase<R>(tl, ph, v);
-      }
     }
-    if (!sdd) {
-      __syncthreads();
+    double2* __restrict__ out = a + (base | gl_st);
 #pragma unroll
-      for (int j = 0; j < NV; ++j) v[j] = ldv(t + padl(tid + j * nt));
-    }
-    double2* __restrict__ out = a + tile_base(tile) + gl_st;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) gst<NT>(out + blk.so[j], v[j]);
+    for (int j = 0; j < NV; ++j) gst<NT>(out + register_image(j, blk.st_r), v[j]);
     tile += gridDim.x;
     if (tile >= ntiles) break;
-    take_loaded();
-    if (tile + gridDim.x < ntiles) load_tile(tile + gridDim.x);
+    base = advance(base);
   }
 }
 
 }  // namespace
 
-size_t fused_rb_lds_bytes(int k) { return sizeof(double2) * ((1u << k) + (1u << k) / 16); }
-
-int fused_rb_enable_lds() {
-  int rc = NWQ_OK;
-  for (const void* f : {(const void*)k_fused_rb<4, kRbSetVQE, false>, (const void*)k_fused_rb<4, kRbSetVQE, true>})
-    if (!rc) rc = enable_dynamic_lds(f);
-  return rc;
-}
-
-void launch_fused_rb(hipStream_t s, double2* a, int nbits, const FusedBlockDev& blk, const FusedPhase* phases,
-                     const RbOp* ops, const double2* mats, int rbits, int set, int batch, int mat_stride, int max_grid,
-                     int flags, unsigned long long tile_mask) {
-  const int k = blk.c + blk.m;
-  unsigned long long ntiles = 1ull << (nbits - k);
-  const bool sparse = tile_mask != ~0ull && __builtin_popcountll(tile_mask) < nbits - k;
-  if (sparse) ntiles = 1ull << __builtin_popcountll(tile_mask);
-  // about four tiles per workgroup (so that the next tile's loads overlap
-  // this one's phases), at least 2048 workgroups
-  const unsigned long long cap = max_grid > 0 ? (unsigned long long)max_grid
-                                              : (ntiles / 4 > 2048 ? ntiles / 4 : 2048);
+void launch_fused_rb(hipStream_t s, double2* a, int nbits, const RbBlock& blk, const RbPhase* phases, const RbOp* ops,
+                     const double2* mats, int rbits, int set, bool non_temporal, unsigned long long mask, int batch,
+                     int mat_stride, int max_grid) {
+  const unsigned long long ntiles = 1ull << __builtin_popcountll(mask);
+  // 768 workgroups of width 12 run at a time; many more of them than that keep
+  // the last round short (n=30: 286 ms with 4096, 278 with 16384)
+  const unsigned long long cap = max_grid > 0 ? (unsigned long long)max_grid : 16384;
   const unsigned grid = (unsigned)(ntiles < cap ? ntiles : cap);
-  const size_t lds = fused_rb_lds_bytes(k);
+  const size_t lds = sizeof(double) << blk.k;   // at most 64 KiB
   const unsigned long long stride = batch > 1 ? (1ull << nbits) : 0ull;
-  RbBlockArgs b{};
-  b.c = blk.c;
-  b.m = blk.m;
-  for (int i = 0; i < 8; ++i) b.hi[i] = blk.hi[i];
-  b.op_begin = blk.op_begin;
-  b.op_count = blk.op_count;
-  b.direct = (flags & kFusedDirect) ? blk.direct : 0;
-  b.sparse = sparse ? 1 : 0;
-  b.tmask = sparse ? tile_mask : 0ull;
-  b.warm_ops = blk.prog_ops;
-  b.warm_mats = blk.prog_mats;
-  for (int j = 0; j < 16; ++j) {
-    b.lo[j] = (b.direct & 1) ? blk.jdir[j] : blk.joff[j];
-    b.so[j] = (b.direct & 2) ? blk.sdir[j] : blk.joff[j];
+  unsigned long long step = 0;   // gridDim.x deposited at the mask's bits
+  {
+    unsigned long long m = mask;
+    for (unsigned v = grid; v && m; v >>= 1, m &= m - 1)
+      if (v & 1u) step |= m & (~m + 1ull);
   }
-  auto go = [&](auto kern, int rb) {
-    if (lds > 65536) (void)enable_dynamic_lds((const void*)kern);
-    hipLaunchKernelGGL(kern, dim3(grid, batch), dim3(1u << (k - rb)), lds, s, a, nbits, b, phases, ops, mats,
-                       stride, mat_stride, ntiles);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(grid, batch), dim3(1u << (blk.k - rbits)), lds, s, a, blk, phases, ops, mats, stride,
+                       mat_stride, ntiles, mask, step);
   };
-  const bool nt = (flags & kFusedNonTemporal) != 0;
+  auto pick = [&](auto R, auto SET) {
+    if (non_temporal) go(k_fused_rb<decltype(R)::value, decltype(SET)::value, true>);
+    else go(k_fused_rb<decltype(R)::value, decltype(SET)::value, false>);
+  };
+  using R3 = std::integral_constant<int, 3>;
+  using R4 = std::integral_constant<int, 4>;
   if (set == kRbSetVQE) {   // 4 register bits only
-    if (nt) go(k_fused_rb<4, kRbSetVQE, true>, 4);
-    else go(k_fused_rb<4, kRbSetVQE, false>, 4);
+    pick(R4{}, std::integral_constant<int, kRbSetVQE>{});
   } else if (set == kRbSetDM) {
-    if (rbits == 3) {
-      if (nt) go(k_fused_rb<3, kRbSetDM, true>, 3);
-      else go(k_fused_rb<3, kRbSetDM, false>, 3);
-    } else {
-      if (nt) go(k_fused_rb<4, kRbSetDM, true>, 4);
-      else go(k_fused_rb<4, kRbSetDM, false>, 4);
-    }
+    if (rbits == 3) pick(R3{}, std::integral_constant<int, kRbSetDM>{});
+    else pick(R4{}, std::integral_constant<int, kRbSetDM>{});
   } else {
-    if (rbits == 3) {
-      if (nt) go(k_fused_rb<3, kRbSetSV, true>, 3);
-      else go(k_fused_rb<3, kRbSetSV, false>, 3);
-    } else {
-      if (nt) go(k_fused_rb<4, kRbSetSV, true>, 4);
-      else go(k_fused_rb<4, kRbSetSV, false>, 4);
-    }
+    if (rbits == 3) pick(R3{}, std::integral_constant<int, kRbSetSV>{});
+    else pick(R4{}, std::integral_constant<int, kRbSetSV>{});
   }
 }
 

@@ -153,34 +153,21 @@ struct FusedBlockDev {
   int c, m;                 // tile = low c bits + m high bits
   int hi[8];
   int op_begin, op_count;   // range in the op table
-  // register-blocked kernels: global offset of tile entry j * 2^(k - rbits)
+  // VQE backward kernel: global offset of tile entry j * 2^(k - rbits)
   // (the per-thread part of an entry's index is added to it)
   unsigned long long joff[16];
-  // Register-blocked SV kernel: bit 0 = the first phase's register bits all
-  // lie above the low c tile bits, so its registers are loaded straight from
-  // HBM (register j from the tile entry at jdir[j] plus the thread's part);
-  // bit 1 = the same for the last phase, stored straight to HBM (sdir).
-  // Such a phase skips its LDS round trip and barrier.
-  int direct;
-  unsigned long long jdir[16], sdir[16];
-  // register-blocked kernels: ops and matrix entries of the block's program,
-  // contiguous from its first op's (0: the matrices lie elsewhere)
-  int prog_ops, prog_mats;
 };
 void launch_fused_block(hipStream_t s, double2* a, int nbits, const FusedBlockDev& blk,
                         const FusedOp* ops, const double2* mats, int lds_k);
-// Register-blocked blocks: blk.op_begin / op_count index a phase table; each
-// phase holds rbits (3 or 4) register bits (tile-local, ascending; unused
-// entries of reg ignored) and a range of RbOps (an even number at 4 register
-// bits); the op table ends with two spare entries.  Tiles of 2^k amplitudes,
-// 8 <= k <= 13, 2^(k-rbits) threads.
+// A register phase of the VQE backward kernel: its register bits (tile-local,
+// ascending; unused entries ignored) and its ops.
 struct FusedPhase {
   int reg[4];
   int op_begin, op_count;
   int pad0, pad1;
-  // Register-blocked SV kernel: the padded LDS offset (over the phase's
-  // register bits) that register j is loaded from and stored to.  Permutation
-  // gates at the start or the end of a phase are folded into these.
+  // The padded LDS offset (over the phase's register bits) that register j is
+  // loaded from and stored to.  Permutation gates at the start or the end of a
+  // phase are folded into these.
   unsigned short ld_off[16], st_off[16];
 };
 // ld_perm[j] / st_perm[j]: register-bit index whose entry register j loads /
@@ -198,25 +185,49 @@ inline void fill_phase_offsets(FusedPhase& fp, int rbits, const int* ld_perm, co
     fp.st_off[j] = in ? off(st_perm ? st_perm[j] : j) : 0;
   }
 }
-size_t fused_rb_lds_bytes(int k);
-// enable_dynamic_lds for the register-blocked VQE instances (outside graph capture)
-int fused_rb_enable_lds();
+// Register-blocked blocks (kernels_fuse.hip).  A tile of 2^k entries belongs
+// to 2^(k - R) threads of 2^R registers each (R = 3 or 4, 8 <= k <= 13).  In
+// each phase R tile bits are register bits and the others thread bits; every
+// index map (global address, LDS address) is linear over GF(2) in the thread
+// and register bits, so a map is given by the images of the single bits, which
+// are XORed together.
+constexpr int kRbThreadBits = 10;   // most thread bits (k = 13, R = 3)
+constexpr int kRbBarrierBefore = 1, kRbBarrierInside = 2;
+struct RbPhase {
+  int op_begin;             // RbOps (an even number at 4 register bits; the op table ends with two spare entries)
+  short op_count, flags;
+  // The LDS exchange that leads into this phase (not for the first): entries
+  // where the previous phase's registers are written and where this phase's
+  // are read.  kRbBarrierBefore: other waves may still read the entries that
+  // are written; kRbBarrierInside: a wave reads entries of others (else all it
+  // reads are its own, and LDS serves a wave in order).
+  unsigned short wr_t[kRbThreadBits], wr_r[4], rd_t[kRbThreadBits], rd_r[4];
+};
+struct RbBlock {
+  int k;
+  int ph_begin, ph_count;   // range in the phase table
+  // ops and matrix entries of the block's program, contiguous from its first
+  // op's (0 entries: the matrices lie elsewhere)
+  int prog_ops, prog_mats;
+  unsigned long long tile;  // the tile's bits of the global index
+  // global index of the first phase's entries (loaded) and the last's (stored)
+  unsigned long long ld_t[kRbThreadBits], ld_r[4], st_t[kRbThreadBits], st_r[4];
+};
 // batch > 1: blockIdx.y = batch element b works on a + b * 2^nbits with the
-// matrix table mats + b * mat_stride; max_grid caps the tiles' grid (0 = 2^20).
-// flags: kFusedNonTemporal = non-temporal global loads and stores of the
-// tiles; kFusedDirect = load the first phase / store the last phase straight
-// between HBM and registers where the block allows it (FusedBlockDev::direct).
-// tile_mask != ~0 runs only the tiles whose index is zero outside tile_mask
-// (the block leaves the others alone: used when they are known to hold zeros,
+// matrix table mats + b * mat_stride; max_grid caps the tiles' grid (0: 16384).
+// non_temporal: global loads and stores of the tiles.  mask: bits of the global
+// index outside the tile that the block's tiles run over (the block leaves
+// tiles with other bits set alone: used when they are known to hold zeros,
 // which a block maps to zeros).
+void launch_fused_rb(hipStream_t s, double2* a, int nbits, const RbBlock& blk, const RbPhase* phases, const RbOp* ops,
+                     const double2* mats, int rbits, int set, bool non_temporal, unsigned long long mask,
+                     int batch = 1, int mat_stride = 0, int max_grid = 0);
+// nwq_set_fusion_flags / nwq_vqe_set_flags bits
 constexpr int kFusedNonTemporal = 1;
-constexpr int kFusedDirect = 2;
-// SV circuits (host side): gate products before the blocks are planned, where
-// they save FP64 work (circuit.hip, gate_products).
-constexpr int kFusedGateFusion = 4;
-void launch_fused_rb(hipStream_t s, double2* a, int nbits, const FusedBlockDev& blk, const FusedPhase* phases,
-                     const RbOp* ops, const double2* mats, int rbits, int set, int batch = 1, int mat_stride = 0,
-                     int max_grid = 0, int flags = 0, unsigned long long tile_mask = ~0ull);
+constexpr int kFusedDirect = 2;      // first / last phase straight between HBM and registers where its lanes
+                                     // cover contiguous runs
+constexpr int kFusedGateFusion = 4;  // SV circuits (host side): gate products before the blocks are planned,
+                                     // where they save FP64 work, and merged diagonals (circuit.hip)
 
 // ---- error handling (engine.hip) ------------------------------------------
 int set_error(int code, const std::string& msg);

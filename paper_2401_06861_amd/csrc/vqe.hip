@@ -1381,7 +1381,8 @@ struct nwq_vqe {
   int fused_rbits = 4;         // register bits per phase of the forward kernel
   bool bwd_rb = false;         // backward sweep register-blocked (3 bits) when every tile has >= 2^9 entries
   size_t fused_rop_off = 0;    // offset of the register-blocked backward ops in d_fused
-  std::vector<nwq::FusedBlockDev> fwd_blocks, bwd_blocks;
+  std::vector<nwq::RbBlock> fwd_blocks;
+  std::vector<nwq::FusedBlockDev> bwd_blocks;
   // Tiles of each backward dispatch: tile indices with bits in the mask only.
   // Before a block's gates phi is zero wherever a qubit that no earlier block
   // touched is set, so tiles set on such a qubit (outside the block's own) add
@@ -1398,8 +1399,8 @@ struct nwq_vqe {
   };
   std::vector<HLaunch> hlaunch;
   size_t fused_hterm_off = 0, fused_widx_off = 0;
-  void* d_fused = nullptr;     // [forward phases][forward ops][backward ops]
-  size_t fused_ops_off = 0, fused_bwd_off = 0;
+  void* d_fused = nullptr;     // [backward phases][forward phases][forward ops][backward ops][H terms]
+  size_t fused_fph_off = 0, fused_ops_off = 0, fused_bwd_off = 0;
   nwq::VqeConfig cfg;
   std::map<std::pair<int, int>, hipGraphExec_t> graphs;   // (B, want_grad) -> exec
   int fused_flags = 3;         // fused schedule: bit 0 non-temporal tile loads and stores, bit 1 direct
@@ -1550,7 +1551,8 @@ static int build_fused(nwq_vqe* h) {
   const int k = std::min(h->fused_k, n);
   const std::vector<Block> blocks = plan_blocks(g, n, std::max(k, 6), low, kVqeSeeds, true);
   if (blocks.empty() && h->nops > 0) return set_error(NWQ_EINVAL, "fusion planner made no progress");
-  std::vector<FusedPhase> phases;
+  std::vector<RbPhase> fphases;     // forward
+  std::vector<FusedPhase> phases;   // backward
   std::vector<RbOp> fops;
   std::vector<VqeBwdOp> bops;
   h->fwd_blocks.clear();
@@ -1568,13 +1570,10 @@ static int build_fused(nwq_vqe* h) {
       lb[gi] = {local_bit(b, g[gi].q[0]), g[gi].nq == 2 ? local_bit(b, g[gi].q[1]) : 0};
       nq[gi] = g[gi].nq;
     }
-    FusedBlockDev d{};
-    d.c = b.c;
-    d.m = b.m;
-    for (int i = 0; i < b.m; ++i) d.hi[i] = b.hi[i];
-    d.op_begin = (int)phases.size();
+    const int fops0 = (int)fops.size();
+    std::vector<RbStage> stages;
     for (const Phase& ph : plan_phases(b.gates, lb, nq, kb, b.c, h->fused_rbits)) {
-      FusedPhase fp{};
+      RbStage fp{};
       for (int i = 0; i < 4; ++i) fp.reg[i] = ph.reg[i] < 0 ? 0 : ph.reg[i];
       fp.op_begin = (int)fops.size();
       auto ridx = [&](int bit) {
@@ -1602,21 +1601,19 @@ static int build_fused(nwq_vqe* h) {
         else f.o.code = kRbSwap + pair, f.perm = 2;
         pops.push_back(f);
       }
-      int ld_perm[16], st_perm[16];
       fold_permutations(
           pops, h->fused_rbits, [](const FwdOp& o) { return o.perm != 0; }, [](const FwdOp& o) { return o.bits; },
-          [](const FwdOp& o, int j) { return o.perm == 1 ? reg_cx(o.b0, o.b1, j) : reg_swap(o.b0, o.b1, j); }, ld_perm,
-          st_perm);
+          [](const FwdOp& o, int j) { return o.perm == 1 ? reg_cx(o.b0, o.b1, j) : reg_swap(o.b0, o.b1, j); },
+          fp.ld_perm, fp.st_perm);
       for (const FwdOp& f : pops) fops.push_back(f.o);
       if (pops.size() % 2) fops.push_back(RbOp{kRbCopy, fops.back().mat});
       fp.op_count = (int)fops.size() - fp.op_begin;
-      fill_phase_offsets(fp, h->fused_rbits, ld_perm, st_perm);
-      phases.push_back(fp);
+      stages.push_back(fp);
     }
-    d.op_count = (int)phases.size() - d.op_begin;
-    d.prog_ops = (int)fops.size() - phases[d.op_begin].op_begin;   // matrices: per-vector table
-    fill_entry_offsets(d, h->fused_rbits);
-    set_direct_io(d, phases[d.op_begin], phases.back(), h->fused_rbits);
+    if (stages.empty()) continue;
+    RbBlock d;
+    layout_rb_block(b, std::move(stages), h->fused_rbits, (h->fused_flags & kFusedDirect) != 0, d, fphases);
+    d.prog_ops = (int)fops.size() - fops0;   // matrices: per-vector table
     h->fwd_blocks.push_back(d);
   }
   for (int i = 0; i < 2; ++i) fops.push_back(RbOp{kRbCopy, 0});   // read ahead, not run
@@ -1821,7 +1818,8 @@ static int build_fused(nwq_vqe* h) {
     }
   }
   const size_t ph_bytes = phases.size() * sizeof(FusedPhase);
-  h->fused_ops_off = (ph_bytes + 255) & ~size_t(255);
+  h->fused_fph_off = (ph_bytes + 255) & ~size_t(255);
+  h->fused_ops_off = (h->fused_fph_off + fphases.size() * sizeof(RbPhase) + 255) & ~size_t(255);
   h->fused_bwd_off = (h->fused_ops_off + fops.size() * sizeof(RbOp) + 255) & ~size_t(255);
   h->fused_rop_off = (h->fused_bwd_off + bops.size() * sizeof(VqeBwdOp) + 255) & ~size_t(255);
   h->fused_hterm_off = (h->fused_rop_off + rops.size() * sizeof(VqeBwdRop) + 255) & ~size_t(255);
@@ -1829,6 +1827,7 @@ static int build_fused(nwq_vqe* h) {
   const size_t total = h->fused_widx_off + widx.size() * sizeof(int) + 16;
   std::vector<char> prog(total, 0);
   if (!phases.empty()) std::memcpy(prog.data(), phases.data(), ph_bytes);
+  if (!fphases.empty()) std::memcpy(prog.data() + h->fused_fph_off, fphases.data(), fphases.size() * sizeof(RbPhase));
   if (!fops.empty()) std::memcpy(prog.data() + h->fused_ops_off, fops.data(), fops.size() * sizeof(RbOp));
   if (!bops.empty()) std::memcpy(prog.data() + h->fused_bwd_off, bops.data(), bops.size() * sizeof(VqeBwdOp));
   if (!rops.empty()) std::memcpy(prog.data() + h->fused_rop_off, rops.data(), rops.size() * sizeof(VqeBwdRop));
@@ -1845,7 +1844,6 @@ static int build_fused(nwq_vqe* h) {
                         (const void*)k_vqe_hphi_tile<false, true>, (const void*)k_vqe_hphi_tile<true, true>,
                         (const void*)k_vqe_bwd_rb<3, false>, (const void*)k_vqe_bwd_rb<3, true>})
     if (!rc) rc = enable_dynamic_lds(f);
-  if (!rc) rc = fused_rb_enable_lds();
   if (!rc) rc = check_hip(hipMalloc(&h->d_fused, total), "hipMalloc(vqe fused program)");
   if (!rc) rc = check_hip(hipMemcpy(h->d_fused, prog.data(), total, hipMemcpyHostToDevice), "hipMemcpy(vqe fused program)");
   if (rc) return rc;
@@ -1869,6 +1867,7 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
   const int G = fused_grid(h);
   const dim3 grid(G, B);
   const FusedPhase* dph = static_cast<const FusedPhase*>(h->d_fused);
+  const RbPhase* dfp = reinterpret_cast<const RbPhase*>(static_cast<char*>(h->d_fused) + h->fused_fph_off);
   const RbOp* dfo = reinterpret_cast<const RbOp*>(static_cast<char*>(h->d_fused) + h->fused_ops_off);
   const VqeBwdOp* dbo = reinterpret_cast<const VqeBwdOp*>(static_cast<char*>(h->d_fused) + h->fused_bwd_off);
   const int stride = 8 * h->nops;
@@ -1881,14 +1880,10 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
   // on its non-tile qubits outside that support (the first block: tile 0)
   unsigned long long support = 0;
   for (size_t bi = 0; bi < h->fwd_blocks.size(); ++bi) {
-    const FusedBlockDev& d = h->fwd_blocks[bi];
-    unsigned long long tiles_of = 0;
-    for (int q = 0; q < d.c; ++q) tiles_of |= 1ull << q;
-    for (int i = 0; i < d.m; ++i) tiles_of |= 1ull << d.hi[i];
-    const unsigned long long tile_mask = tile_mask_of(tiles_of, support, h->n);
-    support |= tiles_of;
-    launch_fused_rb(s, h->d_phi, h->n, d, dph, dfo, h->d_table, h->fused_rbits, kRbSetVQE, B, stride, G,
-                    h->fused_flags, tile_mask);
+    const RbBlock& d = h->fwd_blocks[bi];
+    launch_fused_rb(s, h->d_phi, h->n, d, dfp, dfo, h->d_table, h->fused_rbits, kRbSetVQE,
+                    (h->fused_flags & kFusedNonTemporal) != 0, support & ~d.tile, B, stride, G);
+    support |= d.tile;
   }
   const HTerm* dht = reinterpret_cast<const HTerm*>(static_cast<char*>(h->d_fused) + h->fused_hterm_off);
   const int* dwi = reinterpret_cast<const int*>(static_cast<char*>(h->d_fused) + h->fused_widx_off);
@@ -2130,6 +2125,13 @@ int nwq_vqe_set_config(nwq_vqe_handle h, int mode, int threads, int blocks_per_s
   return NWQ_OK;
 }
 
+static void drop_fused(nwq_vqe* h) {   // the stream is idle and no graph holds the program
+  if (h->d_fused) (void)hipFree(h->d_fused);
+  h->d_fused = nullptr;
+  h->fused_built = false;
+  h->fused_bytes = 0;
+}
+
 int nwq_vqe_set_flags(nwq_vqe_handle h, int flags) {
   if (!h) return vqe_fail(NWQ_EINVAL, "NULL handle");
   if (flags < 0 || flags > 3) return vqe_fail(NWQ_EINVAL, "flags must be in [0, 3]");
@@ -2137,6 +2139,7 @@ int nwq_vqe_set_flags(nwq_vqe_handle h, int flags) {
     (void)hipStreamSynchronize(h->stream);
     for (auto& kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
     h->graphs.clear();
+    if ((flags ^ h->fused_flags) & kFusedDirect) drop_fused(h);   // the phases' layouts are planned again on next use
     h->fused_flags = flags;
   }
   return NWQ_OK;
@@ -2149,10 +2152,7 @@ int nwq_vqe_set_lowbits(nwq_vqe_handle h, int c) {
     (void)hipStreamSynchronize(h->stream);
     for (auto& kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
     h->graphs.clear();
-    if (h->d_fused) (void)hipFree(h->d_fused);
-    h->d_fused = nullptr;
-    h->fused_built = false;
-    h->fused_bytes = 0;
+    drop_fused(h);
     h->low_bits = c;
   }
   return NWQ_OK;

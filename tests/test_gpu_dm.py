@@ -504,3 +504,29 @@ def test_dm_errors(nwq):
     assert e.value.code == nwq.NWQ_EINVAL
     assert maxerr(st.numpy(), rho0) == 0.0
     st.close()
+
+
+@pytest.mark.parametrize("n,k", [(4, 8), (5, 10), (6, 12), (7, 12)])
+def test_fused_superoperator_kinds(nwq, n, k):
+    """Fused superoperators of every kind the kernel tells apart: real (RY),
+    real and imaginary by parity (RX), dense (U3, H after S) 4x4 forms, 16x16
+    forms in the Pauli pattern (RZZ) and dense (CX), each with its noise, on
+    all qubits and both operator orders, against the oracle."""
+    rng = np.random.default_rng(10 * n + k)
+    ops = []
+    for q in range(n):
+        t = [float(x) for x in rng.uniform(-3, 3, 5)]
+        a, b = q, (q + 1 + int(rng.integers(n - 1))) % n
+        gates = [("ry", (q,), (t[0],)), ("rx", (q,), (t[1],)), ("u3", (q,), tuple(t[2:])), ("s", (q,), ()),
+                 ("h", (q,), ()), ("rzz", (a, b), (t[0],)), ("rx", (b,), (t[1],)), ("cx", (b, a), ()),
+                 ("ry", (a,), (t[2],)), ("rzz", (b, a), (t[3],))]
+        ops += W.with_noise(gates, W.NoiseSpec())
+    want = tensor.dm_run(ops, n)
+    st = nwq.DMState(n)
+    st.set_fusion(k)
+    for rb in (1, 2):
+        nwq.nwq_set_fusion_kernel(st.h, rb)
+        st.reset()
+        st.run(ops)
+        assert maxerr(st.numpy(), want) <= TOL, (n, k, rb)
+    st.close()

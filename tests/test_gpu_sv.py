@@ -663,3 +663,31 @@ def test_run_circuit_from_zero(nwq, n, k, lead):
         nwq.nwq_apply_circuit(st.h, *arrays)
         assert np.array_equal(st.numpy(), got), (n, k, rb)
         st.close()
+
+
+@pytest.mark.parametrize("n,k", [(8, 8), (10, 8), (11, 11), (13, 12), (13, 13), (15, 13), (17, 10)])
+def test_fused_phase_layouts(nwq, n, k):
+    """Register phases, their LDS exchanges (inside a wave and across waves,
+    with permutations folded in), merged diagonals and the RX kind: circuits
+    of every gate kind on random pairs, tiles of one to eight waves and of the
+    whole register, both register-blocked kernels, with the phases' HBM
+    accesses direct or through a phase of their own and with or without
+    products, against the oracle."""
+    gates = W.random_gate_list(n, 150, seed=n * 31 + k)
+    rng = np.random.default_rng(n + k)
+    for _ in range(30):   # diagonals on both sides of permutations, RX between
+        a, b, c = (int(x) for x in rng.choice(n, size=3, replace=False))
+        t = [float(x) for x in rng.uniform(-3, 3, 4)]
+        gates += [("rzz", (a, b), (t[0],)), ("cx", (a, c), ()), ("rz", (c,), (t[1],)), ("swap", (b, c), ()),
+                  ("cz", (a, b), ()), ("rx", (b,), (t[2],)), ("cx", (c, b), ()), ("rzz", (b, c), (t[3],))]
+    want = tensor.sv_run(gates, n)
+    arrays = nwq.circuit_arrays(gates)
+    st = nwq.SVState(n)
+    st.set_fusion(k)
+    for rb in (1, 2):
+        nwq.nwq_set_fusion_kernel(st.h, rb)
+        for flags in (7, 5, 3, 0):
+            nwq.nwq_set_fusion_flags(st.h, flags)
+            nwq.nwq_run_circuit(st.h, *arrays)
+            assert maxerr(st.numpy(), want) <= TOL, (n, k, rb, flags)
+    st.close()

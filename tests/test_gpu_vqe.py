@@ -343,3 +343,22 @@ def test_vqe_batch_one_call(V, torch):
     with pytest.raises(nwq.NwqError) as e:
         V.vqe_batch(31, 1, 1.0, 1.0, torch.zeros(1, 62, dtype=torch.float64, device="cuda"))
     assert e.value.code == nwq.NWQ_ERANGE
+
+
+@pytest.mark.parametrize("n,L,B", [(13, 9, 2), (16, 6, 3), (18, 3, 1)])
+def test_fused_sweep_matches_per_gate_schedule(V, torch, n, L, B):
+    """Blocks of more ops than one backward dispatch takes (n=13, L=9: light
+    cones of hundreds of gates), several wave layouts, and the backward tiles
+    kept to the support of the blocks before them: the fused schedule against
+    one kernel per gate, whose arithmetic differs in order only."""
+    theta, h = W.vqe_batch(n, L, B=B)
+    ctx = V.VQE(n, W.hea_ansatz(n, L), W.tfim_hamiltonian(n, 1.0, h))
+    t = torch.from_numpy(theta).cuda()
+    got = {}
+    for mode in (2, 3):
+        ctx.set_config(mode, 256, 0)
+        E, G = ctx.eval(t)
+        got[mode] = (E.cpu().numpy(), G.cpu().numpy())
+    assert np.max(np.abs(got[3][0] - got[2][0])) <= 1e-12
+    assert np.max(np.abs(got[3][1] - got[2][1])) <= 1e-12
+    ctx.close()
