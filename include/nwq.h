@@ -335,8 +335,8 @@ int nwq_vqe_memory(nwq_vqe_handle h, int B, size_t* held, size_t* at_B);
 
 /* Batched path: B parameter vectors theta_dev[B][n_params] (device, FP64)
  * -> energy_dev[B] and, if grad_dev is non-NULL, grad_dev[B][n_params]
- * (device).  n <= 12 runs one persistent LDS-resident kernel (one workgroup
- * per vector); larger n run the fused-block schedule over all B states
+ * (device).  n <= 12 runs one persistent kernel that keeps each vector's state
+ * on chip (one workgroup per vector); larger n run the fused-block schedule over all B states
  * (see nwq_vqe_set_config), captured once per (B, with/without gradient)
  * into a hipGraph and replayed.  Results for a vector do not depend on B or
  * on the other vectors. */
@@ -359,7 +359,8 @@ int nwq_vqe_eval_single(nwq_vqe_handle h, const double* theta_dev, double* energ
  * register-blocked block kernel over all B states, backward with tiles of phi
  * and lambda in LDS); all but the LDS-resident path run as one hipGraph per
  * batch size.  threads: workgroup size of the LDS kernel (64..1024, power of
- * two); blocks_per_state: workgroups per state of modes 2 and 3 (0 = default). */
+ * two), which mode 1 runs for programs too long for the register-resident
+ * kernel (that one takes 2^(n-3) threads, at least 64); blocks_per_state: workgroups per state of modes 2 and 3 (0 = default). */
 int nwq_vqe_set_config(nwq_vqe_handle h, int mode, int threads, int blocks_per_state);
 int nwq_vqe_get_config(nwq_vqe_handle h, int* mode, int* threads, int* blocks_per_state);
 /* Flags of the fused schedule's tile kernels (forward and backward): bit 0 =

@@ -706,17 +706,17 @@ struct TileMap {
   int tbits = 0;
   unsigned t[kRbThreadBits] = {0}, r[4] = {0};
 };
-TileMap tile_map(const int* reg, const int* perm, unsigned wave, int rbits, int k) {
+TileMap tile_map(const int* reg, const int* perm, unsigned wave, int rbits, int k, int banks) {
   TileMap m;
   unsigned S = wave;
   for (int i = 0; i < rbits; ++i) S |= 1u << reg[i];
-  // Sixteen consecutive lanes (one LDS access of 128 bytes) have to cover
-  // different banks: lane bits 0..3 take tile bits of different residue mod 4
-  // (entry_slot), the lowest ones.
+  // 2^banks consecutive lanes (one LDS access of 128 bytes) have to cover
+  // different banks: the low lane bits take tile bits of different residue
+  // mod `banks` (entry_slot), the lowest ones.
   unsigned lanes = ~S & ((1u << k) - 1u), res = 0;
-  for (int b = 0; b < k && res != 15u; ++b)
-    if (((lanes >> b) & 1u) && !((res >> (b % 4)) & 1u)) {
-      res |= 1u << (b % 4);
+  for (int b = 0; b < k && res + 1 != 1u << banks; ++b)
+    if (((lanes >> b) & 1u) && !((res >> (b % banks)) & 1u)) {
+      res |= 1u << (b % banks);
       m.t[m.tbits++] = 1u << b;
       lanes &= ~(1u << b);
     }
@@ -729,44 +729,22 @@ TileMap tile_map(const int* reg, const int* perm, unsigned wave, int rbits, int 
   return m;
 }
 
-// LDS slot of a tile entry: bit i < 4 is the parity of the entry's bits that
-// are i mod 4, so that a step along any tile bit changes the bank.
-unsigned short entry_slot(unsigned entry) {
-  unsigned s = entry & ~15u;
-  for (int i = 0; i < 4; ++i) s |= (unsigned)(__builtin_popcount(entry & (0x1111u << i)) & 1) << i;
+}  // namespace
+
+// LDS slot of a tile entry: bit i < banks is the parity of the entry's bits
+// that are i mod banks, so that a step along any tile bit changes the bank.
+unsigned short entry_slot(unsigned entry, int banks) {
+  unsigned s = entry >> banks << banks;
+  for (int i = 0; i < banks; ++i)
+    for (int b = i; b < 16; b += banks) s ^= b == i ? entry & (1u << i) : ((entry >> b) & 1u) << i;
   return (unsigned short)s;
 }
 
-}  // namespace
-
-// Lays a block's register phases out (appends them to `out`).  The first and
-// the last phase move between HBM and registers themselves, so their lanes
-// have to cover contiguous runs (no register bit below the low bits) -- else,
-// or without `direct`, a phase without ops on the top bits goes before (after).
-void layout_rb_block(const Block& b, std::vector<RbStage> st, int rbits, bool direct, RbBlock& d,
-                     std::vector<RbPhase>& out) {
-  const int k = b.c + b.m;
-  d = RbBlock{};
-  d.k = k;
-  d.tile = tile_entry_offset(b.c, b.m, b.hi, (1u << k) - 1u);
-  auto contiguous = [&](const RbStage& s) {
-    for (int r = 0; r < rbits; ++r)
-      if (s.reg[r] < std::min(b.c, k - rbits)) return false;
-    return true;
-  };
-  RbStage top{};
-  for (int r = 0; r < rbits; ++r) top.reg[r] = k - rbits + r;
-  for (int j = 0; j < 16; ++j) top.ld_perm[j] = top.st_perm[j] = j;
-  if (!direct || !contiguous(st.front())) {
-    top.op_begin = st.front().op_begin;
-    st.insert(st.begin(), top);
-  }
-  if (!direct || !contiguous(st.back())) {
-    top.op_begin = st.back().op_begin;
-    st.push_back(top);
-  }
-  d.ph_begin = (int)out.size();
-  d.ph_count = (int)st.size();
+// Lays register phases out over the k bits of a tile (appends them to `out`):
+// lanes of the first and last keep the `low` low bits, entries of the LDS
+// exchanges are 128 >> banks bytes.
+void layout_phases(const std::vector<RbStage>& st, int rbits, int k, int low, int banks, std::vector<RbPhase>& out,
+                   RbTileIo& io) {
   // Bits of the wave index: phases in a row share them as long as enough bits
   // above the low ones stay off all their register bits (the exchanges between
   // such phases stay inside a wave).
@@ -774,7 +752,7 @@ void layout_rb_block(const Block& b, std::vector<RbStage> st, int rbits, bool di
   std::vector<unsigned> wave(st.size(), 0);
   std::vector<char> local(st.size(), 0);   // exchange into phase i stays inside a wave
   for (size_t i = 0; i < st.size();) {
-    unsigned busy = (1u << std::min(std::min(b.c, 4), k - rbits - wbits)) - 1u;   // 256-byte runs at least
+    unsigned busy = (1u << std::min(low, std::max(0, k - rbits - wbits))) - 1u;
     size_t e = i;
     for (; e < st.size(); ++e) {
       unsigned S = busy;
@@ -782,7 +760,7 @@ void layout_rb_block(const Block& b, std::vector<RbStage> st, int rbits, bool di
       if (e > i && k - __builtin_popcount(S) < wbits) break;
       busy = S;
       if (k - __builtin_popcount(S) < wbits) {   // one phase: its lanes give up low bits
-        busy &= ~((1u << b.c) - 1u);
+        busy = 0;
         for (int r = 0; r < rbits; ++r) busy |= 1u << st[e].reg[r];
         ++e;
         break;
@@ -807,15 +785,15 @@ void layout_rb_block(const Block& b, std::vector<RbStage> st, int rbits, bool di
     ph.op_begin = st[i].op_begin;
     ph.op_count = (short)st[i].op_count;
     if (i > 0) {
-      const TileMap wr = tile_map(st[i - 1].reg, st[i - 1].st_perm, wave[i - 1], rbits, k);
-      const TileMap rd = tile_map(st[i].reg, st[i].ld_perm, wave[i], rbits, k);
+      const TileMap wr = tile_map(st[i - 1].reg, st[i - 1].st_perm, wave[i - 1], rbits, k, banks);
+      const TileMap rd = tile_map(st[i].reg, st[i].ld_perm, wave[i], rbits, k, banks);
       for (int j = 0; j < kRbThreadBits; ++j) {
-        ph.wr_t[j] = entry_slot(wr.t[j]);
-        ph.rd_t[j] = entry_slot(rd.t[j]);
+        ph.wr_t[j] = entry_slot(wr.t[j], banks);
+        ph.rd_t[j] = entry_slot(rd.t[j], banks);
       }
       for (int j = 0; j < 4; ++j) {
-        ph.wr_r[j] = entry_slot(wr.r[j]);
-        ph.rd_r[j] = entry_slot(rd.r[j]);
+        ph.wr_r[j] = entry_slot(wr.r[j], banks);
+        ph.rd_r[j] = entry_slot(rd.r[j], banks);
       }
       // A phase's registers go back to the entries they came from (its
       // permutations stay among one thread's), so only the first exchange of a
@@ -825,15 +803,55 @@ void layout_rb_block(const Block& b, std::vector<RbStage> st, int rbits, bool di
     }
     out.push_back(ph);
   }
-  const TileMap ld = tile_map(st.front().reg, st.front().ld_perm, wave.front(), rbits, k);
-  const TileMap sv = tile_map(st.back().reg, st.back().st_perm, wave.back(), rbits, k);
+  const TileMap ld = tile_map(st.front().reg, st.front().ld_perm, wave.front(), rbits, k, banks);
+  const TileMap sv = tile_map(st.back().reg, st.back().st_perm, wave.back(), rbits, k, banks);
   for (int j = 0; j < kRbThreadBits; ++j) {
-    d.ld_t[j] = tile_entry_offset(b.c, b.m, b.hi, ld.t[j]);
-    d.st_t[j] = tile_entry_offset(b.c, b.m, b.hi, sv.t[j]);
+    io.ld_t[j] = (unsigned short)ld.t[j];
+    io.st_t[j] = (unsigned short)sv.t[j];
   }
   for (int j = 0; j < 4; ++j) {
-    d.ld_r[j] = tile_entry_offset(b.c, b.m, b.hi, ld.r[j]);
-    d.st_r[j] = tile_entry_offset(b.c, b.m, b.hi, sv.r[j]);
+    io.ld_r[j] = (unsigned short)ld.r[j];
+    io.st_r[j] = (unsigned short)sv.r[j];
+  }
+}
+
+// Lays a block's register phases out.  The first and the last phase move
+// between HBM and registers themselves, so their lanes have to cover
+// contiguous runs (no register bit below the low bits) -- else, or without
+// `direct`, a phase without ops on the top bits goes before (after).
+void layout_rb_block(const Block& b, std::vector<RbStage> st, int rbits, bool direct, RbBlock& d,
+                     std::vector<RbPhase>& out) {
+  const int k = b.c + b.m;
+  d = RbBlock{};
+  d.k = k;
+  d.tile = tile_entry_offset(b.c, b.m, b.hi, (1u << k) - 1u);
+  auto contiguous = [&](const RbStage& s) {
+    for (int r = 0; r < rbits; ++r)
+      if (s.reg[r] < std::min(b.c, k - rbits)) return false;
+    return true;
+  };
+  RbStage top{};
+  for (int r = 0; r < rbits; ++r) top.reg[r] = k - rbits + r;
+  for (int j = 0; j < 16; ++j) top.ld_perm[j] = top.st_perm[j] = j;
+  if (!direct || !contiguous(st.front())) {
+    top.op_begin = st.front().op_begin;
+    st.insert(st.begin(), top);
+  }
+  if (!direct || !contiguous(st.back())) {
+    top.op_begin = st.back().op_begin;
+    st.push_back(top);
+  }
+  d.ph_begin = (int)out.size();
+  d.ph_count = (int)st.size();
+  RbTileIo io;
+  layout_phases(st, rbits, k, std::min(b.c, 4), 4, out, io);   // 256-byte runs at least; doubles
+  for (int j = 0; j < kRbThreadBits; ++j) {
+    d.ld_t[j] = tile_entry_offset(b.c, b.m, b.hi, io.ld_t[j]);
+    d.st_t[j] = tile_entry_offset(b.c, b.m, b.hi, io.st_t[j]);
+  }
+  for (int j = 0; j < 4; ++j) {
+    d.ld_r[j] = tile_entry_offset(b.c, b.m, b.hi, io.ld_r[j]);
+    d.st_r[j] = tile_entry_offset(b.c, b.m, b.hi, io.st_r[j]);
   }
 }
 

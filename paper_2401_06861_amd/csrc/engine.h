@@ -180,6 +180,15 @@ struct RbStage {
   int ld_perm[16], st_perm[16];
   int op_begin, op_count;
 };
+// Tile entries of the first phase's thread and register bits as it takes the
+// tile up, and of the last's as it leaves it.
+struct RbTileIo {
+  unsigned short ld_t[kRbThreadBits], ld_r[4], st_t[kRbThreadBits], st_r[4];
+};
+// LDS slot of a tile entry (layout_phases).
+unsigned short entry_slot(unsigned entry, int banks);
+void layout_phases(const std::vector<RbStage>& st, int rbits, int k, int low, int banks, std::vector<RbPhase>& out,
+                   RbTileIo& io);
 void layout_rb_block(const Block& b, std::vector<RbStage> stages, int rbits, bool direct, RbBlock& d,
                      std::vector<RbPhase>& out);
 // c: the block's low tile bits; a phase with fewer gate bits than rbits is

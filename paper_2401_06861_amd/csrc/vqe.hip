@@ -8,9 +8,10 @@
 // phi <- U_k^dag phi,  lambda <- U_k^dag lambda.
 //
 // Two execution paths share the op encoding:
-//  * LDS-resident (n <= 12): one workgroup owns one theta vector and keeps
-//    phi and lambda in LDS for the whole forward pass, H application and
-//    backward sweep; a persistent grid walks the batch.  One launch per batch.
+//  * Resident (n <= 12): one workgroup owns one theta vector and keeps phi and
+//    lambda in registers (k_vqe_reg; programs too long for its tables: in LDS,
+//    k_vqe_lds) for the whole forward pass, H application and backward sweep;
+//    a persistent grid walks the batch.  One launch per batch.
 //  * Global (any n): one launch per gate over all B states (blockIdx.y = batch
 //    element), phi and lambda in HBM, gradient partials per (state, gate, block)
 //    reduced in a fixed order; the whole schedule is captured once per batch
@@ -262,7 +263,8 @@ __device__ __forceinline__ vd2 h_apply_at(const double2* phi, unsigned long long
 }
 
 // ---------------------------------------------------------------------------
-// LDS-resident persistent kernel (n <= 12)
+// LDS-resident persistent kernel (n <= 12), for programs whose tables and
+// gradient partials do not fit the register-resident kernel's LDS
 // ---------------------------------------------------------------------------
 template <int NT>
 __global__ __launch_bounds__(NT) void k_vqe_lds(int n, const VqeOp* __restrict__ ops, int nops,
@@ -323,6 +325,505 @@ __global__ __launch_bounds__(NT) void k_vqe_lds(int n, const VqeOp* __restrict__
         for (int w = 0; w < NW; ++w) v += gpart[s * NW + w];
         grad[(size_t)b * P + slot_param[s]] += v;
       }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Register-resident kernel (n <= 12).  One workgroup per theta vector holds
+// phi (and lambda on the way back) in registers, 8 amplitudes per thread over
+// 3 register bits; the program runs as register phases (as the fused blocks
+// do) with an LDS exchange between them, forward and then backward through
+// the same phases.  k_vqe_lds passes the whole state through LDS, with a
+// barrier, for every gate, and one thread adds up the gradient.  Here LDS is
+// crossed once per phase (40 phases for the 280 gates of n=12, L=8, 29 of them
+// inside a wave), the angles' sines are computed once per vector, the program
+// and the Hamiltonian's terms are read from LDS, RZ and RZZ turn only the half
+// of the amplitudes whose phase differs (a global phase changes neither the
+// energy nor the gradient), RY and RX are three shears in place, and each
+// parameter's slots are added by a thread of its own.  256 vectors with
+// gradients: n=8, L=4 149 -> 76 us, n=12, L=8 1020 -> 251 us a call.
+// What bounds it: the chain of ops of one vector on one CU.  At n=12 an op
+// takes about 0.4 us forward, half of it FP64 issue of the two waves per SIMD,
+// the rest the dispatch; at n=8 one wave has the CU to itself.
+// ---------------------------------------------------------------------------
+struct RegOpV {
+  int code;          // RegVCode + 32 (gradient slot + 1)
+  int mat;           // fixed 2x2: index into the fixed-matrix table; RV_YZ: gradient slot of RZ
+  int param, param2; // theta indices (RV_YZ: of RY and RZ) or -1
+};
+// register-bit pairs B0 < B1 numbered as rb_pair
+enum RegVCode { RV_ROT = 0 /* + 3 axis + B */, RV_FIX = 9 /* + B */, RV_RZZ = 12 /* + pair */, RV_CZ = 15,
+                RV_CX = 18 /* + 2 pair + (control is B1) */, RV_SWAP = 24,
+                RV_YZ = 27 /* + B: RY, then RZ with the next entry's numbers and slot */ };
+
+// A turn by an angle f as three shears, x0 -= t x1; x1 += s x0; x0 -= t x1 with
+// t = tan(f / 2) and s = sin f: three FMAs per pair and component instead of
+// two products and two FMAs, each in place (products into new registers end
+// every case of the op switch with copies back into the loop's registers, as
+// long as the arithmetic itself).  RX and RY take f = theta / 2 modulo pi,
+// within [-pi/2, pi/2] and so |t| <= 1: a multiple of pi is a global sign.
+// Against 80-bit arithmetic (n=8, L=4, 32 vectors) the gradients are 7.4e-16
+// off with shears, 8.2e-16 with the products, 9.8e-16 with k_vqe_lds.
+__device__ __forceinline__ vd2 shear_of(double theta) {
+  double f = 0.5 * theta;
+  f = fma(-M_PI, rint(f * M_1_PI), f);
+  f = fma(-1.2246467991473532e-16, rint(0.5 * theta * M_1_PI), f);   // pi - (double)pi
+  double sf, cf;
+  sincos(f, &sf, &cf);
+  return mk(sf / (1.0 + cf), sf);   // tan(f / 2), sin f; cos f >= 0
+}
+
+// Eight amplitudes as separate doubles (as 16-byte vectors in the op loop, every
+// case of the switch builds new register tuples and copies them back).
+struct Amp8 {
+  double x[8], y[8];
+};
+
+// Gate `code` on the registers with (c, s) its angle's shear_of (RX, RY) or the
+// cosine and sine of the whole angle (RZ, RZZ), or F its fixed matrix; DAG: the
+// adjoint, with the sum of Im<l|P|p> over the registers first (g) and both
+// vectors turned.
+template <int B, int AX>
+__device__ __forceinline__ void rv_turn(Amp8& v, double c, double s) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (j & (1 << B)) continue;
+    const int k = j | (1 << B);
+    if constexpr (AX == 0) {          // [[cos, -i sin], [-i sin, cos]]
+      v.x[j] = fma(c, v.y[k], v.x[j]);
+      v.y[j] = fma(-c, v.x[k], v.y[j]);
+      v.x[k] = fma(s, v.y[j], v.x[k]);
+      v.y[k] = fma(-s, v.x[j], v.y[k]);
+      v.x[j] = fma(c, v.y[k], v.x[j]);
+      v.y[j] = fma(-c, v.x[k], v.y[j]);
+    } else if constexpr (AX == 1) {   // [[cos, -sin], [sin, cos]]
+      v.x[j] = fma(-c, v.x[k], v.x[j]);
+      v.y[j] = fma(-c, v.y[k], v.y[j]);
+      v.x[k] = fma(s, v.x[j], v.x[k]);
+      v.y[k] = fma(s, v.y[j], v.y[k]);
+      v.x[j] = fma(-c, v.x[k], v.x[j]);
+      v.y[j] = fma(-c, v.y[k], v.y[j]);
+    } else {                          // diag(1, e^{i theta})
+      const double t = s * v.y[k];
+      v.y[k] = fma(c, v.y[k], s * v.x[k]);
+      v.x[k] = fma(c, v.x[k], -t);
+    }
+  }
+}
+// Im<l|P|p> of the generator on register bit B, in four chains (one would be as
+// many dependent FMAs).
+template <int B, int AX>
+__device__ __forceinline__ double rv_grad(const Amp8& p, const Amp8& l) {
+  double g[4] = {0.0, 0.0, 0.0, 0.0};
+  int n = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (j & (1 << B)) continue;
+    const int k = j | (1 << B);
+    double& h = g[n++ & 3];
+    if constexpr (AX == 0) {
+      h = fma(l.x[j], p.y[k], h);
+      h = fma(-l.y[j], p.x[k], h);
+      h = fma(l.x[k], p.y[j], h);
+      h = fma(-l.y[k], p.x[j], h);
+    } else if constexpr (AX == 1) {
+      h = fma(l.x[k], p.x[j], h);
+      h = fma(l.y[k], p.y[j], h);
+      h = fma(-l.x[j], p.x[k], h);
+      h = fma(-l.y[j], p.y[k], h);
+    } else {
+      h = fma(l.x[j], p.y[j], h);
+      h = fma(-l.y[j], p.x[j], h);
+      h = fma(-l.x[k], p.y[k], h);
+      h = fma(l.y[k], p.x[k], h);
+    }
+  }
+  return (g[0] + g[1]) + (g[2] + g[3]);
+}
+template <int B, int AX, bool DAG>
+__device__ __forceinline__ void rv_rot(Amp8& p, Amp8& l, double c, double s, double& g) {
+  if constexpr (DAG) {
+    g = rv_grad<B, AX>(p, l);
+    s = -s;
+    if constexpr (AX != 2) c = -c;
+  }
+  rv_turn<B, AX>(p, c, s);
+  if constexpr (DAG) rv_turn<B, AX>(l, c, s);
+}
+template <int B, bool DAG>
+__device__ __forceinline__ void rv_yz(Amp8& p, Amp8& l, vd2 ay, vd2 az, double& gy, double& gz) {
+  if constexpr (DAG) {
+    rv_rot<B, 2, true>(p, l, az.x, az.y, gz);
+    rv_rot<B, 1, true>(p, l, ay.x, ay.y, gy);
+  } else {
+    rv_turn<B, 1>(p, ay.x, ay.y);
+    rv_turn<B, 2>(p, az.x, az.y);
+  }
+}
+template <int B>
+__device__ __forceinline__ void rv_mat(Amp8& v, const double2* __restrict__ M) {
+  const vd2 m0 = ld(M), m1 = ld(M + 1), m2 = ld(M + 2), m3 = ld(M + 3);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (j & (1 << B)) continue;
+    const int k = j | (1 << B);
+    const vd2 a = mk(v.x[j], v.y[j]), b = mk(v.x[k], v.y[k]);
+    const vd2 u = cfma(m0, a, cmul(m1, b)), w = cfma(m2, a, cmul(m3, b));
+    v.x[j] = u.x;
+    v.y[j] = u.y;
+    v.x[k] = w.x;
+    v.y[k] = w.y;
+  }
+}
+template <int B, bool DAG>
+__device__ __forceinline__ void rv_fix(Amp8& p, Amp8& l, const double2* __restrict__ F) {
+  rv_mat<B>(p, F + (DAG ? 4 : 0));
+  if constexpr (DAG) rv_mat<B>(l, F + 4);
+}
+template <int B0, int B1, bool DAG>
+__device__ __forceinline__ void rv_rzz(Amp8& p, Amp8& l, double c, double s, double& g) {
+  if constexpr (DAG) s = -s;
+  double g2[2] = {0.0, 0.0};
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const bool odd = ((j >> B0) ^ (j >> B1)) & 1;
+    if constexpr (DAG) {
+      g2[j & 1] = fma(odd ? -l.x[j] : l.x[j], p.y[j], g2[j & 1]);
+      g2[j & 1] = fma(odd ? l.y[j] : -l.y[j], p.x[j], g2[j & 1]);
+      if (j == 7) g = g2[0] + g2[1];
+    }
+    if (!odd) continue;
+    auto turn = [&](Amp8& v) {
+      const double t = s * v.y[j];
+      v.y[j] = fma(c, v.y[j], s * v.x[j]);
+      v.x[j] = fma(c, v.x[j], -t);
+    };
+    turn(p);
+    if constexpr (DAG) turn(l);
+  }
+}
+template <int B0, int B1, bool DAG>
+__device__ __forceinline__ void rv_cz(Amp8& p, Amp8& l) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if (((j >> B0) & (j >> B1)) & 1) {
+      p.x[j] = -p.x[j];
+      p.y[j] = -p.y[j];
+      if constexpr (DAG) {
+        l.x[j] = -l.x[j];
+        l.y[j] = -l.y[j];
+      }
+    }
+}
+template <int MASK, int OA, int OB, bool DAG>
+__device__ __forceinline__ void rv_swap(Amp8& p, Amp8& l) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (j & MASK) continue;
+    auto swap = [](double& a, double& b) {
+      const double t = a;
+      a = b;
+      b = t;
+    };
+    swap(p.x[j | OA], p.x[j | OB]);
+    swap(p.y[j | OA], p.y[j | OB]);
+    if constexpr (DAG) {
+      swap(l.x[j | OA], l.x[j | OB]);
+      swap(l.y[j | OA], l.y[j | OB]);
+    }
+  }
+}
+
+template <bool DAG>
+__device__ __forceinline__ void rv_apply(int code, Amp8& p, Amp8& l, vd2 a, vd2 az, const double2* __restrict__ F,
+                                         double& g, double& gz) {
+  const double c = a.x, s = a.y;
+#define NWQ_RV_ROT(AX) \
+  case RV_ROT + 3 * AX + 0: rv_rot<0, AX, DAG>(p, l, c, s, g); break; \
+  case RV_ROT + 3 * AX + 1: rv_rot<1, AX, DAG>(p, l, c, s, g); break; \
+  case RV_ROT + 3 * AX + 2: rv_rot<2, AX, DAG>(p, l, c, s, g); break;
+#define NWQ_RV_PAIR(P, LO, HI) \
+  case RV_RZZ + P: rv_rzz<LO, HI, DAG>(p, l, c, s, g); break; \
+  case RV_CZ + P: rv_cz<LO, HI, DAG>(p, l); break; \
+  case RV_CX + 2 * P: rv_swap<(1 << LO) | (1 << HI), (1 << LO), (1 << LO) | (1 << HI), DAG>(p, l); break; \
+  case RV_CX + 2 * P + 1: rv_swap<(1 << LO) | (1 << HI), (1 << HI), (1 << LO) | (1 << HI), DAG>(p, l); break; \
+  case RV_SWAP + P: rv_swap<(1 << LO) | (1 << HI), (1 << LO), (1 << HI), DAG>(p, l); break;
+  switch (code) {
+    NWQ_RV_ROT(0)
+    NWQ_RV_ROT(1)
+    NWQ_RV_ROT(2)
+    case RV_FIX + 0: rv_fix<0, DAG>(p, l, F); break;
+    case RV_FIX + 1: rv_fix<1, DAG>(p, l, F); break;
+    case RV_FIX + 2: rv_fix<2, DAG>(p, l, F); break;
+    NWQ_RV_PAIR(0, 0, 1)
+    NWQ_RV_PAIR(1, 0, 2)
+    NWQ_RV_PAIR(2, 1, 2)
+    case RV_YZ + 0: rv_yz<0, DAG>(p, l, a, az, g, gz); break;
+    case RV_YZ + 1: rv_yz<1, DAG>(p, l, a, az, g, gz); break;
+    case RV_YZ + 2: rv_yz<2, DAG>(p, l, a, az, g, gz); break;
+    default: break;
+  }
+#undef NWQ_RV_ROT
+#undef NWQ_RV_PAIR
+}
+
+constexpr int kRegMaxThreads = 512;   // n = 12
+constexpr int kRegTerms = 64;         // Hamiltonian terms staged at a time
+
+// Sum over each row of 16 lanes, in every lane.
+__device__ __forceinline__ double row_sum(double v) {
+  v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]
+  v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]
+  v += dpp_move<0x141>(v);   // row_half_mirror
+  v += dpp_move<0x140>(v);   // row_mirror
+  return v;
+}
+
+// A phase's exchange read from the LDS copy of the program: images of thread
+// and register bits as packed 16-bit pairs, wave-uniform.
+struct RegMap {
+  unsigned t[5], r[2];
+};
+__device__ __forceinline__ unsigned uni(unsigned x) { return (unsigned)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ __forceinline__ RegMap reg_map(const unsigned* w) {
+  RegMap m;
+#pragma unroll
+  for (int i = 0; i < 5; ++i) m.t[i] = uni(w[i]);
+  m.r[0] = uni(w[5]);
+  m.r[1] = uni(w[6]);
+  return m;
+}
+__device__ __forceinline__ unsigned thread_slot(unsigned v, const RegMap& m) {
+  unsigned x = 0;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) x ^= (unsigned)((int)(v << (31 - i)) >> 31) & ((m.t[i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
+  return x;
+}
+__device__ __forceinline__ unsigned register_slot(int j, const RegMap& m) {
+  return ((j & 1) ? m.r[0] & 0xFFFFu : 0u) ^ ((j & 2) ? m.r[0] >> 16 : 0u) ^ ((j & 4) ? m.r[1] & 0xFFFFu : 0u);
+}
+// layout_phases' slot of an entry of 8 bytes
+__device__ __forceinline__ unsigned slot8(unsigned e) {
+  const unsigned f = e ^ (e >> 4) ^ (e >> 8);   // n <= 12
+  return (e & ~15u) | (f & 15u);
+}
+
+// phases[0 .. P): the program's; phases[P]: where the last phase's registers go
+// in LDS (wr_*) and which entries they are (rd_*).  pslots[poff[p] .. poff[p+1])
+// are the slots of parameter p.
+__global__ __launch_bounds__(kRegMaxThreads) void k_vqe_reg(
+    int n, const RbPhase* __restrict__ phases, int P, const RegOpV* __restrict__ ops, int nops,
+    const double2* __restrict__ fixed, const VqeTerm* __restrict__ terms, int nterms, int nslots,
+    const int* __restrict__ poff, const int* __restrict__ pslots, const double* __restrict__ theta, int nparams, int B,
+    const double* __restrict__ coeffs, double* __restrict__ E, double* __restrict__ grad) {
+  extern __shared__ double2 lds[];
+  const unsigned tid = threadIdx.x, nt = blockDim.x;
+  const int lane = tid & (kWave - 1), wave = tid / kWave, NW = (int)(nt + kWave - 1) / kWave;
+  const int nb = n < 3 ? 3 : n;
+  // entries of threads beyond the state (fewer than 8 * 64 amplitudes) stay zero and off LDS
+  const bool live = (tid >> (nb - 3)) == 0;
+  double* bufx = reinterpret_cast<double*>(lds);                 // real parts of 2^nb entries
+  double* bufy = bufx + (1u << nb);                              // imaginary parts
+  double2* cs = lds + (1u << nb);                                // [nops][2] the angles' two numbers
+  unsigned* lph = reinterpret_cast<unsigned*>(cs + 2 * nops);        // [P + 1] phases (16 words each)
+  int2* lop = reinterpret_cast<int2*>(lph + 16 * (P + 1));       // [nops] (code, mat)
+  double* red = reinterpret_cast<double*>(lop + nops);           // [8]
+  int4* lterm = reinterpret_cast<int4*>(red + 8);                // [kRegTerms] Hamiltonian terms
+  double* gpart = reinterpret_cast<double*>(lterm + kRegTerms);  // [nslots][NW][4]
+  // The program is copied to LDS once: read op by op through the scalar cache
+  // it would be a chain of misses (0.7 us per op).
+  static_assert(sizeof(RbPhase) == 64, "16 words");
+  for (int i = tid; i < 16 * (P + 1); i += nt) lph[i] = reinterpret_cast<const unsigned*>(phases)[i];
+  for (int i = tid; i < nops; i += nt) lop[i] = *reinterpret_cast<const int2*>(ops + i);
+  Amp8 p, l;
+  auto write = [&](const Amp8& v, const RegMap& m) {
+    const unsigned t = thread_slot(tid, m);
+    if (!live) return;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      bufx[t ^ register_slot(j, m)] = v.x[j];
+      bufy[t ^ register_slot(j, m)] = v.y[j];
+    }
+  };
+  auto read = [&](Amp8& v, const RegMap& m) {
+    const unsigned t = thread_slot(tid, m);
+    if (!live) return;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      v.x[j] = bufx[t ^ register_slot(j, m)];
+      v.y[j] = bufy[t ^ register_slot(j, m)];
+    }
+  };
+  for (int b = blockIdx.x; b < B; b += gridDim.x) {
+    const double* th = theta + (size_t)b * nparams;
+    __syncthreads();   // the previous vector's readers of cs, buf and gpart are done
+    for (int i = tid; i < 2 * nops; i += nt) {
+      const RegOpV op = ops[i >> 1];
+      const int code = op.code & 31, param = (i & 1) ? op.param2 : op.param;
+      if (param < 0) continue;
+      const bool whole = (i & 1) || (code >= RV_ROT + 6 && code < RV_YZ);   // RZ, RZZ
+      vd2 a;
+      if (whole) {
+        double s, c;
+        sincos(th[param], &s, &c);
+        a = mk(c, s);
+      } else {
+        a = shear_of(th[param]);
+      }
+      st(cs + i, a);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p.x[j] = p.y[j] = 0.0;
+    if (tid == 0) p.x[0] = 1.0;
+    __syncthreads();
+    // phase words: op_begin, op_count and flags, wr_t (5), wr_r (2), rd_t (5), rd_r (2)
+    double none = 0.0;
+    int2 od = lop[0];
+    vd2 a = ld(cs), az = ld(cs + 1);
+    for (int pi = 0; pi < P; ++pi) {
+      const unsigned* ph = lph + 16 * pi;
+      const int begin = (int)uni(ph[0]), cf = (int)uni(ph[1]);
+      const int count = (short)(cf & 0xFFFF);
+      if (pi > 0) {
+        const RegMap wr = reg_map(ph + 2), rd = reg_map(ph + 9);
+        write(p, wr);
+        if ((cf >> 16) & kRbBarrierInside) __syncthreads();
+        read(p, rd);
+      }
+      for (int i = begin; i < begin + count; ++i) {   // the next op is read while this one runs
+        const int in = i + 1 < nops ? i + 1 : 0;
+        const int2 odn = lop[in];
+        const vd2 an = ld(cs + 2 * in), azn = ld(cs + 2 * in + 1);
+        const int code = (int)uni((unsigned)od.x) & 31;
+        rv_apply<false>(code, p, l, a, az, fixed + 8 * (int)uni((unsigned)od.y), none, none);
+        od = odn;
+        a = an;
+        az = azn;
+      }
+    }
+    // lambda = H phi and E = Re <phi|lambda>: every register's partners are in buf
+#pragma unroll
+    for (int j = 0; j < 8; ++j) l.x[j] = l.y[j] = 0.0;
+    {
+      const RegMap wr = reg_map(lph + 16 * P + 2), en = reg_map(lph + 16 * P + 9);
+      write(p, wr);
+      __syncthreads();
+      const unsigned et = thread_slot(tid, en);
+      double e = 0.0;
+      for (int t0 = 0; t0 < nterms; t0 += kRegTerms) {   // terms through LDS, kRegTerms at a time
+        const int cnt = min(kRegTerms, nterms - t0);
+        if (t0 > 0) __syncthreads();
+        for (int i = tid; i < cnt; i += nt) {
+          const VqeTerm T = terms[t0 + i];
+          const double tc = coeffs ? coeffs[(size_t)b * nterms + t0 + i] : T.c;
+          lterm[i] = make_int4(__double2loint(tc), __double2hiint(tc), (int)((unsigned)T.x | ((unsigned)T.z << 16)), T.y);
+        }
+        __syncthreads();
+        if (!live) continue;
+        int4 w = lterm[0];
+        for (int t = 0; t < cnt; ++t) {
+          const int4 wn = lterm[t + 1 < cnt ? t + 1 : t];
+          const unsigned x = uni((unsigned)w.z) & 0xFFFFu, z = uni((unsigned)w.z) >> 16;
+          const int y = (int)uni((unsigned)w.w) & 3;
+          const double tc = __hiloint2double(w.y, w.x);
+          w = wn;
+          // signs (-1)^{|k & z|} of the entries k = e ^ x, e this register's: the
+          // thread's part once, the registers' parts uniform (parities are linear)
+          const double tp = (((unsigned)__popc((et ^ x) & z) ^ ((unsigned)y >> 1)) & 1u) ? -tc : tc;
+          auto sign = [&](int j) { return (__popc(register_slot(j, en) & z) & 1) ? -tp : tp; };
+          if (x == 0) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              l.x[j] = fma(sign(j), p.x[j], l.x[j]);
+              l.y[j] = fma(sign(j), p.y[j], l.y[j]);
+            }
+            continue;
+          }
+          const unsigned lx = slot8(et ^ x);
+          double vx[8], vy[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const unsigned sl = lx ^ slot8(register_slot(j, en));
+            vx[j] = bufx[sl];
+            vy[j] = bufy[sl];
+          }
+          if (y & 1) {   // i^y: 1, i, -1, -i
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              l.x[j] = fma(-sign(j), vy[j], l.x[j]);
+              l.y[j] = fma(sign(j), vx[j], l.y[j]);
+            }
+          } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              l.x[j] = fma(sign(j), vx[j], l.x[j]);
+              l.y[j] = fma(sign(j), vy[j], l.y[j]);
+            }
+          }
+        }
+      }
+      if (live) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) e += p.x[j] * l.x[j] + p.y[j] * l.y[j];
+      }
+      e = wave_sum_full(e);
+      if (lane == 0) red[wave] = e;
+      __syncthreads();
+      if (tid == 0) {
+        double s = 0.0;
+        for (int w = 0; w < NW; ++w) s += red[w];
+        E[b] = s;
+      }
+    }
+    if (!grad) continue;
+    if (nops > 0) {
+      od = lop[nops - 1];
+      a = ld(cs + 2 * nops - 2);
+      az = ld(cs + 2 * nops - 1);
+    }
+    for (int pi = P - 1; pi >= 0; --pi) {
+      const unsigned* ph = lph + 16 * pi;
+      const int begin = (int)uni(ph[0]), cf = (int)uni(ph[1]);
+      const int count = (short)(cf & 0xFFFF);
+      for (int i = begin + count - 1; i >= begin; --i) {
+        const int in = i > 0 ? i - 1 : 0;
+        const int2 odn = lop[in];
+        const vd2 an = ld(cs + 2 * in), azn = ld(cs + 2 * in + 1);
+        const int word = (int)uni((unsigned)od.x), mat = (int)uni((unsigned)od.y);
+        double g = 0.0, gz = 0.0;
+        rv_apply<true>(word & 31, p, l, a, az, fixed + 8 * mat, g, gz);
+        // sums over the 16 lanes of each row; the rows and waves are added at the end
+        if (word >= 32) {
+          g = row_sum(g);
+          if ((lane & 15) == 0) gpart[(((word >> 5) - 1) * NW + wave) * 4 + (lane >> 4)] = g;
+        }
+        if ((word & 31) >= RV_YZ) {
+          gz = row_sum(gz);
+          if ((lane & 15) == 0) gpart[(mat * NW + wave) * 4 + (lane >> 4)] = gz;
+        }
+        od = odn;
+        a = an;
+        az = azn;
+      }
+      if (pi > 0) {   // back through the exchange that led into this phase
+        const RegMap wr = reg_map(ph + 9), rd = reg_map(ph + 2);
+        const bool across = ((cf >> 16) & kRbBarrierInside) != 0;
+        write(p, wr);
+        if (across) __syncthreads();
+        read(p, rd);
+        if (across) __syncthreads();
+        write(l, wr);
+        if (across) __syncthreads();
+        read(l, rd);
+      }
+    }
+    __syncthreads();
+    for (int q = tid; q < nparams; q += nt) {
+      double v = 0.0;
+      for (int i = poff[q]; i < poff[q + 1]; ++i)
+        for (int w = 0; w < 4 * NW; ++w) v += gpart[pslots[i] * 4 * NW + w];
+      grad[(size_t)b * nparams + q] = v;
     }
   }
 }
@@ -1362,6 +1863,10 @@ struct nwq_vqe {
   nwq::VqeTerm* d_terms = nullptr;
   std::vector<nwq::VqeTerm> terms;   // host copy of the term table
   int* d_slot_param = nullptr;
+  // register-resident path (n <= 12): phases, ops, parameter slots in one allocation
+  void* d_reg = nullptr;
+  int reg_phases = 0, reg_ops = 0;
+  size_t reg_ops_off = 0, reg_poff_off = 0, reg_pslots_off = 0;
   // global path buffers
   int Bcap = 0;
   double2* d_phi = nullptr;
@@ -1431,12 +1936,37 @@ static size_t lds_bytes(const nwq_vqe* h, int threads, bool want_grad) {
          (want_grad ? (size_t)h->nslots * NW * sizeof(double) : 0);
 }
 
+static bool reg_fits(const nwq_vqe* h);
 static bool lds_fits(const nwq_vqe* h, int threads, bool want_grad) {
-  return h->n <= 12 && lds_bytes(h, threads, want_grad) <= 160 * 1024;
+  return h->n <= 12 && (reg_fits(h) || lds_bytes(h, threads, want_grad) <= 160 * 1024);
+}
+
+// The register-resident kernel: threads and LDS; its program is built with the
+// context for n <= 12.
+static int reg_threads(const nwq_vqe* h) { return std::max(kWave, h->n > 3 ? 1 << (h->n - 3) : 1); }
+static size_t reg_lds_bytes(const nwq_vqe* h) {
+  return (sizeof(double2) << std::max(3, h->n)) + (size_t)h->reg_ops * (2 * sizeof(double2) + sizeof(int2)) +
+         (size_t)(h->reg_phases + 1) * sizeof(RbPhase) + kRegTerms * sizeof(int4) +
+         (8 + (size_t)h->nslots * 4 * (reg_threads(h) / kWave)) * sizeof(double);
+}
+static bool reg_fits(const nwq_vqe* h) { return h->d_reg != nullptr && reg_lds_bytes(h) <= 160 * 1024; }
+
+static int launch_reg(nwq_vqe* h, int B, const double* theta, const double* coeffs, double* E, double* grad,
+                      hipStream_t s) {
+  const size_t lds = reg_lds_bytes(h);
+  if (lds > 65536) (void)enable_dynamic_lds((const void*)k_vqe_reg);
+  const char* d = static_cast<const char*>(h->d_reg);
+  hipLaunchKernelGGL(k_vqe_reg, dim3(std::min(B, 4096)), dim3(reg_threads(h)), lds, s, h->n,
+                     reinterpret_cast<const RbPhase*>(d), h->reg_phases,
+                     reinterpret_cast<const RegOpV*>(d + h->reg_ops_off), h->reg_ops, h->d_fixed, h->d_terms,
+                     h->nterms, h->nslots, reinterpret_cast<const int*>(d + h->reg_poff_off),
+                     reinterpret_cast<const int*>(d + h->reg_pslots_off), theta, h->P, B, coeffs, E, grad);
+  return check_hip(hipGetLastError(), "k_vqe_reg");
 }
 
 static int launch_lds(nwq_vqe* h, int B, const double* theta, const double* coeffs, double* E, double* grad,
                       hipStream_t s) {
+  if (reg_fits(h)) return launch_reg(h, B, theta, coeffs, E, grad, s);
   const int T = h->cfg.threads;
   const size_t lds = lds_bytes(h, T, grad != nullptr);
   const int grid = std::min(B, 4096);
@@ -1852,6 +2382,109 @@ static int build_fused(nwq_vqe* h) {
   return NWQ_OK;
 }
 
+// Program of the register-resident path: the ops in phases of 3 register bits
+// over the whole register (CX and SWAP folded into the exchanges where they
+// can be), and the slots of each parameter in slot order.
+static std::vector<char> build_reg(nwq_vqe* h) {
+  const int nb = std::max(3, h->n);
+  std::vector<std::array<int, 4>> lb(h->nops);
+  std::vector<int> nq(h->nops), order(h->nops);
+  for (int i = 0; i < h->nops; ++i) {
+    const VqeOp& op = h->ops[i];
+    const bool two = op.kind == OP_RZZ || op.kind == OP_CX || op.kind == OP_CZ || op.kind == OP_SWAP;
+    lb[i] = {op.q0, two ? op.q1 : 0, 0, 0};
+    nq[i] = two ? 2 : 1;
+    order[i] = i;
+  }
+  struct Op {
+    RegOpV o;
+    int perm, b0, b1;   // perm: 1 CX, 2 SWAP
+    unsigned bits;
+  };
+  std::vector<RbStage> stages;
+  std::vector<RegOpV> rops;
+  std::vector<unsigned> rbits;   // register bits of each op
+  std::vector<Phase> plan = plan_phases(order, lb, nq, nb, 0, 3);
+  if (plan.empty()) plan.push_back(Phase{{0, 1, 2, -1}, {}});   // no ops
+  for (const Phase& ph : plan) {
+    RbStage stg{};
+    for (int i = 0; i < 3; ++i) stg.reg[i] = ph.reg[i];
+    stg.op_begin = (int)rops.size();
+    auto ridx = [&](int bit) {
+      for (int i = 0; i < 3; ++i)
+        if (ph.reg[i] == bit) return i;
+      return -1;
+    };
+    std::vector<Op> pops;
+    for (int gi : ph.gates) {
+      const VqeOp& op = h->ops[gi];
+      const int r0 = ridx(op.q0), r1 = nq[gi] == 2 ? ridx(op.q1) : 0;
+      const int pair = nq[gi] == 2 ? rb_pair(std::min(r0, r1), std::max(r0, r1)) : 0;
+      Op o{{0, std::max(0, op.mat), op.param, -1}, 0, r0, r1, nq[gi] == 2 ? (1u << r0) | (1u << r1) : 1u << r0};
+      if (op.kind == OP_ROT) o.o.code = RV_ROT + 3 * op.axis + r0;
+      else if (op.kind == OP_FIX1) o.o.code = RV_FIX + r0;
+      else if (op.kind == OP_RZZ) o.o.code = RV_RZZ + pair;
+      else if (op.kind == OP_CZ) o.o.code = RV_CZ + pair;
+      else if (op.kind == OP_CX) o.o.code = RV_CX + 2 * pair + (r0 > r1 ? 1 : 0), o.perm = 1;
+      else o.o.code = RV_SWAP + pair, o.perm = 2;
+      o.o.code += 32 * (op.slot + 1);
+      pops.push_back(o);
+    }
+    fold_permutations(
+        pops, 3, [](const Op& o) { return o.perm != 0; }, [](const Op& o) { return o.bits; },
+        [](const Op& o, int j) { return o.perm == 1 ? reg_cx(o.b0, o.b1, j) : reg_swap(o.b0, o.b1, j); }, stg.ld_perm,
+        stg.st_perm);
+    for (size_t i = 0; i < pops.size(); ++i) {
+      const Op& o = pops[i];
+      // an RZ joins the RY before it on its bit when nothing between them touches the bit
+      if ((o.o.code & 31) >= RV_ROT + 6 && (o.o.code & 31) < RV_FIX) {
+        int j = (int)rops.size() - 1;
+        while (j >= stg.op_begin && !(rbits[j] & o.bits)) --j;
+        if (j >= stg.op_begin && (rops[j].code & 31) == RV_ROT + 3 + o.b0) {
+          rops[j].code += RV_YZ - (RV_ROT + 3);
+          rops[j].mat = (o.o.code >> 5) - 1;
+          rops[j].param2 = o.o.param;
+          continue;
+        }
+      }
+      rops.push_back(o.o);
+      rbits.push_back(o.bits);
+    }
+    stg.op_count = (int)rops.size() - stg.op_begin;
+    stages.push_back(stg);
+  }
+  std::vector<RbPhase> phases;
+  RbTileIo io;
+  layout_phases(stages, 3, nb, 0, 4, phases, io);
+  RbPhase end{};
+  for (int j = 0; j < kRbThreadBits; ++j) {
+    end.rd_t[j] = io.st_t[j];
+    end.wr_t[j] = entry_slot(io.st_t[j], 4);
+  }
+  for (int j = 0; j < 4; ++j) {
+    end.rd_r[j] = io.st_r[j];
+    end.wr_r[j] = entry_slot(io.st_r[j], 4);
+  }
+  h->reg_phases = (int)phases.size();
+  h->reg_ops = (int)rops.size();
+  phases.push_back(end);
+  std::vector<int> poff(h->P + 1, 0), pslots(h->nslots);
+  for (int p : h->slot_param) ++poff[p + 1];
+  for (int p = 0; p < h->P; ++p) poff[p + 1] += poff[p];
+  std::vector<int> at(poff.begin(), poff.end() - 1);
+  for (int sl = 0; sl < h->nslots; ++sl) pslots[at[h->slot_param[sl]]++] = sl;
+  auto up = [](size_t x) { return (x + 63) & ~size_t(63); };
+  h->reg_ops_off = up(phases.size() * sizeof(RbPhase));
+  h->reg_poff_off = up(h->reg_ops_off + rops.size() * sizeof(RegOpV));
+  h->reg_pslots_off = up(h->reg_poff_off + poff.size() * sizeof(int));
+  std::vector<char> prog(h->reg_pslots_off + pslots.size() * sizeof(int) + 16, 0);
+  std::memcpy(prog.data(), phases.data(), phases.size() * sizeof(RbPhase));
+  if (!rops.empty()) std::memcpy(prog.data() + h->reg_ops_off, rops.data(), rops.size() * sizeof(RegOpV));
+  std::memcpy(prog.data() + h->reg_poff_off, poff.data(), poff.size() * sizeof(int));
+  if (!pslots.empty()) std::memcpy(prog.data() + h->reg_pslots_off, pslots.data(), pslots.size() * sizeof(int));
+  return prog;
+}
+
 static int fused_grid(const nwq_vqe* h) {
   // workgroups per state, shared by the forward and backward launches (the
   // gradient partials have one slot per workgroup): sized on the backward tiles
@@ -2052,6 +2685,10 @@ int nwq_vqe_create(int n, int n_ops, const int* types, const int* qubits, const 
   if (!rc) rc = up((void**)&h->d_fixed, fixed.data(), fixed.size() * sizeof(double2));
   if (!rc) rc = up((void**)&h->d_terms, terms.data(), terms.size() * sizeof(VqeTerm));
   if (!rc) rc = up((void**)&h->d_slot_param, h->slot_param.data(), h->slot_param.size() * sizeof(int));
+  if (!rc && n <= 12 && h->nops <= 4096) {   // more does not fit the LDS
+    const std::vector<char> prog = build_reg(h.get());
+    rc = up(&h->d_reg, prog.data(), prog.size());
+  }
   if (rc) {
     nwq_vqe_destroy(h.release());
     return rc;
@@ -2067,7 +2704,7 @@ int nwq_vqe_destroy(nwq_vqe_handle h) {
   for (auto& kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
   for (void* p : {(void*)h->d_ops, (void*)h->d_fixed, (void*)h->d_terms, (void*)h->d_slot_param, (void*)h->d_phi,
                   (void*)h->d_lam, (void*)h->d_epart, (void*)h->d_gpart, (void*)h->d_theta, (void*)h->d_E,
-                  (void*)h->d_grad, (void*)h->d_coeffs, (void*)h->d_table, (void*)h->d_ssum, h->d_fused})
+                  (void*)h->d_grad, (void*)h->d_coeffs, (void*)h->d_table, (void*)h->d_ssum, h->d_fused, h->d_reg})
     if (p) (void)hipFree(p);
   if (h->ev_in) (void)hipEventDestroy(h->ev_in);
   if (h->ev_out) (void)hipEventDestroy(h->ev_out);

@@ -362,3 +362,57 @@ def test_fused_sweep_matches_per_gate_schedule(V, torch, n, L, B):
     assert np.max(np.abs(got[3][0] - got[2][0])) <= 1e-12
     assert np.max(np.abs(got[3][1] - got[2][1])) <= 1e-12
     ctx.close()
+
+
+@pytest.mark.parametrize("n,gates,terms", [(1, 12, 3), (2, 20, 15), (3, 40, 30), (7, 120, 70), (9, 150, 20),
+                                           (10, 200, 130), (12, 260, 64)])
+def test_resident_path_generic_programs(V, torch, n, gates, terms):
+    """The resident path (mode 1) on registers below one thread's 8
+    amplitudes, of one wave and of many, with every gate kind on random
+    qubits, shared parameters, angles beyond pi, Pauli sums with Y factors
+    longer than one staging of terms, per-vector coefficients and more vectors
+    than one: against one kernel per gate (mode 2), whose arithmetic differs
+    in order only."""
+    A = W.AnsatzGate
+    rng = np.random.default_rng(100 * n + gates)
+    P = max(3, gates // 4)
+    kinds = ["rx", "ry", "rz", "h", "s", "t", "x"] + (["rzz", "cz", "cx", "swap", "cx"] if n > 1 else [])
+    prog = []
+    for i in range(gates):
+        name = kinds[int(rng.integers(len(kinds)))]
+        q = tuple(int(x) for x in rng.choice(n, size=2 if name in ("rzz", "cz", "cx", "swap") else 1, replace=False))
+        param = int(rng.integers(P)) if name in ("rx", "ry", "rz", "rzz") else -1
+        prog.append(A(name, q, param))
+        if name == "ry":
+            prog.append(A("rz", q, int(rng.integers(P))))
+    ctx = V.VQE(n, prog, W.random_pauli_sum(n, terms, seed=n), n_params=P)
+    t = torch.from_numpy(rng.uniform(-8.0, 8.0, (3, P))).cuda()
+    c = torch.from_numpy(rng.uniform(-1.0, 1.0, (3, terms))).cuda()
+    got = {}
+    for mode in (1, 2):
+        ctx.set_config(mode, 128, 0)
+        E, G = ctx.eval(t)
+        Ec, Gc = ctx.eval_coeffs(t, c)
+        Eo, _ = ctx.eval(t, grad=False)
+        assert torch.equal(E, Eo)
+        got[mode] = [x.cpu().numpy() for x in (E, G, Ec, Gc)]
+    for a, b in zip(got[1], got[2]):
+        assert np.max(np.abs(a - b)) <= 1e-12 * terms
+    ctx.close()
+
+
+def test_resident_path_long_program(V, torch):
+    """A program too long for the register-resident kernel's tables runs in
+    LDS (mode 1) and agrees with one kernel per gate."""
+    n, L = 6, 90
+    theta, h = W.vqe_batch(n, L, B=2, seed=5)
+    ctx = V.VQE(n, W.hea_ansatz(n, L), W.tfim_hamiltonian(n, 1.0, h))
+    t = torch.from_numpy(theta).cuda()
+    got = {}
+    for n_rep, mode in ((1, 1), (1, 2)):
+        ctx.set_config(mode, 64, 0)
+        E, G = ctx.eval(t)
+        got[mode] = (E.cpu().numpy(), G.cpu().numpy())
+    assert np.max(np.abs(got[1][0] - got[2][0])) <= 1e-11
+    assert np.max(np.abs(got[1][1] - got[2][1])) <= 1e-11
+    ctx.close()
