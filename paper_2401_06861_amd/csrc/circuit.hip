@@ -783,7 +783,7 @@ void layout_phases(const std::vector<RbStage>& st, int rbits, int k, int low, in
   for (size_t i = 0; i < st.size(); ++i) {
     RbPhase ph{};
     ph.op_begin = st[i].op_begin;
-    ph.op_count = (short)st[i].op_count;
+    ph.count_flags = st[i].op_count << kRbFlagBits;
     if (i > 0) {
       const TileMap wr = tile_map(st[i - 1].reg, st[i - 1].st_perm, wave[i - 1], rbits, k, banks);
       const TileMap rd = tile_map(st[i].reg, st[i].ld_perm, wave[i], rbits, k, banks);
@@ -799,7 +799,7 @@ void layout_phases(const std::vector<RbStage>& st, int rbits, int k, int low, in
       // permutations stay among one thread's), so only the first exchange of a
       // tile can overwrite entries that another wave still reads: the last
       // phase's of the tile before.
-      ph.flags = (short)((local[i] ? 0 : kRbBarrierInside) | (i == 1 && !all_local ? kRbBarrierBefore : 0));
+      ph.count_flags |= (local[i] ? 0 : kRbBarrierInside) | (i == 1 && !all_local ? kRbBarrierBefore : 0);
     }
     out.push_back(ph);
   }

@@ -551,8 +551,8 @@ __global__ __launch_bounds__(R == 4 ? 512 : 1024) __attribute__((amdgpu_waves_pe
       const RbPhase ph = pp[pi];
       if (pi > 0) {
         const unsigned wa = thread_image(tid, ph.wr_t) << 3, ra = thread_image(tid, ph.rd_t) << 3;
-        const bool across = (ph.flags & kRbBarrierInside) != 0;
-        if (ph.flags & kRbBarrierBefore) __syncthreads();
+        const bool across = (ph.count_flags & kRbBarrierInside) != 0;
+        if (ph.count_flags & kRbBarrierBefore) __syncthreads();
 #pragma unroll
         for (int j = 0; j < NV; ++j) *lds_at(wa ^ (register_image(j, ph.wr_r) << 3)) = v[j].x;
         if (across) __syncthreads();
@@ -566,13 +566,14 @@ __global__ __launch_bounds__(R == 4 ? 512 : 1024) __attribute__((amdgpu_waves_pe
         for (int j = 0; j < NV; ++j) v[j].y = *lds_at(ra ^ (register_image(j, ph.rd_r) << 3));
       }
       const RbOp* __restrict__ po = ops + ph.op_begin;
+      const int nops = ph.count_flags >> kRbFlagBits;
       // the next ops' codes are loaded while this one runs (the table ends
       // with two spare entries)
       if constexpr (R == 4) {
         // two gates per trip, v -> w -> v (the host pads an odd count with a copy)
         vd2 w[NV];
         RbOp o0 = po[0], o1 = po[1];
-        for (int oi = 0; oi < ph.op_count; oi += 2) {
+        for (int oi = 0; oi < nops; oi += 2) {
           const RbOp n0 = po[oi + 2], n1 = po[oi + 3];
           rb_apply<R, SET>(o0.code, mats + o0.mat, v, w);
           rb_apply<R, SET>(o1.code, mats + o1.mat, w, v);
@@ -581,7 +582,7 @@ __global__ __launch_bounds__(R == 4 ? 512 : 1024) __attribute__((amdgpu_waves_pe
         }
       } else {
         RbOp o = po[0];
-        for (int oi = 0; oi < ph.op_count; ++oi) {
+        for (int oi = 0; oi < nops; ++oi) {
           const RbOp nx = po[oi + 1];
           rb_apply<R, SET>(o.code, mats + o.mat, v, v);
           o = nx;

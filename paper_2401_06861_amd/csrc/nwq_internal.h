@@ -192,10 +192,10 @@ inline void fill_phase_offsets(FusedPhase& fp, int rbits, const int* ld_perm, co
 // and register bits, so a map is given by the images of the single bits, which
 // are XORed together.
 constexpr int kRbThreadBits = 10;   // most thread bits (k = 13, R = 3)
-constexpr int kRbBarrierBefore = 1, kRbBarrierInside = 2;
+constexpr int kRbBarrierBefore = 1, kRbBarrierInside = 2, kRbFlagBits = 2;
 struct RbPhase {
   int op_begin;             // RbOps (an even number at 4 register bits; the op table ends with two spare entries)
-  short op_count, flags;
+  int count_flags;          // op count << kRbFlagBits | flags
   // The LDS exchange that leads into this phase (not for the first): entries
   // where the previous phase's registers are written and where this phase's
   // are read.  kRbBarrierBefore: other waves may still read the entries that

@@ -684,11 +684,11 @@ __global__ __launch_bounds__(kRegMaxThreads) void k_vqe_reg(
     for (int pi = 0; pi < P; ++pi) {
       const unsigned* ph = lph + 16 * pi;
       const int begin = (int)uni(ph[0]), cf = (int)uni(ph[1]);
-      const int count = (short)(cf & 0xFFFF);
+      const int count = cf >> kRbFlagBits;
       if (pi > 0) {
         const RegMap wr = reg_map(ph + 2), rd = reg_map(ph + 9);
         write(p, wr);
-        if ((cf >> 16) & kRbBarrierInside) __syncthreads();
+        if (cf & kRbBarrierInside) __syncthreads();
         read(p, rd);
       }
       for (int i = begin; i < begin + count; ++i) {   // the next op is read while this one runs
@@ -785,7 +785,7 @@ __global__ __launch_bounds__(kRegMaxThreads) void k_vqe_reg(
     for (int pi = P - 1; pi >= 0; --pi) {
       const unsigned* ph = lph + 16 * pi;
       const int begin = (int)uni(ph[0]), cf = (int)uni(ph[1]);
-      const int count = (short)(cf & 0xFFFF);
+      const int count = cf >> kRbFlagBits;
       for (int i = begin + count - 1; i >= begin; --i) {
         const int in = i > 0 ? i - 1 : 0;
         const int2 odn = lop[in];
@@ -808,7 +808,7 @@ __global__ __launch_bounds__(kRegMaxThreads) void k_vqe_reg(
       }
       if (pi > 0) {   // back through the exchange that led into this phase
         const RegMap wr = reg_map(ph + 9), rd = reg_map(ph + 2);
-        const bool across = ((cf >> 16) & kRbBarrierInside) != 0;
+        const bool across = (cf & kRbBarrierInside) != 0;
         write(p, wr);
         if (across) __syncthreads();
         read(p, rd);

@@ -513,6 +513,24 @@ def test_gate_products_in_blocks(nwq, n, k):
             st.close()
 
 
+@pytest.mark.parametrize("rb", [1, 2])
+def test_fused_phase_of_many_ops(nwq, rb):
+    """One register phase that holds more gates than a 16-bit count: rotations
+    about one axis add up, so the circuit is one rotation.  Tolerance: each of
+    the 2 x 33000 gates may move the state by a few 1e-16."""
+    n, reps = 8, 33000
+    psi0 = W.random_state(n, seed=4)
+    st = nwq.SVState(n, reset=False)
+    st.load(psi0)
+    st.set_fusion(8)
+    nwq.nwq_set_fusion_kernel(st.h, rb)
+    nwq.nwq_set_fusion_flags(st.h, 3)                # gates stay separate
+    st.run_circuit([("rx", (0,), (1e-4,)), ("rx", (1,), (2e-4,))] * reps)
+    want = tensor.sv_run([("rx", (0,), (1e-4 * reps,)), ("rx", (1,), (2e-4 * reps,))], n, psi0)
+    assert maxerr(st.numpy(), want) <= 2 * reps * 4e-16
+    st.close()
+
+
 def test_fused_identity_only_circuit(nwq):
     """A circuit of identities through the fused path (gate products drop
     them): no error, the state unchanged, no block launched."""
