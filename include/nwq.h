@@ -128,7 +128,9 @@ int nwq_apply_matrix(nwq_handle h, const int* qubits, int k, const double* m);
  * qubits[2*i .. 2*i+1] (second entry ignored for 1-qubit gates) and
  * params[3*i .. 3*i+2] (unused entries ignored).  With fusion enabled on an
  * SV handle (nwq_set_fusion) consecutive gates are grouped into k-qubit
- * blocks, each applied in one pass through LDS. */
+ * blocks, each applied in one pass through LDS.  With fusion off, an SV handle
+ * of at most 13 qubits runs 8 or more gates one by one inside one launch (per
+ * 2048 gates) -- unless timing is enabled or the stream is being captured. */
 int nwq_apply_circuit(nwq_handle h, int n_gates, const int* types,
                       const int* qubits, const double* params);
 /* Reset to |0...0> and apply the circuit (arguments as nwq_apply_circuit,
@@ -159,7 +161,7 @@ int nwq_qasm_parse(const char* text, int* n_qubits, int* n_gates, int capacity, 
                    double* params);
 int nwq_apply_qasm(nwq_handle h, const char* text);
 
-/* Fused-block width: 0 = off (one kernel per gate), else the number of bits
+/* Fused-block width: 0 = off (gates are applied one by one), else the number of bits
  * a block may touch (6..13; the register-blocked kernels use at most 12 of
  * them on registers of more than 13).  SV handles: nwq_apply_circuit runs its gates
  * through fused blocks.  DM handles: each 1q gate with the channels composed

@@ -70,17 +70,19 @@ bool grow_sets(const std::vector<u64>& masks, u64 all, u64 low, int room, int se
   std::vector<int> rem(masks.size());
   std::vector<u64> rm(masks);   // masks of the remaining gates
   for (size_t i = 0; i < rem.size(); ++i) rem[i] = (int)i;
+  size_t first = 0;   // the remaining gates: from here on
   std::vector<u64> front, cand;
+  std::vector<int> left;
   // a gate of several bits weighs more: one-bit gates join whichever set holds their bit
   auto weight = [](u64 m) { return (m & (m - 1)) ? 4 : 1; };
-  while (!rem.empty()) {
+  while (first < rm.size()) {
     front.clear();
     u64 blocked = 0;
-    for (size_t r = 0; r < rm.size() && blocked != all; ++r) {
+    for (size_t r = first; r < rm.size() && blocked != all; ++r) {
       const u64 m = rm[r];
       if (!(m & blocked)) {
         const u64 s = m & ~low;
-        if (r == 0 && bits_of(s) > room) return false;
+        if (r == first && bits_of(s) > room) return false;
         if (bits_of(s) <= room && std::find(front.begin(), front.end(), s) == front.end()) front.push_back(s);
       }
       blocked |= m;
@@ -98,7 +100,7 @@ bool grow_sets(const std::vector<u64>& masks, u64 all, u64 low, int room, int se
         cand.clear();
         score = 0;
         blocked = 0;
-        for (size_t r = 0; r < rm.size() && blocked != all; ++r) {
+        for (size_t r = first; r < rm.size() && blocked != all; ++r) {
           const u64 m = rm[r];
           if (m & blocked) {
             blocked |= m;
@@ -117,7 +119,7 @@ bool grow_sets(const std::vector<u64>& masks, u64 all, u64 low, int room, int se
           const u64 T2 = T | need;
           int s2 = 0;
           blocked = 0;
-          for (size_t r = 0; r < rm.size() && blocked != all; ++r) {
+          for (size_t r = first; r < rm.size() && blocked != all; ++r) {
             const u64 m = rm[r];
             if ((m & blocked) || (m & ~T2)) blocked |= m;
             else s2 += weight(m);
@@ -138,20 +140,26 @@ bool grow_sets(const std::vector<u64>& masks, u64 all, u64 low, int room, int se
     BitSet b;
     b.H = best_H;
     const u64 T = low | best_H;
+    // take the gates the set reaches; those left out on the way move up to
+    // the gates behind, so that a round costs time in what it visits
     blocked = 0;
-    size_t w = 0;
-    for (size_t r = 0; r < rm.size(); ++r) {
+    left.clear();
+    size_t r = first;
+    for (; r < rm.size() && blocked != all; ++r) {
       const u64 m = rm[r];
       if ((m & blocked) || (m & ~T)) {
         blocked |= m;
-        rem[w] = rem[r];
-        rm[w++] = m;
+        left.push_back((int)r);
       } else {
         b.gates.push_back(rem[r]);
       }
     }
-    rem.resize(w);
-    rm.resize(w);
+    for (size_t i = left.size(); i-- > 0;) {
+      --r;
+      rem[r] = rem[left[i]];
+      rm[r] = rm[left[i]];
+    }
+    first = r;
     out.push_back(std::move(b));
   }
   return true;
@@ -657,14 +665,14 @@ std::vector<FuseItem> gate_products(const std::vector<int>& seq, const std::vect
 // so the phase can move between registers and HBM directly when it is the
 // block's first or last).  Empty when a gate has more than rbits bits.
 std::vector<Phase> plan_phases(const std::vector<int>& order, const std::vector<std::array<int, 4>>& lb,
-                               const std::vector<int>& nq, int k, int c, int rbits) {
+                               const std::vector<int>& nq, int k, int c, int rbits, bool quick) {
   std::vector<u64> masks(order.size());
   for (size_t i = 0; i < order.size(); ++i)
     for (int t = 0; t < nq[order[i]]; ++t) masks[i] |= 1ull << lb[order[i]][t];
   const u64 all = (1ull << k) - 1ull;
   std::vector<BitSet> sets, other;
-  if (!grow_sets(masks, all, 0, rbits, 2, sets)) return {};
-  if (sets.size() > 1 && grow_sets_from_end(masks, all, 0, rbits, 2, other) && other.size() < sets.size())
+  if (!grow_sets(masks, all, 0, rbits, quick ? 1 : 2, sets)) return {};
+  if (!quick && sets.size() > 1 && grow_sets_from_end(masks, all, 0, rbits, 2, other) && other.size() < sets.size())
     sets.swap(other);
   std::vector<Phase> out(sets.size());
   for (size_t i = 0; i < sets.size(); ++i) {
@@ -734,10 +742,10 @@ TileMap tile_map(const int* reg, const int* perm, unsigned wave, int rbits, int 
 // LDS slot of a tile entry: bit i < banks is the parity of the entry's bits
 // that are i mod banks, so that a step along any tile bit changes the bank.
 unsigned short entry_slot(unsigned entry, int banks) {
-  unsigned s = entry >> banks << banks;
-  for (int i = 0; i < banks; ++i)
-    for (int b = i; b < 16; b += banks) s ^= b == i ? entry & (1u << i) : ((entry >> b) & 1u) << i;
-  return (unsigned short)s;
+  unsigned low = 0;
+  for (int b = 0; b < 16; b += banks) low ^= entry >> b;
+  const unsigned m = (1u << banks) - 1u;
+  return (unsigned short)((entry & ~m) | (low & m));
 }
 
 // Lays register phases out over the k bits of a tile (appends them to `out`):
@@ -859,13 +867,20 @@ void layout_rb_block(const Block& b, std::vector<RbStage> st, int rbits, bool di
 // qubit count for a state vector; 2n for the vectorised density matrix, whose
 // queued 1q superoperators arrive as kGateMat4 gates with matrices in `side`).
 int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, const std::vector<cd>* side_in,
-                bool from_zero) {
+                bool from_zero, bool one_tile) {
+  // One tile: the kernel that is fastest where one workgroup runs everything.
+  // Up to 8 bits the LDS kernel (300 gates of a TFIM on 8 qubits 201 us against
+  // 216 with R = 3; on 10 qubits 272 against 250), up to 12 bits R = 3 (380
+  // gates on 10 qubits 293 us against 313 with R = 4), then R = 4 (500 gates
+  // on 13 qubits 494 us against 530).
+  const int kernel = one_tile ? (nbits < 9 ? 0 : nbits < 13 ? 2 : 1) : h->fuse_rb;
+  const int flags = one_tile ? kFusedDirect : h->fuse_flags;
   // Gate products over the whole circuit (state vectors, register-blocked
   // kernels): they act on at most two qubits, so the blocks and their register
   // phases are planned over them as over gates, and no boundary cuts one.
   std::vector<PGate> prod_gates;
   std::vector<cd> prod_side;
-  const bool products = (h->fuse_flags & kFusedGateFusion) && side_in == nullptr && h->fuse_rb != 0;
+  const bool products = (flags & kFusedGateFusion) && side_in == nullptr && kernel != 0;
   if (products) {
     std::vector<int> seq, r0, r1;
     for (size_t i = 0; i < gates_in.size(); ++i) {
@@ -899,8 +914,8 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
   // dearer: a pass over 2^22 entries takes about 25 us, and each seed adds
   // about 0.1 ms to planning a deep circuit.
   const int seeds = nbits < 22 ? 1 : (nbits < 26 ? 2 : 8);
-  const std::vector<Block> blocks =
-      plan_blocks(gates, nbits, fusion_width(h, nbits), fusion_low_bits(h, nbits), seeds, false);
+  const std::vector<Block> blocks = plan_blocks(gates, nbits, one_tile ? nbits : fusion_width(h, nbits),
+                                                one_tile ? nbits : fusion_low_bits(h, nbits), seeds, false);
   if (blocks.empty()) return set_error(NWQ_EINVAL, "fusion planner made no progress");
   // Program: [phase table][op table][matrix table] in one upload.
   std::vector<RbPhase> phases;
@@ -909,16 +924,16 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
   std::vector<double2> mats;
   const int set = h->kind == NWQ_KIND_DM ? kRbSetDM : kRbSetSV;
   struct Launch { FusedBlockDev d; RbBlock r; bool rb; };
-  const int rbits = h->fuse_rb == 2 ? 3 : 4;
+  const int rbits = kernel == 2 ? 3 : 4;
   std::vector<Launch> launches;
   for (Block b : blocks) {
-    if (h->fuse_rb != 0 && b.c + b.m < 8 && nbits >= 8) pad_block(b, nbits, 8);
+    if (kernel != 0 && b.c + b.m < 8 && nbits >= 8) pad_block(b, nbits, 8);
     FusedBlockDev d{};
     d.c = b.c;
     d.m = b.m;
     for (int i = 0; i < b.m; ++i) d.hi[i] = b.hi[i];
     const int k = b.c + b.m;
-    const bool rb = h->fuse_rb != 0 && k >= 8;
+    const bool rb = kernel != 0 && k >= 8;
     if (!rb) {
       d.op_begin = (int)ops.size();
       for (int gi : b.gates) {
@@ -949,7 +964,7 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
     if (order.empty()) continue;
     const size_t rops0 = rops.size(), mats0 = mats.size();
     std::vector<RbStage> stages;
-    for (const Phase& ph : plan_phases(order, lb, nq, k, b.c, rbits)) {
+    for (const Phase& ph : plan_phases(order, lb, nq, k, b.c, rbits, one_tile)) {
       RbStage stg{};
       for (int i = 0; i < 4; ++i) stg.reg[i] = ph.reg[i] < 0 ? 0 : ph.reg[i];
       stg.op_begin = (int)rops.size();
@@ -965,7 +980,7 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
         RegOp op;
         if (make_reg_op(gates[gid[li]], rb_bits, rbits, side, op)) pops.push_back(std::move(op));
       }
-      if (h->fuse_flags & kFusedGateFusion) merge_diagonals(pops, rbits);
+      if (flags & kFusedGateFusion) merge_diagonals(pops, rbits);
       fold_permutations(
           pops, rbits, [](const RegOp& o) { return o.perm(); }, [](const RegOp& o) { return o.bits; },
           [](const RegOp& o, int j) { return o.map(j); }, stg.ld_perm, stg.st_perm);
@@ -975,7 +990,7 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
       stages.push_back(stg);
     }
     RbBlock r;
-    layout_rb_block(b, std::move(stages), rbits, (h->fuse_flags & kFusedDirect) != 0, r, phases);
+    layout_rb_block(b, std::move(stages), rbits, (flags & kFusedDirect) != 0, r, phases);
     r.prog_ops = (int)(rops.size() - rops0);
     r.prog_mats = (int)(mats.size() - mats0);
     launches.push_back({d, r, true});
@@ -1031,16 +1046,17 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
     if (L.rb) {
       const unsigned long long outside = ((1ull << nbits) - 1ull) & ~L.r.tile;
       launch_fused_rb(h->stream, h->data, nbits, L.r, dph, drops, dmats, rbits, set,
-                      (h->fuse_flags & kFusedNonTemporal) != 0, from_zero ? outside & support : outside);
+                      (flags & kFusedNonTemporal) != 0, from_zero ? outside & support : outside);
       support |= L.r.tile;
     } else {
-      launch_fused_block(h->stream, h->data, nbits, L.d, dops, dmats, h->fuse_k);
+      launch_fused_block(h->stream, h->data, nbits, L.d, dops, dmats);
       support = ~0ull;   // runs every tile (and may have touched any qubit)
     }
     timing_end(h);
     const int rc = check_hip(hipGetLastError(), "fused_block");
     if (rc) return rc;
   }
+  if (one_tile) return NWQ_OK;
   h->last_blocks = (int)launches.size();
   h->last_fused_gates = 0;
   for (const PGate& g : gates_in) h->last_fused_gates += g.type != NWQ_GATE_I;
@@ -1085,6 +1101,27 @@ static int parse_circuit(int n, int n_gates, const int* types, const int* qubits
   return NWQ_OK;
 }
 
+// A register of up to 13 qubits is one workgroup's tile: with fusion off its
+// gates run one by one in a single launch (per 2048 gates, a program of at
+// most 1.5 MB) instead of a launch each.  Launches are all that such a circuit
+// costs, 3 us per gate: 380 gates of a TFIM on 10 qubits 1168 -> 250 us, 500
+// on 13 1545 -> 415 us, of which planning takes 60 and 77.  Per-gate launches
+// stay for a handful of gates (4 take 30 us, 8 take 62 against 26 to 36), for
+// timed handles (times are kept per kernel class), for a stream under capture
+// (a replay would read the upload ring again) and where there is no memory for
+// the upload.
+constexpr int kOneTileBits = 13, kOneTileMinGates = 8, kOneTileChunk = 2048;
+static bool one_tile_circuit(nwq_state* h, int n_gates) {
+  if (h->n > kOneTileBits || n_gates < kOneTileMinGates || h->timing) return false;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(h->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone ||
+      arena_ready(h) != NWQ_OK) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return true;
+}
+
 static int apply_circuit_common(nwq_handle h, int n_gates, const int* types, const int* qubits, const double* params,
                                 bool from_zero) {
   if (h == nullptr) return set_error(NWQ_EINVAL, "NULL handle");
@@ -1100,6 +1137,14 @@ static int apply_circuit_common(nwq_handle h, int n_gates, const int* types, con
   h->last_fused_gates = 0;
   h->last_phases = 0;
   if (h->kind == NWQ_KIND_SV && h->fuse_k > 0 && n_gates > 0) return apply_fused(h, gates, h->n, nullptr, from_zero);
+  if (h->kind == NWQ_KIND_SV && one_tile_circuit(h, n_gates)) {
+    for (size_t i = 0; i < gates.size(); i += kOneTileChunk) {
+      const size_t e = std::min(gates.size(), i + kOneTileChunk);
+      const int rc = apply_fused(h, {gates.begin() + i, gates.begin() + e}, h->n, nullptr, false, true);
+      if (rc) return rc;
+    }
+    return NWQ_OK;
+  }
   for (const PGate& g : gates) {
     int rc;
     if (h->kind == NWQ_KIND_SV) {

@@ -115,9 +115,11 @@ constexpr int kGateMat4 = 1000;
 constexpr int kGateDiag4 = 1001;
 constexpr int kGateMat2 = 1002;
 constexpr int kGateMat16 = 1003;
-// from_zero: the state is |0...0> (the first block then runs tile 0 only)
+// from_zero: the state is |0...0> (the first block then runs tile 0 only).
+// one_tile: the whole register is one tile whatever the handle's fusion width,
+// and every gate is applied by itself (no gate products, no fusion statistics).
 int apply_fused(nwq_state* h, const std::vector<PGate>& gates, int nbits, const std::vector<cd>* side,
-                bool from_zero = false);
+                bool from_zero = false, bool one_tile = false);
 // Fold the permutation gates that can open or close a register phase into its
 // LDS offsets instead of moving registers.  A permutation moves past a
 // following (preceding) non-permutation gate on other register bits, since the
@@ -192,11 +194,12 @@ void layout_phases(const std::vector<RbStage>& st, int rbits, int k, int low, in
 void layout_rb_block(const Block& b, std::vector<RbStage> stages, int rbits, bool direct, RbBlock& d,
                      std::vector<RbPhase>& out);
 // c: the block's low tile bits; a phase with fewer gate bits than rbits is
-// padded with tile bits from c up first.
+// padded with tile bits from c up first.  quick: one search from the front.
 std::vector<Phase> plan_phases(const std::vector<int>& order, const std::vector<std::array<int, 4>>& lb,
-                               const std::vector<int>& nq, int k, int c, int rbits);
+                               const std::vector<int>& nq, int k, int c, int rbits, bool quick = false);
 
 void gate_matrix(int type, const double* p, cd* m);
+int arena_ready(nwq_state* h);
 int arena_put(nwq_state* h, const void* src, size_t bytes, void** dev_out);
 void timing_begin(nwq_state* h, int cls);
 void timing_end(nwq_state* h);

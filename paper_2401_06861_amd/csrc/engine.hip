@@ -144,14 +144,20 @@ static int check_handle(const nwq_state* h) {
 // ---------------------------------------------------------------------------
 static constexpr size_t kArenaBytes = 4u << 20;
 
-int arena_put(nwq_state* h, const void* src, size_t bytes, void** dev_out) {
-  bytes = (bytes + 255) & ~size_t(255);
-  if (bytes > kArenaBytes) return set_error(NWQ_EINVAL, "upload larger than the arena");
-  if (h->arena_dev == nullptr) {
-    NWQ_TRY_HIP(hipMalloc(&h->arena_dev, kArenaBytes), "hipMalloc(arena)");
+int arena_ready(nwq_state* h) {
+  if (h->arena_dev == nullptr) NWQ_TRY_HIP(hipMalloc(&h->arena_dev, kArenaBytes), "hipMalloc(arena)");
+  if (h->arena_host == nullptr) {
     NWQ_TRY_HIP(hipHostMalloc(&h->arena_host, kArenaBytes, hipHostMallocDefault), "hipHostMalloc(arena)");
     h->arena_off = 0;
   }
+  return NWQ_OK;
+}
+
+int arena_put(nwq_state* h, const void* src, size_t bytes, void** dev_out) {
+  bytes = (bytes + 255) & ~size_t(255);
+  if (bytes > kArenaBytes) return set_error(NWQ_EINVAL, "upload larger than the arena");
+  const int rc = arena_ready(h);
+  if (rc) return rc;
   if (h->arena_off + bytes > kArenaBytes) {
     NWQ_TRY_HIP(hipStreamSynchronize(h->stream), "hipStreamSynchronize(arena wrap)");
     h->arena_off = 0;

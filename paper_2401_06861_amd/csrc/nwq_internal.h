@@ -158,7 +158,7 @@ struct FusedBlockDev {
   unsigned long long joff[16];
 };
 void launch_fused_block(hipStream_t s, double2* a, int nbits, const FusedBlockDev& blk,
-                        const FusedOp* ops, const double2* mats, int lds_k);
+                        const FusedOp* ops, const double2* mats);
 // A register phase of the VQE backward kernel: its register bits (tile-local,
 // ascending; unused entries ignored) and its ops.
 struct FusedPhase {

@@ -531,6 +531,71 @@ def test_fused_phase_of_many_ops(nwq, rb):
     st.close()
 
 
+@pytest.mark.parametrize("n", [1, 2, 7, 8, 9, 12, 13])
+@pytest.mark.parametrize("count", [7, 8, 300])
+def test_small_register_in_one_launch(nwq, n, count):
+    """Fusion off on registers of one tile: fewer gates than the line (a launch
+    each), the line and many gates, from any state and from |0...0>, with the
+    statistics of an unfused circuit; a timed handle keeps per-gate launches."""
+    gates = W.random_gate_list(n, count, seed=n * 7 + count)
+    if n == 1:
+        gates = [g for g in gates if len(g[1]) == 1] * 2
+    psi0 = W.random_state(n, seed=n)
+    st = nwq.SVState(n, reset=False)
+    st.load(psi0)
+    st.run_circuit(gates)
+    assert maxerr(st.numpy(), tensor.sv_run(gates, n, psi0)) <= TOL
+    assert nwq.nwq_fusion_stats(st.h) == (0, 0)
+    zero = np.zeros(1 << n, complex)
+    zero[0] = 1
+    nwq.nwq_run_circuit(st.h, *nwq.circuit_arrays(gates))
+    assert maxerr(st.numpy(), tensor.sv_run(gates, n, zero)) <= TOL
+    nwq.nwq_timing_enable(st.h, True)
+    st.load(psi0)
+    st.run_circuit(gates)
+    assert maxerr(st.numpy(), tensor.sv_run(gates, n, psi0)) <= TOL
+    st.close()
+
+
+@pytest.mark.parametrize("n", [6, 11])
+def test_small_register_many_gates(nwq, n):
+    """More gates than one launch takes (2048).  Tolerance: 1e-16 a gate."""
+    gates = W.random_gate_list(n, 4500, seed=n)
+    psi0 = W.random_state(n, seed=n)
+    st = nwq.SVState(n, reset=False)
+    st.load(psi0)
+    st.run_circuit(gates)
+    assert maxerr(st.numpy(), tensor.sv_run(gates, n, psi0)) <= TOL
+    st.close()
+
+
+def test_small_register_under_capture(nwq):
+    """A captured unfused circuit replays with eager work on other gates (and
+    the upload ring) in between."""
+    import torch
+    n = 10
+    gates, other = (W.random_gate_list(n, 40, seed=s) for s in (1, 2))
+    psi = W.random_state(n, seed=3)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        st = nwq.SVState(n, reset=False)
+        st.load(psi)
+        st.run_circuit(other)
+    psi = tensor.sv_run(other, n, psi)
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        st.run_circuit(gates)
+    for _ in range(3):
+        with torch.cuda.stream(s):
+            g.replay()
+            st.run_circuit(other)
+        s.synchronize()
+        psi = tensor.sv_run(other, n, tensor.sv_run(gates, n, psi))
+        assert maxerr(st.numpy(), psi) <= TOL
+    st.close()
+
+
 def test_fused_identity_only_circuit(nwq):
     """A circuit of identities through the fused path (gate products drop
     them): no error, the state unchanged, no block launched."""
