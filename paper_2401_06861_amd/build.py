@@ -43,6 +43,7 @@ CFLAGS = [
 UNIFORM = ["-mllvm", "-structurizecfg-skip-uniform-regions=1"]
 FILE_FLAGS = {
     "kernels_fuse.hip": ["-mllvm", "-simplifycfg-sink-common=false"] + UNIFORM,
+    "kernels_reduce.hip": UNIFORM,
     "vqe.hip": UNIFORM,
 }
 

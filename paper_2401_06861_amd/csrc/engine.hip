@@ -789,8 +789,10 @@ struct PassPlan {
 
 static std::vector<PassPlan> plan_pauli_passes(int n, const std::vector<int>& ids, const uint64_t* xm) {
   std::vector<PassPlan> passes;
-  const int c = n <= 11 ? n : 6;
-  const int mmax = n <= 11 ? 0 : std::min(5, n - c);   // tile <= 2^11 amplitudes (32 KiB LDS)
+  // one tile up to 11 bits; tiles of 2^11 with runs of 2^6 while 2^12 would
+  // give too few of them, then 2^12 with runs of 2^4 (8 more bits per pass)
+  const int c = n <= 11 ? n : n < 20 ? 6 : 4;
+  const int mmax = n <= 11 ? 0 : std::min(n < 20 ? 5 : 8, n - c);
   const uint64_t lowmask = c >= 64 ? ~0ull : ((1ull << c) - 1ull);
   for (int t : ids) {
     const uint64_t hx = xm[t] & ~lowmask;
@@ -799,7 +801,7 @@ static std::vector<PassPlan> plan_pauli_passes(int n, const std::vector<int>& id
       if ((hx >> b) & 1ull) bits.push_back(b);
     int chosen = -1;
     for (size_t p = 0; p < passes.size() && chosen < 0; ++p) {
-      if ((int)passes[p].terms.size() >= 16 || passes[p].shape.m < 0) continue;
+      if ((int)passes[p].terms.size() >= kTileTerms || passes[p].shape.m < 0) continue;
       std::vector<int> u(passes[p].shape.hi, passes[p].shape.hi + passes[p].shape.m);
       for (int b : bits)
         if (std::find(u.begin(), u.end(), b) == u.end()) u.push_back(b);
@@ -840,20 +842,6 @@ static std::vector<PassPlan> plan_pauli_passes(int n, const std::vector<int>& id
   return passes;
 }
 
-static uint64_t to_local(uint64_t mask, const TileShape& s) {
-  const uint64_t low = mask & ((s.c >= 64) ? ~0ull : ((1ull << s.c) - 1ull));
-  uint64_t l = low;
-  for (int i = 0; i < s.m; ++i)
-    if ((mask >> s.hi[i]) & 1ull) l |= 1ull << (s.c + i);
-  return l;
-}
-
-static uint64_t inside_mask(const TileShape& s) {
-  uint64_t m = (s.c >= 64) ? ~0ull : ((1ull << s.c) - 1ull);
-  for (int i = 0; i < s.m; ++i) m |= 1ull << s.hi[i];
-  return m;
-}
-
 // Reduce T Pauli terms; results_dev[0..T) = Re <P_t>, and if coeffs:
 // results_dev[T] = sum_t coeffs[t] Re <P_t>.  Leaves the copy to the caller.
 static int run_pauli(nwq_state* h, int T, const uint64_t* xm, const uint64_t* zm, const double* coeffs,
@@ -867,7 +855,9 @@ static int run_pauli(nwq_state* h, int T, const uint64_t* xm, const uint64_t* zm
     // rows 2t, 2t+1: Re and Im of Tr(rho P_t)
     std::vector<TermDev> td(T);
     for (int t = 0; t < T; ++t) {
-      td[t] = TermDev{xm[t], zm[t], 0ull, __builtin_popcountll(xm[t] & zm[t]) & 3, 0};
+      td[t].xl = xm[t];
+      td[t].zl = zm[t];
+      td[t].y = __builtin_popcountll(xm[t] & zm[t]) & 3;
     }
     const int G = dm_pauli_grid(n);
     int rc = ensure_partials(h, (size_t)2 * T * G);
@@ -902,33 +892,30 @@ static int run_pauli(nwq_state* h, int T, const uint64_t* xm, const uint64_t* zm
     return last_launch("reduce_rows");
   }
   // terms with no flipped bits (Z strings) run in streaming passes of their
-  // own, up to 16 consecutive rows each; the others are planned into tiles
+  // own, up to kDiagTerms each; the others are planned into tiles
   std::vector<int> flip_ids;
   for (int t = 0; t < T; ++t)
     if (xm[t] != 0) flip_ids.push_back(t);
   std::vector<PassPlan> passes = plan_pauli_passes(n, flip_ids, xm);
-  const int G = pauli_tile_grid(n, TileShape{n <= 11 ? n : 6, n <= 11 ? 0 : 5, {}});
+  const int G = pauli_grid(n);
   int rc = ensure_partials(h, (size_t)T * G);
   if (rc) return rc;
   rc = ensure_results(h, (size_t)T + 1);
   if (rc) return rc;
   for (int t = 0; t < T;) {
-    if (xm[t] != 0) {
-      ++t;
-      continue;
-    }
     ZMasks zs{};
     int cnt = 0;
-    while (t + cnt < T && cnt < 16 && xm[t + cnt] == 0) {
-      zs.z[cnt] = zm[t + cnt];
-      ++cnt;
-    }
+    for (; t < T && cnt < kDiagTerms; ++t)
+      if (xm[t] == 0) {
+        zs.z[cnt] = zm[t];
+        zs.row[cnt++] = t;
+      }
+    if (cnt == 0) break;
     timing_begin(h, KC_REDUCE);
-    launch_pauli_diag(h->stream, h->data, n, zs, cnt, h->partials, t, G);
+    launch_pauli_diag(h->stream, h->data, n, zs, cnt, h->partials, G);
     timing_end(h);
     rc = last_launch("pauli_diag");
     if (rc) return rc;
-    t += cnt;
   }
   // rows follow the caller's term order
   for (auto& pp : passes) {
@@ -943,27 +930,16 @@ static int run_pauli(nwq_state* h, int T, const uint64_t* xm, const uint64_t* zm
       continue;
     }
     std::vector<TermDev> td;
-    for (int t : pp.terms) {
-      const uint64_t in = inside_mask(pp.shape);
-      td.push_back(TermDev{to_local(xm[t], pp.shape), to_local(zm[t] & in, pp.shape), zm[t] & ~in,
-                           __builtin_popcountll(xm[t] & zm[t]) & 3, 0});
-    }
-    // terms of one pass are contiguous rows only if in order; launch per run of consecutive rows
-    size_t i = 0;
-    while (i < pp.terms.size()) {
-      size_t j = i + 1;
-      while (j < pp.terms.size() && pp.terms[j] == pp.terms[j - 1] + 1) ++j;
-      void* dterms = nullptr;
-      rc = arena_put(h, td.data() + i, (j - i) * sizeof(TermDev), &dterms);
-      if (rc) return rc;
-      timing_begin(h, KC_REDUCE);
-      launch_pauli_tile(h->stream, h->data, n, pp.shape, static_cast<const TermDev*>(dterms), (int)(j - i),
-                        h->partials, pp.terms[i], G);
-      timing_end(h);
-      rc = last_launch("pauli_tile");
-      if (rc) return rc;
-      i = j;
-    }
+    for (int t : pp.terms) td.push_back(pauli_term(pp.shape, xm[t], zm[t], t));
+    void* dterms = nullptr;
+    rc = arena_put(h, td.data(), td.size() * sizeof(TermDev), &dterms);
+    if (rc) return rc;
+    timing_begin(h, KC_REDUCE);
+    launch_pauli_tile(h->stream, h->data, n, pp.shape, static_cast<const TermDev*>(dterms), (int)td.size(),
+                      h->partials, G);
+    timing_end(h);
+    rc = last_launch("pauli_tile");
+    if (rc) return rc;
   }
   const double* dco = nullptr;
   if (coeffs) {

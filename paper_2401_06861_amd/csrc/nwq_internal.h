@@ -70,31 +70,40 @@ void launch_sv_kq(hipStream_t s, double2* a, int nbits, int k, const int* qubits
                   const LaunchCfg& cfg, bool pauli = false);
 
 // ---- reductions (kernels_reduce.hip) --------------------------------------
-// One pass of the tiled Pauli-term kernel.  `terms` is a device table of
-// `count` TermDev rows; partial sums go to partials[row * grid + block] with
-// row = first_row + term index.
-struct TermDev {
-  unsigned long long xl;    // x mask in tile-local bit positions
-  unsigned long long zl;    // z bits inside the tile, tile-local positions
-  unsigned long long zo;    // z bits outside the tile, global positions
-  int y;                    // popcount(x & z) mod 4
-  int pad;
-};
 struct TileShape {
   int c;                    // low contiguous bits in the tile
   int m;                    // number of high bits
   int hi[8];                // the high bit positions, ascending
 };
-int pauli_tile_grid(int nbits, const TileShape& t);
-// Terms with no flipped bits (x = 0): up to 16 z masks (global bit
-// positions) by value; partials as above, with the same grid.
+// Blocks of a reduction over 2^nbits entries: one row of partials has as many.
+int pauli_grid(int nbits);
+// One pass of the tiled Pauli-term kernel: a device table of `count` terms;
+// partial sums go to partials[row * grid + block].
+constexpr int kTileTerms = 16;
+struct TermDev {
+  unsigned long long xl;    // x mask in tile-local bit positions
+  unsigned long long zl;    // z bits inside the tile, tile-local positions
+  unsigned long long zo;    // z bits outside the tile, global positions
+  int y;                    // popcount(x & z) mod 4
+  int row;
+  // one amplitude of each pair: half > 0, those with register bit half - 1
+  // clear; waves != 0, those on waves with even parity under it; else all
+  int half;
+  unsigned waves;
+  double scale;             // sign of Re(i^y w), 2 where each pair counts once
+};
+TermDev pauli_term(const TileShape& t, unsigned long long x, unsigned long long z, int row);
+void launch_pauli_tile(hipStream_t s, const double2* a, int nbits, const TileShape& t,
+                       const TermDev* terms, int count, double* partials, int grid);
+// Terms with no flipped bits (x = 0): z masks (global bit positions) and
+// rows by value; partials as above, with the same grid.
+constexpr int kDiagTerms = 32;
 struct ZMasks {
-  unsigned long long z[16];
+  unsigned long long z[kDiagTerms];
+  int row[kDiagTerms];
 };
 void launch_pauli_diag(hipStream_t s, const double2* a, int nbits, const ZMasks& zs, int count, double* partials,
-                       int first_row, int grid);
-void launch_pauli_tile(hipStream_t s, const double2* a, int nbits, const TileShape& t,
-                       const TermDev* terms, int count, double* partials, int first_row, int grid);
+                       int grid);
 // One term with wide x support, pairs read from global memory; partials[block].
 void launch_pauli_pairs(hipStream_t s, const double2* a, int nbits, unsigned long long x, unsigned long long z,
                         int y, double* partials, int grid);

@@ -177,6 +177,29 @@ def test_diagonal_terms_streaming_pass(nwq, n):
     st.close()
 
 
+@pytest.mark.parametrize("n", [11, 15, 20, 21])
+def test_pauli_tile_splits(nwq, n):
+    """Every way a term's pairs are split over a tile (flipped bits on lanes
+    only, up to a wave bit, up to a register bit), with and without signs on
+    the register bits and Y factors, more than 16 such terms, in an order that
+    alternates with more than 32 Z strings; tiles of 2^11 and 2^12."""
+    rng = np.random.default_rng(n)
+    psi = W.random_state(n, seed=70 + n)
+    flips = [1, 1 << 5, 3, 0x21, 1 << 6, 0x41, 0xC0, 1 << 7, 0x1C1, 1 << (n - 1), 1 << (n - 2), (1 << (n - 1)) | 1]
+    flips += [1 << q for q in range(n)] + [0x700 & ((1 << n) - 1), (1 << (n - 1)) | (1 << (n - 3)) | 0x40]
+    terms = []
+    for x in flips:
+        terms += [(x, 0, 1.0), (0, int(rng.integers(1, 1 << n)), 1.0), (x, int(rng.integers(1, 1 << n)), 0.5)]
+    st = nwq.SVState(n, reset=False)
+    st.load(psi)
+    got = st.expvals(terms)
+    want = np.array([tensor.sv_expval(psi, x, z, n).real for x, z, _ in terms])
+    assert maxerr(got, want) <= TOL
+    assert np.array_equal(st.expvals(terms), got)
+    assert abs(st.pauli_sum(terms) - sum(c * w for (_, _, c), w in zip(terms, want))) <= TOL * len(terms)
+    st.close()
+
+
 def test_tfim_energy_matches_dense(nwq):
     n = 9
     terms = W.tfim_hamiltonian(n, 1.0, 0.8)
