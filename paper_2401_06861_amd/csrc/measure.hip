@@ -10,8 +10,8 @@
 //     matrix), one streaming pass;
 //   * readout noise: per qubit a column-stochastic 2x2 confusion matrix
 //     C[r][t] = P(read r | true t) applied on that qubit's bit of the outcome
-//     index, up to five qubits per pass with the group's entries in
-//     registers;
+//     index, up to 12 qubits per pass through LDS tiles or five with the
+//     group's entries in registers;
 //   * sampling by inverse transform on an integer CDF: q_j = floor(p_j 2^61)
 //     (exact power-of-two scaling), C_j = q_0 + ... + q_j in 64-bit integers
 //     (a tiled scan: per-tile totals, one workgroup for the tile offsets, then
@@ -19,6 +19,7 @@
 //     smallest j with C_j > floor(floor(u 2^53) Q / 2^53), Q = C_{N-1}.
 //     Integer sums are exact and associative, so the CDF is the same in any
 //     order, monotone, and never selects a zero-probability outcome.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -118,6 +119,84 @@ __global__ __launch_bounds__(kBlock) void k_readout(double* __restrict__ p, unsi
   }
 }
 
+// Confusion matrices of up to 12 qubits in one pass: a tile of the 4 low
+// outcome bits (128-byte runs) and 8 others, 16 entries per thread on 4
+// register bits.  The tile's upper four bits go first (as loaded), then
+// through LDS the lower four, then the middle four, whose layout also stores
+// runs of 128 bytes.  A slot's low five bits take in the five above, so every
+// layout's 32 lanes cover all banks.  Bound by the streams: 27 qubits take 3
+// passes of 0.41 ms (2^27 entries read and written: 5.2 TB/s) instead of 6 of
+// 0.38 with five qubits per pass in registers.
+constexpr int kConfTileBits = 12, kConfTileHigh = 8;
+struct ConfTile {
+  int hi[kConfTileHigh];       // the outcome bits of tile bits 4 to 11, ascending
+  unsigned on;                 // tile bits that carry a matrix
+  double cm[kConfTileBits][4];
+};
+__global__ __launch_bounds__(kBlock) void k_readout_tile(double* __restrict__ p, unsigned long long ntiles,
+                                                         ConfTile ct) {
+  static_assert(kBlock == 256, "16 entries of 2^12 per thread");
+  __shared__ double s[1 << kConfTileBits];
+  const unsigned t = threadIdx.x;
+  auto scatter = [&](unsigned e) {
+    unsigned long long g = e & 15u;
+#pragma unroll
+    for (int i = 0; i < kConfTileHigh; ++i)
+      if ((e >> (4 + i)) & 1u) g |= 1ull << ct.hi[i];
+    return g;
+  };
+  auto slot = [](unsigned e) { return e ^ ((e >> 5) & 31u); };
+  // thread parts of the layouts; lane bit 4 of the last takes tile bit 9 for the banks
+  const unsigned tA = t, tC = t << 4, tB = (t & 15u) | ((t & 16u) << 5) | ((t & 32u) << 3) | ((t & 192u) << 4);
+  const unsigned long long gA = scatter(tA), gB = scatter(tB);
+  double v[16];
+  auto apply = [&](int b0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (!((ct.on >> (b0 + i)) & 1u)) continue;
+      const double c00 = ct.cm[b0 + i][0], c01 = ct.cm[b0 + i][1], c10 = ct.cm[b0 + i][2], c11 = ct.cm[b0 + i][3];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        if ((u >> i) & 1) continue;
+        const double t0 = v[u], t1 = v[u | (1 << i)];
+        v[u] = c00 * t0 + c01 * t1;
+        v[u | (1 << i)] = c10 * t0 + c11 * t1;
+      }
+    }
+  };
+  const bool low = (ct.on & 0xFu) != 0, mid = (ct.on & 0xF0u) != 0;
+  for (unsigned long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    unsigned long long base = tile << 4;
+#pragma unroll
+    for (int i = 0; i < kConfTileHigh; ++i) base = ins0m(base, ct.hi[i]);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = p[(base | scatter((unsigned)j << 8)) | gA];
+    apply(8);
+    if (!low && !mid) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) p[(base | scatter((unsigned)j << 8)) | gA] = v[j];
+      continue;
+    }
+    __syncthreads();   // the tile before has been read
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s[slot(tA | ((unsigned)j << 8))] = v[j];
+    __syncthreads();
+    if (low) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) v[j] = s[slot(tC | (unsigned)j)];
+      apply(0);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) s[slot(tC | (unsigned)j)] = v[j];
+      __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = s[slot(tB | ((unsigned)j << 4))];
+    apply(4);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) p[(base | scatter((unsigned)j << 4)) | gB] = v[j];
+  }
+}
+
 // Tile totals of the quantised distribution (exact integer sums).
 __global__ __launch_bounds__(kScanThreads) void k_scan_totals(const double* __restrict__ p, unsigned long long N,
                                                               unsigned long long* __restrict__ totals) {
@@ -141,26 +220,28 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_totals(const double* __re
 }
 
 // Exclusive prefix of the tile totals (one workgroup; each thread takes a
-// contiguous chunk).
+// contiguous chunk, chunk sums are scanned within the waves and over them:
+// 32768 tiles 71 us with one thread scanning the chunk sums, 27 us).
 __global__ __launch_bounds__(1024) void k_scan_offsets(const unsigned long long* __restrict__ totals, int ntiles,
                                                        unsigned long long* __restrict__ offsets) {
-  __shared__ unsigned long long part[1024];
+  __shared__ unsigned long long wsum[1024 / kWave];
   const int per = (ntiles + 1023) / 1024;
-  const int b0 = threadIdx.x * per, b1 = min(ntiles, b0 + per);
+  const int b0 = min(ntiles, (int)threadIdx.x * per), b1 = min(ntiles, b0 + per);
   unsigned long long s = 0;
+#pragma unroll 8
   for (int b = b0; b < b1; ++b) s += totals[b];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long run = 0;
-    for (int t = 0; t < 1024; ++t) {
-      const unsigned long long v = part[t];
-      part[t] = run;
-      run += v;
-    }
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  unsigned long long incl = s;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const unsigned long long up = __shfl_up(incl, o, kWave);
+    if (lane >= o) incl += up;
   }
+  if (lane == kWave - 1) wsum[wave] = incl;
   __syncthreads();
-  unsigned long long run = part[threadIdx.x];
+  unsigned long long run = incl - s;
+  for (int w = 0; w < wave; ++w) run += wsum[w];
+#pragma unroll 8
   for (int b = b0; b < b1; ++b) {
     offsets[b] = run;
     run += totals[b];
@@ -320,7 +401,39 @@ int nwq_readout_noise(int n, double* probs_dev, const double* confusion, void* s
     if (!(c[0] == 1.0 && c[3] == 1.0)) qs.push_back(q);
   }
   // The per-qubit matrices act on different bits and commute, so any grouping
-  // gives the same result up to rounding.  Pass k takes qubits k, k + P,
+  // gives the same result up to rounding.  Tiles take the low four bits and
+  // eight more per pass; where that saves no pass, a pass takes up to five
+  // qubits in registers.
+  size_t low = 0;
+  while (low < qs.size() && qs[low] < 4) ++low;
+  const size_t high = qs.size() - low, tiled = std::max<size_t>(1, (high + kConfTileHigh - 1) / kConfTileHigh);
+  if (n >= kConfTileBits && tiled < (qs.size() + kReadoutMaxGroup - 1) / kReadoutMaxGroup) {
+    for (size_t k = 0; k < tiled; ++k) {
+      ConfTile ct{};
+      std::vector<int> bits(qs.begin() + low + k * kConfTileHigh,
+                            qs.begin() + low + std::min(high, (k + 1) * kConfTileHigh));
+      std::vector<int> hi(bits);   // filled up with other bits
+      for (int b = 4; (int)hi.size() < kConfTileHigh; ++b)
+        if (std::find(bits.begin(), bits.end(), b) == bits.end()) hi.push_back(b);
+      std::sort(hi.begin(), hi.end());
+      auto put = [&](int tile_bit, int q) {
+        ct.on |= 1u << tile_bit;
+        for (int e = 0; e < 4; ++e) ct.cm[tile_bit][e] = confusion[4 * q + e];
+      };
+      for (int i = 0; i < kConfTileHigh; ++i) {
+        ct.hi[i] = hi[i];
+        if (std::find(bits.begin(), bits.end(), hi[i]) != bits.end()) put(4 + i, hi[i]);
+      }
+      if (k == 0)
+        for (size_t i = 0; i < low; ++i) put(qs[i], qs[i]);
+      const unsigned long long nt = 1ull << (n - kConfTileBits);
+      hipLaunchKernelGGL(k_readout_tile, dim3(grid_n(nt, 1, 1u << 20)), dim3(kBlock), 0, s, probs_dev, nt, ct);
+      const int rc = check_hip(hipGetLastError(), "readout noise");
+      if (rc) return rc;
+    }
+    return NWQ_OK;
+  }
+  // Pass k takes qubits k, k + P,
   // k + 2P, ... of the list (P passes): the low bits, whose groups would
   // otherwise be read as short per-thread runs, are spread over the passes.
   const size_t P = (qs.size() + kReadoutMaxGroup - 1) / kReadoutMaxGroup;

@@ -69,6 +69,22 @@ def test_readout_noise(nwq, torch, n):
     assert np.max(np.abs(t.cpu().numpy() - M.readout_noise(p, cs, n))) <= 1e-15
 
 
+@pytest.mark.parametrize("n,qubits", [(12, range(12)), (13, range(13)), (14, range(4, 14)), (17, range(17)),
+                                      (20, [0, 3, 5, 9, 11, 14, 19]), (20, range(11, 20)), (20, range(20)),
+                                      (22, [1, 2, 3, 18, 19, 20, 21]), (21, range(21))])
+def test_readout_noise_tiles(nwq, torch, n, qubits):
+    """Passes through LDS tiles: one, two and three of them, with matrices on
+    the low bits only in the first, on some of a tile's bits, on its upper
+    bits alone.  Tolerance: that of the passes in registers."""
+    rng = np.random.default_rng(n)
+    p = rng.dirichlet(np.ones(1 << n))
+    full = confusions(n, seed=n + 1, identity_every=n + 1)
+    cs = [full[q] if q in qubits else np.eye(2) for q in range(n)]
+    t = torch.from_numpy(p).cuda()
+    nwq.nwq_readout_noise(n, t, cs)
+    assert np.max(np.abs(t.cpu().numpy() - M.readout_noise(p, cs, n))) <= 1e-15
+
+
 def test_readout_noise_rejects_bad_matrices(nwq, torch):
     t = torch.zeros(8, dtype=torch.float64, device="cuda")
     bad = [np.eye(2), np.array([[0.9, 0.0], [0.2, 1.0]]), np.eye(2)]    # column 0 sums to 1.1
