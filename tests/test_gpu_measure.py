@@ -111,6 +111,29 @@ def test_sampling_bit_exact(nwq, torch, n, zeros):
     assert not np.isin(out.cpu().numpy(), zeros).any()
 
 
+@pytest.mark.parametrize("n", [2, 7, 11, 12, 13, 15, 17])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_sampling_tiles(nwq, torch, n, shift):
+    """Below, at and above a scan tile of 4096 entries, whole tiles of zero
+    probability at the start, in the middle and at the end, and a distribution
+    that starts off a 16-byte line: shots and CDF bit for bit."""
+    rng = np.random.default_rng(n)
+    p = rng.dirichlet(np.ones(1 << n) * 0.5)
+    if n > 13:
+        p[:5000] = 0.0
+        p[3 * 4096:6 * 4096] = 0.0
+        p[-4097:] = 0.0
+    p /= p.sum()
+    u = rng.uniform(0, 1, 5000)
+    u[:3] = [0.0, 0.5, 1.0 - 2.0 ** -53]
+    pt = torch.empty((1 << n) + shift, dtype=torch.float64, device="cuda")[shift:]
+    pt.copy_(torch.from_numpy(p))
+    work = torch.empty(nwq.nwq_sample_workspace_bytes(n) // 8, dtype=torch.int64, device="cuda")
+    out = nwq.sample_shots(n, pt, torch.from_numpy(u).cuda(), work)
+    assert np.array_equal(out.cpu().numpy(), M.sample(p, u))
+    assert np.array_equal(work[: 1 << n].cpu().numpy().view(np.uint64), np.cumsum(M.quantize(p), dtype=np.uint64))
+
+
 def test_sampling_edges(nwq, torch):
     n = 6
     work = torch.empty(nwq.nwq_sample_workspace_bytes(n) // 8, dtype=torch.int64, device="cuda")
