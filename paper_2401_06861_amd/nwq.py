@@ -122,13 +122,20 @@ def _check(rc: int) -> None:
         raise NwqError(rc, nwq_last_error())
 
 
+# Array types of the short argument lists of gates and channels (building the
+# type costs as much as the call that takes it).
+_SHORT_INTS = [C.c_int * max(k, 1) for k in range(5)]
+_SHORT_DOUBLES = [C.c_double * max(k, 1) for k in range(5)]
+
+
 def _ints(xs: Sequence[int]):
-    arr = (C.c_int * max(len(xs), 1))(*[int(x) for x in xs])
-    return arr
+    n = len(xs)
+    return (_SHORT_INTS[n] if n < 5 else C.c_int * n)(*map(int, xs))
 
 
 def _doubles(xs: Sequence[float]):
-    return (C.c_double * max(len(xs), 1))(*[float(x) for x in xs])
+    n = len(xs)
+    return (_SHORT_DOUBLES[n] if n < 5 else C.c_double * n)(*map(float, xs))
 
 
 def _u64(xs: Sequence[int]):
