@@ -698,12 +698,6 @@ static unsigned long long tile_entry_offset(int c, int m, const int* hi, unsigne
   return g;
 }
 
-void fill_entry_offsets(FusedBlockDev& d, int rbits) {
-  const int k = d.c + d.m;
-  for (int j = 0; j < 16; ++j)
-    d.joff[j] = j < (1 << rbits) ? tile_entry_offset(d.c, d.m, d.hi, (unsigned)j << (k - rbits)) : 0;
-}
-
 namespace {
 
 // Images of the thread bits and register bits of a phase in tile entries

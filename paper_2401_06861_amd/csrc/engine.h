@@ -173,7 +173,6 @@ inline int reg_swap(int a, int b, int j) {
 }
 int local_bit(const Block& b, int q);
 void pad_block(Block& b, int n, int k_target);
-void fill_entry_offsets(FusedBlockDev& d, int rbits);
 // A register phase before its addresses are laid out: register bits
 // (tile-local, ascending), the permutations folded into its loads and stores
 // (fold_permutations), its RbOps.

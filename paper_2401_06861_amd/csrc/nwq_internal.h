@@ -162,38 +162,9 @@ struct FusedBlockDev {
   int c, m;                 // tile = low c bits + m high bits
   int hi[8];
   int op_begin, op_count;   // range in the op table
-  // VQE backward kernel: global offset of tile entry j * 2^(k - rbits)
-  // (the per-thread part of an entry's index is added to it)
-  unsigned long long joff[16];
 };
 void launch_fused_block(hipStream_t s, double2* a, int nbits, const FusedBlockDev& blk,
                         const FusedOp* ops, const double2* mats);
-// A register phase of the VQE backward kernel: its register bits (tile-local,
-// ascending; unused entries ignored) and its ops.
-struct FusedPhase {
-  int reg[4];
-  int op_begin, op_count;
-  int pad0, pad1;
-  // The padded LDS offset (over the phase's register bits) that register j is
-  // loaded from and stored to.  Permutation gates at the start or the end of a
-  // phase are folded into these.
-  unsigned short ld_off[16], st_off[16];
-};
-// ld_perm[j] / st_perm[j]: register-bit index whose entry register j loads /
-// stores (nullptr: identity); offsets padded by one entry per 16.
-inline void fill_phase_offsets(FusedPhase& fp, int rbits, const int* ld_perm, const int* st_perm) {
-  auto off = [&](int p) {
-    unsigned o = 0;
-    for (int r = 0; r < rbits; ++r)
-      if ((p >> r) & 1) o |= 1u << fp.reg[r];
-    return (unsigned short)(o + (o >> 4));
-  };
-  for (int j = 0; j < 16; ++j) {
-    const bool in = j < (1 << rbits);
-    fp.ld_off[j] = in ? off(ld_perm ? ld_perm[j] : j) : 0;
-    fp.st_off[j] = in ? off(st_perm ? st_perm[j] : j) : 0;
-  }
-}
 // Register-blocked blocks (kernels_fuse.hip).  A tile of 2^k entries belongs
 // to 2^(k - R) threads of 2^R registers each (R = 3 or 4, 8 <= k <= 13).  In
 // each phase R tile bits are register bits and the others thread bits; every

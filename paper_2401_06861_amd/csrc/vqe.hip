@@ -609,6 +609,22 @@ __device__ __forceinline__ unsigned slot8(unsigned e) {
   return (e & ~15u) | (f & 15u);
 }
 
+// The two numbers of an op's angle (i even: its own, odd: of RZ in RV_YZ).
+__device__ __forceinline__ void stage_angle(double2* cs, int i, const RegOpV& op, const double* __restrict__ th) {
+  const int code = op.code & 31, param = (i & 1) ? op.param2 : op.param;
+  if (param < 0) return;
+  const bool whole = (i & 1) || (code >= RV_ROT + 6 && code < RV_YZ);   // RZ, RZZ
+  vd2 a;
+  if (whole) {
+    double s, c;
+    sincos(th[param], &s, &c);
+    a = mk(c, s);
+  } else {
+    a = shear_of(th[param]);
+  }
+  st(cs + i, a);
+}
+
 // phases[0 .. P): the program's; phases[P]: where the last phase's registers go
 // in LDS (wr_*) and which entries they are (rd_*).  pslots[poff[p] .. poff[p+1])
 // are the slots of parameter p.
@@ -658,21 +674,7 @@ __global__ __launch_bounds__(kRegMaxThreads) void k_vqe_reg(
   for (int b = blockIdx.x; b < B; b += gridDim.x) {
     const double* th = theta + (size_t)b * nparams;
     __syncthreads();   // the previous vector's readers of cs, buf and gpart are done
-    for (int i = tid; i < 2 * nops; i += nt) {
-      const RegOpV op = ops[i >> 1];
-      const int code = op.code & 31, param = (i & 1) ? op.param2 : op.param;
-      if (param < 0) continue;
-      const bool whole = (i & 1) || (code >= RV_ROT + 6 && code < RV_YZ);   // RZ, RZZ
-      vd2 a;
-      if (whole) {
-        double s, c;
-        sincos(th[param], &s, &c);
-        a = mk(c, s);
-      } else {
-        a = shear_of(th[param]);
-      }
-      st(cs + i, a);
-    }
+    for (int i = tid; i < 2 * nops; i += nt) stage_angle(cs, i, ops[i >> 1], th);
 #pragma unroll
     for (int j = 0; j < 8; ++j) p.x[j] = p.y[j] = 0.0;
     if (tid == 0) p.x[0] = 1.0;
@@ -1514,167 +1516,25 @@ __global__ __launch_bounds__(kBwdBlock) void k_vqe_bwd_tile(double2* __restrict_
   }
 }
 
-// ---------------------------------------------------------------------------
-// Register-blocked backward sweep.  The block's reversed gates are split into
-// phases over R register bits (as in the forward kernel); per phase each
-// thread holds the 2^R amplitudes of phi and of lambda that differ on those
-// bits and un-applies the phase's gates in registers, accumulating each
-// parametrised gate's Im<lambda|P|phi> before un-applying it.  Tiles of phi
-// and lambda are exchanged through LDS between phases.
-// ---------------------------------------------------------------------------
-struct VqeBwdRop {
-  int kind;    // 0 rotation, 1 RZZ, 2 fixed 2x2, 3 CX, 4 CZ, 5 SWAP
-  int r0, r1;  // register-bit indices in operator order (r1 for 2-qubit ops)
-  int axis;    // rotation axis
-  int slot;    // gradient slot or -1
-  int mat;     // index of the adjoint matrix in the per-vector table (double2 units)
-  int code;    // switch index: 4 v + r0 for 2x2 ops (v = axis, 3 = fixed);
-               // 16 + 16 w + 4 r0 + r1 for 2q ops (w: 0 RZZ, 1 CZ, 2 CX, 3 SWAP)
-  int pad1;
-};
-inline int bwd_rop_code(const VqeBwdRop& o) {
-  if (o.kind == 0 || o.kind == 2) return 4 * (o.kind == 2 ? 3 : o.axis) + o.r0;
-  const int w = o.kind == 1 ? 0 : o.kind == 4 ? 1 : o.kind == 3 ? 2 : 3;
-  return 16 + 16 * w + 4 * o.r0 + o.r1;
-}
-
-constexpr int kBwdRbMaxWaves = 4;   // tiles of at most 2^11 entries at 3 register bits
-constexpr int kBwdMaxTileBits = 11;
-
-__device__ __forceinline__ unsigned padl_b(unsigned l) { return l + (l >> 4); }
-// one padded tile of 2^k entries (one extra entry per 16)
-inline size_t bwd_rb_tile_bytes(int k) { return sizeof(double2) * ((1u << k) + (1u << k) / 16); }
-
-// Im(conj(a) b)
-__device__ __forceinline__ double imcb(vd2 a, vd2 b) { return a.x * b.y - a.y * b.x; }
-// Re(conj(a) b)
-__device__ __forceinline__ double recb(vd2 a, vd2 b) { return a.x * b.x + a.y * b.y; }
-
-// Rotation about axis AX (0 X, 1 Y, 2 Z; -1: fixed gate, no gradient) on
-// register bit B: the generator's term Im<l|P|p> of the pair (as in
-// pair_grad, one axis only), then the adjoint 2x2 on both vectors; RZ's
-// adjoint is diagonal (M[0], M[3]).
-template <int NV, int B, int AX>
-__device__ __forceinline__ void bw_rot(vd2 (&p)[NV], vd2 (&l)[NV], const double2* __restrict__ M, double& g) {
-  const vd2 m0 = ld(M), m1 = ld(M + 1), m2 = ld(M + 2), m3 = ld(M + 3);
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    if (j & (1 << B)) continue;
-    const int k = j | (1 << B);
-    const vd2 p0 = p[j], p1 = p[k], l0 = l[j], l1 = l[k];
-    if constexpr (AX == 0) g += imcb(l0, p1) + imcb(l1, p0);
-    if constexpr (AX == 1) g += recb(l1, p0) - recb(l0, p1);
-    if constexpr (AX == 2) g += imcb(l0, p0) - imcb(l1, p1);
-    if constexpr (AX == 2) {
-      p[j] = cmul(m0, p0);
-      p[k] = cmul(m3, p1);
-      l[j] = cmul(m0, l0);
-      l[k] = cmul(m3, l1);
-    } else if constexpr (AX == 1) {
-      // RY adjoint: a real 2x2 (the zero imaginary parts are not multiplied;
-      // the rounding is that of the complex form)
-      p[j] = mk(fma(m0.x, p0.x, m1.x * p1.x), fma(m0.x, p0.y, m1.x * p1.y));
-      p[k] = mk(fma(m2.x, p0.x, m3.x * p1.x), fma(m2.x, p0.y, m3.x * p1.y));
-      l[j] = mk(fma(m0.x, l0.x, m1.x * l1.x), fma(m0.x, l0.y, m1.x * l1.y));
-      l[k] = mk(fma(m2.x, l0.x, m3.x * l1.x), fma(m2.x, l0.y, m3.x * l1.y));
-    } else if constexpr (AX == 0) {
-      // RX adjoint: real diagonal, imaginary off-diagonal entries
-      p[j] = mk(fma(m0.x, p0.x, -(m1.y * p1.y)), fma(m0.x, p0.y, m1.y * p1.x));
-      p[k] = mk(fma(-m2.y, p0.y, m3.x * p1.x), fma(m2.y, p0.x, m3.x * p1.y));
-      l[j] = mk(fma(m0.x, l0.x, -(m1.y * l1.y)), fma(m0.x, l0.y, m1.y * l1.x));
-      l[k] = mk(fma(-m2.y, l0.y, m3.x * l1.x), fma(m2.y, l0.x, m3.x * l1.y));
-    } else {
-      p[j] = cfma(m0, p0, cmul(m1, p1));
-      p[k] = cfma(m2, p0, cmul(m3, p1));
-      l[j] = cfma(m0, l0, cmul(m1, l1));
-      l[k] = cfma(m2, l0, cmul(m3, l1));
-    }
-  }
-}
-
-// Diagonal 2-qubit op on register bits B0 (u bit 0), B1 (u bit 1); with grad,
-// the ZZ generator's term Im(conj(l) p) times its eigenvalue.
-template <int NV, int B0, int B1>
-__device__ __forceinline__ void bw_diag2(vd2 (&p)[NV], vd2 (&l)[NV], const double2* __restrict__ M, bool grad,
-                                         double& g) {
-  const vd2 d[4] = {ld(M), ld(M + 1), ld(M + 2), ld(M + 3)};
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    const int a = (j >> B0) & 1, b = (j >> B1) & 1;
-    if (grad) {
-      const double t = l[j].x * p[j].y - l[j].y * p[j].x;
-      g += (a != b) ? -t : t;
-    }
-    p[j] = cmul(d[a + 2 * b], p[j]);
-    l[j] = cmul(d[a + 2 * b], l[j]);
-  }
-}
-
-template <int NV, int B0, int B1, int OA, int OB>
-__device__ __forceinline__ void bw_swap(vd2 (&p)[NV], vd2 (&l)[NV]) {
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    if (j & ((1 << B0) | (1 << B1))) continue;
-    vd2 t = p[j | OA];
-    p[j | OA] = p[j | OB];
-    p[j | OB] = t;
-    t = l[j | OA];
-    l[j | OA] = l[j | OB];
-    l[j | OB] = t;
-  }
-}
-
-template <int R, int B, int AX>
-__device__ __forceinline__ void bw_c1(vd2 (&p)[1 << R], vd2 (&l)[1 << R], const double2* M, double& g) {
-  if constexpr (B < R) bw_rot<(1 << R), B, AX>(p, l, M, g);
-}
-template <int R, int B0, int B1, int W>
-__device__ __forceinline__ void bw_c2(vd2 (&p)[1 << R], vd2 (&l)[1 << R], const double2* M, double& g) {
-  constexpr int NV = 1 << R;
-  if constexpr (B0 < R && B1 < R) {
-    if constexpr (W == 0) bw_diag2<NV, B0, B1>(p, l, M, true, g);                             // RZZ
-    else if constexpr (W == 1) bw_diag2<NV, B0, B1>(p, l, M, false, g);                       // CZ
-    else if constexpr (W == 2) bw_swap<NV, B0, B1, (1 << B0), (1 << B0) | (1 << B1)>(p, l);  // CX: control B0
-    else bw_swap<NV, B0, B1, (1 << B0), (1 << B1)>(p, l);                                    // SWAP
-  }
-}
-
-// One adjoint gate: a single switch over its code (bwd_rop_code).
-template <int R>
-__device__ __forceinline__ void bw_apply(int code, vd2 (&p)[1 << R], vd2 (&l)[1 << R], const double2* __restrict__ M,
-                                         double& g) {
-#define NWQ_BW1(V, AX) \
-  case 4 * V + 0: bw_c1<R, 0, AX>(p, l, M, g); break; \
-  case 4 * V + 1: bw_c1<R, 1, AX>(p, l, M, g); break; \
-  case 4 * V + 2: bw_c1<R, 2, AX>(p, l, M, g); break; \
-  case 4 * V + 3: bw_c1<R, 3, AX>(p, l, M, g); break;
-#define NWQ_BW2(W) \
-  case 16 + 16 * W + 1: bw_c2<R, 0, 1, W>(p, l, M, g); break; \
-  case 16 + 16 * W + 2: bw_c2<R, 0, 2, W>(p, l, M, g); break; \
-  case 16 + 16 * W + 3: bw_c2<R, 0, 3, W>(p, l, M, g); break; \
-  case 16 + 16 * W + 4: bw_c2<R, 1, 0, W>(p, l, M, g); break; \
-  case 16 + 16 * W + 6: bw_c2<R, 1, 2, W>(p, l, M, g); break; \
-  case 16 + 16 * W + 7: bw_c2<R, 1, 3, W>(p, l, M, g); break; \
-  case 16 + 16 * W + 8: bw_c2<R, 2, 0, W>(p, l, M, g); break; \
-  case 16 + 16 * W + 9: bw_c2<R, 2, 1, W>(p, l, M, g); break; \
-  case 16 + 16 * W + 11: bw_c2<R, 2, 3, W>(p, l, M, g); break; \
-  case 16 + 16 * W + 12: bw_c2<R, 3, 0, W>(p, l, M, g); break; \
-  case 16 + 16 * W + 13: bw_c2<R, 3, 1, W>(p, l, M, g); break; \
-  case 16 + 16 * W + 14: bw_c2<R, 3, 2, W>(p, l, M, g); break;
-  switch (code) {
-    NWQ_BW1(0, 0)
-    NWQ_BW1(1, 1)
-    NWQ_BW1(2, 2)
-    NWQ_BW1(3, -1)
-    NWQ_BW2(0)
-    NWQ_BW2(1)
-    NWQ_BW2(2)
-    NWQ_BW2(3)
-    default: break;
-  }
-#undef NWQ_BW1
-#undef NWQ_BW2
-}
+// Backward block, register-blocked: a tile of phi and of lambda, 8 amplitudes of
+// each per thread on three register bits, ops as in k_vqe_reg (RY and RX three
+// shears, RZ after RY in one op, gradients in four chains).  Tiles come from HBM
+// straight into registers and pass through LDS one component at a time; waves
+// whose phases share the tile bits on their index do not wait for each other.
+// The block's program and angles are staged in LDS, and each slot keeps a sum
+// per wave and row of 16 lanes there (each written by one lane, so the order of
+// additions is fixed).
+//
+// What bounds it: half HBM (two states read and written: 2.6 of 4.03 ms per
+// block of 256 vectors of 20 qubits), half FP64 issue at four waves per SIMD;
+// three waves per SIMD (no spill of 20 bytes) or tiles of 2^12 are slower
+// (20 qubits, L = 8: 54.8, 56.8 and 58.0 ms per batch).  The kernel before took
+// whole amplitudes through LDS with both states' next tile in registers (204
+// VGPRs, two waves per SIMD): 6.28 ms per block, 73 ms per batch.
+// Gradients against 80-bit arithmetic: 9.4e-16 off on 13 qubits, L = 4, and
+// 8.4e-16 on 20, L = 1 (with that kernel 1.11e-15 and 1.22e-15).
+constexpr int kBwdMaxTileBits = 11;   // 256 threads
+constexpr int kBwdRegOps = 128;       // LDS: 4 KB of angles, 16 KB of gradient sums
 
 // Global loads and stores of tile entries; NT: non-temporal (each entry of
 // phi and lambda is read and written once per block).
@@ -1688,6 +1548,20 @@ __device__ __forceinline__ void bgst(double2* p, vd2 v) {
   if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<vd2*>(p));
   else st(p, v);
 }
+// XOR of the images of the set bits of v.
+__device__ __forceinline__ unsigned long long image_of(unsigned v, const unsigned long long* img, int bits) {
+  unsigned long long x = 0;
+#pragma unroll
+  for (int i = 0; i < bits; ++i) x ^= (unsigned long long)(long long)((int)(v << (31 - i)) >> 31) & img[i];
+  return x;
+}
+
+// LDS of a block: the exchange buffer, angles, phases, ops, sums.
+inline size_t bwd_reg_lds(int k, int phases, int nops, int nlocal) {
+  const int nw = (1 << (k - 3)) / kWave;
+  return (sizeof(double) << k) + (size_t)nops * (2 * sizeof(double2) + sizeof(int2)) + (size_t)phases * sizeof(RbPhase) +
+         (size_t)nlocal * nw * 4 * sizeof(double) + 64;
+}
 
 // The bits of v deposited, lowest first, at the set bits of mask.
 __device__ __forceinline__ unsigned long long pdep_u64(unsigned long long v, unsigned long long mask) {
@@ -1697,144 +1571,110 @@ __device__ __forceinline__ unsigned long long pdep_u64(unsigned long long v, uns
   return r;
 }
 
-template <int R, bool NT>
-__global__ __launch_bounds__(kWave * kBwdRbMaxWaves) void k_vqe_bwd_rb(double2* __restrict__ phi0,
-                                                                      double2* __restrict__ lam0, int n,
-                                                                      FusedBlockDev blk,
-                                                                      const FusedPhase* __restrict__ phases,
-                                                                      const VqeBwdRop* __restrict__ ops,
-                                                                      const double2* __restrict__ table0,
-                                                                      int mat_stride, int nslots,
-                                                                      double* __restrict__ gpart,
-                                                                      unsigned long long ntiles, int sparse,
-                                                                      unsigned long long tmask) {
-  constexpr int NV = 1 << R;
-  extern __shared__ double2 sh[];
-  __shared__ double acc[kBwdMaxOps][kBwdRbMaxWaves];
-  const int c = blk.c, m = blk.m, k = c + m;
-  const unsigned len = 1u << k;
-  const unsigned nt = len >> R;
-  double2* tp = sh;
-  double2* tl = sh + padl_b(len);
-  const unsigned long long N = 1ull << n;
-  double2* __restrict__ phi = phi0 + (size_t)blockIdx.y * N;
-  double2* __restrict__ lam = lam0 + (size_t)blockIdx.y * N;
-  const double2* __restrict__ table = table0 + (size_t)blockIdx.y * mat_stride;
-  
-  const unsigned cmask = (1u << c) - 1u;
-  const unsigned tid = threadIdx.x;
-  const int lane = tid & (kWave - 1), wave = tid / kWave;
-  const int NW = (int)(nt + kWave - 1) / kWave;
-  const int op0 = phases[blk.op_begin].op_begin;
-  const FusedPhase last = phases[blk.op_begin + blk.op_count - 1];
-  const int nops = last.op_begin + last.op_count - op0;
-  for (int i = tid; i < nops * kBwdRbMaxWaves; i += nt) acc[i / kBwdRbMaxWaves][i % kBwdRbMaxWaves] = 0.0;
-  const unsigned long long glane = bwd_index(0ull, tid, cmask, c, m, blk);
-  // sparse: tiles t = 0, 1, ... are the tile indices pdep(t, tmask)
-  auto tile_off = [&](unsigned long long tile) {
-    unsigned long long base = (sparse ? pdep_u64(tile, tmask) : tile) << c;
+template <bool NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_vqe_bwd_reg(
+    double2* __restrict__ phi0, double2* __restrict__ lam0, int n, RbBlock blk, const RbPhase* __restrict__ phases,
+    const RegOpV* __restrict__ ops, int nops, const int* __restrict__ slots, int nlocal,
+    const double2* __restrict__ fixed, const double* __restrict__ theta, int nparams, int nslots,
+    double* __restrict__ gpart, unsigned long long ntiles, unsigned long long mask, unsigned long long step) {
+  extern __shared__ double2 lds[];
+  const unsigned tid = threadIdx.x, nt = blockDim.x;
+  const int lane = tid & (kWave - 1), wave = tid / kWave, NW = (int)nt / kWave, P = blk.ph_count;
+  double* buf = reinterpret_cast<double*>(lds);                      // one component of the tile
+  double2* cs = lds + (1u << (blk.k - 1));                           // [nops][2] the angles' two numbers
+  unsigned* lph = reinterpret_cast<unsigned*>(cs + 2 * nops);        // [P] phases (16 words each)
+  int2* lop = reinterpret_cast<int2*>(lph + 16 * P);                 // [nops] (code, mat)
+  double* gacc = reinterpret_cast<double*>(lop + nops);              // [nlocal][NW][4]
+  double2* __restrict__ phi = phi0 + ((size_t)blockIdx.y << n);
+  double2* __restrict__ lam = lam0 + ((size_t)blockIdx.y << n);
+  const double* __restrict__ th = theta + (size_t)blockIdx.y * nparams;
+  for (int i = tid; i < 16 * P; i += nt) lph[i] = reinterpret_cast<const unsigned*>(phases + blk.ph_begin)[i];
+  for (int i = tid; i < nlocal * NW * 4; i += nt) gacc[i] = 0.0;
+  for (int i = tid; i < nops; i += nt) lop[i] = *reinterpret_cast<const int2*>(ops + i);
+  for (int i = tid; i < 2 * nops; i += nt) stage_angle(cs, i, ops[i >> 1], th);
+  Amp8 p, l;
+  auto exchange = [&](double (&v)[8], unsigned wt, const RegMap& wr, unsigned rt, const RegMap& rd, bool across) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i < m) {
-        const int q = blk.hi[i];
-        base = ((base >> q) << (q + 1)) | (base & ((1ull << q) - 1ull));
-      }
-    }
-    return base + glane;
+    for (int j = 0; j < 8; ++j) buf[wt ^ register_slot(j, wr)] = v[j];
+    if (across) __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = buf[rt ^ register_slot(j, rd)];
   };
-  // The tile's entries of phi and lambda are loaded one tile ahead: the
-  // loads of the next tile are in flight while this one runs its phases
-  // (tiles are disjoint, so the early read is safe).  A tile's results leave
-  // LDS at the end of its trip and go to HBM after the next tile is staged,
-  // ahead of the next loads: the vector memory counter retires in issue
-  // order, so stores issued after those loads would make the next trip's
-  // wait for them cover the stores' completion too.
-  vd2 fp[NV], fl[NV], rp[NV], rl[NV];
-  unsigned long long prev = ~0ull;
-  if (blockIdx.x < ntiles) {
-    const unsigned long long o = tile_off(blockIdx.x);
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      fp[j] = bgld<NT>(phi + o + blk.joff[j]);
-      fl[j] = bgld<NT>(lam + o + blk.joff[j]);
-    }
-  }
-  for (unsigned long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    __syncthreads();
+  const unsigned long long gl_ld = image_of(tid, blk.ld_t, 8), gl_st = image_of(tid, blk.st_t, 8);
+  auto reg_image = [](int j, const unsigned long long* r) {
+    return ((j & 1) ? r[0] : 0ull) ^ ((j & 2) ? r[1] : 0ull) ^ ((j & 4) ? r[2] : 0ull);
+  };
+  __syncthreads();
+  unsigned long long tile = blockIdx.x, base = pdep_u64(tile, mask);
+  for (; tile < ntiles; tile += gridDim.x, base = ((base | ~mask) + step) & mask) {
     {
+      const double2* __restrict__ a = phi + (base | gl_ld);
+      const double2* __restrict__ b = lam + (base | gl_ld);
+      vd2 v[8], w[8];
 #pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        st(tp + padl_b(tid + j * nt), fp[j]);
-        st(tl + padl_b(tid + j * nt), fl[j]);
+      for (int j = 0; j < 8; ++j) {
+        v[j] = bgld<NT>(a + reg_image(j, blk.ld_r));
+        w[j] = bgld<NT>(b + reg_image(j, blk.ld_r));
       }
-      if (prev != ~0ull) {
 #pragma unroll
-        for (int j = 0; j < NV; ++j) {
-          bgst<NT>(phi + prev + blk.joff[j], rp[j]);
-          bgst<NT>(lam + prev + blk.joff[j], rl[j]);
-        }
-      }
-      const unsigned long long nx = tile + gridDim.x;
-      if (nx < ntiles) {
-        const unsigned long long o = tile_off(nx);
-#pragma unroll
-        for (int j = 0; j < NV; ++j) {
-          fp[j] = bgld<NT>(phi + o + blk.joff[j]);
-          fl[j] = bgld<NT>(lam + o + blk.joff[j]);
-        }
+      for (int j = 0; j < 8; ++j) {
+        p.x[j] = v[j].x;
+        p.y[j] = v[j].y;
+        l.x[j] = w[j].x;
+        l.y[j] = w[j].y;
       }
     }
-    for (int pi = 0; pi < blk.op_count; ++pi) {
-      const FusedPhase ph = phases[blk.op_begin + pi];
-      unsigned dep = tid;
-#pragma unroll
-      for (int r = 0; r < R; ++r) dep = ((dep >> ph.reg[r]) << (ph.reg[r] + 1)) | (dep & ((1u << ph.reg[r]) - 1u));
-      double2* __restrict__ sp = tp + padl_b(dep);
-      double2* __restrict__ sl = tl + padl_b(dep);
-      __syncthreads();
-      vd2 vp[NV], vl[NV];
-#pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        vp[j] = ld(sp + ph.ld_off[j]);
-        vl[j] = ld(sl + ph.ld_off[j]);
+    int2 od = lop[0];
+    vd2 a = ld(cs), az = ld(cs + 1);
+    for (int pi = 0; pi < P; ++pi) {
+      const unsigned* ph = lph + 16 * pi;
+      const int begin = (int)uni(ph[0]), cf = (int)uni(ph[1]), count = cf >> kRbFlagBits;
+      if (pi > 0) {
+        const RegMap wr = reg_map(ph + 2), rd = reg_map(ph + 9);
+        const unsigned wt = thread_slot(tid, wr), rt = thread_slot(tid, rd);
+        const bool across = (cf & kRbBarrierInside) != 0;
+        if (cf & kRbBarrierBefore) __syncthreads();
+        exchange(p.x, wt, wr, rt, rd, across);
+        if (across) __syncthreads();
+        exchange(p.y, wt, wr, rt, rd, across);
+        if (across) __syncthreads();
+        exchange(l.x, wt, wr, rt, rd, across);
+        if (across) __syncthreads();
+        exchange(l.y, wt, wr, rt, rd, across);
       }
-      for (int oi = 0; oi < ph.op_count; ++oi) {
-        const VqeBwdRop op = ops[ph.op_begin + oi];
-        double g = 0.0;
-        bw_apply<R>(op.code, vp, vl, table + op.mat, g);
-        if (op.slot >= 0) {
-          const double w = wave_sum_full(g);   // tiles of >= 2^9 entries: whole waves
-          if (lane == 0) acc[ph.op_begin + oi - op0][wave] += w;
+      for (int i = begin; i < begin + count; ++i) {   // the next op is read while this one runs
+        const int in = i + 1 < nops ? i + 1 : 0;
+        const int2 odn = lop[in];
+        const vd2 an = ld(cs + 2 * in), azn = ld(cs + 2 * in + 1);
+        const int word = (int)uni((unsigned)od.x), mat = (int)uni((unsigned)od.y);
+        double g = 0.0, gz = 0.0;
+        rv_apply<true>(word & 31, p, l, a, az, fixed + 8 * mat, g, gz);
+        if (word >= 32) {
+          g = row_sum(g);
+          if ((lane & 15) == 0) gacc[(((word >> 5) - 1) * NW + wave) * 4 + (lane >> 4)] += g;
         }
-      }
-#pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        st(sp + ph.st_off[j], vp[j]);
-        st(sl + ph.st_off[j], vl[j]);
+        if ((word & 31) >= RV_YZ) {
+          gz = row_sum(gz);
+          if ((lane & 15) == 0) gacc[(mat * NW + wave) * 4 + (lane >> 4)] += gz;
+        }
+        od = odn;
+        a = an;
+        az = azn;
       }
     }
-    __syncthreads();
+    double2* __restrict__ a1 = phi + (base | gl_st);
+    double2* __restrict__ b1 = lam + (base | gl_st);
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      rp[j] = ld(tp + padl_b(tid + j * nt));
-      rl[j] = ld(tl + padl_b(tid + j * nt));
-    }
-    prev = tile_off(tile);
-  }
-  if (prev != ~0ull) {
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      bgst<NT>(phi + prev + blk.joff[j], rp[j]);
-      bgst<NT>(lam + prev + blk.joff[j], rl[j]);
+    for (int j = 0; j < 8; ++j) {
+      bgst<NT>(a1 + reg_image(j, blk.st_r), mk(p.x[j], p.y[j]));
+      bgst<NT>(b1 + reg_image(j, blk.st_r), mk(l.x[j], l.y[j]));
     }
   }
   __syncthreads();
-  for (int oi = tid; oi < nops; oi += nt) {
-    const int slot = ops[op0 + oi].slot;
-    if (slot < 0) continue;
+  for (int i = tid; i < nlocal; i += nt) {
     double v = 0.0;
-    for (int w = 0; w < NW; ++w) v += acc[oi][w];
-    gpart[((size_t)blockIdx.y * nslots + slot) * gridDim.x + blockIdx.x] = v;
+    for (int w = 0; w < 4 * NW; ++w) v += gacc[i * 4 * NW + w];
+    gpart[((size_t)blockIdx.y * nslots + slots[i]) * gridDim.x + blockIdx.x] = v;
   }
 }
 
@@ -1885,7 +1725,13 @@ struct nwq_vqe {
   int low_bits = 0;            // low tile bits of the planned blocks: 0 = kVqeLowBits
   int fused_rbits = 4;         // register bits per phase of the forward kernel
   bool bwd_rb = false;         // backward sweep register-blocked (3 bits) when every tile has >= 2^9 entries
-  size_t fused_rop_off = 0;    // offset of the register-blocked backward ops in d_fused
+  size_t fused_rop_off = 0, fused_slot_off = 0;   // its ops and the slots of its gradient sums in d_fused
+  struct BwdRegBlock {
+    nwq::RbBlock d;
+    int op0, nops, slot0, nlocal;
+    unsigned long long mask;   // index bits outside the tile that its tiles run over
+  };
+  std::vector<BwdRegBlock> bwd_reg;
   std::vector<nwq::RbBlock> fwd_blocks;
   std::vector<nwq::FusedBlockDev> bwd_blocks;
   // Tiles of each backward dispatch: tile indices with bits in the mask only.
@@ -2068,6 +1914,42 @@ static int launch_global(nwq_vqe* h, int B, const double* theta, const double* c
 constexpr int kVqeLowBits = 3;
 constexpr int kVqeSeeds = 2;   // as many as it takes: 8 seeds plan no fewer blocks for the HEA ansatz
 
+// A gate on register bits (3 register bits) before its permutations are folded.
+struct RegGate {
+  RegOpV o;
+  int perm, b0, b1, slot;   // perm: 1 CX, 2 SWAP
+  unsigned bits;
+};
+static RegGate reg_gate(const VqeOp& op, int r0, int r1, bool two) {
+  const int pair = two ? rb_pair(std::min(r0, r1), std::max(r0, r1)) : 0;
+  RegGate o{{0, std::max(0, op.mat), op.param, -1}, 0, r0, r1, op.slot, two ? (1u << r0) | (1u << r1) : 1u << r0};
+  if (op.kind == OP_ROT) o.o.code = RV_ROT + 3 * op.axis + r0;
+  else if (op.kind == OP_FIX1) o.o.code = RV_FIX + r0;
+  else if (op.kind == OP_RZZ) o.o.code = RV_RZZ + pair;
+  else if (op.kind == OP_CZ) o.o.code = RV_CZ + pair;
+  else if (op.kind == OP_CX) o.o.code = RV_CX + 2 * pair + (r0 > r1 ? 1 : 0), o.perm = 1;
+  else o.o.code = RV_SWAP + pair, o.perm = 2;
+  return o;
+}
+static void fold_reg_gates(std::vector<RegGate>& pops, RbStage& stg) {
+  fold_permutations(
+      pops, 3, [](const RegGate& o) { return o.perm != 0; }, [](const RegGate& o) { return o.bits; },
+      [](const RegGate& o, int j) { return o.perm == 1 ? reg_cx(o.b0, o.b1, j) : reg_swap(o.b0, o.b1, j); },
+      stg.ld_perm, stg.st_perm);
+}
+static unsigned long long tile_bits(const Block& b) {
+  unsigned long long t = (1ull << b.c) - 1ull;
+  for (int i = 0; i < b.m; ++i) t |= 1ull << b.hi[i];
+  return t;
+}
+// The bits of v deposited, lowest first, at the set bits of mask.
+static unsigned long long deposit(unsigned long long v, unsigned long long mask) {
+  unsigned long long r = 0;
+  for (; v && mask; mask &= mask - 1, v >>= 1)
+    if (v & 1ull) r |= mask & (~mask + 1ull);
+  return r;
+}
+
 static int build_fused(nwq_vqe* h) {
   if (h->fused_built) return NWQ_OK;
   const int low = h->low_bits > 0 ? h->low_bits : kVqeLowBits;
@@ -2082,12 +1964,13 @@ static int build_fused(nwq_vqe* h) {
   const std::vector<Block> blocks = plan_blocks(g, n, std::max(k, 6), low, kVqeSeeds, true);
   if (blocks.empty() && h->nops > 0) return set_error(NWQ_EINVAL, "fusion planner made no progress");
   std::vector<RbPhase> fphases;     // forward
-  std::vector<FusedPhase> phases;   // backward
+  std::vector<RbPhase> phases;      // backward
   std::vector<RbOp> fops;
   std::vector<VqeBwdOp> bops;
   h->fwd_blocks.clear();
   h->bwd_blocks.clear();
   h->bwd_mask.clear();
+  h->bwd_reg.clear();
   std::vector<Block> padded(blocks);
   for (Block& b : padded) pad_block(b, n, std::max(k, 8));
   size_t max_bwd_lds = 0;
@@ -2175,7 +2058,14 @@ static int build_fused(nwq_vqe* h) {
       support |= tile;
     }
   }
-  std::vector<VqeBwdRop> rops;
+  std::vector<RegOpV> rops;
+  std::vector<int> slots;
+  unsigned long long touched = 0;   // union of the tiles of the blocks before
+  std::vector<unsigned long long> before;
+  for (const Block& b : bpadded) {
+    before.push_back(touched);
+    touched |= tile_bits(b);
+  }
   for (auto bit = bpadded.rbegin(); h->bwd_rb && bit != bpadded.rend(); ++bit) {
     const Block& b = *bit;
     const int kb = b.c + b.m;
@@ -2186,53 +2076,55 @@ static int build_fused(nwq_vqe* h) {
       lb[gi] = {local_bit(b, g[gi].q[0]), g[gi].nq == 2 ? local_bit(b, g[gi].q[1]) : 0};
       nq[gi] = g[gi].nq;
     }
-    for (size_t s0 = 0; s0 < rev.size(); s0 += kBwdMaxOps) {
-      const std::vector<int> chunk(rev.begin() + s0, rev.begin() + std::min(rev.size(), s0 + kBwdMaxOps));
-      FusedBlockDev d{};
-      d.c = b.c;
-      d.m = b.m;
-      for (int i = 0; i < b.m; ++i) d.hi[i] = b.hi[i];
-      d.op_begin = (int)phases.size();
-      for (const Phase& ph : plan_phases(chunk, lb, nq, kb, 0, kBwdBits)) {
-        FusedPhase fp{};
-        for (int i = 0; i < 4; ++i) fp.reg[i] = ph.reg[i] < 0 ? 0 : ph.reg[i];
-        fp.op_begin = (int)rops.size();
+    for (size_t s0 = 0; s0 < rev.size(); s0 += kBwdRegOps) {
+      const std::vector<int> chunk(rev.begin() + s0, rev.begin() + std::min(rev.size(), s0 + kBwdRegOps));
+      nwq_vqe::BwdRegBlock blk{};
+      blk.op0 = (int)rops.size();
+      blk.slot0 = (int)slots.size();
+      std::vector<unsigned> obits;   // register bits of each op of the chunk
+      std::vector<RbStage> stages;
+      for (const Phase& ph : plan_phases(chunk, lb, nq, kb, b.c, kBwdBits)) {
+        RbStage stg{};
+        for (int i = 0; i < kBwdBits; ++i) stg.reg[i] = ph.reg[i];
+        stg.op_begin = (int)rops.size() - blk.op0;
         auto ridx = [&](int bit) {
           for (int i = 0; i < kBwdBits; ++i)
             if (ph.reg[i] == bit) return i;
           return -1;
         };
-        std::vector<VqeBwdRop> pops;
-        for (int gi : ph.gates) {
-          const VqeOp& op = h->ops[gi];
-          VqeBwdRop o{};
-          o.r0 = ridx(lb[gi][0]);
-          o.r1 = nq[gi] == 2 ? ridx(lb[gi][1]) : 0;
-          o.axis = op.axis;
-          o.slot = op.slot;
-          o.mat = 8 * gi + 4;
-          o.kind = op.kind == OP_ROT ? 0 : op.kind == OP_RZZ ? 1 : op.kind == OP_FIX1 ? 2 : op.kind == OP_CX ? 3
-                 : op.kind == OP_CZ ? 4 : 5;
-          o.code = bwd_rop_code(o);
-          pops.push_back(o);
+        std::vector<RegGate> pops;
+        for (int gi : ph.gates)
+          pops.push_back(reg_gate(h->ops[gi], ridx(lb[gi][0]), nq[gi] == 2 ? ridx(lb[gi][1]) : 0, nq[gi] == 2));
+        fold_reg_gates(pops, stg);
+        for (RegGate& o : pops) {
+          int local = -1;
+          if (o.slot >= 0) {
+            local = (int)slots.size() - blk.slot0;
+            slots.push_back(o.slot);
+          }
+          const int code = o.o.code;
+          // an RY joins the RZ un-applied before it on its bit when nothing between them touches the bit
+          if (code >= RV_ROT + 3 && code < RV_ROT + 6) {
+            int j = (int)rops.size() - 1;
+            while (j >= blk.op0 + stg.op_begin && !(obits[j - blk.op0] & o.bits)) --j;
+            if (j >= blk.op0 + stg.op_begin && (rops[j].code & 31) == RV_ROT + 6 + o.b0) {
+              rops[j] = RegOpV{RV_YZ + o.b0 + 32 * (local + 1), (rops[j].code >> 5) - 1, o.o.param, rops[j].param};
+              continue;
+            }
+          }
+          o.o.code += 32 * (local + 1);
+          rops.push_back(o.o);
+          obits.push_back(o.bits);
         }
-        int ld_perm[16], st_perm[16];
-        fold_permutations(
-            pops, kBwdBits, [](const VqeBwdRop& o) { return o.kind == 3 || o.kind == 5; },
-            [](const VqeBwdRop& o) {
-              return (o.kind == 0 || o.kind == 2) ? (1u << o.r0) : ((1u << o.r0) | (1u << o.r1));
-            },
-            [](const VqeBwdRop& o, int j) { return o.kind == 3 ? reg_cx(o.r0, o.r1, j) : reg_swap(o.r0, o.r1, j); },
-            ld_perm, st_perm);
-        rops.insert(rops.end(), pops.begin(), pops.end());
-        fp.op_count = (int)rops.size() - fp.op_begin;
-        fill_phase_offsets(fp, kBwdBits, ld_perm, st_perm);
-        phases.push_back(fp);
+        stg.op_count = (int)rops.size() - blk.op0 - stg.op_begin;
+        stages.push_back(stg);
       }
-      d.op_count = (int)phases.size() - d.op_begin;
-      fill_entry_offsets(d, kBwdBits);
-      h->bwd_blocks.push_back(d);
-      h->bwd_mask.push_back(masks[bpadded.rend() - bit - 1]);
+      blk.nops = (int)rops.size() - blk.op0;
+      blk.nlocal = (int)slots.size() - blk.slot0;
+      layout_rb_block(b, std::move(stages), kBwdBits, true, blk.d, phases);
+      blk.mask = before[bpadded.rend() - bit - 1] & ~blk.d.tile;
+      max_bwd_lds = std::max(max_bwd_lds, bwd_reg_lds(kb, blk.d.ph_count, blk.nops, blk.nlocal));
+      h->bwd_reg.push_back(blk);
     }
   }
   for (auto bit = bpadded.rbegin(); !h->bwd_rb && bit != bpadded.rend(); ++bit) {
@@ -2347,12 +2239,13 @@ static int build_fused(nwq_vqe* h) {
       h->hlaunch[i].p.last = i + 1 == h->hlaunch.size();
     }
   }
-  const size_t ph_bytes = phases.size() * sizeof(FusedPhase);
+  const size_t ph_bytes = phases.size() * sizeof(RbPhase);
   h->fused_fph_off = (ph_bytes + 255) & ~size_t(255);
   h->fused_ops_off = (h->fused_fph_off + fphases.size() * sizeof(RbPhase) + 255) & ~size_t(255);
   h->fused_bwd_off = (h->fused_ops_off + fops.size() * sizeof(RbOp) + 255) & ~size_t(255);
   h->fused_rop_off = (h->fused_bwd_off + bops.size() * sizeof(VqeBwdOp) + 255) & ~size_t(255);
-  h->fused_hterm_off = (h->fused_rop_off + rops.size() * sizeof(VqeBwdRop) + 255) & ~size_t(255);
+  h->fused_slot_off = (h->fused_rop_off + rops.size() * sizeof(RegOpV) + 255) & ~size_t(255);
+  h->fused_hterm_off = (h->fused_slot_off + slots.size() * sizeof(int) + 255) & ~size_t(255);
   h->fused_widx_off = (h->fused_hterm_off + hterms.size() * sizeof(HTerm) + 255) & ~size_t(255);
   const size_t total = h->fused_widx_off + widx.size() * sizeof(int) + 16;
   std::vector<char> prog(total, 0);
@@ -2360,19 +2253,18 @@ static int build_fused(nwq_vqe* h) {
   if (!fphases.empty()) std::memcpy(prog.data() + h->fused_fph_off, fphases.data(), fphases.size() * sizeof(RbPhase));
   if (!fops.empty()) std::memcpy(prog.data() + h->fused_ops_off, fops.data(), fops.size() * sizeof(RbOp));
   if (!bops.empty()) std::memcpy(prog.data() + h->fused_bwd_off, bops.data(), bops.size() * sizeof(VqeBwdOp));
-  if (!rops.empty()) std::memcpy(prog.data() + h->fused_rop_off, rops.data(), rops.size() * sizeof(VqeBwdRop));
+  if (!rops.empty()) std::memcpy(prog.data() + h->fused_rop_off, rops.data(), rops.size() * sizeof(RegOpV));
+  if (!slots.empty()) std::memcpy(prog.data() + h->fused_slot_off, slots.data(), slots.size() * sizeof(int));
   if (!hterms.empty()) std::memcpy(prog.data() + h->fused_hterm_off, hterms.data(), hterms.size() * sizeof(HTerm));
   if (!widx.empty()) std::memcpy(prog.data() + h->fused_widx_off, widx.data(), widx.size() * sizeof(int));
   // dynamic LDS above 64 KiB is enabled here, outside any graph capture
-  const int kbt = std::min(std::min(h->fused_k, kBwdMaxTileBits), n);
-  const size_t max_rb_lds = 2 * bwd_rb_tile_bytes(kbt < 8 ? 8 : kbt);
-  if (max_bwd_lds > (size_t)kMaxDynamicLds || max_rb_lds > (size_t)kMaxDynamicLds ||
+  if (max_bwd_lds > (size_t)kMaxDynamicLds ||
       sizeof(double2) * hpad(1u << kHTileBits) > (size_t)kMaxDynamicLds)
     return set_error(NWQ_EINVAL, "VQE tile larger than the dynamic LDS limit");
   int rc = enable_dynamic_lds((const void*)k_vqe_bwd_tile);
   for (const void* f : {(const void*)k_vqe_hphi_tile<false, false>, (const void*)k_vqe_hphi_tile<true, false>,
                         (const void*)k_vqe_hphi_tile<false, true>, (const void*)k_vqe_hphi_tile<true, true>,
-                        (const void*)k_vqe_bwd_rb<3, false>, (const void*)k_vqe_bwd_rb<3, true>})
+                        (const void*)k_vqe_bwd_reg<false>, (const void*)k_vqe_bwd_reg<true>})
     if (!rc) rc = enable_dynamic_lds(f);
   if (!rc) rc = check_hip(hipMalloc(&h->d_fused, total), "hipMalloc(vqe fused program)");
   if (!rc) rc = check_hip(hipMemcpy(h->d_fused, prog.data(), total, hipMemcpyHostToDevice), "hipMemcpy(vqe fused program)");
@@ -2396,11 +2288,6 @@ static std::vector<char> build_reg(nwq_vqe* h) {
     nq[i] = two ? 2 : 1;
     order[i] = i;
   }
-  struct Op {
-    RegOpV o;
-    int perm, b0, b1;   // perm: 1 CX, 2 SWAP
-    unsigned bits;
-  };
   std::vector<RbStage> stages;
   std::vector<RegOpV> rops;
   std::vector<unsigned> rbits;   // register bits of each op
@@ -2415,27 +2302,15 @@ static std::vector<char> build_reg(nwq_vqe* h) {
         if (ph.reg[i] == bit) return i;
       return -1;
     };
-    std::vector<Op> pops;
+    std::vector<RegGate> pops;
     for (int gi : ph.gates) {
       const VqeOp& op = h->ops[gi];
-      const int r0 = ridx(op.q0), r1 = nq[gi] == 2 ? ridx(op.q1) : 0;
-      const int pair = nq[gi] == 2 ? rb_pair(std::min(r0, r1), std::max(r0, r1)) : 0;
-      Op o{{0, std::max(0, op.mat), op.param, -1}, 0, r0, r1, nq[gi] == 2 ? (1u << r0) | (1u << r1) : 1u << r0};
-      if (op.kind == OP_ROT) o.o.code = RV_ROT + 3 * op.axis + r0;
-      else if (op.kind == OP_FIX1) o.o.code = RV_FIX + r0;
-      else if (op.kind == OP_RZZ) o.o.code = RV_RZZ + pair;
-      else if (op.kind == OP_CZ) o.o.code = RV_CZ + pair;
-      else if (op.kind == OP_CX) o.o.code = RV_CX + 2 * pair + (r0 > r1 ? 1 : 0), o.perm = 1;
-      else o.o.code = RV_SWAP + pair, o.perm = 2;
-      o.o.code += 32 * (op.slot + 1);
-      pops.push_back(o);
+      pops.push_back(reg_gate(op, ridx(op.q0), nq[gi] == 2 ? ridx(op.q1) : 0, nq[gi] == 2));
+      pops.back().o.code += 32 * (op.slot + 1);
     }
-    fold_permutations(
-        pops, 3, [](const Op& o) { return o.perm != 0; }, [](const Op& o) { return o.bits; },
-        [](const Op& o, int j) { return o.perm == 1 ? reg_cx(o.b0, o.b1, j) : reg_swap(o.b0, o.b1, j); }, stg.ld_perm,
-        stg.st_perm);
+    fold_reg_gates(pops, stg);
     for (size_t i = 0; i < pops.size(); ++i) {
-      const Op& o = pops[i];
+      const RegGate& o = pops[i];
       // an RZ joins the RY before it on its bit when nothing between them touches the bit
       if ((o.o.code & 31) >= RV_ROT + 6 && (o.o.code & 31) < RV_FIX) {
         int j = (int)rops.size() - 1;
@@ -2499,7 +2374,6 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
   if (rc) return rc;
   const int G = fused_grid(h);
   const dim3 grid(G, B);
-  const FusedPhase* dph = static_cast<const FusedPhase*>(h->d_fused);
   const RbPhase* dfp = reinterpret_cast<const RbPhase*>(static_cast<char*>(h->d_fused) + h->fused_fph_off);
   const RbOp* dfo = reinterpret_cast<const RbOp*>(static_cast<char*>(h->d_fused) + h->fused_ops_off);
   const VqeBwdOp* dbo = reinterpret_cast<const VqeBwdOp*>(static_cast<char*>(h->d_fused) + h->fused_bwd_off);
@@ -2536,27 +2410,25 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
     }
   }
   if (grad != nullptr) {
-    const VqeBwdRop* dro = reinterpret_cast<const VqeBwdRop*>(static_cast<char*>(h->d_fused) + h->fused_rop_off);
+    const RbPhase* dph = static_cast<const RbPhase*>(h->d_fused);
+    const RegOpV* dro = reinterpret_cast<const RegOpV*>(static_cast<char*>(h->d_fused) + h->fused_rop_off);
+    const int* dsl = reinterpret_cast<const int*>(static_cast<char*>(h->d_fused) + h->fused_slot_off);
+    for (const auto& b : h->bwd_reg) {
+      const unsigned long long nt = 1ull << __builtin_popcountll(b.mask);
+      auto kern = (h->fused_flags & kFusedNonTemporal) ? k_vqe_bwd_reg<true> : k_vqe_bwd_reg<false>;
+      hipLaunchKernelGGL(kern, grid, dim3(1u << (b.d.k - 3)),
+                         bwd_reg_lds(b.d.k, b.d.ph_count, b.nops, b.nlocal), s, h->d_phi, h->d_lam, h->n, b.d, dph,
+                         dro + b.op0, b.nops, dsl + b.slot0, b.nlocal, h->d_fixed, theta, h->P, h->nslots, h->d_gpart,
+                         nt, b.mask, deposit(G, b.mask));
+    }
     for (size_t bi = 0; bi < h->bwd_blocks.size(); ++bi) {
       const FusedBlockDev& d = h->bwd_blocks[bi];
       const int kb = d.c + d.m;
-      const unsigned long long mask = h->bwd_mask[bi], nt = 1ull << __builtin_popcountll(mask);
-      const int sparse = __builtin_popcountll(mask) < h->n - kb ? 1 : 0;
-      if (h->bwd_rb) {
-        if (h->fused_flags & kFusedNonTemporal)
-          hipLaunchKernelGGL((k_vqe_bwd_rb<3, true>), grid, dim3(1u << (kb - 3)), 2 * bwd_rb_tile_bytes(kb), s,
-                             h->d_phi, h->d_lam, h->n, d, dph, dro, h->d_table, stride, h->nslots, h->d_gpart, nt, sparse,
-                             mask);
-        else
-          hipLaunchKernelGGL((k_vqe_bwd_rb<3, false>), grid, dim3(1u << (kb - 3)), 2 * bwd_rb_tile_bytes(kb), s,
-                             h->d_phi, h->d_lam, h->n, d, dph, dro, h->d_table, stride, h->nslots, h->d_gpart, nt, sparse,
-                             mask);
-      } else {
-        // tiles below 2^9 entries: the whole state is one tile
-        const size_t lds = 2 * sizeof(double2) << kb;
-        hipLaunchKernelGGL(k_vqe_bwd_tile, grid, dim3(kBwdBlock), lds, s, h->d_phi, h->d_lam, h->n, d, dbo,
-                           h->d_table, stride, h->nslots, h->d_gpart, nt);
-      }
+      const unsigned long long nt = 1ull << __builtin_popcountll(h->bwd_mask[bi]);
+      // tiles below 2^9 entries: the whole state is one tile
+      const size_t lds = 2 * sizeof(double2) << kb;
+      hipLaunchKernelGGL(k_vqe_bwd_tile, grid, dim3(kBwdBlock), lds, s, h->d_phi, h->d_lam, h->n, d, dbo,
+                         h->d_table, stride, h->nslots, h->d_gpart, nt);
     }
   }
   if (grad != nullptr && h->nslots > 0)

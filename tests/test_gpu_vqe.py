@@ -364,6 +364,38 @@ def test_fused_sweep_matches_per_gate_schedule(V, torch, n, L, B):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,gates,span", [(9, 300, 9), (10, 60, 10), (11, 200, 4), (13, 150, 13), (16, 200, 16)])
+@pytest.mark.parametrize("flags", [0, 3])
+def test_fused_backward_generic_programs(V, torch, n, gates, span, flags):
+    """The register-blocked backward sweep on every gate kind over qubits
+    0 .. span-1: one wave and four per tile, one tile and many, more ops than
+    one dispatch takes, RZ merged into RY or held apart by a gate between them,
+    shared parameters and angles beyond pi: against one kernel per gate (mode
+    2), whose arithmetic differs in order only."""
+    A = W.AnsatzGate
+    rng = np.random.default_rng(10 * n + gates)
+    P = max(3, gates // 4)
+    kinds = ["rx", "ry", "rz", "h", "s", "t", "x", "rzz", "cz", "cx", "swap", "cx"]
+    prog = []
+    for _ in range(gates):
+        name = kinds[int(rng.integers(len(kinds)))]
+        q = tuple(int(x) for x in rng.choice(span, size=2 if name in ("rzz", "cz", "cx", "swap") else 1, replace=False))
+        prog.append(A(name, q, int(rng.integers(P)) if name in ("rx", "ry", "rz", "rzz") else -1))
+        if name == "ry":
+            prog.append(A("rz", q, int(rng.integers(P))))
+    ctx = V.VQE(n, prog, W.random_pauli_sum(n, 12, seed=n), n_params=P)
+    t = torch.from_numpy(rng.uniform(-8.0, 8.0, (3, P))).cuda()
+    ctx.set_config(2, 256, 0)
+    E2, G2 = ctx.eval(t)
+    E2, G2 = E2.cpu().numpy(), G2.cpu().numpy()
+    ctx.set_config(3, 256, 0)
+    ctx.set_flags(flags)
+    E3, G3 = ctx.eval(t)
+    assert np.max(np.abs(E3.cpu().numpy() - E2)) <= 1e-12
+    assert np.max(np.abs(G3.cpu().numpy() - G2)) <= 1e-12
+    ctx.close()
+
+
 @pytest.mark.parametrize("n,gates,terms", [(1, 12, 3), (2, 20, 15), (3, 40, 30), (7, 120, 70), (9, 150, 20),
                                            (10, 200, 130), (12, 260, 64)])
 def test_resident_path_generic_programs(V, torch, n, gates, terms):
