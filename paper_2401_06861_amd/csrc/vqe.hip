@@ -991,8 +991,9 @@ __global__ __launch_bounds__(kVqeBlock) void k_vqe_hphi(const double2* __restric
 // energy partial of its workgroup.  Terms whose flipped bits fit no tile
 // take a gather pass of their own (k_vqe_hphi_wide).
 // ---------------------------------------------------------------------------
-constexpr int kHBlock = 1024;     // threads per tile workgroup
-constexpr int kHTileBits = 13;    // tiles of at most 2^13 entries (128 KiB of LDS)
+constexpr int kHBlock = 512;      // threads per tile workgroup
+constexpr int kHTileBits = 12;    // tiles of at most 2^12 entries: two workgroups per CU, one loads while one sums
+constexpr int kHLow = 4;          // low bits of the later passes' tiles (8 high bits each)
 constexpr int kHPer = (1 << kHTileBits) / kHBlock;
 constexpr int kHMaxTerms = 128;   // terms per launch
 
@@ -1012,10 +1013,13 @@ struct HPass {
   int pad;
 };
 
-__host__ __device__ inline unsigned hpad(unsigned l) { return l + (l >> 4); }
-
+// Bound by the streams: 256 vectors of 20 qubits, Ising chain, 2.08 ms for the
+// first pass (12 bits, 19 + 12 terms; 4.1 TB/s) and 2.36 for the second (8
+// bits; 5.5 TB/s).  Tiles of 2^13, one workgroup per CU that loads or sums, with
+// a select per term and entry, took 3.69 and 4.40.
 template <bool FIRST, bool LAST>
-__global__ __launch_bounds__(kHBlock) void k_vqe_hphi_tile(const double2* __restrict__ phi0, double2* __restrict__ lam0,
+__global__ __launch_bounds__(kHBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_vqe_hphi_tile(
+                                                           const double2* __restrict__ phi0, double2* __restrict__ lam0,
                                                            int n, HPass ps, const HTerm* __restrict__ hterms,
                                                            const VqeTerm* __restrict__ terms, int nterms,
                                                            const double* __restrict__ coeffs,
@@ -1036,18 +1040,18 @@ __global__ __launch_bounds__(kHBlock) void k_vqe_hphi_tile(const double2* __rest
     s_c[i] = coeffs ? coeffs[(size_t)blockIdx.y * nterms + t] : terms[t].c;
   }
   // Entry r of this thread is tile entry l = tid + r kHBlock; its global
-  // index is the tile base plus a tile-independent part, computed once.
-  const unsigned cmask = (1u << ps.c) - 1u;
-  unsigned long long sc[kHPer];
-#pragma unroll
-  for (int r = 0; r < kHPer; ++r) {
-    const unsigned l = tid + r * kHBlock;
-    unsigned long long gi = l & cmask;
+  // index is the tile base plus the thread's part and a uniform part.
+  auto scatter = [&](unsigned l) {
+    unsigned long long gi = l & ((1u << ps.c) - 1u);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       if (i < ps.m && ((l >> (ps.c + i)) & 1u)) gi |= 1ull << ps.hi[i];
-    sc[r] = gi;
-  }
+    return gi;
+  };
+  const unsigned long long own = scatter(tid);
+  static_assert(kHPer == 8, "three register bits");
+  constexpr int kHShift = 9;
+  static_assert(1 << kHShift == kHBlock, "register bits above the thread's");
   double e = 0.0;
   for (unsigned long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     unsigned long long base = tile << ps.c;
@@ -1058,66 +1062,96 @@ __global__ __launch_bounds__(kHBlock) void k_vqe_hphi_tile(const double2* __rest
         base = ((base >> q) << (q + 1)) | (base & ((1ull << q) - 1ull));
       }
     }
-    vd2 v[kHPer], acc[kHPer];
-    __syncthreads();   // the previous tile's readers are done (and s_c is written)
+    vd2 v[kHPer];
+    double ax[kHPer], ay[kHPer];
 #pragma unroll
     for (int r = 0; r < kHPer; ++r) {
-      const unsigned l = tid + r * kHBlock;
-      if (l < len) {
-        v[r] = __builtin_nontemporal_load(reinterpret_cast<const vd2*>(phi + (base | sc[r])));
-        acc[r] = FIRST ? mk(0.0, 0.0) : __builtin_nontemporal_load(reinterpret_cast<const vd2*>(lam + (base | sc[r])));
-        st(tl + hpad(l), v[r]);
+      v[r] = mk(0.0, 0.0);
+      vd2 a = mk(0.0, 0.0);
+      if (tid + r * kHBlock < len) {
+        const unsigned long long at = (base | scatter(r * kHBlock)) | own;
+        v[r] = __builtin_nontemporal_load(reinterpret_cast<const vd2*>(phi + at));
+        if (!FIRST) a = __builtin_nontemporal_load(reinterpret_cast<const vd2*>(lam + at));
       }
+      ax[r] = a.x;
+      ay[r] = a.y;
     }
+    __syncthreads();   // the previous tile's readers are done (and s_c is written)
+#pragma unroll
+    for (int r = 0; r < kHPer; ++r)
+      if (tid + r * kHBlock < len) st(tl + tid + r * kHBlock, v[r]);
     __syncthreads();
     // The sign of a term at entry l: the parity of (l & zl) splits into the
     // thread's bits (tid & zl) and the entry slot's (r kHBlock & zl); the bits
     // outside the tile (base & zo) and x & z are per tile and term.
     if (ps.n_diag > 0) {
+      // the coefficients by their sign pattern over r, then one Walsh-Hadamard
+      // transform: an add per term and thread, not one per entry
       double d[kHPer];
 #pragma unroll
       for (int r = 0; r < kHPer; ++r) d[r] = 0.0;
       for (int i = 0; i < ps.n_diag; ++i) {
         const HTerm T = hterms[ps.t_begin + i];
-        const double c = s_c[i];
-        const unsigned pb = (unsigned)(__popcll(base & T.zo) + __popc(tid & T.zl)) & 1u;
-#pragma unroll
-        for (int r = 0; r < kHPer; ++r) {
-          const unsigned sg = pb ^ ((unsigned)__popc((unsigned)(r * kHBlock) & T.zl) & 1u);
-          d[r] += sg ? -c : c;
+        const unsigned pb = (unsigned)(__builtin_popcountll(base & T.zo) + __popc(tid & T.zl)) & 1u;
+        const double c = pb ? -s_c[i] : s_c[i];
+#define NWQ_HD(I) \
+  case I: d[I] += c; asm volatile("" : "+v"(d[I])); break;
+        switch ((T.zl >> kHShift) & 7u) {
+          NWQ_HD(0) NWQ_HD(1) NWQ_HD(2) NWQ_HD(3) NWQ_HD(4) NWQ_HD(5) NWQ_HD(6) NWQ_HD(7)
         }
+#undef NWQ_HD
       }
 #pragma unroll
+      for (int h = 1; h < kHPer; h <<= 1)
+#pragma unroll
+        for (int r = 0; r < kHPer; ++r)
+          if (!(r & h)) {
+            const double a = d[r], b = d[r | h];
+            d[r] = a + b;
+            d[r | h] = a - b;
+          }
+#pragma unroll
       for (int r = 0; r < kHPer; ++r) {
-        acc[r].x = fma(d[r], v[r].x, acc[r].x);
-        acc[r].y = fma(d[r], v[r].y, acc[r].y);
+        ax[r] = fma(d[r], v[r].x, ax[r]);
+        ay[r] = fma(d[r], v[r].y, ay[r]);
       }
     }
     for (int i = ps.n_diag; i < nt; ++i) {
       const HTerm T = hterms[ps.t_begin + i];
-      const double c = s_c[i];
-      const unsigned pb = (unsigned)(__popcll(base & T.zo) + __popc(tid & T.zl) + T.sx) & 1u;
-      const int y = T.y & 3;
+      // i^y: 1, i, -1, -i; the sign of 2 and 3 with the others
+      const unsigned pb = (unsigned)(__builtin_popcountll(base & T.zo) + __popc(tid & T.zl) + T.sx + (T.y >> 1)) & 1u;
+      const double c = pb ? -s_c[i] : s_c[i];
+      const unsigned at = tid ^ (T.xl & (kHBlock - 1)), xr = T.xl >> kHShift, zr = (T.zl >> kHShift) & 7u;
+      vd2 p[kHPer];
 #pragma unroll
-      for (int r = 0; r < kHPer; ++r) {
-        const unsigned l = tid + r * kHBlock;
-        if (l >= len) continue;
-        vd2 p = ld(tl + hpad(l ^ T.xl));
-        if (y == 1) p = mk(-p.y, p.x);
-        else if (y == 2) p = mk(-p.x, -p.y);
-        else if (y == 3) p = mk(p.y, -p.x);
-        const unsigned sg = pb ^ ((unsigned)__popc((unsigned)(r * kHBlock) & T.zl) & 1u);
-        const double cf = sg ? -c : c;
-        acc[r].x = fma(cf, p.x, acc[r].x);
-        acc[r].y = fma(cf, p.y, acc[r].y);
+      for (int r = 0; r < kHPer; ++r) p[r] = ld(tl + ((at + (((unsigned)r ^ xr) << kHShift)) & (len - 1u)));
+      auto cf = [&](int r) {   // the slot's sign is uniform
+        const unsigned sg = (unsigned)(__builtin_popcount(r & zr) & 1) << 31;
+        return __hiloint2double((int)((unsigned)__double2hiint(c) ^ sg), __double2loint(c));
+      };
+      if (T.y & 1) {
+#pragma unroll
+        for (int r = 0; r < kHPer; ++r) {
+          ax[r] = fma(-cf(r), p[r].y, ax[r]);
+          ay[r] = fma(cf(r), p[r].x, ay[r]);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < kHPer; ++r) {
+          ax[r] = fma(cf(r), p[r].x, ax[r]);
+          ay[r] = fma(cf(r), p[r].y, ay[r]);
+        }
       }
     }
 #pragma unroll
     for (int r = 0; r < kHPer; ++r) {
-      const unsigned l = tid + r * kHBlock;
-      if (l >= len) continue;
-      __builtin_nontemporal_store(acc[r], reinterpret_cast<vd2*>(lam + (base | sc[r])));
-      if (LAST) e += v[r].x * acc[r].x + v[r].y * acc[r].y;
+      if (tid + r * kHBlock >= len) continue;
+      __builtin_nontemporal_store(mk(ax[r], ay[r]),
+                                  reinterpret_cast<vd2*>(lam + ((base | scatter(r * kHBlock)) | own)));
+      if (LAST) {   // from LDS again: held in registers it spills
+        const vd2 a = ld(tl + tid + r * kHBlock);
+        e += a.x * ax[r] + a.y * ay[r];
+      }
     }
   }
   if (LAST) {
@@ -2160,7 +2194,7 @@ static int build_fused(nwq_vqe* h) {
   }
   // lambda = H phi: the first pass takes tiles of the low kt bits with every
   // diagonal term and the terms whose flipped bits lie there; further passes
-  // take tiles of the 6 low bits plus up to kt - 6 high bits, greedily, for
+  // take tiles of kHLow low bits plus up to kt - kHLow high bits, greedily, for
   // the remaining terms; terms needing more high bits than that go to a
   // gather pass.  Tiles are widened to 2^kt entries with unused high bits.
   std::vector<HTerm> hterms;
@@ -2173,7 +2207,7 @@ static int build_fused(nwq_vqe* h) {
       const unsigned long long x = h->terms[t].x;
       if (x == 0) diag.push_back(t);
       else if ((x >> kt) == 0) rest.push_back(t);   // in the first pass
-      else if (__builtin_popcountll(x >> 6) > kt - 6) wide.push_back(t);
+      else if (__builtin_popcountll(x >> kHLow) > kt - kHLow) wide.push_back(t);
       else rest.push_back(t);
     }
     auto add_pass = [&](int c, std::vector<int> hi, const std::vector<int>& dg, const std::vector<int>& fl) {
@@ -2209,7 +2243,7 @@ static int build_fused(nwq_vqe* h) {
     std::vector<int> first_flips, later;
     for (int t : rest) ((h->terms[t].x >> kt) == 0 ? first_flips : later).push_back(t);
     add_pass(kt, {}, diag, first_flips);
-    const int c = std::min(6, kt);
+    const int c = std::min(kHLow, kt);
     while (!later.empty()) {
       std::vector<int> hi, take, keep;
       for (int t : later) {
@@ -2259,7 +2293,7 @@ static int build_fused(nwq_vqe* h) {
   if (!widx.empty()) std::memcpy(prog.data() + h->fused_widx_off, widx.data(), widx.size() * sizeof(int));
   // dynamic LDS above 64 KiB is enabled here, outside any graph capture
   if (max_bwd_lds > (size_t)kMaxDynamicLds ||
-      sizeof(double2) * hpad(1u << kHTileBits) > (size_t)kMaxDynamicLds)
+      (sizeof(double2) << kHTileBits) > (size_t)kMaxDynamicLds)
     return set_error(NWQ_EINVAL, "VQE tile larger than the dynamic LDS limit");
   int rc = enable_dynamic_lds((const void*)k_vqe_bwd_tile);
   for (const void* f : {(const void*)k_vqe_hphi_tile<false, false>, (const void*)k_vqe_hphi_tile<true, false>,
@@ -2404,7 +2438,7 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
     } else {
       auto kt = sel == 0 ? k_vqe_hphi_tile<false, false> : sel == 1 ? k_vqe_hphi_tile<true, false>
               : sel == 2 ? k_vqe_hphi_tile<false, true> : k_vqe_hphi_tile<true, true>;
-      const size_t lds = sizeof(double2) * hpad(1u << (L.p.c + L.p.m));
+      const size_t lds = sizeof(double2) << (L.p.c + L.p.m);
       hipLaunchKernelGGL(kt, grid, dim3(kHBlock), lds, s, h->d_phi, h->d_lam, h->n, L.p, dht, h->d_terms, h->nterms,
                          coeffs, h->d_epart);
     }
