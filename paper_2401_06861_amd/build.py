@@ -39,7 +39,7 @@ CFLAGS = [
 #    for every region) threads each op through a chain of flow blocks and copies
 #    the registers at each join: the VQE backward kernel has 986 64-bit moves
 #    and 188 branches that way, 375 and 157 without, and the fused kernel takes
-#    135 VGPRs instead of 119.
+#    135 VGPRs instead of 118.
 UNIFORM = ["-mllvm", "-structurizecfg-skip-uniform-regions=1"]
 FILE_FLAGS = {
     "kernels_fuse.hip": ["-mllvm", "-simplifycfg-sink-common=false"] + UNIFORM,

@@ -17,10 +17,10 @@
 namespace nwq {
 
 // The register-blocked kernels run a width of 13 in tiles of 2^12 (unless one
-// tile holds the whole register): three workgroups of 2^12 tiles share a CU
-// against one of 2^13, which costs more than the fewer blocks of width 13 save
-// (30-qubit brickwork: 278 ms in 32 blocks against 300 in 29; random pairs on
-// 24 qubits 1.48 against 1.96).
+// tile holds the whole register): four workgroups of 2^12 tiles share a CU
+// against two of 2^13, which costs more than the fewer blocks of width 13 save
+// (with three against one: 30-qubit brickwork 278 ms in 32 blocks against 300 in
+// 29; random pairs on 24 qubits 1.48 against 1.96).
 int fusion_width(const nwq_state* h, int nbits) {
   return h->fuse_rb != 0 && nbits > h->fuse_k ? std::min(h->fuse_k, 12) : h->fuse_k;
 }

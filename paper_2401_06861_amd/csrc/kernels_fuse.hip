@@ -186,21 +186,24 @@ void launch_fused_block(hipStream_t s, double2* a, int nbits, const FusedBlockDe
 // then its imaginary parts, so that a tile of 2^12 takes 32 KB.
 //
 // R trades registers for phases: R = 4 applies more gates per exchange but
-// needs about 135 VGPRs (two register sets); R = 3 fits 70, updates in place
-// and takes twice the phases.
+// needs 117 to 128 VGPRs (two register sets; the density-matrix set would take
+// 132, and spills nine to keep four waves on a SIMD: 14 qubits 52.4 -> 50.5 ms,
+// 11 qubits 1.80 -> 1.69); R = 3 fits 70, updates in place and takes twice the
+// phases.
 //
 // What bounds it: the vector units and the power they draw.  On the 30-qubit
 // depth-40 brickwork the HBM traffic of the 32 blocks of width 12 takes 0.18 s
 // and their FP64 instructions 0.13 s; with every tile read from cache 274 of
 // 284 ms remained, and the VALU is busy 69 % of the cycles at a clock that
-// sinks to 2.0 GHz (2.3 GHz at 52 %).  Three workgroups of four waves share a
+// sinks to 2.0 GHz (2.3 GHz at 52 %).  Four workgroups of four waves share a
 // CU (no tile is loaded ahead: the other workgroups' arithmetic hides a
 // tile's loads, and the exchanges of one wave the scalar loads of another).
 // Exchanges whose two phases keep the same tile bits on the wave index stay
 // inside a wave and need no barrier.  Against one workgroup of 2^13 tiles with
-// the next tile loaded ahead (221 VGPRs, 128 KB): 284 -> 278 ms; a 24-qubit
-// circuit of random pairs 1.72 -> 1.48 ms, the noisy TFIM on 14 qubits 58.3 ->
-// 54.8 ms, VQE n=20 L=8 (256 vectors) 79.7 -> 77.3 ms.
+// the next tile loaded ahead (221 VGPRs, 128 KB), three per CU (135 VGPRs, op
+// switch structurised) and four: 284, 278 and 277 ms; a 24-qubit circuit of
+// random pairs 1.72, 1.48 and 1.35 ms, the noisy TFIM on 14 qubits 58.3, 54.8
+// and 50.5 ms.
 // ===========================================================================
 namespace nwq {
 namespace {
@@ -509,7 +512,7 @@ typedef __attribute__((address_space(3))) double* lds_double;
 __device__ __forceinline__ lds_double lds_at(unsigned byte) { return (lds_double)byte; }
 
 template <int R, int SET, bool NT>
-__global__ __launch_bounds__(R == 4 ? 512 : 1024) __attribute__((amdgpu_waves_per_eu(R == 4 ? 3 : 4))) void k_fused_rb(double2* __restrict__ a0, RbBlock blk,
+__global__ __launch_bounds__(R == 4 ? 512 : 1024) __attribute__((amdgpu_waves_per_eu(4))) void k_fused_rb(double2* __restrict__ a0, RbBlock blk,
                                                                   const RbPhase* __restrict__ phases,
                                                                   const RbOp* __restrict__ ops,
                                                                   const double2* __restrict__ mats0,
@@ -616,7 +619,7 @@ void launch_fused_rb(hipStream_t s, double2* a, int nbits, const RbBlock& blk, c
                      const double2* mats, int rbits, int set, bool non_temporal, unsigned long long mask, int batch,
                      int mat_stride, int max_grid) {
   const unsigned long long ntiles = 1ull << __builtin_popcountll(mask);
-  // 768 workgroups of width 12 run at a time; many more of them than that keep
+  // 1024 workgroups of width 12 run at a time; many more of them than that keep
   // the last round short (n=30: 286 ms with 4096, 278 with 16384)
   const unsigned long long cap = max_grid > 0 ? (unsigned long long)max_grid : 16384;
   const unsigned grid = (unsigned)(ntiles < cap ? ntiles : cap);
