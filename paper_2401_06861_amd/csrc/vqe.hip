@@ -1737,8 +1737,9 @@ struct nwq_vqe {
   nwq::VqeTerm* d_terms = nullptr;
   std::vector<nwq::VqeTerm> terms;   // host copy of the term table
   int* d_slot_param = nullptr;
-  // register-resident path (n <= 12): phases, ops, parameter slots in one allocation
-  void* d_reg = nullptr;
+  // register-resident path (n <= 12): phases, ops, parameter slots
+  void* d_reg = nullptr;       // part of d_program
+  void* d_program = nullptr;   // d_ops, d_fixed, d_terms, d_slot_param and d_reg
   int reg_phases = 0, reg_ops = 0;
   size_t reg_ops_off = 0, reg_poff_off = 0, reg_pslots_off = 0;
   // global path buffers
@@ -1790,7 +1791,7 @@ struct nwq_vqe {
   std::map<std::pair<int, int>, hipGraphExec_t> graphs;   // (B, want_grad) -> exec
   int fused_flags = 3;         // fused schedule: bit 0 non-temporal tile loads and stores, bit 1 direct
                                // HBM loads / stores of a forward block's first / last phase
-  size_t program_bytes = 0;    // device bytes of d_ops, d_fixed, d_terms, d_slot_param
+  size_t program_bytes = 0;    // device bytes of d_program
   size_t fused_bytes = 0;      // device bytes of d_fused once built
 };
 
@@ -1938,13 +1939,12 @@ static int launch_global(nwq_vqe* h, int B, const double* theta, const double* c
 }
 
 // Fused program: blocks over the ops at tile width fused_k, forward phases for
-// the register-blocked kernel, backward ops in reverse per block (chunks of
-// at most kBwdMaxOps).
+// the register-blocked kernel, backward ops in reverse per block (at most
+// kBwdRegOps per dispatch, kBwdMaxOps for tiles below 2^9).
 // Low tile bits of the fused schedule's blocks (clamped to [k - 8, k - 2] at
-// width k).  A batch of 2^20-amplitude states at n=20 plans the HEA ansatz
-// (L=8) into 26 backward blocks of width 11 with 6 low bits and 18 with 3; the
-// shorter runs cost less than the passes they save (n=20, L=8, B=256: 129 ->
-// 119 ms per batch).
+// width k).  Fewer low bits give shorter runs and fewer blocks, which saves more
+// (n=20, L=8, 256 vectors, blocks filled in gate order: 26 backward blocks with
+// 6 low bits, 18 with 3, 129 -> 119 ms per batch).
 constexpr int kVqeLowBits = 3;
 constexpr int kVqeSeeds = 2;   // as many as it takes: 8 seeds plan no fewer blocks for the HEA ansatz
 
@@ -2579,21 +2579,27 @@ int nwq_vqe_create(int n, int n_ops, const int* types, const int* qubits, const 
   int rc = check_hip(hipStreamCreateWithFlags(&h->stream, hipStreamNonBlocking), "hipStreamCreate");
   if (!rc) rc = check_hip(hipEventCreateWithFlags(&h->ev_in, hipEventDisableTiming), "hipEventCreate");
   if (!rc) rc = check_hip(hipEventCreateWithFlags(&h->ev_out, hipEventDisableTiming), "hipEventCreate");
-  auto up = [&](void** dst, const void* src, size_t bytes) -> int {
-    const size_t b = std::max<size_t>(bytes, 16);
-    int r = check_hip(hipMalloc(dst, b), "hipMalloc(vqe program)");
-    if (r) return r;
-    h->program_bytes += b;
-    if (bytes) r = check_hip(hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice), "hipMemcpy(vqe program)");
-    return r;
+  // the program's tables in one allocation and one copy
+  std::vector<char> prog;
+  std::vector<std::pair<void**, size_t>> parts;
+  auto add = [&](void** dst, const void* src, size_t bytes) {
+    parts.emplace_back(dst, prog.size());
+    prog.resize((prog.size() + std::max<size_t>(bytes, 16) + 255) & ~size_t(255), 0);
+    if (bytes) std::memcpy(prog.data() + parts.back().second, src, bytes);
   };
-  if (!rc) rc = up((void**)&h->d_ops, h->ops.data(), h->ops.size() * sizeof(VqeOp));
-  if (!rc) rc = up((void**)&h->d_fixed, fixed.data(), fixed.size() * sizeof(double2));
-  if (!rc) rc = up((void**)&h->d_terms, terms.data(), terms.size() * sizeof(VqeTerm));
-  if (!rc) rc = up((void**)&h->d_slot_param, h->slot_param.data(), h->slot_param.size() * sizeof(int));
-  if (!rc && n <= 12 && h->nops <= 4096) {   // more does not fit the LDS
-    const std::vector<char> prog = build_reg(h.get());
-    rc = up(&h->d_reg, prog.data(), prog.size());
+  add((void**)&h->d_ops, h->ops.data(), h->ops.size() * sizeof(VqeOp));
+  add((void**)&h->d_fixed, fixed.data(), fixed.size() * sizeof(double2));
+  add((void**)&h->d_terms, terms.data(), terms.size() * sizeof(VqeTerm));
+  add((void**)&h->d_slot_param, h->slot_param.data(), h->slot_param.size() * sizeof(int));
+  if (n <= 12 && h->nops <= 4096) {   // more does not fit the LDS
+    const std::vector<char> reg = build_reg(h.get());
+    add(&h->d_reg, reg.data(), reg.size());
+  }
+  if (!rc) rc = check_hip(hipMalloc(&h->d_program, prog.size()), "hipMalloc(vqe program)");
+  if (!rc) rc = check_hip(hipMemcpy(h->d_program, prog.data(), prog.size(), hipMemcpyHostToDevice), "hipMemcpy(vqe program)");
+  if (!rc) {
+    h->program_bytes = prog.size();
+    for (const auto& p : parts) *p.first = static_cast<char*>(h->d_program) + p.second;
   }
   if (rc) {
     nwq_vqe_destroy(h.release());
@@ -2608,9 +2614,9 @@ int nwq_vqe_destroy(nwq_vqe_handle h) {
   if (!h) return NWQ_OK;
   if (h->stream) (void)hipStreamSynchronize(h->stream);
   for (auto& kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
-  for (void* p : {(void*)h->d_ops, (void*)h->d_fixed, (void*)h->d_terms, (void*)h->d_slot_param, (void*)h->d_phi,
-                  (void*)h->d_lam, (void*)h->d_epart, (void*)h->d_gpart, (void*)h->d_theta, (void*)h->d_E,
-                  (void*)h->d_grad, (void*)h->d_coeffs, (void*)h->d_table, (void*)h->d_ssum, h->d_fused, h->d_reg})
+  for (void* p : {h->d_program, (void*)h->d_phi, (void*)h->d_lam,
+                  (void*)h->d_epart, (void*)h->d_gpart, (void*)h->d_theta, (void*)h->d_E,
+                  (void*)h->d_grad, (void*)h->d_coeffs, (void*)h->d_table, (void*)h->d_ssum, h->d_fused})
     if (p) (void)hipFree(p);
   if (h->ev_in) (void)hipEventDestroy(h->ev_in);
   if (h->ev_out) (void)hipEventDestroy(h->ev_out);

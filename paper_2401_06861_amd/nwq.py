@@ -257,7 +257,7 @@ def nwq_set_fusion_flags(h: int, flags: int) -> None:
 
 
 def nwq_set_fusion_lowbits(h: int, c: int) -> None:
-    """Low tile bits of fused blocks: 0 = default (6 for SV, 4 for DM), else 3..8."""
+    """Low tile bits of fused blocks: 0 = default (3 for SV, 4 for DM), else 3..8."""
     _check(lib.nwq_set_fusion_lowbits(h, int(c)))
 
 
