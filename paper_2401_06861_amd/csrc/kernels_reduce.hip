@@ -56,8 +56,8 @@ __device__ __forceinline__ unsigned long long scatter_local(unsigned l, int c, i
 // Bound by HBM and LDS reads: 16 bytes per amplitude and pass, and the same
 // again from LDS per term, half of it where pairs are split.  The Ising
 // chain's 27 X terms on 27 qubits: 5.2 ms in 5 passes of 2^11 tiles with a
-// pair test per lane -> 1.44 ms in 3 passes of 2^12 (512
-// threads; the first, 12 terms, 0.56, the others, 8 and 7, 0.44: 4.8 TB/s).
+// pair test per lane -> 1.41 ms in 3 passes of 2^12 (512
+// threads; the first, 12 terms, 0.54, the others, 8 and 7, 0.43: 5 TB/s).
 typedef double vd2r __attribute__((ext_vector_type(2)));
 constexpr int kTileRegs = 8;
 __device__ __forceinline__ double flip(double v, unsigned sign) {
@@ -88,7 +88,7 @@ __device__ __forceinline__ double tile_term(const vd2r (&v)[kTileRegs], const vd
   return zr == 0u ? tile_sum<IM, H, false>(v, t, at, xr, zr, shift, mask)
                   : tile_sum<IM, H, true>(v, t, at, xr, zr, shift, mask);
 }
-template <int TPL>   // 16 accumulators
+template <int TPL, bool NT>   // 16 accumulators
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_pauli_tile(
     const double2* __restrict__ a, int nbits, TileShape t, int shift, const TermDev* __restrict__ terms, int count,
     double* __restrict__ partials) {
@@ -120,8 +120,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     vd2r v[kTileRegs];
 #pragma unroll
     for (int j = 0; j < kTileRegs; ++j)
-      v[j] = (tid | ((unsigned)j << shift)) < tile_len ? *reinterpret_cast<const vd2r*>(a + ((base | off[j]) | own))
-                                                       : vd2r{0.0, 0.0};
+      {
+        const vd2r* from = reinterpret_cast<const vd2r*>(a + ((base | off[j]) | own));
+        v[j] = vd2r{0.0, 0.0};
+        if ((tid | ((unsigned)j << shift)) < tile_len) v[j] = NT ? __builtin_nontemporal_load(from) : *from;
+      }
     // the terms' lines into the scalar cache at once, not one miss per term (9
     // to 11 qubits: 16 -> 10 us)
     if (tile == blockIdx.x) {
@@ -451,8 +454,11 @@ void launch_pauli_tile(hipStream_t s, const double2* a, int nbits, const TileSha
                        int count, double* partials, int grid) {
   const int shift = tile_shift(t.c + t.m);
   const size_t lds = std::max<size_t>(sizeof(double2) << (t.c + t.m), (sizeof(double) * kTileTerms << shift) / kWave);
-  hipLaunchKernelGGL(k_pauli_tile<kTileTerms>, dim3(grid), dim3(1u << shift), lds, s, a, nbits, t, shift, terms, count,
-                     partials);
+  // States beyond the 256 MB cache are read past it (27 X terms on 27 qubits: 1.47
+  // -> 1.41 ms); smaller ones stay in it from pass to pass (24 qubits 0.28 ms
+  // against 0.30).
+  auto kern = nbits >= 25 ? k_pauli_tile<kTileTerms, true> : k_pauli_tile<kTileTerms, false>;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(1u << shift), lds, s, a, nbits, t, shift, terms, count, partials);
 }
 
 void launch_pauli_diag(hipStream_t s, const double2* a, int nbits, const ZMasks& zs, int count, double* partials,
