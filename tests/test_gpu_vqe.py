@@ -448,3 +448,34 @@ def test_resident_path_long_program(V, torch):
     assert np.max(np.abs(got[1][0] - got[2][0])) <= 1e-11
     assert np.max(np.abs(got[1][1] - got[2][1])) <= 1e-11
     ctx.close()
+
+
+@pytest.mark.parametrize("n,mode", [(4, 1), (12, 1), (9, 3), (13, 3)])
+def test_angles_of_any_size(V, torch, n, mode):
+    """Angles up to 1e300, where theta / 2 modulo pi needs more bits of pi than
+    two doubles hold: energies against the oracle, gradients against one
+    kernel per gate (mode 2), on the resident path and the fused sweep."""
+    A = W.AnsatzGate
+    rng = np.random.default_rng(n)
+    prog, P = [], 0
+    for name in ("ry", "rx", "rz", "ry"):
+        for q in range(n):
+            prog.append(A(name, (q,), P))
+            P += 1
+        prog += [A("cx", (q, q + 1), -1) for q in range(n - 1)]
+    prog.append(A("rzz", (0, n - 1), P))
+    P += 1
+    theta = rng.uniform(1.0, 10.0, (3, P)) * 10.0 ** rng.integers(12, 25, (3, P)) * rng.choice([-1.0, 1.0], (3, P))
+    theta[2] = 10.0 ** rng.uniform(200.0, 300.0, P)
+    terms = W.random_pauli_sum(n, 12, seed=n)
+    ctx = V.VQE(n, prog, terms, n_params=P)
+    t = torch.from_numpy(theta).cuda()
+    got = {}
+    for m in (2, mode):
+        ctx.set_config(m, 256, 0)
+        E, G = ctx.eval(t)
+        got[m] = (E.cpu().numpy(), G.cpu().numpy())
+    for b in range(3):
+        assert abs(got[mode][0][b] - OV.energy(prog, theta[b], terms, n)) <= 1e-10, b
+    assert np.max(np.abs(got[mode][1] - got[2][1])) <= 1e-12 * len(terms)
+    ctx.close()
