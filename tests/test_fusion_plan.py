@@ -2,6 +2,8 @@
 exactly one block, a block's tile holds all its gates' qubits and at most k
 qubits, gates that share a qubit keep their order across blocks, and the
 planner terminates for every width (including k = 6 on wider registers)."""
+import time
+
 import numpy as np
 import pytest
 
@@ -67,3 +69,34 @@ def test_blocks_follow_the_light_cone(nwq, n, k, at_most):
     layers deep (w^2/4 of its pairs), so the planner must need far fewer
     blocks than taking gates in list order (73 at n=30, k=13)."""
     assert check_plan(nwq, W.brickwork_circuit(n, 40, seed=0), n, k) <= at_most
+
+
+def _pairs(span, count, seed):
+    rng = np.random.default_rng(seed)
+    return [("cx", tuple(int(x) for x in rng.choice(span, 2, replace=False)), ()) for _ in range(count)]
+
+
+@pytest.mark.parametrize("name", ["idle brickwork", "idle pairs", "late gate", "early gates", "few qubits"])
+def test_planning_time_with_idle_qubits(nwq, name):
+    """A qubit that no gate touches, that one gate touches at the very end, or
+    whose gates are all early must not make the planner walk the whole list
+    for every block: the time per gate stays that of a circuit that keeps every
+    qubit busy (walking the list takes 15 times as long and more)."""
+    n = 30
+    gates = {"idle brickwork": W.brickwork_circuit(n - 1, 500, seed=0),
+             "idle pairs": _pairs(n - 1, 12000, 0),
+             "late gate": W.brickwork_circuit(n - 1, 500, seed=0) + [("h", (n - 1,), ())],
+             "early gates": [("h", (q,), ()) for q in range(n)] + W.brickwork_circuit(n - 1, 500, seed=0),
+             "few qubits": _pairs(16, 12000, 0)}[name]
+    busy = _pairs(n, 12000, 0) if "pairs" in name or "few" in name else W.brickwork_circuit(n, 500, seed=0)
+
+    def per_gate(gs):
+        types, qs, _ = nwq.circuit_arrays(gs)
+        best = np.inf
+        for _ in range(3):
+            t = time.perf_counter()
+            nwq.nwq_fusion_plan(n, 12, types, qs)
+            best = min(best, time.perf_counter() - t)
+        return best / len(gs)
+
+    assert per_gate(gates) <= 4.0 * per_gate(busy)
