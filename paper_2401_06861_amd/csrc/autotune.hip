@@ -133,6 +133,7 @@ int nwq_set_launch(nwq_handle h, int cls, int bucket, int ppt, int nontemporal) 
     if (bucket >= 0 && b != bucket) continue;
     h->cfg[cls][b].ppt = ppt;
     h->cfg[cls][b].nt = nontemporal;
+    h->cset[cls][b] = true;
   }
   for (int q = 0; q < kMaxTargetBits; ++q)   // the bucket's shape now holds for each of its targets
     if (bucket < 0 || bucket_of(q) == bucket) h->tset[cls][q] = false;
@@ -251,6 +252,7 @@ int nwq_autotune(nwq_handle h, int reps, double* best_ms) {
         }
       }
       h->cfg[j.cls][b] = cands[best];
+      h->cset[j.cls][b] = true;
       if (best_ms) best_ms[j.cls * kBuckets + b] = bsum[b] / bcnt[b];
     }
   }

@@ -28,6 +28,7 @@ struct nwq_state {
   // per-target shapes chosen by the autotuner; a target without one uses its bucket's
   nwq::LaunchCfg tcfg[nwq::KC_COUNT][nwq::kMaxTargetBits];
   bool tset[nwq::KC_COUNT][nwq::kMaxTargetBits] = {};
+  bool cset[nwq::KC_COUNT][nwq::kBuckets] = {};   // buckets whose shape the caller or the autotuner chose
   const nwq::LaunchCfg& shape(int cls, int lowest_bit) const {
     if (lowest_bit >= 0 && lowest_bit < nwq::kMaxTargetBits && tset[cls][lowest_bit]) return tcfg[cls][lowest_bit];
     return cfg[cls][nwq::bucket_of(lowest_bit)];

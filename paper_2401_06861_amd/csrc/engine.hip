@@ -246,6 +246,24 @@ static int drain_timing(nwq_state* h) {
 // ---------------------------------------------------------------------------
 static int last_launch(const char* what) { return check_hip(hipGetLastError(), what); }
 
+// Launch shape of a gate on two qubits, `lo` the lower.  The default shapes of
+// the low bits past the cache (default_shapes) are the fastest for neighbours,
+// where every line that is read is used whole.  With the other qubit further up
+// (`apart`: a group's entries share lines with other groups') the
+// non-temporal ones fetch lines twice and one group per thread keeps too few in
+// flight, so the plain shapes stay there: CX with its control on bit 0 or 1 and
+// its target from 6 up 1.72 ms against 2.06 at n=28, a dense 4x4 on (0..2, 6 and
+// up) 1.57 against 1.90, a noisy CX between qubits 0 or 1 and 13 of a 14-qubit
+// density matrix 1.63 against 3.12.
+static constexpr int kStreamBits = 26;
+static LaunchCfg pair_shape(const nwq_state* h, int cls, int lo, bool apart) {
+  if (!apart || lo >= 3 || h->nbits < kStreamBits || h->tset[cls][lo] || h->cset[cls][bucket_of(lo)])
+    return h->shape(cls, lo);
+  LaunchCfg plain;
+  if (cls == KC_DM2) plain.ppt = 1;
+  return plain;
+}
+
 int sv_apply_gate_validated(nwq_state* h, int type, const int* q, const double* p) {
   cd m[16];
   gate_matrix(type, p, m);
@@ -278,13 +296,13 @@ int sv_apply_gate_validated(nwq_state* h, int type, const int* q, const double* 
     case NWQ_GATE_CX:
       timing_begin(h, KC_PERM);
       launch_sv_swap2(h->stream, h->data, nb, q[0], q[1], 1ull << q[0], (1ull << q[0]) + (1ull << q[1]),
-                      h->shape(KC_PERM, std::min(q[0], q[1])));
+                      pair_shape(h, KC_PERM, std::min(q[0], q[1]), q[0] < 2 && q[1] >= 6));
       timing_end(h);
       return last_launch("sv_swap2(cx)");
     case NWQ_GATE_SWAP:
       timing_begin(h, KC_PERM);
       launch_sv_swap2(h->stream, h->data, nb, q[0], q[1], 1ull << q[0], 1ull << q[1],
-                      h->shape(KC_PERM, std::min(q[0], q[1])));
+                      pair_shape(h, KC_PERM, std::min(q[0], q[1]), std::min(q[0], q[1]) < 2 && std::max(q[0], q[1]) >= 6));
       timing_end(h);
       return last_launch("sv_swap2(swap)");
     case NWQ_GATE_CZ: case NWQ_GATE_RZZ: {
@@ -312,7 +330,8 @@ int sv_apply_matrix_validated(nwq_state* h, const int* q, int k, const cd* m) {
   Mat4 M;
   for (int i = 0; i < 16; ++i) M.m[i] = d2(m[i]);
   timing_begin(h, KC_SV2Q);
-  launch_sv_2q(h->stream, h->data, h->nbits, q[0], q[1], M, h->shape(KC_SV2Q, std::min(q[0], q[1])));
+  launch_sv_2q(h->stream, h->data, h->nbits, q[0], q[1], M,
+               pair_shape(h, KC_SV2Q, std::min(q[0], q[1]), std::max(q[0], q[1]) >= 6));
   timing_end(h);
   return last_launch("sv_2q");
 }
@@ -378,8 +397,8 @@ static int dm_superop2_pass(nwq_state* h, int q0, int q1, const cd* S) {
   if (rc != NWQ_OK) return rc;
   const int vq[4] = {q0, q1, q0 + h->n, q1 + h->n};
   timing_begin(h, KC_DM2);
-  launch_sv_kq(h->stream, h->data, h->nbits, 4, vq, static_cast<const double2*>(dev), h->shape(KC_DM2, std::min(q0, q1)),
-               pauli);
+  launch_sv_kq(h->stream, h->data, h->nbits, 4, vq, static_cast<const double2*>(dev),
+               pair_shape(h, KC_DM2, std::min(q0, q1), std::max(q0, q1) >= 8), pauli);
   timing_end(h);
   return last_launch("dm_superop_2q");
 }
@@ -522,14 +541,18 @@ const char* nwq_last_error(void) { return g_last_error.c_str(); }
 // hint, one entry per thread: the split workgroups (32, 64, 128) or the
 // XCD-contiguous diagonal kernel; the plain shapes take 1.58 instead of 1.27
 // ms per U3 at n=28 and 0.39 instead of 0.31-0.35 ms per noisy gate on 13
-// qubits.
+// qubits.  The tuner times neighbouring qubits; pair_shape covers the others on
+// low bits, and 2q DM gates on qubits 3 to 10 keep one 16-entry group per thread
+// with the hint, which gains on every pair (n=14: 1.43-1.61 ms against
+// 1.54-1.67 plain) where the split workgroups lose on some (qubits 6 and 9:
+// 2.12).
 static void default_shapes(nwq_state* h) {
   auto set = [&](int cls, LaunchCfg low, LaunchCfg mid, LaunchCfg high) {
     h->cfg[cls][0] = low;
     h->cfg[cls][1] = mid;
     h->cfg[cls][2] = high;
   };
-  if (h->nbits < 26) {
+  if (h->nbits < kStreamBits) {
     set(KC_DM2, {1, 0}, {1, 0}, {1, 0});
     return;
   }
@@ -538,7 +561,7 @@ static void default_shapes(nwq_state* h) {
   set(KC_PERM, {32, 3}, {32, 3}, {128, 3});
   set(KC_SV2Q, {1, 0}, {32, 1}, {32, 1});
   set(KC_DM1, {4, 1}, {32, 1}, {32, 1});
-  set(KC_DM2, {1, 1}, {64, 1}, {64, 1});
+  set(KC_DM2, {1, 1}, {1, 1}, {64, 1});
 }
 
 static int create_common(int kind, int n, void* dev_ptr, void* stream, nwq_handle* out) {

@@ -194,3 +194,61 @@ def test_dm_noisy_gate_sampled(nwq, torch, n, kind, qubits, shape):
     st.close()
     del v
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("kind,n,op,qubits", [
+    ("sv", 26, "cx", (0, 25)), ("sv", 26, "cx", (1, 6)), ("sv", 26, "swap", (14, 1)), ("sv", 26, "mat4", (0, 13)),
+    ("sv", 26, "mat4", (25, 2)), ("sv", 26, "mat4", (6, 1)), ("sv", 26, "cx", (25, 0)), ("sv", 26, "cx", (2, 20)),
+    ("dm", 13, "cx", (0, 12)), ("dm", 13, "rzz", (12, 1)), ("dm", 13, "cx", (2, 8)), ("dm", 13, "rzz", (7, 8)),
+    ("dm", 14, "rzz", (6, 9)), ("dm", 14, "cx", (6, 7)), ("dm", 14, "rzz", (0, 1)), ("dm", 14, "cx", (13, 12)),
+])
+def test_default_shapes_on_distant_pairs(nwq, torch, kind, n, op, qubits):
+    """A handle as created against the plain shapes (four groups per thread, one
+    for 2q DM gates, no hint), past the cache and with the qubits of a pair near
+    and apart: the same bits, and no slower (1.12 for the spread of a minimum
+    over 8 calls; the shapes picked on neighbouring qubits took 1.2 to 1.95 times
+    as long on pairs like these)."""
+    U = np.linalg.qr(np.random.default_rng(0).normal(size=(4, 4)) + 1j)[0]
+    cls = 7 if kind == "dm" else 4 if op == "mat4" else 3
+
+    def make(plain):
+        st = (nwq.DMState if kind == "dm" else nwq.SVState)(n)
+        if plain:
+            nwq.nwq_set_launch(st.h, cls, -1, 1 if cls == 7 else 4, 0)
+        if kind == "sv":
+            for q in set(qubits) | {3, 7}:
+                st.run([("u3", (q,), (0.3 + q, 1.1, 0.4))])
+        return st
+
+    def call(st, a, b):
+        if op == "mat4":
+            nwq.nwq_apply_matrix(st.h, (a, b), U)
+        else:
+            nwq.nwq_apply_gate(st.h, op, (a, b), (0.3,) if op == "rzz" else ())
+        if kind == "dm":
+            nwq.nwq_depolarize(st.h, (a, b), 0.01)
+
+    def both(st):
+        call(st, *qubits)
+        if kind == "dm":       # on another pair order: the superoperators do not compose
+            call(st, qubits[1], qubits[0])
+
+    best, data = {}, {}
+    states = {p: make(p) for p in (False, True)}
+    for p, st in states.items():
+        both(st)
+        data[p] = (st.trace() if kind == "dm" else None, st.probabilities())
+        best[p] = np.inf
+    assert data[False][0] == data[True][0] and torch.equal(data[False][1], data[True][1])
+    e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    for _ in range(8):
+        for p, st in states.items():
+            e0.record()
+            both(st)
+            both(st)
+            e1.record()
+            e1.synchronize()
+            best[p] = min(best[p], e0.elapsed_time(e1))
+    for st in states.values():
+        st.close()
+    assert best[False] <= 1.12 * best[True], best
