@@ -231,6 +231,11 @@ double passes_from_zero(const std::vector<BitSet>& sets, u64 all, u64 low) {
 
 }  // namespace
 
+// First gates tried per block of a circuit.  The search is widened as the
+// passes it saves get dearer: a pass over 2^22 entries takes about 25 us, and
+// each seed adds about 0.05 ms to planning a deep circuit.
+static int plan_seeds(int nbits) { return nbits < 22 ? 1 : (nbits < 26 ? 2 : 8); }
+
 // Every block has at least two high slots (c <= k - 2), so the first
 // remaining one- or two-qubit gate always fits and each round absorbs at
 // least one gate (a four-bit DM superoperator is queued only when the width
@@ -939,12 +944,8 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
     h->last_blocks = h->last_fused_gates = h->last_phases = 0;
     return NWQ_OK;
   }
-  // The search for each block's bits is widened as the passes it saves get
-  // dearer: a pass over 2^22 entries takes about 25 us, and each seed adds
-  // about 0.1 ms to planning a deep circuit.
-  const int seeds = nbits < 22 ? 1 : (nbits < 26 ? 2 : 8);
   const std::vector<Block> blocks = plan_blocks(gates, nbits, one_tile ? nbits : fusion_width(h, nbits),
-                                                one_tile ? nbits : fusion_low_bits(h, nbits), seeds, false);
+                                                one_tile ? nbits : fusion_low_bits(h, nbits), plan_seeds(nbits), false);
   if (blocks.empty()) return set_error(NWQ_EINVAL, "fusion planner made no progress");
   // Program: [phase table][op table][matrix table] in one upload.
   std::vector<RbPhase> phases;
@@ -1312,7 +1313,7 @@ int nwq_fusion_plan(int n, int k, int n_gates, const int* types, const int* qubi
   nwq_state defaults;   // a state vector's settings (no device memory)
   defaults.fuse_k = k;
   const std::vector<Block> blocks =
-      plan_blocks(gates, n, fusion_width(&defaults, n), fusion_low_bits(&defaults, n), 8, false);
+      plan_blocks(gates, n, fusion_width(&defaults, n), fusion_low_bits(&defaults, n), plan_seeds(n), false);
   if (n_gates > 0 && blocks.empty()) return set_error(NWQ_EINVAL, "fusion planner made no progress");
   *n_blocks = (int)blocks.size();
   for (size_t b = 0; b < blocks.size(); ++b) {

@@ -797,3 +797,17 @@ def test_fused_phase_layouts(nwq, n, k):
             nwq.nwq_run_circuit(st.h, *arrays)
             assert maxerr(st.numpy(), want) <= TOL, (n, k, rb, flags)
     st.close()
+
+
+@pytest.mark.parametrize("n,k", [(9, 12), (16, 12), (20, 12), (20, 13), (22, 10), (24, 12), (26, 12)])
+def test_fusion_plan_is_the_plan_that_runs(nwq, n, k):
+    """nwq_fusion_plan gives the blocks of nwq_apply_circuit (gate products
+    off) at every register size, whatever the search costs there."""
+    st = nwq.SVState(n)
+    st.set_fusion(k)
+    nwq.nwq_set_fusion_flags(st.h, 3)
+    for seed in range(4):
+        arrays = nwq.circuit_arrays([g for g in W.random_gate_list(n, 40 * n, seed=seed) if g[0] != "i"])
+        nwq.nwq_apply_circuit(st.h, *arrays)
+        assert nwq.nwq_fusion_stats(st.h)[0] == nwq.nwq_fusion_plan(n, k, *arrays[:2])[0], seed
+    st.close()
