@@ -144,7 +144,18 @@ static int check_handle(const nwq_state* h) {
 // ---------------------------------------------------------------------------
 static constexpr size_t kArenaBytes = 4u << 20;
 
+// Calls that another thread's graph capture in global mode forbids (and that
+// invalidate it) are allowed in relaxed mode: none here touches a captured
+// stream.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 int arena_ready(nwq_state* h) {
+  if (h->arena_dev != nullptr && h->arena_host != nullptr) return NWQ_OK;
+  RelaxedCapture relaxed;
   if (h->arena_dev == nullptr) NWQ_TRY_HIP(hipMalloc(&h->arena_dev, kArenaBytes), "hipMalloc(arena)");
   if (h->arena_host == nullptr) {
     NWQ_TRY_HIP(hipHostMalloc(&h->arena_host, kArenaBytes, hipHostMallocDefault), "hipHostMalloc(arena)");
@@ -159,6 +170,7 @@ int arena_put(nwq_state* h, const void* src, size_t bytes, void** dev_out) {
   const int rc = arena_ready(h);
   if (rc) return rc;
   if (h->arena_off + bytes > kArenaBytes) {
+    RelaxedCapture relaxed;
     NWQ_TRY_HIP(hipStreamSynchronize(h->stream), "hipStreamSynchronize(arena wrap)");
     h->arena_off = 0;
   }

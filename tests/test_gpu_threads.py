@@ -76,3 +76,45 @@ def test_concurrent_handles_match_one_thread(nwq, torch):
             assert np.array_equal(w[0], g[0]) and w[1] == g[1], i
         else:
             assert np.array_equal(w, g), i
+
+
+def test_first_circuit_while_another_thread_captures(nwq, torch):
+    """A handle's first circuit allocates its upload ring; a graph that another
+    thread captures in global mode (torch's default) meanwhile stays valid, and
+    the circuit gives the bits that it gives without a capture."""
+    n = 8
+    arrays = nwq.circuit_arrays(W.random_gate_list(n, 300, seed=3))
+
+    def handle():
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            return nwq.SVState(n, stream=stream, owned=True)
+
+    quiet = handle()
+    nwq.nwq_run_circuit(quiet.h, *arrays)
+    want = quiet.numpy()
+    quiet.close()
+    st, errors = handle(), []
+    x = torch.zeros(1 << 10, device="cuda")
+    torch.cuda.synchronize()
+
+    def work():
+        try:
+            nwq.nwq_run_circuit(st.h, *arrays)
+        except Exception as e:          # reported below, on the test's thread
+            errors.append(e)
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        x += 1.0
+        t = threading.Thread(target=work)
+        t.start()
+        t.join()
+        x += 1.0
+    assert not errors
+    for i in range(3):
+        g.replay()
+        assert x[0].item() == 2.0 * (i + 1)
+        assert np.array_equal(st.numpy(), want)
+    st.close()
+
