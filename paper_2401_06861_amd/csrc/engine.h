@@ -44,7 +44,9 @@ struct nwq_state {
   // upload arena (pinned host ring + device ring)
   void* arena_dev = nullptr;
   void* arena_host = nullptr;
-  size_t arena_off = 0;
+  size_t arena_cap = 0, arena_off = 0;
+  void* arena_first_dev = nullptr;   // the first, smaller ring, once outgrown
+  void* arena_first_host = nullptr;
 
   // DM: pending superoperator (gate + following channels on the same qubits)
   bool pend_active = false;

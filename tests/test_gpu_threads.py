@@ -118,3 +118,24 @@ def test_first_circuit_while_another_thread_captures(nwq, torch):
         assert np.array_equal(st.numpy(), want)
     st.close()
 
+
+def test_upload_ring_grows_and_wraps(nwq, torch):
+    """Circuits with no read in between whose programs pass the end of the
+    first upload ring (256 KiB) and of the second (4 MiB): every program arrives
+    whole (the same bits as with a read after each)."""
+    n = 10
+    circuits = [nwq.circuit_arrays(W.random_gate_list(n, 1500, seed=s)) for s in range(40)]
+    states, grown = [], []
+    for read in (False, True):
+        st = nwq.SVState(n)
+        empty = nwq.nwq_memory(st.h)
+        for c in circuits:
+            nwq.nwq_apply_circuit(st.h, *c)
+            grown.append(nwq.nwq_memory(st.h) - empty)
+            if read:
+                st.numpy()
+        states.append(st.numpy())
+        st.close()
+    assert np.array_equal(*states)
+    assert grown[0] >= 256 << 10 and grown[39] == (4 << 20) + (256 << 10) and grown[:40] == grown[40:]
+    assert abs(np.sum(np.abs(states[0]) ** 2) - 1.0) <= 1e-10
