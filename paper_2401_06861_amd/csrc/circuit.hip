@@ -82,57 +82,75 @@ struct BitLists {
       used |= v;
       for (; v; v &= v - 1) ++first[__builtin_ctzll(v) + 1];
     }
-    for (int b = 0; b < 64; ++b) first[b + 1] += first[b] + 1;
-    items.assign(first[64], -1);
+    const int nb = 64 - __builtin_clzll(used | 1ull);
+    for (int b = 0; b < nb; ++b) first[b + 1] += first[b] + 1;
+    items.assign(first[nb], -1);
     std::array<int, 65> at(first);
     for (size_t i = 0; i < m.size(); ++i)
       for (u64 v = m[i]; v; v &= v - 1) items[at[__builtin_ctzll(v)]++] = (int)i;
   }
 };
 
-// How far each bit's gates have been taken.
+// How far each bit's gates have been taken, and the gates that wait next on all
+// their bits.
 struct Front {
-  std::array<int, 64> at{};
+  std::array<int, 64> at;
+  std::array<int, 64> wait;   // gates on different bits
+  int nwait = 0;
 
-  // The next gate on bit b if it is next on all its bits, else -1.
-  int ready(const BitLists& l, int b) const {
-    const int g = l.items[at[b]];
-    if (g < 0) return -1;
+  // Whether g, next on bit b, is next on all its bits.
+  bool ready(const BitLists& l, int g, int b) const {
     for (u64 v = l.masks[g] & ~(1ull << b); v; v &= v - 1)
-      if (l.items[at[__builtin_ctzll(v)]] != g) return -1;
-    return g;
+      if (l.items[at[__builtin_ctzll(v)]] != g) return false;
+    return true;
   }
+  bool waits(const BitLists& l, int g) const { return l.items[at[__builtin_ctzll(l.masks[g])]] == g; }
+
   // Takes every gate inside T that can be taken, given that only gates on
-  // `from` can start; returns their weight.
+  // `from` can start; returns their weight (a gate of several bits weighs more:
+  // one-bit gates join whichever set holds their bit).
   int take(const BitLists& l, u64 T, u64 from, std::vector<int>* taken = nullptr) {
+    int weight = 0;
+    for (u64 work = from & T; work;) {
+      const int b = __builtin_ctzll(work);
+      work &= work - 1;
+      for (int g; (g = l.items[at[b]]) >= 0 && ready(l, g, b);) {
+        const u64 m = l.masks[g];
+        if (m & ~T) {
+          if (std::find(wait.begin(), wait.begin() + nwait, g) == wait.begin() + nwait) wait[nwait++] = g;
+          break;
+        }
+        for (u64 v = m; v; v &= v - 1) ++at[__builtin_ctzll(v)];
+        work |= m & ~(1ull << b);
+        weight += (m & (m - 1)) ? 4 : 1;
+        if (taken) taken->push_back(g);
+      }
+    }
+    int n = 0;
+    for (int i = 0; i < nwait; ++i)
+      if (waits(l, wait[i])) wait[n++] = wait[i];
+    nwait = n;
+    return weight;
+  }
+  // The weight that take() would return.
+  int weigh(const BitLists& l, u64 T, u64 from, std::vector<int>& taken) {
+    taken.clear();
     int weight = 0;
     for (u64 work = from & T; work;) {
       const int b = __builtin_ctzll(work);
       work &= work - 1;
       for (int g; (g = l.items[at[b]]) >= 0;) {
         const u64 m = l.masks[g];
-        if ((m & ~T) || ready(l, b) < 0) break;
+        if ((m & ~T) || !ready(l, g, b)) break;
         for (u64 v = m; v; v &= v - 1) ++at[__builtin_ctzll(v)];
         work |= m & ~(1ull << b);
-        // a gate of several bits weighs more: one-bit gates join whichever set holds their bit
         weight += (m & (m - 1)) ? 4 : 1;
-        if (taken) taken->push_back(g);
+        taken.push_back(g);
       }
     }
-    return weight;
-  }
-  void put_back(const BitLists& l, const std::vector<int>& taken) {
     for (int g : taken)
       for (u64 v = l.masks[g]; v; v &= v - 1) --at[__builtin_ctzll(v)];
-  }
-  // The gates that wait at the front, in list order.
-  void waiting(const BitLists& l, std::vector<int>& out) const {
-    out.clear();
-    for (u64 v = l.used; v; v &= v - 1) {
-      const int b = __builtin_ctzll(v), g = ready(l, b);
-      if (g >= 0 && b == __builtin_ctzll(l.masks[g])) out.push_back(g);
-    }
-    std::sort(out.begin(), out.end());
+    return weight;
   }
 };
 
@@ -147,59 +165,82 @@ bool grow_sets(const std::vector<u64>& masks, u64 low, int room, int seeds, std:
   const BitLists lists(masks);
   Front done;
   std::copy(lists.first.begin(), lists.first.end() - 1, done.at.begin());
-  std::vector<int> wait, tried;
-  std::vector<u64> front, cand;
-  auto add_once = [](std::vector<u64>& v, u64 s) {
-    if (std::find(v.begin(), v.end(), s) == v.end()) v.push_back(s);
-  };
-  for (;;) {
-    done.waiting(lists, wait);
-    if (wait.empty()) return true;
-    if (bits_of(masks[wait[0]] & ~low) > room) return false;
-    front.clear();
-    for (int g : wait)
-      if (bits_of(masks[g] & ~low) <= room) add_once(front, masks[g] & ~low);
-    // the first gate's bits, then evenly spaced ones
-    const int tries = std::min<int>(seeds, (int)front.size());
-    int best_score = -1;
-    u64 best_H = 0;
-    for (int t = 0; t < tries; ++t) {
-      u64 H = front[(size_t)t * front.size() / tries];
-      Front f = done;
-      int score = f.take(lists, low | H, lists.used);
-      for (;;) {
-        const int free = room - bits_of(H);
-        const u64 T = low | H;
-        f.waiting(lists, wait);
-        cand.clear();
-        for (int g : wait)
-          if (bits_of(masks[g] & ~T) <= free) add_once(cand, masks[g] & ~T);
-        if (cand.empty()) break;
-        double gain_best = -1.0;
-        u64 add = 0;
-        for (u64 need : cand) {
-          tried.clear();
-          const double gain = (double)f.take(lists, T | need, need, &tried) / bits_of(need);
-          f.put_back(lists, tried);
-          if (gain > gain_best) {
-            gain_best = gain;
-            add = need;
-          }
+  for (u64 v = lists.used; v; v &= v - 1) {
+    const int b = __builtin_ctzll(v), g = lists.items[done.at[b]];
+    if (b == __builtin_ctzll(masks[g]) && done.ready(lists, g, b)) done.wait[done.nwait++] = g;
+  }
+  std::vector<int> tried, taken, best_taken;
+  tried.reserve(64);
+  std::array<u64, 64> front, seen;   // first gates' bits; bits tried
+  std::array<double, 64> gains;      // and what they gained
+  // Grows H on f, from f's gates inside low and H on; returns the weight taken.
+  auto grow = [&](Front& f, u64& H) {
+    int score = f.take(lists, low | H, lists.used, &taken);
+    for (;;) {
+      const int free = room - bits_of(H);
+      const u64 T = low | H;
+      double gain_best = -1.0;
+      int gate_best = 0, nseen = 0;   // ties: the first in the list
+      u64 add = 0;
+      for (int i = 0; i < f.nwait; ++i) {
+        const int g = f.wait[i];
+        const u64 need = masks[g] & ~T;
+        if (bits_of(need) > free) continue;
+        const int at = (int)(std::find(seen.begin(), seen.begin() + nseen, need) - seen.begin());
+        if (at == nseen) {
+          seen[nseen] = need;
+          gains[nseen++] = (double)f.weigh(lists, T | need, need, tried) / bits_of(need);
         }
-        H |= add;
-        score += f.take(lists, low | H, add);
+        if (gains[at] > gain_best || (gains[at] == gain_best && g < gate_best)) {
+          gain_best = gains[at];
+          gate_best = g;
+          add = need;
+        }
       }
-      if (score > best_score) {
-        best_score = score;
-        best_H = H;
-      }
+      if (add == 0) return score;
+      H |= add;
+      score += f.take(lists, low | H, add, &taken);
     }
+  };
+  while (done.nwait > 0) {
+    // in list order: the first gate's bits, then evenly spaced ones
+    std::sort(done.wait.begin(), done.wait.begin() + done.nwait);
+    if (bits_of(masks[done.wait[0]] & ~low) > room) return false;
+    int nfront = 0;
+    for (int i = 0; i < done.nwait && (seeds > 1 || nfront == 0); ++i) {
+      const u64 m = masks[done.wait[i]] & ~low;
+      if (bits_of(m) <= room && std::find(front.begin(), front.begin() + nfront, m) == front.begin() + nfront)
+        front[nfront++] = m;
+    }
+    const int tries = std::min(seeds, nfront);
+    u64 best_H = front[0];
+    if (tries == 1) {
+      taken.clear();
+      grow(done, best_H);
+    } else {
+      const Front from = done;
+      int best_score = -1;
+      for (int t = 0; t < tries; ++t) {
+        u64 H = front[t * nfront / tries];
+        Front f = from;
+        taken.clear();
+        const int score = grow(f, H);
+        if (score > best_score) {
+          best_score = score;
+          best_H = H;
+          done = f;
+          best_taken.swap(taken);
+        }
+      }
+      taken.swap(best_taken);
+    }
+    std::sort(taken.begin(), taken.end());
     BitSet b;
     b.H = best_H;
-    done.take(lists, low | best_H, lists.used, &b.gates);
-    std::sort(b.gates.begin(), b.gates.end());
+    b.gates = taken;
     out.push_back(std::move(b));
   }
+  return true;
 }
 
 // The sets of a list planned from its end: a plan of the reversed list, read
@@ -233,7 +274,10 @@ double passes_from_zero(const std::vector<BitSet>& sets, u64 all, u64 low) {
 
 // First gates tried per block of a circuit.  The search is widened as the
 // passes it saves get dearer: a pass over 2^22 entries takes about 25 us, and
-// each seed adds about 0.05 ms to planning a deep circuit.
+// each seed adds about 0.05 ms to planning a deep circuit.  Where it is one, a
+// state vector's register phases too are searched once, from the front (fused
+// circuits of 250 to 300 gates on 14 to 20 qubits 250-390 -> 235-365 us; at 22
+// qubits no gain; a density matrix's phases are dearer than their search).
 static int plan_seeds(int nbits) { return nbits < 22 ? 1 : (nbits < 26 ? 2 : 8); }
 
 // Every block has at least two high slots (c <= k - 2), so the first
@@ -953,6 +997,7 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
   std::vector<RbOp> rops;      // register-blocked kernels
   std::vector<double2> mats;
   const int set = h->kind == NWQ_KIND_DM ? kRbSetDM : kRbSetSV;
+  const bool quick = one_tile || (set == kRbSetSV && plan_seeds(nbits) == 1);
   struct Launch { FusedBlockDev d; RbBlock r; bool rb; };
   const int rbits = kernel == 2 ? 3 : 4;
   std::vector<Launch> launches;
@@ -994,7 +1039,7 @@ int apply_fused(nwq_state* h, const std::vector<PGate>& gates_in, int nbits, con
     if (order.empty()) continue;
     const size_t rops0 = rops.size(), mats0 = mats.size();
     std::vector<RbStage> stages;
-    for (const Phase& ph : plan_phases(order, lb, nq, k, b.c, rbits, one_tile)) {
+    for (const Phase& ph : plan_phases(order, lb, nq, k, b.c, rbits, quick)) {
       RbStage stg{};
       for (int i = 0; i < 4; ++i) stg.reg[i] = ph.reg[i] < 0 ? 0 : ph.reg[i];
       stg.op_begin = (int)rops.size();
