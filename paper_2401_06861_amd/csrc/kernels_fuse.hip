@@ -567,16 +567,16 @@ __global__ __launch_bounds__(R == 4 ? 512 : 1024) __attribute__((amdgpu_waves_pe
       if (pi > 0) {
         const unsigned wa = thread_image(tid, ph.wr_t) << 3, ra = thread_image(tid, ph.rd_t) << 3;
         const bool across = (ph.count_flags & kRbBarrierInside) != 0;
-        if (ph.count_flags & kRbBarrierBefore) __syncthreads();
+        exchange_barrier((ph.count_flags & kRbBarrierBefore) != 0);
 #pragma unroll
         for (int j = 0; j < NV; ++j) *lds_at(wa ^ (register_image(j, ph.wr_r) << 3)) = v[j].x;
-        if (across) __syncthreads();
+        exchange_barrier(across);
 #pragma unroll
         for (int j = 0; j < NV; ++j) v[j].x = *lds_at(ra ^ (register_image(j, ph.rd_r) << 3));
-        if (across) __syncthreads();
+        exchange_barrier(across);
 #pragma unroll
         for (int j = 0; j < NV; ++j) *lds_at(wa ^ (register_image(j, ph.wr_r) << 3)) = v[j].y;
-        if (across) __syncthreads();
+        exchange_barrier(across);
 #pragma unroll
         for (int j = 0; j < NV; ++j) v[j].y = *lds_at(ra ^ (register_image(j, ph.rd_r) << 3));
       }

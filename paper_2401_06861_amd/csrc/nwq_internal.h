@@ -183,6 +183,18 @@ struct RbPhase {
   // reads are its own, and LDS serves a wave in order).
   unsigned short wr_t[kRbThreadBits], wr_r[4], rd_t[kRbThreadBits], rd_r[4];
 };
+// Between the LDS writes and reads of an exchange (and back): a barrier where
+// waves exchange entries.  Inside a wave LDS serves accesses in order, and the
+// fence, which takes no instruction, keeps the compiler to that order.
+__device__ __forceinline__ void exchange_barrier(bool across_waves) {
+  if (across_waves) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+  }
+}
 struct RbBlock {
   int k;
   int ph_begin, ph_count;   // range in the phase table

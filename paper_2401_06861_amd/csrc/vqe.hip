@@ -692,7 +692,7 @@ __global__ __launch_bounds__(kRegMaxThreads) void k_vqe_reg(
       if (pi > 0) {
         const RegMap wr = reg_map(ph + 2), rd = reg_map(ph + 9);
         write(p, wr);
-        if (cf & kRbBarrierInside) __syncthreads();
+        exchange_barrier((cf & kRbBarrierInside) != 0);
         read(p, rd);
       }
       for (int i = begin; i < begin + count; ++i) {   // the next op is read while this one runs
@@ -814,11 +814,11 @@ __global__ __launch_bounds__(kRegMaxThreads) void k_vqe_reg(
         const RegMap wr = reg_map(ph + 9), rd = reg_map(ph + 2);
         const bool across = (cf & kRbBarrierInside) != 0;
         write(p, wr);
-        if (across) __syncthreads();
+        exchange_barrier(across);
         read(p, rd);
-        if (across) __syncthreads();
+        exchange_barrier(across);
         write(l, wr);
-        if (across) __syncthreads();
+        exchange_barrier(across);
         read(l, rd);
       }
     }
@@ -1632,7 +1632,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   auto exchange = [&](double (&v)[8], unsigned wt, const RegMap& wr, unsigned rt, const RegMap& rd, bool across) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) buf[wt ^ register_slot(j, wr)] = v[j];
-    if (across) __syncthreads();
+    exchange_barrier(across);
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = buf[rt ^ register_slot(j, rd)];
   };
@@ -1669,13 +1669,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         const RegMap wr = reg_map(ph + 2), rd = reg_map(ph + 9);
         const unsigned wt = thread_slot(tid, wr), rt = thread_slot(tid, rd);
         const bool across = (cf & kRbBarrierInside) != 0;
-        if (cf & kRbBarrierBefore) __syncthreads();
+        exchange_barrier((cf & kRbBarrierBefore) != 0);
         exchange(p.x, wt, wr, rt, rd, across);
-        if (across) __syncthreads();
+        exchange_barrier(across);
         exchange(p.y, wt, wr, rt, rd, across);
-        if (across) __syncthreads();
+        exchange_barrier(across);
         exchange(l.x, wt, wr, rt, rd, across);
-        if (across) __syncthreads();
+        exchange_barrier(across);
         exchange(l.y, wt, wr, rt, rd, across);
       }
       for (int i = begin; i < begin + count; ++i) {   // the next op is read while this one runs
