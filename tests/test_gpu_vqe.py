@@ -479,3 +479,69 @@ def test_angles_of_any_size(V, torch, n, mode):
         assert abs(got[mode][0][b] - OV.energy(prog, theta[b], terms, n)) <= 1e-10, b
     assert np.max(np.abs(got[mode][1] - got[2][1])) <= 1e-12 * len(terms)
     ctx.close()
+
+
+@pytest.mark.parametrize("n,ops,threads", [(6, 3900, (64, 128, 256)), (6, 4500, (64, 256)), (3, 4100, (64,)),
+                                           (12, 0, (64, 128, 256, 512))])
+def test_lds_path_programs_beyond_the_register_tables(V, torch, n, ops, threads):
+    """Programs whose angles (two 16-byte numbers and 8 bytes per op, an RZ
+    sharing its RY's at best) and gradient sums (32 bytes per slot and wave)
+    alone exceed the 160 KiB of the register-resident kernel, or with more than
+    4096 ops, run in the LDS kernel (mode 1) at every workgroup size, with and
+    without gradients: against one kernel per gate.  ops = 0: the 15-layer
+    ansatz."""
+    A = W.AnsatzGate
+    rng = np.random.default_rng(ops + n)
+    if ops:
+        P = 60
+        prog = []
+        for _ in range(ops):
+            name = ["rx", "ry", "rz", "rx", "ry", "h", "cx", "rzz"][int(rng.integers(8))]
+            q = tuple(int(x) for x in rng.choice(n, size=2 if name in ("cx", "rzz") else 1, replace=False))
+            prog.append(A(name, q, int(rng.integers(P)) if name not in ("h", "cx") else -1))
+        theta = rng.uniform(-3.0, 3.0, (2, P))
+    else:
+        prog = W.hea_ansatz(n, 15)
+        theta, _ = W.vqe_batch(n, 15, B=2)
+        P = theta.shape[1]
+    slots = sum(g.param >= 0 for g in prog)
+    own = sum(g.param >= 0 and g.name != "rz" for g in prog)
+    waves = max(64, 1 << (n - 3)) // 64
+    assert len(prog) > 4096 or (16 << n) + 40 * own + 32 * waves * slots > 160 * 1024
+    ctx = V.VQE(n, prog, W.random_pauli_sum(n, 20, seed=n), n_params=P)
+    t = torch.from_numpy(theta).cuda()
+    ctx.set_config(2, 256, 0)
+    E2, G2 = ctx.eval(t)
+    for th in threads:
+        ctx.set_config(1, th, 0)
+        E, G = ctx.eval(t)
+        Eo, _ = ctx.eval(t, grad=False)
+        assert torch.max(torch.abs(E - Eo)).item() <= 1e-12, th
+        assert torch.max(torch.abs(E - E2)).item() <= 1e-10, th
+        assert torch.max(torch.abs(G - G2)).item() <= 1e-10, th
+    ctx.set_config(1, 1024, 0)          # its gradient sums do not fit the LDS, its energies do
+    Eo, _ = ctx.eval(t, grad=False)
+    assert torch.max(torch.abs(Eo - E2)).item() <= 1e-10
+    from paper_2401_06861_amd import nwq
+    if slots * 16 * 8 + (32 << n) > 160 * 1024:
+        with pytest.raises(nwq.NwqError):
+            ctx.eval(t)
+    ctx.close()
+
+
+@pytest.mark.parametrize("L,B", [(1, 3), (9, 2), (20, 5)])
+def test_fused_sweep_on_one_small_tile(V, torch, L, B):
+    """n = 8, the only register whose fused sweep (mode 3) keeps phi and lambda
+    in LDS: energies and gradients against one kernel per gate, over programs of
+    one dispatch and of several."""
+    n = 8
+    theta, h = W.vqe_batch(n, L, B=B)
+    ctx = V.VQE(n, W.hea_ansatz(n, L), W.tfim_hamiltonian(n, 1.0, h))
+    t = torch.from_numpy(theta).cuda()
+    got = {}
+    for mode in (2, 3):
+        ctx.set_config(mode, 256, 0)
+        got[mode] = [x.cpu().numpy() for x in ctx.eval(t)]
+    assert np.max(np.abs(got[3][0] - got[2][0])) <= 1e-12
+    assert np.max(np.abs(got[3][1] - got[2][1])) <= 1e-12
+    ctx.close()
