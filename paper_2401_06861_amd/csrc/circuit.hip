@@ -310,18 +310,6 @@ std::vector<Block> plan_blocks(const std::vector<PGate>& g, int n, int k, int c_
   return out;
 }
 
-// Tile index bit j is the j-th qubit (ascending) outside the tile.
-unsigned long long tile_mask_of(unsigned long long tile, unsigned long long support, int nbits) {
-  unsigned long long mask = 0;
-  int j = 0;
-  for (int q = 0; q < nbits; ++q) {
-    if ((tile >> q) & 1ull) continue;
-    if ((support >> q) & 1ull) mask |= 1ull << j;
-    ++j;
-  }
-  return mask;
-}
-
 // Widen a block's tile with unused high qubits (ascending) up to width
 // k_target (or n): more amplitudes per tile, same gates, same result.
 void pad_block(Block& b, int n, int k_target) {

@@ -102,10 +102,6 @@ struct Phase {
 // when the n bits fit one tile.  seeds: first gates tried per block.
 // from_zero: the plan only ever runs from |0...0>, so its first blocks are cheap.
 std::vector<Block> plan_blocks(const std::vector<PGate>& g, int n, int k, int c, int seeds, bool from_zero);
-// The tile indices (over the nbits qubits outside the tile's mask `tile`) that
-// can hold nonzero entries when the state is zero outside `support`: those with
-// bits in the returned mask only.
-unsigned long long tile_mask_of(unsigned long long tile, unsigned long long support, int nbits);
 // Tile width and low tile bits of a handle's fused blocks over nbits bits.
 int fusion_width(const nwq_state* h, int nbits);
 int fusion_low_bits(const nwq_state* h, int nbits);

@@ -1357,34 +1357,11 @@ namespace {
 // Fused path (any n > tile): gates grouped into k-qubit blocks as for state
 // vectors; the forward pass runs the register-blocked fused kernel over all
 // B states with a per-vector matrix table, the backward pass holds tiles of
-// phi and lambda in LDS and sweeps each block's gates in reverse.
+// phi and lambda in registers and sweeps each block's gates in reverse.
 // ---------------------------------------------------------------------------
-struct VqeBwdOp {
-  int kind;    // 0 rotation, 1 RZZ, 2 fixed 2x2, 3 CX, 4 CZ, 5 SWAP
-  int lo, hi;  // sorted tile-local bits
-  int b0, b1;  // tile-local bits in operator order
-  int axis;    // rotation axis
-  int slot;    // gradient slot or -1
-  int mat;     // index of the adjoint matrix in the per-vector table (double2 units)
-};
-
-constexpr int kBwdBlock = 256;
-constexpr int kBwdMaxOps = 256;   // 8 KiB of partial sums; two workgroups per CU still fit the LDS
-constexpr int kBwdStage = 8;   // tile entries per thread staged together (loads issued before LDS writes)
-
-__device__ __forceinline__ unsigned long long bwd_index(unsigned long long base, unsigned l, unsigned cmask, int c,
-                                                        int m, const FusedBlockDev& blk) {
-  unsigned long long g = base | (l & cmask);
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-    if (i < m && ((l >> (c + i)) & 1u)) g |= 1ull << blk.hi[i];
-  return g;
-}
-
-// Per-vector matrix table: for op i, entries [8i, 8i+4) hold the forward
+// Per-vector matrix table of the forward pass: entries [4i, 4i+4) hold op i's
 // matrix (2x2 row-major, or the 4 diagonal entries of RZZ / CZ indexed by
-// u = bit q0 + 2 bit q1) and [8i+4, 8i+8) the adjoint.  Every case stores
-// inside its own branch.
+// u = bit q0 + 2 bit q1).  Every case stores inside its own branch.
 __global__ __launch_bounds__(256) void k_vqe_mats(const VqeOp* __restrict__ ops, int nops,
                                                   const double2* __restrict__ fixed,
                                                   const double* __restrict__ theta, int P,
@@ -1394,161 +1371,20 @@ __global__ __launch_bounds__(256) void k_vqe_mats(const VqeOp* __restrict__ ops,
   const int b = blockIdx.y;
   const VqeOp op = ops[i];
   const double* th = theta + (size_t)b * P;
-  double2* t = table + ((size_t)b * nops + i) * 8;
+  double2* t = table + ((size_t)b * nops + i) * 4;
   if (op.kind == OP_ROT) {
     const M2 f = rot_matrix(op.axis, th[op.param], false);
     st(t + 0, f.m0); st(t + 1, f.m1); st(t + 2, f.m2); st(t + 3, f.m3);
-    const M2 a = rot_matrix(op.axis, th[op.param], true);
-    st(t + 4, a.m0); st(t + 5, a.m1); st(t + 6, a.m2); st(t + 7, a.m3);
   } else if (op.kind == OP_RZZ) {
     vd2 e, o;
     rzz_phases(th[op.param], false, e, o);
     st(t + 0, e); st(t + 1, o); st(t + 2, o); st(t + 3, e);
-    rzz_phases(th[op.param], true, e, o);
-    st(t + 4, e); st(t + 5, o); st(t + 6, o); st(t + 7, e);
   } else if (op.kind == OP_FIX1) {
-    for (int k = 0; k < 8; ++k) t[k] = fixed[8 * op.mat + k];
+    for (int k = 0; k < 4; ++k) t[k] = fixed[8 * op.mat + k];
   } else if (op.kind == OP_CZ) {
-    for (int k = 0; k < 8; ++k) st(t + k, mk((k & 3) == 3 ? -1.0 : 1.0, 0.0));
+    for (int k = 0; k < 4; ++k) st(t + k, mk(k == 3 ? -1.0 : 1.0, 0.0));
   } else {
-    for (int k = 0; k < 8; ++k) st(t + k, mk(0.0, 0.0));
-  }
-}
-
-__global__ __launch_bounds__(kBwdBlock) void k_vqe_bwd_tile(double2* __restrict__ phi0, double2* __restrict__ lam0,
-                                                            int n, FusedBlockDev blk,
-                                                            const VqeBwdOp* __restrict__ ops,
-                                                            const double2* __restrict__ table0, int mat_stride,
-                                                            int nslots, double* __restrict__ gpart,
-                                                            unsigned long long ntiles) {
-  extern __shared__ double2 sh[];
-  __shared__ double acc[kBwdMaxOps][kBwdBlock / kWave];
-  constexpr int NW = kBwdBlock / kWave;
-  const int c = blk.c, m = blk.m, k = c + m;
-  const unsigned len = 1u << k;
-  double2* tp = sh;
-  double2* tl = sh + len;
-  const unsigned long long N = 1ull << n;
-  double2* __restrict__ phi = phi0 + (size_t)blockIdx.y * N;
-  double2* __restrict__ lam = lam0 + (size_t)blockIdx.y * N;
-  const double2* __restrict__ table = table0 + (size_t)blockIdx.y * mat_stride;
-  
-  const unsigned cmask = (1u << c) - 1u;
-  const unsigned tid = threadIdx.x;
-  const int lane = tid & (kWave - 1), wave = tid / kWave;
-  for (int i = tid; i < blk.op_count * NW; i += kBwdBlock) acc[i / NW][i % NW] = 0.0;
-  for (unsigned long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    unsigned long long base = tile << c;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i < m) {
-        const int q = blk.hi[i];
-        base = ((base >> q) << (q + 1)) | (base & ((1ull << q) - 1ull));
-      }
-    }
-    __syncthreads();
-    if (len >= kBwdStage * kBwdBlock) {
-      for (unsigned l0 = tid; l0 < len; l0 += kBwdStage * kBwdBlock) {
-        vd2 rp[kBwdStage], rl[kBwdStage];
-#pragma unroll
-        for (int j = 0; j < kBwdStage; ++j) {
-          const unsigned long long g = bwd_index(base, l0 + j * kBwdBlock, cmask, c, m, blk);
-          rp[j] = ld(phi + g);
-          rl[j] = ld(lam + g);
-        }
-#pragma unroll
-        for (int j = 0; j < kBwdStage; ++j) {
-          st(tp + l0 + j * kBwdBlock, rp[j]);
-          st(tl + l0 + j * kBwdBlock, rl[j]);
-        }
-      }
-    } else {
-      for (unsigned l = tid; l < len; l += kBwdBlock) {
-        const unsigned long long g = bwd_index(base, l, cmask, c, m, blk);
-        tp[l] = phi[g];
-        tl[l] = lam[g];
-      }
-    }
-    for (int oi = 0; oi < blk.op_count; ++oi) {
-      const VqeBwdOp op = ops[blk.op_begin + oi];
-      const double2* M = table + op.mat;
-      __syncthreads();
-      double g = 0.0;
-      if (op.kind == 0 || op.kind == 2) {
-        const vd2 m0 = ld(M), m1 = ld(M + 1), m2 = ld(M + 2), m3 = ld(M + 3);
-        const unsigned off = 1u << op.lo;
-        for (unsigned p = tid; p < (len >> 1); p += kBwdBlock) {
-          const unsigned i0 = ins0(p, op.lo);
-          const vd2 p0 = ld(tp + i0), p1 = ld(tp + i0 + off);
-          const vd2 l0 = ld(tl + i0), l1 = ld(tl + i0 + off);
-          if (op.kind == 0) g += pair_grad(op.axis, p0, p1, l0, l1);
-          st(tp + i0, cfma(m0, p0, cmul(m1, p1)));
-          st(tp + i0 + off, cfma(m2, p0, cmul(m3, p1)));
-          st(tl + i0, cfma(m0, l0, cmul(m1, l1)));
-          st(tl + i0 + off, cfma(m2, l0, cmul(m3, l1)));
-        }
-      } else if (op.kind == 1 || op.kind == 4) {
-        const vd2 d0 = ld(M), d1 = ld(M + 1), d2 = ld(M + 2), d3 = ld(M + 3);
-        for (unsigned l = tid; l < len; l += kBwdBlock) {
-          const bool a = (l >> op.b0) & 1u, b = (l >> op.b1) & 1u;
-          const vd2 f = b ? (a ? d3 : d2) : (a ? d1 : d0);
-          const vd2 pv = ld(tp + l), lv = ld(tl + l);
-          if (op.kind == 1) {
-            const double t = lv.x * pv.y - lv.y * pv.x;   // Im(conj(l) p) times the ZZ eigenvalue
-            g += (a != b) ? -t : t;
-          }
-          st(tp + l, cmul(f, pv));
-          st(tl + l, cmul(f, lv));
-        }
-      } else {   // 3 CX (control b0, target b1), 5 SWAP
-        const unsigned oa = 1u << op.b0;
-        const unsigned ob = op.kind == 3 ? (1u << op.b0) + (1u << op.b1) : (1u << op.b1);
-        for (unsigned p = tid; p < (len >> 2); p += kBwdBlock) {
-          const unsigned b = ins0(ins0(p, op.lo), op.hi);
-          const vd2 x = ld(tp + b + oa), y = ld(tp + b + ob);
-          st(tp + b + oa, y);
-          st(tp + b + ob, x);
-          const vd2 u = ld(tl + b + oa), w = ld(tl + b + ob);
-          st(tl + b + oa, w);
-          st(tl + b + ob, u);
-        }
-      }
-      if (op.slot >= 0) {
-        const double w = wave_sum(g);
-        if (lane == 0) acc[oi][wave] += w;
-      }
-    }
-    __syncthreads();
-    if (len >= kBwdStage * kBwdBlock) {
-      for (unsigned l0 = tid; l0 < len; l0 += kBwdStage * kBwdBlock) {
-        vd2 rp[kBwdStage], rl[kBwdStage];
-#pragma unroll
-        for (int j = 0; j < kBwdStage; ++j) {
-          rp[j] = ld(tp + l0 + j * kBwdBlock);
-          rl[j] = ld(tl + l0 + j * kBwdBlock);
-        }
-#pragma unroll
-        for (int j = 0; j < kBwdStage; ++j) {
-          const unsigned long long g = bwd_index(base, l0 + j * kBwdBlock, cmask, c, m, blk);
-          st(phi + g, rp[j]);
-          st(lam + g, rl[j]);
-        }
-      }
-    } else {
-      for (unsigned l = tid; l < len; l += kBwdBlock) {
-        const unsigned long long g = bwd_index(base, l, cmask, c, m, blk);
-        phi[g] = tp[l];
-        lam[g] = tl[l];
-      }
-    }
-  }
-  __syncthreads();
-  for (int oi = tid; oi < blk.op_count; oi += kBwdBlock) {
-    const int slot = ops[blk.op_begin + oi].slot;
-    if (slot < 0) continue;
-    double v = 0.0;
-    for (int w = 0; w < NW; ++w) v += acc[oi][w];
-    gpart[((size_t)blockIdx.y * nslots + slot) * gridDim.x + blockIdx.x] = v;
+    for (int k = 0; k < 4; ++k) st(t + k, mk(0.0, 0.0));
   }
 }
 
@@ -1594,7 +1430,7 @@ __device__ __forceinline__ unsigned long long image_of(unsigned v, const unsigne
 
 // LDS of a block: the exchange buffer, angles, phases, ops, sums.
 inline size_t bwd_reg_lds(int k, int phases, int nops, int nlocal) {
-  const int nw = (1 << (k - 3)) / kWave;
+  const int nw = std::max(1, (1 << (k - 3)) / kWave);
   return (sizeof(double) << k) + (size_t)nops * (2 * sizeof(double2) + sizeof(int2)) + (size_t)phases * sizeof(RbPhase) +
          (size_t)nlocal * nw * 4 * sizeof(double) + 64;
 }
@@ -1615,7 +1451,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     double* __restrict__ gpart, unsigned long long ntiles, unsigned long long mask, unsigned long long step) {
   extern __shared__ double2 lds[];
   const unsigned tid = threadIdx.x, nt = blockDim.x;
-  const int lane = tid & (kWave - 1), wave = tid / kWave, NW = (int)nt / kWave, P = blk.ph_count;
+  const int lane = tid & (kWave - 1), wave = tid / kWave, NW = (int)(nt + kWave - 1) / kWave, P = blk.ph_count;
   double* buf = reinterpret_cast<double*>(lds);                      // one component of the tile
   double2* cs = lds + (1u << (blk.k - 1));                           // [nops][2] the angles' two numbers
   unsigned* lph = reinterpret_cast<unsigned*>(cs + 2 * nops);        // [P] phases (16 words each)
@@ -1761,8 +1597,12 @@ struct nwq_vqe {
   int fused_k = 12;
   int low_bits = 0;            // low tile bits of the planned blocks: 0 = kVqeLowBits
   int fused_rbits = 4;         // register bits per phase of the forward kernel
-  bool bwd_rb = false;         // backward sweep register-blocked (3 bits) when every tile has >= 2^9 entries
-  size_t fused_rop_off = 0, fused_slot_off = 0;   // its ops and the slots of its gradient sums in d_fused
+  size_t fused_rop_off = 0, fused_slot_off = 0;   // backward ops and the slots of their gradient sums in d_fused
+  // Before a block's gates phi is zero wherever a qubit that no earlier block
+  // touched is set, so tiles set on such a qubit (outside the block's own) add
+  // nothing to any Im<lambda|P|phi>; the dispatches that follow in the sweep
+  // (earlier blocks, smaller supports) read none of them, and neither vector
+  // is read after the sweep.  The first planned block runs tile 0 only.
   struct BwdRegBlock {
     nwq::RbBlock d;
     int op0, nops, slot0, nlocal;
@@ -1770,14 +1610,6 @@ struct nwq_vqe {
   };
   std::vector<BwdRegBlock> bwd_reg;
   std::vector<nwq::RbBlock> fwd_blocks;
-  std::vector<nwq::FusedBlockDev> bwd_blocks;
-  // Tiles of each backward dispatch: tile indices with bits in the mask only.
-  // Before a block's gates phi is zero wherever a qubit that no earlier block
-  // touched is set, so tiles set on such a qubit (outside the block's own) add
-  // nothing to any Im<lambda|P|phi>; the dispatches that follow in the sweep
-  // (earlier blocks, smaller supports) read none of them, and neither vector
-  // is read after the sweep.  The first planned block runs tile 0 only.
-  std::vector<unsigned long long> bwd_mask;
   // lambda = H phi of the fused schedule: tiled passes (and a gather pass for
   // terms that fit no tile), in launch order
   struct HLaunch {
@@ -1788,7 +1620,7 @@ struct nwq_vqe {
   std::vector<HLaunch> hlaunch;
   size_t fused_hterm_off = 0, fused_widx_off = 0;
   void* d_fused = nullptr;     // [backward phases][forward phases][forward ops][backward ops][H terms]
-  size_t fused_fph_off = 0, fused_ops_off = 0, fused_bwd_off = 0;
+  size_t fused_fph_off = 0, fused_ops_off = 0;
   nwq::VqeConfig cfg;
   std::map<std::pair<int, int>, hipGraphExec_t> graphs;   // (B, want_grad) -> exec
   int fused_flags = 3;         // fused schedule: bit 0 non-temporal tile loads and stores, bit 1 direct
@@ -1877,7 +1709,7 @@ static size_t global_bytes_per_vector(const nwq_vqe* h) {
   const size_t G = (size_t)blocks_per_state(h);
   const size_t P = std::max(1, h->P), S = std::max(1, h->nslots), T = std::max(1, h->nterms), O = std::max(1, h->nops);
   return 2 * N * sizeof(double2) + G * sizeof(double) + S * G * sizeof(double) + 2 * P * sizeof(double) +
-         sizeof(double) + T * sizeof(double) + O * 8 * sizeof(double2) + S * sizeof(double);
+         sizeof(double) + T * sizeof(double) + O * 4 * sizeof(double2) + S * sizeof(double);
 }
 
 static int ensure_global(nwq_vqe* h, int B) {
@@ -1902,7 +1734,7 @@ static int ensure_global(nwq_vqe* h, int B) {
   if (!rc) rc = check_hip(hipMalloc(&h->d_E, (size_t)B * sizeof(double)), "hipMalloc(vqe E)");
   if (!rc) rc = check_hip(hipMalloc(&h->d_grad, (size_t)B * std::max(1, h->P) * sizeof(double)), "hipMalloc(vqe grad)");
   if (!rc) rc = check_hip(hipMalloc(&h->d_coeffs, (size_t)B * std::max(1, h->nterms) * sizeof(double)), "hipMalloc(vqe coeffs)");
-  if (!rc) rc = check_hip(hipMalloc(&h->d_table, (size_t)B * std::max(1, h->nops) * 8 * sizeof(double2)), "hipMalloc(vqe table)");
+  if (!rc) rc = check_hip(hipMalloc(&h->d_table, (size_t)B * std::max(1, h->nops) * 4 * sizeof(double2)), "hipMalloc(vqe table)");
   if (!rc) rc = check_hip(hipMalloc(&h->d_ssum, (size_t)B * std::max(1, h->nslots) * sizeof(double)), "hipMalloc(vqe slot sums)");
   if (rc) return rc;
   h->Bcap = B;
@@ -1942,7 +1774,7 @@ static int launch_global(nwq_vqe* h, int B, const double* theta, const double* c
 
 // Fused program: blocks over the ops at tile width fused_k, forward phases for
 // the register-blocked kernel, backward ops in reverse per block (at most
-// kBwdRegOps per dispatch, kBwdMaxOps for tiles below 2^9).
+// kBwdRegOps per dispatch).
 // Low tile bits of the fused schedule's blocks (clamped to [k - 8, k - 2] at
 // width k).  Fewer low bits give shorter runs and fewer blocks, which saves more
 // (n=20, L=8, 256 vectors, blocks filled in gate order: 26 backward blocks with
@@ -2002,10 +1834,7 @@ static int build_fused(nwq_vqe* h) {
   std::vector<RbPhase> fphases;     // forward
   std::vector<RbPhase> phases;      // backward
   std::vector<RbOp> fops;
-  std::vector<VqeBwdOp> bops;
   h->fwd_blocks.clear();
-  h->bwd_blocks.clear();
-  h->bwd_mask.clear();
   h->bwd_reg.clear();
   std::vector<Block> padded(blocks);
   for (Block& b : padded) pad_block(b, n, std::max(k, 8));
@@ -2041,7 +1870,7 @@ static int build_fused(nwq_vqe* h) {
         const VqeOp& op = h->ops[gi];
         const int r0 = ridx(lb[gi][0]), r1 = nq[gi] == 2 ? ridx(lb[gi][1]) : 0;
         const int pair = nq[gi] == 2 ? rb_pair(std::min(r0, r1), std::max(r0, r1)) : 0;
-        FwdOp f{{0, 8 * gi}, 0, r0, r1, nq[gi] == 2 ? (1u << r0) | (1u << r1) : 1u << r0};
+        FwdOp f{{0, 4 * gi}, 0, r0, r1, nq[gi] == 2 ? (1u << r0) | (1u << r1) : 1u << r0};
         // the parts of a rotation that are zero for every theta are skipped
         if (op.kind == OP_ROT) f.o.code = (op.axis == 2 ? kRbDiag1 : op.axis == 1 ? kRbReal1 : kRbXt1) + r0;
         else if (op.kind == OP_FIX1) f.o.code = kRbGen1 + r0;
@@ -2066,8 +1895,6 @@ static int build_fused(nwq_vqe* h) {
     h->fwd_blocks.push_back(d);
   }
   for (int i = 0; i < 2; ++i) fops.push_back(RbOp{kRbCopy, 0});   // read ahead, not run
-  // Backward: register-blocked with 3 register bits when every tile gives at
-  // least one full wave (2^(k-3) >= 64), else one LDS pass per gate.
   constexpr int kBwdBits = 3;
   // The backward sweep plans its own blocks when the forward width exceeds
   // what its kernels take (tiles of at most 2^11: 256 threads x 8 amplitudes):
@@ -2081,19 +1908,6 @@ static int build_fused(nwq_vqe* h) {
     if (bpadded.empty() && h->nops > 0) return set_error(NWQ_EINVAL, "fusion planner made no progress");
     for (Block& b : bpadded) pad_block(b, n, std::max(kbw, 8));
   }
-  for (const Block& b : bpadded) max_bwd_lds = std::max(max_bwd_lds, (size_t)2 * sizeof(double2) << (b.c + b.m));
-  h->bwd_rb = true;
-  for (const Block& b : bpadded) h->bwd_rb = h->bwd_rb && (b.c + b.m) - kBwdBits >= 6;
-  std::vector<unsigned long long> masks;   // tile masks of bpadded, in its order
-  {
-    unsigned long long support = 0;
-    for (const Block& b : bpadded) {
-      unsigned long long tile = (1ull << b.c) - 1ull;
-      for (int i = 0; i < b.m; ++i) tile |= 1ull << b.hi[i];
-      masks.push_back(tile_mask_of(tile, support, n));
-      support |= tile;
-    }
-  }
   std::vector<RegOpV> rops;
   std::vector<int> slots;
   unsigned long long touched = 0;   // union of the tiles of the blocks before
@@ -2102,7 +1916,7 @@ static int build_fused(nwq_vqe* h) {
     before.push_back(touched);
     touched |= tile_bits(b);
   }
-  for (auto bit = bpadded.rbegin(); h->bwd_rb && bit != bpadded.rend(); ++bit) {
+  for (auto bit = bpadded.rbegin(); bit != bpadded.rend(); ++bit) {
     const Block& b = *bit;
     const int kb = b.c + b.m;
     std::vector<std::array<int, 4>> lb(g.size());
@@ -2161,37 +1975,6 @@ static int build_fused(nwq_vqe* h) {
       blk.mask = before[bpadded.rend() - bit - 1] & ~blk.d.tile;
       max_bwd_lds = std::max(max_bwd_lds, bwd_reg_lds(kb, blk.d.ph_count, blk.nops, blk.nlocal));
       h->bwd_reg.push_back(blk);
-    }
-  }
-  for (auto bit = bpadded.rbegin(); !h->bwd_rb && bit != bpadded.rend(); ++bit) {
-    const Block& b = *bit;
-    std::vector<VqeBwdOp> rev;
-    for (auto it = b.gates.rbegin(); it != b.gates.rend(); ++it) {
-      const int gi = *it;
-      const VqeOp& op = h->ops[gi];
-      VqeBwdOp o{};
-      o.b0 = local_bit(b, op.q0);
-      o.b1 = g[gi].nq == 2 ? local_bit(b, op.q1) : 0;
-      o.lo = g[gi].nq == 2 ? std::min(o.b0, o.b1) : o.b0;
-      o.hi = g[gi].nq == 2 ? std::max(o.b0, o.b1) : 0;
-      o.axis = op.axis;
-      o.slot = op.slot;
-      o.mat = 8 * gi + 4;
-      o.kind = op.kind == OP_ROT ? 0 : op.kind == OP_RZZ ? 1 : op.kind == OP_FIX1 ? 2 : op.kind == OP_CX ? 3
-             : op.kind == OP_CZ ? 4 : 5;
-      rev.push_back(o);
-    }
-    for (size_t s0 = 0; s0 < rev.size(); s0 += kBwdMaxOps) {
-      FusedBlockDev d{};
-      d.c = b.c;
-      d.m = b.m;
-      for (int i = 0; i < b.m; ++i) d.hi[i] = b.hi[i];
-      d.op_begin = (int)bops.size();
-      const size_t e = std::min(rev.size(), s0 + kBwdMaxOps);
-      for (size_t i = s0; i < e; ++i) bops.push_back(rev[i]);
-      d.op_count = (int)(e - s0);
-      h->bwd_blocks.push_back(d);
-      h->bwd_mask.push_back(masks[bpadded.rend() - bit - 1]);
     }
   }
   // lambda = H phi: the first pass takes tiles of the low kt bits with every
@@ -2278,8 +2061,7 @@ static int build_fused(nwq_vqe* h) {
   const size_t ph_bytes = phases.size() * sizeof(RbPhase);
   h->fused_fph_off = (ph_bytes + 255) & ~size_t(255);
   h->fused_ops_off = (h->fused_fph_off + fphases.size() * sizeof(RbPhase) + 255) & ~size_t(255);
-  h->fused_bwd_off = (h->fused_ops_off + fops.size() * sizeof(RbOp) + 255) & ~size_t(255);
-  h->fused_rop_off = (h->fused_bwd_off + bops.size() * sizeof(VqeBwdOp) + 255) & ~size_t(255);
+  h->fused_rop_off = (h->fused_ops_off + fops.size() * sizeof(RbOp) + 255) & ~size_t(255);
   h->fused_slot_off = (h->fused_rop_off + rops.size() * sizeof(RegOpV) + 255) & ~size_t(255);
   h->fused_hterm_off = (h->fused_slot_off + slots.size() * sizeof(int) + 255) & ~size_t(255);
   h->fused_widx_off = (h->fused_hterm_off + hterms.size() * sizeof(HTerm) + 255) & ~size_t(255);
@@ -2288,7 +2070,6 @@ static int build_fused(nwq_vqe* h) {
   if (!phases.empty()) std::memcpy(prog.data(), phases.data(), ph_bytes);
   if (!fphases.empty()) std::memcpy(prog.data() + h->fused_fph_off, fphases.data(), fphases.size() * sizeof(RbPhase));
   if (!fops.empty()) std::memcpy(prog.data() + h->fused_ops_off, fops.data(), fops.size() * sizeof(RbOp));
-  if (!bops.empty()) std::memcpy(prog.data() + h->fused_bwd_off, bops.data(), bops.size() * sizeof(VqeBwdOp));
   if (!rops.empty()) std::memcpy(prog.data() + h->fused_rop_off, rops.data(), rops.size() * sizeof(RegOpV));
   if (!slots.empty()) std::memcpy(prog.data() + h->fused_slot_off, slots.data(), slots.size() * sizeof(int));
   if (!hterms.empty()) std::memcpy(prog.data() + h->fused_hterm_off, hterms.data(), hterms.size() * sizeof(HTerm));
@@ -2297,7 +2078,7 @@ static int build_fused(nwq_vqe* h) {
   if (max_bwd_lds > (size_t)kMaxDynamicLds ||
       (sizeof(double2) << kHTileBits) > (size_t)kMaxDynamicLds)
     return set_error(NWQ_EINVAL, "VQE tile larger than the dynamic LDS limit");
-  int rc = enable_dynamic_lds((const void*)k_vqe_bwd_tile);
+  int rc = NWQ_OK;
   for (const void* f : {(const void*)k_vqe_hphi_tile<false, false>, (const void*)k_vqe_hphi_tile<true, false>,
                         (const void*)k_vqe_hphi_tile<false, true>, (const void*)k_vqe_hphi_tile<true, true>,
                         (const void*)k_vqe_bwd_reg<false>, (const void*)k_vqe_bwd_reg<true>})
@@ -2412,8 +2193,7 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
   const dim3 grid(G, B);
   const RbPhase* dfp = reinterpret_cast<const RbPhase*>(static_cast<char*>(h->d_fused) + h->fused_fph_off);
   const RbOp* dfo = reinterpret_cast<const RbOp*>(static_cast<char*>(h->d_fused) + h->fused_ops_off);
-  const VqeBwdOp* dbo = reinterpret_cast<const VqeBwdOp*>(static_cast<char*>(h->d_fused) + h->fused_bwd_off);
-  const int stride = 8 * h->nops;
+  const int stride = 4 * h->nops;
   hipLaunchKernelGGL(k_vqe_init, grid, dim3(kVqeBlock), 0, s, h->d_phi, h->n);
   hipLaunchKernelGGL(k_vqe_mats, dim3((h->nops + 255) / 256, B), dim3(256), 0, s, h->d_ops, h->nops, h->d_fixed,
                      theta, h->P, h->d_table);
@@ -2456,15 +2236,6 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
                          bwd_reg_lds(b.d.k, b.d.ph_count, b.nops, b.nlocal), s, h->d_phi, h->d_lam, h->n, b.d, dph,
                          dro + b.op0, b.nops, dsl + b.slot0, b.nlocal, h->d_fixed, theta, h->P, h->nslots, h->d_gpart,
                          nt, b.mask, deposit(G, b.mask));
-    }
-    for (size_t bi = 0; bi < h->bwd_blocks.size(); ++bi) {
-      const FusedBlockDev& d = h->bwd_blocks[bi];
-      const int kb = d.c + d.m;
-      const unsigned long long nt = 1ull << __builtin_popcountll(h->bwd_mask[bi]);
-      // tiles below 2^9 entries: the whole state is one tile
-      const size_t lds = 2 * sizeof(double2) << kb;
-      hipLaunchKernelGGL(k_vqe_bwd_tile, grid, dim3(kBwdBlock), lds, s, h->d_phi, h->d_lam, h->n, d, dbo,
-                         h->d_table, stride, h->nslots, h->d_gpart, nt);
     }
   }
   if (grad != nullptr && h->nslots > 0)
