@@ -402,7 +402,8 @@ int nwq_vqe_batch_release(void);
 
 /* Autotuner: times every valid (mode, threads, blocks_per_state) candidate on
  * B zero parameter vectors with HIP events, keeps the fastest and returns
- * its time per batch in *best_ms.  Synchronises. */
+ * its time per batch in *best_ms (mode 1 keeps the threads that are set where
+ * the register-resident kernel runs, which does not use them).  Synchronises. */
 int nwq_vqe_autotune(nwq_vqe_handle h, int B, int with_grad, double* best_ms);
 
 /* ---------------------------------------------------------------------------
@@ -471,8 +472,9 @@ int nwq_autotune(nwq_handle h, int reps, double* best_ms);
  * nwq_apply_circuit) from |0...0> as nwq_run_circuit does (the reset
  * included) once untimed and reps times timed under
  * each candidate: unfused, and every fusion width from 6 to min(13, n) with
- * each fused kernel (the register-blocked ones only on 8 or more qubits).
- * Keeps the fastest on the handle and returns it in *best_k (0 = unfused)
+ * each fused kernel (the register-blocked ones only on 8 or more qubits; a
+ * width that runs the blocks of a narrower one, 13 on registers of more than 13
+ * qubits, takes its time and is not picked).  Keeps the fastest on the handle and returns it in *best_k (0 = unfused)
  * and *best_rb (the nwq_set_fusion_kernel value).  If ms_out is non-NULL it
  * receives NWQ_FUSION_CANDIDATES times in ms per circuit (-1 for candidates
  * not run): index 0 unfused, 1 + 3 * (k - 6) + kernel for width k.

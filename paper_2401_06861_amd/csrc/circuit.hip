@@ -1298,10 +1298,17 @@ int nwq_autotune_fusion(nwq_handle h, int n_gates, const int* types, const int* 
   if (!rc) rc = check_hip(hipEventCreate(&e1), "hipEventCreate");
   double best = 1e300;
   Cand pick{saved_k, saved_rb};
+  std::array<double, NWQ_FUSION_CANDIDATES> timed;   // index: as ms_out
+  auto slot = [](int k, int rb) { return k == 0 ? 0 : 1 + 3 * (k - 6) + rb; };
   for (const Cand& c : cands) {
     if (rc) break;
     h->fuse_k = c.k;
     h->fuse_rb = c.rb;
+    const int runs = c.k == 0 ? 0 : fusion_width(h, h->nbits);
+    if (runs < c.k) {   // the blocks of a narrower width: its time
+      if (ms_out) ms_out[slot(c.k, c.rb)] = timed[slot(runs, c.rb)];
+      continue;
+    }
     double total = 0.0;
     for (int r = 0; r <= reps && !rc; ++r) {   // r == 0 is the untimed run
       rc = check_hip(hipEventRecord(e0, h->stream), "hipEventRecord");
@@ -1314,8 +1321,8 @@ int nwq_autotune_fusion(nwq_handle h, int n_gates, const int* types, const int* 
       if (r > 0) total += ms;
     }
     if (rc) break;
-    const double per = total / reps;
-    if (ms_out) ms_out[c.k == 0 ? 0 : 1 + 3 * (c.k - 6) + c.rb] = per;
+    const double per = timed[slot(c.k, c.rb)] = total / reps;
+    if (ms_out) ms_out[slot(c.k, c.rb)] = per;
     if (per < best) {
       best = per;
       pick = c;

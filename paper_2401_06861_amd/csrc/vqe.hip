@@ -2557,9 +2557,12 @@ int nwq_vqe_autotune(nwq_vqe_handle h, int B, int with_grad, double* best_ms) {
   if (!rc) rc = check_hip(hipEventCreate(&t1), "hipEventCreate");
   struct Cand { int mode, threads, bps; };
   std::vector<Cand> cands;
-  if (h->n <= 12)
+  if (reg_fits(h)) {   // whatever the workgroup size
+    cands.push_back({1, h->cfg.threads, 0});
+  } else if (h->n <= 12) {
     for (int t : {64, 128, 256, 512, 1024})
       if (lds_fits(h, t, with_grad != 0)) cands.push_back({1, t, 0});
+  }
   const unsigned long long pairs = 1ull << (h->n - 1);
   for (int bps : {0, 8, 16, 32, 64, 128, 256, 512, 1024})
     if (bps == 0 || (unsigned long long)bps * 256 <= pairs) cands.push_back({2, h->cfg.threads, bps});

@@ -811,3 +811,14 @@ def test_fusion_plan_is_the_plan_that_runs(nwq, n, k):
         nwq.nwq_apply_circuit(st.h, *arrays)
         assert nwq.nwq_fusion_stats(st.h)[0] == nwq.nwq_fusion_plan(n, k, *arrays[:2])[0], seed
     st.close()
+
+
+def test_fusion_autotuner_picks_a_width_that_runs(nwq):
+    """On more than 13 qubits the register-blocked kernels run width 13 in the
+    blocks of width 12: the tuner gives it that time and does not pick it."""
+    for n, depth in ((14, 12), (17, 6)):
+        st = nwq.SVState(n)
+        k, rb, table = nwq.nwq_autotune_fusion(st.h, *nwq.circuit_arrays(W.brickwork_circuit(n, depth, seed=1)), reps=2)
+        assert table[(13, 1)] == table[(12, 1)] and table[(13, 2)] == table[(12, 2)]
+        assert (k, rb) not in ((13, 1), (13, 2)) and table[(k, rb)] == min(table.values())
+        st.close()

@@ -545,3 +545,17 @@ def test_fused_sweep_on_one_small_tile(V, torch, L, B):
     assert np.max(np.abs(got[3][0] - got[2][0])) <= 1e-12
     assert np.max(np.abs(got[3][1] - got[2][1])) <= 1e-12
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [4, 7, 9])
+def test_autotune_keeps_threads_that_do_not_matter(V, torch, n):
+    """Where the register-resident kernel runs, the workgroup size is not timed
+    (its candidates would be one launch, told apart by noise)."""
+    theta, h = W.vqe_batch(n, 2, B=16)
+    ctx = V.VQE(n, W.hea_ansatz(n, 2), W.tfim_hamiltonian(n, 1.0, h))
+    for threads in (64, 256, 1024, 128, 512):
+        ctx.set_config(0, threads, 0)
+        ctx.autotune(16)
+        mode, got, _ = ctx.get_config()
+        assert got == threads and mode in (1, 2, 3)
+    ctx.close()
