@@ -474,14 +474,6 @@ __device__ __forceinline__ void gst(double2* p, vd2 v) {
   else stv(p, v);
 }
 
-// The bits of v deposited, lowest first, at the set bits of mask.
-__device__ __forceinline__ unsigned long long pdep64(unsigned long long v, unsigned long long mask) {
-  unsigned long long r = 0;
-  for (; mask; mask &= mask - 1, v >>= 1)
-    if (v & 1ull) r |= mask & (~mask + 1ull);
-  return r;
-}
-
 // XOR of the images of the set bits of v; images of register j: a constant
 // combination of the register bits' images.
 __device__ __forceinline__ unsigned thread_image(unsigned v, const unsigned short (&img)[kRbThreadBits]) {
@@ -531,7 +523,7 @@ __global__ __launch_bounds__(R == 4 ? 512 : 1024) __attribute__((amdgpu_waves_pe
   vd2 v[NV];
   // the tile's index bits plus gridDim.x, carried over the mask's gaps
   auto advance = [&](unsigned long long base) { return ((base | ~mask) + step) & mask; };
-  unsigned long long tile = blockIdx.x, base = pdep64(tile, mask);
+  unsigned long long tile = blockIdx.x, base = deposit_bits(tile, mask);
   // One load per 64-byte line brings the block's program into this XCD's L2,
   // ahead of the first tile's loads: each phase and op is read through the
   // scalar cache when its turn comes, one after the other, and a workgroup
@@ -625,12 +617,7 @@ void launch_fused_rb(hipStream_t s, double2* a, int nbits, const RbBlock& blk, c
   const unsigned grid = (unsigned)(ntiles < cap ? ntiles : cap);
   const size_t lds = sizeof(double) << blk.k;   // at most 64 KiB
   const unsigned long long stride = batch > 1 ? (1ull << nbits) : 0ull;
-  unsigned long long step = 0;   // gridDim.x deposited at the mask's bits
-  {
-    unsigned long long m = mask;
-    for (unsigned v = grid; v && m; v >>= 1, m &= m - 1)
-      if (v & 1u) step |= m & (~m + 1ull);
-  }
+  const unsigned long long step = deposit_bits(grid, mask);
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(grid, batch), dim3(1u << (blk.k - rbits)), lds, s, a, blk, phases, ops, mats, stride,
                        mat_stride, ntiles, mask, step);

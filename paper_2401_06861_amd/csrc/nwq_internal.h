@@ -183,6 +183,13 @@ struct RbPhase {
   // reads are its own, and LDS serves a wave in order).
   unsigned short wr_t[kRbThreadBits], wr_r[4], rd_t[kRbThreadBits], rd_r[4];
 };
+// The bits of v deposited, lowest first, at the set bits of mask.
+__host__ __device__ inline unsigned long long deposit_bits(unsigned long long v, unsigned long long mask) {
+  unsigned long long r = 0;
+  for (; mask; mask &= mask - 1, v >>= 1)
+    if (v & 1ull) r |= mask & (~mask + 1ull);
+  return r;
+}
 // Between the LDS writes and reads of an exchange (and back): a barrier where
 // waves exchange entries.  Inside a wave LDS serves accesses in order, and the
 // fence, which takes no instruction, keeps the compiler to that order.

@@ -1435,14 +1435,6 @@ inline size_t bwd_reg_lds(int k, int phases, int nops, int nlocal) {
          (size_t)nlocal * nw * 4 * sizeof(double) + 64;
 }
 
-// The bits of v deposited, lowest first, at the set bits of mask.
-__device__ __forceinline__ unsigned long long pdep_u64(unsigned long long v, unsigned long long mask) {
-  unsigned long long r = 0;
-  for (; mask; mask &= mask - 1, v >>= 1)
-    if (v & 1ull) r |= mask & (~mask + 1ull);
-  return r;
-}
-
 template <bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_vqe_bwd_reg(
     double2* __restrict__ phi0, double2* __restrict__ lam0, int n, RbBlock blk, const RbPhase* __restrict__ phases,
@@ -1477,7 +1469,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     return ((j & 1) ? r[0] : 0ull) ^ ((j & 2) ? r[1] : 0ull) ^ ((j & 4) ? r[2] : 0ull);
   };
   __syncthreads();
-  unsigned long long tile = blockIdx.x, base = pdep_u64(tile, mask);
+  unsigned long long tile = blockIdx.x, base = deposit_bits(tile, mask);
   for (; tile < ntiles; tile += gridDim.x, base = ((base | ~mask) + step) & mask) {
     {
       const double2* __restrict__ a = phi + (base | gl_ld);
@@ -1810,14 +1802,6 @@ static unsigned long long tile_bits(const Block& b) {
   for (int i = 0; i < b.m; ++i) t |= 1ull << b.hi[i];
   return t;
 }
-// The bits of v deposited, lowest first, at the set bits of mask.
-static unsigned long long deposit(unsigned long long v, unsigned long long mask) {
-  unsigned long long r = 0;
-  for (; v && mask; mask &= mask - 1, v >>= 1)
-    if (v & 1ull) r |= mask & (~mask + 1ull);
-  return r;
-}
-
 static int build_fused(nwq_vqe* h) {
   if (h->fused_built) return NWQ_OK;
   const int low = h->low_bits > 0 ? h->low_bits : kVqeLowBits;
@@ -2235,7 +2219,7 @@ static int launch_fused(nwq_vqe* h, int B, const double* theta, const double* co
       hipLaunchKernelGGL(kern, grid, dim3(1u << (b.d.k - 3)),
                          bwd_reg_lds(b.d.k, b.d.ph_count, b.nops, b.nlocal), s, h->d_phi, h->d_lam, h->n, b.d, dph,
                          dro + b.op0, b.nops, dsl + b.slot0, b.nlocal, h->d_fixed, theta, h->P, h->nslots, h->d_gpart,
-                         nt, b.mask, deposit(G, b.mask));
+                         nt, b.mask, deposit_bits(G, b.mask));
     }
   }
   if (grad != nullptr && h->nslots > 0)
