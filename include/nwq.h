@@ -290,8 +290,8 @@ int nwq_expval_pauli_terms_complex(nwq_handle h, int n_terms, const uint64_t* xm
                                    const uint64_t* zmask, double* out_real, double* out_imag);
 
 /* Device bytes the handle holds now: the state if the library allocated it
- * (nwq_*_create, not *_create_from), the 4 MiB upload ring once used,
- * reduction scratch and the fused-block program buffer.  Host-side
+ * (nwq_*_create, not *_create_from), the upload rings once used (256 KiB, then
+ * 4 MiB more), reduction scratch and the fused-block program buffer.  Host-side
  * bookkeeping only: no device call. */
 int nwq_memory(nwq_handle h, size_t* bytes);
 
@@ -355,14 +355,16 @@ int nwq_vqe_eval_coeffs(nwq_vqe_handle h, int B, const double* theta_dev, const 
  * vector, one kernel per gate, no graph, no LDS residency. */
 int nwq_vqe_eval_single(nwq_vqe_handle h, const double* theta_dev, double* energy_dev, double* grad_dev);
 
-/* Launch configuration: mode 0 = automatic (LDS-resident for n <= 12, fused
- * for larger n), 1 = LDS-resident (n <= 12), 2 = one kernel per gate over the
- * batch, 3 = fused blocks (n >= 8: 2^11-amplitude tiles; forward through the
- * register-blocked block kernel over all B states, backward with tiles of phi
- * and lambda in LDS); all but the LDS-resident path run as one hipGraph per
- * batch size.  threads: workgroup size of the LDS kernel (64..1024, power of
- * two), which mode 1 runs for programs too long for the register-resident
- * kernel (that one takes 2^(n-3) threads, at least 64); blocks_per_state: workgroups per state of modes 2 and 3 (0 = default). */
+/* Launch configuration: mode 0 = automatic (resident for n <= 12, fused
+ * for larger n), 1 = resident (n <= 12: each vector's state in registers, or in
+ * LDS for long programs), 2 = one kernel per gate over the batch, 3 = fused
+ * blocks (n >= 8: forward in 2^12-amplitude tiles through the register-blocked
+ * block kernel over all B states, backward in 2^11-amplitude tiles of phi and
+ * lambda in registers, exchanged through LDS); all but the resident path run as
+ * one hipGraph per batch size.  threads: workgroup size of the LDS kernel
+ * (64..1024, power of two), which mode 1 runs for programs too long for the
+ * register-resident kernel (that one takes 2^(n-3) threads, at least 64);
+ * blocks_per_state: workgroups per state of modes 2 and 3 (0 = default). */
 int nwq_vqe_set_config(nwq_vqe_handle h, int mode, int threads, int blocks_per_state);
 int nwq_vqe_get_config(nwq_vqe_handle h, int* mode, int* threads, int* blocks_per_state);
 /* Flags of the fused schedule's tile kernels (forward and backward): bit 0 =
@@ -374,7 +376,7 @@ int nwq_vqe_set_flags(nwq_vqe_handle h, int flags);
 /* Low tile bits of the fused schedule's blocks (mode 3), as
  * nwq_set_fusion_lowbits for circuits: 0 (default) = 3, else c in [3, 8],
  * used as max(k - 8, min(c, k - 2)) at tile width k.  Fewer low bits let a
- * block hold more qubits (n=20, L=8: 26 backward blocks with 6, 18 with 3).
+ * block hold more qubits (n=20, L=8: 16 backward blocks with 6, 8 with 3).
  * Changing it waits for the context's stream and plans the program again
  * on next use.  Results agree to rounding.  Other values: NWQ_EINVAL. */
 int nwq_vqe_set_lowbits(nwq_vqe_handle h, int c);

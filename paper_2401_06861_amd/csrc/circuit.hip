@@ -27,13 +27,13 @@ int fusion_width(const nwq_state* h, int nbits) {
 
 // Fewer low bits leave room for more of the circuit's bits per block and give
 // shorter HBM runs.  State vectors take as few as the block's 8 high slots
-// allow (at least 3: whole 128-byte lines): the depth-40 brickwork on 30
-// qubits runs in 281 ms at width 13 with 5 low bits (29 blocks), 332 with 6
-// (38) and 380 with 7 (49); a 384-gate circuit of random pairs on 24 qubits in
-// 1.69 ms at width 12 with 4, 1.72 with 5 and 1.84 with 6.  On vec(rho) a
-// qubit above the low bits takes two high slots (its column bit q and row bit
-// q + n); density matrices keep at least 4 (n=14, width 12, noisy TFIM: 65 ms
-// and 25 blocks with 4, 83 ms and 41 with 5).
+// allow (at least 3: whole 128-byte lines): at width 12 the depth-40 brickwork
+// on 30 qubits runs in 260 ms with 4 low bits (32 blocks), 301 with 5 (40), 344
+// with 6 (51) and 462 with 7 (74); 384 gates on random pairs of 24 qubits in
+// 2.90 ms (25), 3.11 (27), 3.48 (30) and 3.63 (35).  On vec(rho) a qubit above
+// the low bits takes two high slots (its column bit q and row bit q + n);
+// density matrices keep at least 4 (n=14, width 12, noisy TFIM: 50 ms and 25
+// blocks with 4, 76 ms and 41 with 5).
 int fusion_low_bits(const nwq_state* h, int nbits) {
   const int k = fusion_width(h, nbits);
   if (nbits <= k) return nbits;
@@ -48,9 +48,9 @@ int fusion_low_bits(const nwq_state* h, int nbits) {
 // waiting at the front that lets the most gates in per added bit, and takes
 // every gate the set then reaches.  Growing by gain follows the light cone of
 // the bits it holds instead of the order of the list: the depth-40 brickwork
-// on 30 qubits needs 31 sets of 13 bits (5 low) where taking gates in list
-// order until the set is full needed 73, and the 20-qubit, 8-layer VQE ansatz
-// 8 of 12 bits instead of 17.  `seeds` bounds the first gates tried per round
+// on 30 qubits needs 32 sets of 12 bits (4 low) where taking gates in list
+// order until the set is full needed 73 of 13, and the 20-qubit, 8-layer VQE
+// ansatz 6 of 12 bits instead of 17.  `seeds` bounds the first gates tried per round
 // (the set that takes the most gates is kept).
 //
 // The gates on one bit are taken in order, so what has been taken is a place

@@ -105,7 +105,6 @@ std::vector<Block> plan_blocks(const std::vector<PGate>& g, int n, int k, int c,
 // Tile width and low tile bits of a handle's fused blocks over nbits bits.
 int fusion_width(const nwq_state* h, int nbits);
 int fusion_low_bits(const nwq_state* h, int nbits);
-// internal gate type: dense 4x4 whose matrix is entry p[0] of a side table
 // Internal gate types whose matrix sits in a side table from entry p[0] on:
 // a dense 4x4 (16 entries), a diagonal 4x4 (16 entries, the diagonal at 5u),
 // a 2x2 (4 entries), and a dense 16x16 on the four bits q[0..3] (256 entries,

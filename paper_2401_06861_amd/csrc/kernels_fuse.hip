@@ -2,8 +2,8 @@
 // T = {0..c-1} u {hi_0..hi_{m-1}} is applied to each tile of 2^(c+m)
 // amplitudes staged in LDS, so the block costs one read and one write of the
 // vector instead of one per gate.  The low c bits give 2^m contiguous chunks
-// of 2^c amplitudes (c >= 6: 1 KiB wave-contiguous loads and stores); the
-// high bits pick which chunks form a tile.  Inside LDS each gate is a pass
+// of 2^c amplitudes (c >= 3: whole 128-byte lines); the high bits pick which
+// chunks form a tile.  Inside LDS each gate is a pass
 // over the tile with a barrier between gates.
 #include <type_traits>
 
@@ -193,11 +193,12 @@ void launch_fused_block(hipStream_t s, double2* a, int nbits, const FusedBlockDe
 //
 // What bounds it: the vector units and the power they draw.  On the 30-qubit
 // depth-40 brickwork the HBM traffic of the 32 blocks of width 12 takes 0.18 s
-// and their FP64 instructions 0.13 s; with every tile read from cache 274 of
-// 284 ms remained, and the VALU is busy 69 % of the cycles at a clock that
-// sinks to 2.0 GHz (2.3 GHz at 52 %).  Four workgroups of four waves share a
-// CU (no tile is loaded ahead: the other workgroups' arithmetic hides a
-// tile's loads, and the exchanges of one wave the scalar loads of another).
+// and their FP64 instructions 0.13 s; the VALU is busy 82 % of the cycles at a
+// clock that sinks to 1.9 GHz (density matrices 59 % at 2.15), and with three
+// workgroups per CU and every tile read from cache 274 of 284 ms remained.
+// Four workgroups of four waves share a CU (no tile is loaded ahead: the other
+// workgroups' arithmetic hides a tile's loads, and the exchanges of one wave
+// the scalar loads of another).
 // Exchanges whose two phases keep the same tile bits on the wave index stay
 // inside a wave and need no barrier.  Against one workgroup of 2^13 tiles with
 // the next tile loaded ahead (221 VGPRs, 128 KB), three per CU (135 VGPRs, op

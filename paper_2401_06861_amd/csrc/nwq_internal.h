@@ -233,8 +233,7 @@ int set_error(int code, const std::string& msg);
 int check_hip(hipError_t e, const char* what);
 
 // Dynamic LDS above 64 KiB: up to the CU's whole 160 KiB less the kernel's
-// static LDS (the LDS-resident VQE kernel takes up to that; the fused tiles at
-// most 2^13 amplitudes plus one padding entry per 16).  enable_dynamic_lds
+// static LDS (the resident VQE kernels take up to that).  enable_dynamic_lds
 // raises a kernel's limit to it once per kernel and device, under a lock: the
 // limit is process-wide state of the kernel, so setting it per launch from
 // several host threads raced with launches of the same kernel elsewhere, and a

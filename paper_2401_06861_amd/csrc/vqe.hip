@@ -342,7 +342,7 @@ __global__ __launch_bounds__(NT) void k_vqe_lds(int n, const VqeOp* __restrict__
 // of the amplitudes whose phase differs (a global phase changes neither the
 // energy nor the gradient), RY and RX are three shears in place, and each
 // parameter's slots are added by a thread of its own.  256 vectors with
-// gradients: n=8, L=4 149 -> 76 us, n=12, L=8 1020 -> 251 us a call.
+// gradients: n=8, L=4 149 -> 76 us, n=12, L=8 1020 -> 244 us a call.
 // What bounds it: the chain of ops of one vector on one CU.  At n=12 an op
 // takes about 0.4 us forward, half of it FP64 issue of the two waves per SIMD,
 // the rest the dispatch; at n=8 one wave has the CU to itself.
@@ -1582,7 +1582,7 @@ struct nwq_vqe {
   double* d_E = nullptr;
   double* d_grad = nullptr;
   double* d_coeffs = nullptr;  // staging copy of per-vector coefficients
-  double2* d_table = nullptr;  // fused path: per-vector matrix table [B][nops][8]
+  double2* d_table = nullptr;  // fused path: per-vector matrix table [B][nops][4]
   double* d_ssum = nullptr;    // per-slot gradient sums [B][nslots]
   // fused path program (built on first use)
   bool fused_built = false;
@@ -1768,9 +1768,9 @@ static int launch_global(nwq_vqe* h, int B, const double* theta, const double* c
 // the register-blocked kernel, backward ops in reverse per block (at most
 // kBwdRegOps per dispatch).
 // Low tile bits of the fused schedule's blocks (clamped to [k - 8, k - 2] at
-// width k).  Fewer low bits give shorter runs and fewer blocks, which saves more
-// (n=20, L=8, 256 vectors, blocks filled in gate order: 26 backward blocks with
-// 6 low bits, 18 with 3, 129 -> 119 ms per batch).
+// width k).  Fewer low bits give shorter runs and fewer blocks (n=20, L=8, 256
+// vectors: 6 forward and 8 backward blocks with 3, 51 ms per batch; 11 and 16
+// with 6, 59 ms; 4 take 6 and 12 blocks of twice the run and 46 ms there).
 constexpr int kVqeLowBits = 3;
 constexpr int kVqeSeeds = 2;   // as many as it takes: 8 seeds plan no fewer blocks for the HEA ansatz
 

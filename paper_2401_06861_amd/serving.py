@@ -72,8 +72,8 @@ def sv_footprint(n: int, want_grad: bool = True) -> int:
     return 2 * (16 << n)
 
 
-# scratch of a DM handle beside its 16 4^n-byte matrix: the 4 MiB upload
-# ring, reduction partials and the fused-block program
+# scratch of a DM handle beside its 16 4^n-byte matrix: the upload rings
+# (4.25 MiB), reduction partials and the fused-block program
 DM_SCRATCH_BYTES = 8 << 20
 
 
