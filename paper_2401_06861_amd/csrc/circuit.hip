@@ -1200,15 +1200,18 @@ static int apply_circuit_common(nwq_handle h, int n_gates, const int* types, con
   h->last_fused_gates = 0;
   h->last_phases = 0;
   if (h->kind == NWQ_KIND_SV && h->fuse_k > 0 && n_gates > 0) return apply_fused(h, gates, h->n, nullptr, from_zero);
+  size_t done = 0;   // gates that ran in one launch per chunk
   if (h->kind == NWQ_KIND_SV && one_tile_circuit(h, n_gates)) {
-    for (size_t i = 0; i < gates.size(); i += kOneTileChunk) {
-      const size_t e = std::min(gates.size(), i + kOneTileChunk);
-      const int rc = apply_fused(h, {gates.begin() + i, gates.begin() + e}, h->n, nullptr, false, true);
+    while (done < gates.size()) {
+      const size_t e = std::min(gates.size(), done + kOneTileChunk);
+      const int rc = apply_fused(h, {gates.begin() + done, gates.begin() + e}, h->n, nullptr, false, true);
+      if (rc == NWQ_ENOMEM) break;   // no room for the upload: nothing of the chunk has run
       if (rc) return rc;
+      done = e;
     }
-    return NWQ_OK;
   }
-  for (const PGate& g : gates) {
+  for (; done < gates.size(); ++done) {
+    const PGate& g = gates[done];
     int rc;
     if (h->kind == NWQ_KIND_SV) {
       rc = sv_apply_gate_validated(h, g.type, g.q, g.p);

@@ -161,10 +161,11 @@ struct RelaxedCapture {
 static int arena_alloc(nwq_state* h, size_t bytes) {
   RelaxedCapture relaxed;
   void *dev = nullptr, *host = nullptr;
-  NWQ_TRY_HIP(hipMalloc(&dev, bytes), "hipMalloc(arena)");
-  const int rc = check_hip(hipHostMalloc(&host, bytes, hipHostMallocDefault), "hipHostMalloc(arena)");
+  int rc = check_hip(hipMalloc(&dev, bytes), "hipMalloc(arena)");
+  if (!rc) rc = check_hip(hipHostMalloc(&host, bytes, hipHostMallocDefault), "hipHostMalloc(arena)");
   if (rc) {
-    (void)hipFree(dev);
+    if (dev) (void)hipFree(dev);
+    (void)hipGetLastError();   // callers may go on without: no launch after reports it
     return rc;
   }
   h->arena_first_dev = h->arena_dev;
